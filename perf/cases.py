@@ -242,6 +242,89 @@ def work(case):
     return {"flops": 3 * fwd, "bytes": params * (e + 4) + 4 * act}
 
 
+def _attention64(qkv, heads, d):
+    """Causal softmax attention and its log-sum-exp, in 64 bits, one head at a time.
+    qkv [S, 3*heads*d] with rows [Q heads | K heads | V heads]."""
+    S, P = qkv.shape[0], heads * d
+    masked = torch.ones(S, S, dtype=torch.bool, device=qkv.device).triu(1)
+    outs, lses = [], []
+    for n in range(heads):
+        q, k, v = (qkv[:, i * P + n * d:i * P + (n + 1) * d] for i in range(3))
+        s = (q @ k.t() / d ** 0.5).masked_fill(masked, float("-inf"))
+        outs.append(torch.softmax(s, dim=-1) @ v)
+        lses.append(torch.logsumexp(s.detach(), dim=-1))
+    return torch.cat(outs, dim=1), torch.stack(lses)
+
+
+def _layer64(x, p, case):
+    """One decoder layer in 64 bits; x [batch, seq, hidden], p the layer's twelve tensors."""
+    F = torch.nn.functional
+    Bt, S, H = x.shape
+    g1, b1, wqkv, bqkv, wo, bo, g2, b2, w1, c1, w2, c2 = p
+    qkv = F.linear(F.layer_norm(x, (H,), g1, b1, 1e-5), wqkv, bqkv)
+    c = torch.stack([_attention64(qkv[b], case["heads"], case["head_dim"])[0] for b in range(Bt)])
+    x1 = x + F.linear(c, wo, bo)
+    u = F.linear(F.layer_norm(x1, (H,), g2, b2, 1e-5), w1, c1)
+    return x1 + F.linear(F.gelu(u, approximate="tanh" if case["gelu"] == "tanh" else "none"), w2, c2)
+
+
+def exact(case, seed):
+    """The outputs of run() from torch's 64-bit operators and autograd on the same inputs.  The
+    flat parameter buffer holds, layer by layer, ln1_g, ln1_b, w_qkv, b_qkv, w_o, b_o, ln2_g,
+    ln2_b, w_fc1, b_fc1, w_fc2, b_fc2 without gaps."""
+    s = prepare(case, seed)
+    if case["path"] == "attention":
+        a, d = case["heads"], case["head_dim"]
+        outs, lses, grads = [], [], []
+        for b in range(case["batch"]):
+            qkv = s.qkv[b].double().requires_grad_()
+            out, lse = _attention64(qkv, a, d)
+            out.backward(s.dout[b].double())
+            outs.append(out.detach())
+            lses.append(lse)
+            grads.append(qkv.grad)
+        return [torch.stack(outs), torch.stack(lses), torch.stack(grads)]
+    xs, dys = s.xs, s.dys
+    weights = s.weights if case["path"] == "traversal" else [s.bufs.weights]
+    weights = [w.double() for w in weights]
+    del s                                    # the stage's own buffers are not needed
+    H, P, F = case["hidden"], case["heads"] * case["head_dim"], case["ffn"]
+    shapes = [(H,), (H,), (3 * P, H), (3 * P,), (H, P), (H,), (H,), (H,), (F, H), (F,), (H, F), (H,)]
+    chunks, grads = [], []
+    for w in weights:
+        g, layers, off = torch.zeros_like(w), [], 0
+        for _ in range(case["layers"]):
+            layer = []
+            for shape in shapes:
+                n = 1
+                for size in shape:
+                    n *= size
+                t = w[off:off + n].view(shape).requires_grad_()
+                t.grad = g[off:off + n].view(shape)      # micro-batches add up in place
+                layer.append(t)
+                off += n
+            layers.append(layer)
+        chunks.append(layers)
+        grads.append(g)
+    ys, dxs = [], []
+    for x, dy in zip(xs, dys):
+        x = x.double().requires_grad_()
+        y = x
+        for layers in chunks:
+            for layer in layers:
+                y = _layer64(y, layer, case)
+        if case["path"] != "forward":
+            y.backward(dy.double())
+            dxs.append(x.grad)
+        ys.append(y.detach())
+        del x, y
+    if case["path"] == "forward":
+        return ys
+    if case["path"] == "backward":
+        return dxs + grads
+    return ys + dxs + grads
+
+
 def tolerance(case):
     """Relative error in the 2-norm, and the largest single difference over the tensor's root mean
     square (or the value, where larger): about four times what these cases show against the same
