@@ -56,6 +56,12 @@ struct GemmEpilogue {
 // form 2: Cf32[M,N] += A[K,M]^T B[K,N].
 hipError_t gemm_simple(int dtype, int form, int M, int N, int K, const void* A, const void* B,
                        void* C, const GemmEpilogue& ep, hipStream_t st);
+// fp32 products on the matrix cores (gemm_f32.hip): contiguous dimensions multiples of 4, pointers
+// 16-byte aligned; any M, N, K otherwise.
+bool gemm_f32_supported(int form, int M, int N, int K, const void* A, const void* B, const void* C,
+                        const GemmEpilogue& ep);
+hipError_t gemm_f32(int form, int M, int N, int K, const void* A, const void* B, void* C,
+                    const GemmEpilogue& ep, hipStream_t st);
 // bf16 MFMA path; returns hipErrorNotSupported if the shape does not fit its tiles.
 bool gemm_mfma_supported(int form, int M, int N, int K);
 // Tiled image of a B operand for the 256x256x32 kernel: `transposed` = src is [K,N]

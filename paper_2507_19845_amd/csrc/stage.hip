@@ -263,12 +263,14 @@ struct TraceScope {
     GPTS_TRY(expr, where);                                           \
   } while (0)
 
-// One matrix product of the stage: MFMA path for bf16 shapes it covers, the
-// plain FMA path otherwise (always for fp32).
+// One matrix product of the stage: on the matrix cores for the bf16 and fp32 shapes their kernels
+// cover, the plain FMA path otherwise.
 hipError_t gemm(int dtype, int form, int M, int N, int K, const void* A, const void* B, void* C,
                 const GemmEpilogue& ep, hipStream_t st) {
   if (dtype == GPTS_BF16 && gemm_mfma_supported(form, M, N, K))
     return gemm_mfma(form, M, N, K, A, B, C, ep, st);
+  if (dtype == GPTS_FP32 && gemm_f32_supported(form, M, N, K, A, B, C, ep))
+    return gemm_f32(form, M, N, K, A, B, C, ep, st);
   return gemm_simple(dtype, form, M, N, K, A, B, C, ep, st);
 }
 

@@ -529,6 +529,32 @@ def test_op_gemm_forms(dtype, M, N, K):
     assert max_norm_err(B.to_host(Cf), ref) <= (1e-5 if dtype == "fp32" else 1e-4)
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 4, 4), (33, 36, 60), (32, 32, 64), (31, 100, 68), (65, 60, 132), (4, 4, 1),
+                                   (36, 64, 999), (1216, 1032, 40), (1100, 1284, 36), (8, 6, 8), (10, 12, 7)])
+def test_op_gemm_fp32_edges(M, N, K):
+    """The fp32 matrix-core products at the edges of their two tile sizes (32 and 64), of the slices
+    (64 and 32) and of the rule between them, and the widths that are left to the plain kernel.
+    Every element within (K + 4) roundings of its sum of magnitudes."""
+    print(f"[case] gemm fp32 edges M={M} N={N} K={K}", flush=True)
+    dt, dev = B.GPTS_FP32, lambda a: B.to_device(a, "fp32")
+    eps = (K + 4) * 2.0 ** -23
+    mk = lambda tag, shp: synth.to_storage(synth.make_aux(11, tag, shp), "fp32")
+    A, Bm, bias, res, At, Bn = mk(1, (M, K)), mk(2, (N, K)), mk(3, (N,)), mk(4, (M, N)), mk(5, (K, M)), mk(6, (K, N))
+    f64 = lambda a: a.astype(np.float64)
+    Cd = torch.empty((M, N), dtype=torch.float32, device="cuda")
+
+    def check(got, ref, mag):
+        assert (np.abs(B.to_host(got) - ref) <= eps * mag).all()
+
+    B.gpt_stage_op_gemm(dt, 0, M, N, K, dev(A), dev(Bm), Cd, bias=dev(bias), residual=dev(res))
+    check(Cd, f64(A) @ f64(Bm).T + bias + res, np.abs(f64(A)) @ np.abs(f64(Bm)).T + np.abs(bias) + np.abs(res))
+    B.gpt_stage_op_gemm(dt, 1, M, N, K, dev(A), dev(Bn), Cd)
+    check(Cd, f64(A) @ f64(Bn), np.abs(f64(A)) @ np.abs(f64(Bn)))
+    Cf = dev(res)
+    B.gpt_stage_op_gemm(dt, 2, M, N, K, dev(At), dev(Bn), Cf)
+    check(Cf, f64(At).T @ f64(Bn) + res, np.abs(f64(At)).T @ np.abs(f64(Bn)) + np.abs(res))
+
+
 @pytest.mark.parametrize("dtype,M,N", [("fp32", 100, 136), ("bf16", 4096, 1024), ("bf16", 7, 8), ("bf16", 1000, 4608)])
 def test_op_colsum(dtype, M, N):
     print(f"[case] colsum {dtype} M={M} N={N}", flush=True)
