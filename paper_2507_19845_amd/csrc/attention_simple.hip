@@ -1,4 +1,4 @@
-// Causal softmax attention in fp32 FMA arithmetic (fp32 stages and head sizes the
+// Causal softmax attention in fp32 FMA arithmetic (fp32 buffers that are not 16-byte aligned and sizes the
 // MFMA kernels do not cover).  A query (or key) row is owned by G = D/32
 // adjacent lanes, each holding a 32-wide slice of the head dimension; dot
 // products are completed with xor-shuffles inside the group.  Tiles of 32

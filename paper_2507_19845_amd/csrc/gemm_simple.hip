@@ -1,4 +1,4 @@
-// Plain LDS-tiled matrix product with fp32 FMA arithmetic, for fp32 stages and
+// Plain LDS-tiled matrix product with fp32 FMA arithmetic, for fp32 products of odd widths or unaligned buffers and
 // for shapes the MFMA kernels do not cover.  64x64 output tile, 16-deep slices,
 // 256 threads each owning a 4x4 block.  Operands are addressed through
 // (row, col) strides so the three forms of the stage share one kernel:

@@ -90,6 +90,13 @@ hipError_t attention_bwd_simple(int dtype, int B, int S, int a, int d, const voi
                                 const void* out, const float* lse, const void* dout, void* dqkv,
                                 float* delta, hipStream_t st);
 
+// fp32 attention on the matrix cores (head_dim 32, 64 or 128): every buffer 16-byte aligned (null
+// pointers count as aligned).  No scratch memory.
+bool attention_f32_supported(const void* qkv, const void* out, const void* dout, const void* dqkv);
+hipError_t attention_fwd_f32(int B, int S, int a, int d, const void* qkv, void* out, float* lse, hipStream_t st);
+hipError_t attention_bwd_f32(int B, int S, int a, int d, const void* qkv, const void* out, const float* lse,
+                             const void* dout, void* dqkv, hipStream_t st);
+
 // bf16 MFMA attention (head_dim 32, 64 or 128).  scratch: device memory of
 // attention_mfma_scratch_bytes(B, S, a, d, phase) bytes (phase 0 forward: the transposed
 // image of V; phase 1 backward: delta and the transposed images of Q, K and dO).

@@ -274,7 +274,8 @@ hipError_t gemm(int dtype, int form, int M, int N, int K, const void* A, const v
   return gemm_simple(dtype, form, M, N, K, A, B, C, ep, st);
 }
 
-// Attention: MFMA kernels for bf16 (head_dim 32, 64, 128), the plain FMA kernels for fp32.
+// Attention: on the matrix cores for bf16 and for aligned fp32 buffers, the plain FMA kernels
+// otherwise.
 // scratch: attention_scratch_bytes(.., phase) bytes of device memory.
 bool attention_uses_mfma(int dtype, int B, int S, int a, int d) {
   return dtype == GPTS_BF16 && attention_mfma_supported(B, S, a, d);
@@ -288,6 +289,8 @@ hipError_t attention_fwd(int dtype, int B, int S, int a, int d, const void* qkv,
                          float* lse, void* scratch, hipStream_t st, bool f16 = false) {
   if (attention_uses_mfma(dtype, B, S, a, d)) return attention_fwd_mfma(B, S, a, d, qkv, out, lse, scratch, st, f16);
   if (f16) return hipErrorInvalidValue;
+  if (dtype == GPTS_FP32 && attention_f32_supported(qkv, out, nullptr, nullptr))
+    return attention_fwd_f32(B, S, a, d, qkv, out, lse, st);
   return attention_fwd_simple(dtype, B, S, a, d, qkv, out, lse, st);
 }
 hipError_t attention_bwd(int dtype, int B, int S, int a, int d, const void* qkv, const void* out,
@@ -296,6 +299,8 @@ hipError_t attention_bwd(int dtype, int B, int S, int a, int d, const void* qkv,
   if (attention_uses_mfma(dtype, B, S, a, d))
     return attention_bwd_mfma(B, S, a, d, qkv, out, lse, dout, dqkv, scratch, st, qkv_f16);
   if (qkv_f16) return hipErrorInvalidValue;
+  if (dtype == GPTS_FP32 && attention_f32_supported(qkv, out, dout, dqkv))
+    return attention_bwd_f32(B, S, a, d, qkv, out, lse, dout, dqkv, st);
   return attention_bwd_simple(dtype, B, S, a, d, qkv, out, lse, dout, dqkv, static_cast<float*>(scratch), st);
 }
 

@@ -603,6 +603,53 @@ def test_op_attention(dtype, Bn, S, a, d):
         assert max_norm_err(got[..., i * P:(i + 1) * P], rd[..., i * P:(i + 1) * P]) <= tol, f"d{nm}"
 
 
+def _attention_op(dt, Bn, S, a, d, qkv, dout):
+    """(out, lse, dqkv) of the attention operators on device tensors."""
+    out = torch.empty((Bn, S, a * d), dtype=qkv.dtype, device="cuda")
+    lse = torch.empty((Bn, a, S), dtype=torch.float32, device="cuda")
+    dqkv = torch.empty_like(qkv)
+    scratch = [torch.empty(max(B.gpt_stage_op_attention_scratch_bytes(dt, Bn, S, a, d, ph), 256),
+                           dtype=torch.uint8, device="cuda") for ph in (0, 1)]
+    B.gpt_stage_op_attention_fwd(dt, Bn, S, a, d, qkv, out, lse, scratch[0])
+    B.gpt_stage_op_attention_bwd(dt, Bn, S, a, d, qkv, out, lse, dout, dqkv, scratch[1])
+    return out, lse, dqkv
+
+
+@pytest.mark.parametrize("Bn,S,a,d", [(1, 1, 1, 32), (2, 15, 2, 64), (1, 16, 2, 128), (2, 17, 3, 32), (1, 63, 1, 128),
+                                      (1, 65, 2, 64), (2, 130, 2, 32)])
+def test_op_attention_fp32_edges(Bn, S, a, d):
+    """The fp32 matrix-core attention at the edges of its 16-row blocks and of the four waves' turns
+    (64 rows); a token that is not finite touches no row that cannot see it."""
+    print(f"[case] attention fp32 edges B={Bn} S={S} a={a} d={d}", flush=True)
+    P = a * d
+    qkv = synth.to_storage(synth.make_aux(12, 1, (Bn, S, 3 * P)), "fp32")
+    dout = synth.to_storage(synth.make_aux(12, 2, (Bn, S, P)), "fp32")
+    qd, dd = B.to_device(qkv, "fp32"), B.to_device(dout, "fp32")
+    out, lse, dqkv = _attention_op(B.GPTS_FP32, Bn, S, a, d, qd, dd)
+    # sums of at most S products of O(1) terms in fp32, exponents of magnitude below 32: 32 * S * 2^-24
+    tol = max(1e-5, 32 * S * 2.0 ** -24)
+    assert max_norm_err(B.to_host(out), orc.attention_fwd(qkv, a, d)) <= tol
+    assert max_norm_err(B.to_host(dqkv), orc.attention_bwd(qkv, dout, a, d)) <= tol
+    if S == 1:
+        return
+
+    def same(got, want):   # the same sums in another order: within the tolerance above, NaN never
+        assert max_norm_err(B.to_host(got), B.to_host(want)) <= tol
+
+    bad_last, bad_dout = qd.clone(), dd.clone()   # the last token: nothing before it sees its key and value
+    bad_last[:, -1] = float("nan")
+    o2, l2, g2 = _attention_op(B.GPTS_FP32, Bn, S, a, d, bad_last, bad_dout)
+    same(o2[:, :-1], out[:, :-1])
+    same(l2[..., :-1], lse[..., :-1])
+    same(g2[:, :-1, :P], dqkv[:, :-1, :P])
+    bad_first, bad_dout = qd.clone(), dd.clone()   # the first query: it sees no later key
+    bad_first[:, 0, :P] = float("inf")
+    bad_dout[:, 0] = float("inf")
+    o3, _, g3 = _attention_op(B.GPTS_FP32, Bn, S, a, d, bad_first, bad_dout)
+    same(o3[:, 1:], out[:, 1:])
+    same(g3[:, 1:, P:], dqkv[:, 1:, P:])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_recompute_variant_identical_results_smaller_stash(dtype):
