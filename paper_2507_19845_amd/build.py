@@ -28,8 +28,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=f
 FLAGS += os.environ.get("GPTS_HIPCC_FLAGS", "").split()   # e.g. -DGPTS_BIG_WAVES=8 for experiments
 
 
-# gemm_mi16_kernel keeps its 256 accumulators in AGPRs a0..a255 by hand, across separate inline
-# assembly statements; the compiler only knows them as clobbered.  That is safe as long as the
+# gemm_mi16_kernel<EPI, FORM, F16, MB, NB, ..> keeps its 4 MB NB accumulators in AGPRs a0.. by hand, across
+# separate inline assembly statements; the compiler only knows them as clobbered.  That is safe as long as the
 # register allocator never needs an AGPR of its own in that kernel, i.e. as long as nothing is
 # spilled.  The build checks the compiler's resource report for every instance and fails
 # otherwise (a change of compiler or flags must not corrupt results silently).
@@ -44,11 +44,12 @@ def _check_pinned_accumulators(src: str, remarks: str) -> None:
         if PINNED_AGPR_KERNEL not in name:
             continue
         seen += 1
+        mb, nb = map(int, re.search(r"gemm_mi16_kernelILi\d+ELi\d+ELb[01]ELi(\d+)ELi(\d+)E", name).groups())
         val = {k: int(v) for k, v in re.findall(r"remark:\s+([A-Za-z ]+?)(?: \[bytes/lane\])?: (\d+) \[", b)}
-        ok = (val.get("AGPRs") == 256 and val.get("ScratchSize") == 0 and val.get("VGPRs Spill") == 0
+        ok = (val.get("AGPRs") == 4 * mb * nb and val.get("ScratchSize") == 0 and val.get("VGPRs Spill") == 0
               and val.get("SGPRs Spill") == 0 and val.get("VGPRs", 999) < 256)
         if not ok:
-            raise RuntimeError(f"{src}: {name} must use exactly the 256 hand-placed AGPRs and spill nothing; "
+            raise RuntimeError(f"{src}: {name} must use exactly its {4 * mb * nb} hand-placed AGPRs and spill nothing; "
                                f"the compiler reports {val}")
     if seen == 0:
         raise RuntimeError(f"{src}: no resource report found for {PINNED_AGPR_KERNEL}")
@@ -56,7 +57,7 @@ def _check_pinned_accumulators(src: str, remarks: str) -> None:
 
 def _compile(src: str) -> str:
     obj = os.path.join(OBJ, os.path.basename(src) + ".o")
-    pinned = os.path.basename(src) == "gemm_mfma.hip"
+    pinned = os.path.basename(src) in ("gemm_fwd.hip", "gemm_fwd_f16.hip", "gemm_dgrad.hip", "gemm_wgrad.hip")
     extra = ["-Rpass-analysis=kernel-resource-usage"] if pinned else []
     cmd = [HIPCC, *FLAGS, *extra, "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)

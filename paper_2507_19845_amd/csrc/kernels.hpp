@@ -44,8 +44,7 @@ struct GemmEpilogue {
                                    // written (not added to): column sums of C (fp32, before it is
                                    // rounded for storage), one row per group of tile rows; their sum
                                    // over the rows is sum_m C[m, :]
-  const void* b_image = nullptr;   // forms 0/1, bf16: B re-laid-out by gemm_prepare_image() as the
-                                   // tiled image of its [N rows, K contiguous] view (optional)
+  const void* b_image = nullptr;   // form 0, bf16: B re-laid-out by gemm_prepare_image() (optional)
   // form 2, bf16 MFMA path only (gemm_wgrad_segments_supported): the contraction runs over
   // k_segments pieces of K rows each; piece s of A (B) starts seg_stride_a (seg_stride_b)
   // ELEMENTS after piece s-1.  One launch, one read-modify-write of C.
@@ -64,12 +63,11 @@ hipError_t gemm_f32(int form, int M, int N, int K, const void* A, const void* B,
                     const GemmEpilogue& ep, hipStream_t st);
 // bf16 MFMA path; returns hipErrorNotSupported if the shape does not fit its tiles.
 bool gemm_mfma_supported(int form, int M, int N, int K);
-// Tiled image of a B operand for the 256x256x32 kernel: `transposed` = src is [K,N]
-// (the dgrad view of a weight [out=K, in=N]); else src is [N,K].  N any, K % 32 == 0.
+// Tiled image of a weight src [N,K] as the B operand of form 0; K % 64 == 0 (else the rest of K is
+// left out).  N any.
 size_t gemm_image_elems(int N, int K);
 // to_f16: the image holds the bf16 source values converted to fp16.
-hipError_t gemm_prepare_image(const void* src, void* img, int N, int K, bool transposed, hipStream_t st,
-                              bool to_f16 = false);
+hipError_t gemm_prepare_image(const void* src, void* img, int N, int K, hipStream_t st, bool to_f16 = false);
 // Forward product with fp16 operands on the matrix cores' f16 instructions:
 // C[M,N] = A[M,K] (fp16) W^T, W given as its fp16 image (gemm_prepare_image(.., to_f16 = true));
 // epilogues as form 0: bias; bias + GeLU (C and gelu_out written as fp16); bias + fp32 residual
@@ -80,9 +78,9 @@ hipError_t gemm_fwd_f16(int M, int N, int K, const void* A, const void* b_image,
                         const GemmEpilogue& ep, hipStream_t st);
 hipError_t gemm_mfma(int form, int M, int N, int K, const void* A, const void* B, void* C,
                      const GemmEpilogue& ep, hipStream_t st);
-bool gemm_wgrad_segments_supported(int form, int M, int N, int K);
+bool gemm_wgrad_segments_supported(int M, int N, int K, int segments);
 // rows of GemmEpilogue::colsum_partial that gemm_mfma() writes for an [M,N] product
-int gemm_mfma_colsum_rows(int M, int N);
+int gemm_mfma_colsum_rows(int M, int N, int K);
 
 hipError_t attention_fwd_simple(int dtype, int B, int S, int a, int d, const void* qkv, void* out,
                                 float* lse, hipStream_t st);

@@ -521,7 +521,7 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
     ep.gelu_kind = c.gelu;
     // the matrix-core product also leaves the column sums of dU (the fc1 bias gradient) as
     // per-tile-row partials, when it runs and they fit the column-sum scratch
-    const int cs_rows = (dt == GPTS_BF16 && gemm_mfma_supported(1, D.T, D.F, D.H)) ? gemm_mfma_colsum_rows(D.T, D.F) : 0;
+    const int cs_rows = (dt == GPTS_BF16 && gemm_mfma_supported(1, D.T, D.F, D.H)) ? gemm_mfma_colsum_rows(D.T, D.F, D.H) : 0;
     const bool fused_b1 = cs_rows > 0 && cs_rows <= colsum_splits(D.T);
     if (fused_b1) ep.colsum_partial = cs_part;
     GPTS_OP(GPTS_TR_GEMM_DGRAD, 3, 1, gf(D.T, D.F, D.H), gb(D.T, D.F, D.H, 2 * e), gemm(dt, 1, D.T, D.F, D.H, dY, w(l, GPTS_W_FC2), dU, ep, st), "fc2 dgrad");
@@ -644,7 +644,7 @@ int run_wgrad_flush(const gpt_stage_params* p, int n, const void* const* act_sta
   for (int l = D.L - 1; l >= 0; --l) {
     for (const Lin& L : lins) {
       auto dout_of = [&](int m) { return static_cast<const char*>(grad_stashes[m]) + (size_t)l * gl.end + L.dout; };
-      if (spaced && (n == 1 || gemm_wgrad_segments_supported(2, L.M, L.N, D.T))) {
+      if (spaced && (n == 1 || gemm_wgrad_segments_supported(L.M, L.N, D.T, n))) {
         GemmEpilogue ep;
         ep.k_segments = n;
         ep.seg_stride_a = (size_t)grad_stride / e;
@@ -790,7 +790,7 @@ int gpt_stage_prepare(const gpt_stage_params* p, void* prepared, void* stream) {
   for (int l = 0; l < D.L; ++l)
     for (int i = 0; i < 4; ++i) {
       const bf16* w = W + tensor_off(D, l, L[i].wid);
-      GPTS_TRY(gemm_prepare_image(w, out + prepared_off(D, l, i), L[i].out, L[i].in, false, st, p->cfg.fwd_fp16 != 0), "prepare fwd image");
+      GPTS_TRY(gemm_prepare_image(w, out + prepared_off(D, l, i), L[i].out, L[i].in, st, p->cfg.fwd_fp16 != 0), "prepare fwd image");
     }
   return GPTS_OK;
 }

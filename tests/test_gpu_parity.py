@@ -529,6 +529,36 @@ def test_op_gemm_forms(dtype, M, N, K):
     assert max_norm_err(B.to_host(Cf), ref) <= (1e-5 if dtype == "fp32" else 1e-4)
 
 
+@pytest.mark.parametrize("M,N,K", [(72, 1000, 64), (264, 3000, 128), (520, 2056, 192), (1000, 4104, 128), (2040, 4104, 128),
+                                   (2040, 5112, 192), (2040, 6136, 64), (4088, 4088, 320), (264, 1000, 1024)])
+def test_op_gemm_bf16_tiles(M, N, K):
+    """Each tile of the bf16 products (64x32, 64x64, 128x64, 256x128, 192x192, 256x160, 256x192, 256x256 for
+    the first forms, 64x32 again with a long contraction) with ragged last tiles, one to sixteen slices, and the
+    fp32 epilogues.  fp32 sums of K products of bf16 values: K eps of the sum of magnitudes."""
+    print(f"[case] gemm tiles M={M} N={N} K={K}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    rnd = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    A, Bt, At, U, bias = rnd(M, K), rnd(N, K), rnd(K, M), rnd(M, N), rnd(N)
+    res = torch.empty(M, N, dtype=torch.float32, device="cuda").normal_(generator=gen)
+    bound = 4 * K ** 0.5 * K * 2.0 ** -24 + 1e-6          # of fp32 outputs with |a b| of order 1
+    ref = A.double() @ Bt.double().T
+    out = torch.full((M, N), 7.0, dtype=torch.float32, device="cuda")
+    B.gpt_stage_op_gemm(B.GPTS_BF16, 0, M, N, K, A, Bt, out, bias=bias, residual=res, f32_flags=3)
+    assert (out.double() - (ref + bias.double() + res.double())).abs().max().item() <= bound + 2.0 ** -22 * K ** 0.5
+    out = torch.full((M, N), 0.25, dtype=torch.float32, device="cuda")
+    Bn = Bt.T.contiguous()
+    B.gpt_stage_op_gemm(B.GPTS_BF16, 2, M, N, K, At, Bn, out)
+    assert (out.double() - (At.double().T @ Bn.double() + 0.25)).abs().max().item() <= bound + 2.0 ** -22 * K ** 0.5
+    # data gradient with the GeLU' factor: rounded once to bf16 (2^-9 of the value)
+    out = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    B.gpt_stage_op_gemm(B.GPTS_BF16, 1, M, N, K, A, Bn, out, dgelu_u=U)
+    u = U.double().requires_grad_()
+    torch.nn.functional.gelu(u, approximate="tanh").sum().backward()
+    want = ref * u.grad
+    assert ((out.double() - want).abs() <= want.abs() * 2.0 ** -8 + 2.0 ** -12 * K ** 0.5).all()
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 4, 4), (33, 36, 60), (32, 32, 64), (31, 100, 68), (65, 60, 132), (4, 4, 1),
                                    (36, 64, 999), (1216, 1032, 40), (1100, 1284, 36), (8, 6, 8), (10, 12, 7)])
 def test_op_gemm_fp32_edges(M, N, K):
