@@ -1,6 +1,6 @@
 // Causal softmax attention on the gfx950 matrix cores (bf16 in, fp32 accumulate).
 //
-// Forward, per (batch, head): a workgroup owns 128 query rows (4 waves x 32) and
+// Forward, per (batch, head): a workgroup owns 128 (or, two waves to 32 rows, 64) query rows and
 // walks the key/value rows in tiles of 64 up to the diagonal with an online
 // softmax.  Both products are computed TRANSPOSED so that no value ever has to
 // move between lanes:
@@ -39,9 +39,7 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 // arithmetic fills the gaps (measured: forward +1.7 %, backward +1 %).
 #define GPTS_PRIO(p) __builtin_amdgcn_s_setprio(p)
 
-constexpr int BQ = 128;   // queries per workgroup of the forward kernel
 constexpr int BKV = 64;   // rows per streamed tile
-constexpr int BW = 256;   // rows owned by a workgroup of the backward kernels (8 waves x 32)
 
 __device__ __forceinline__ int swz16(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
@@ -140,11 +138,15 @@ struct TImageArgs {
   size_t ld[3];
   bf16* dst[3];        // image: [b][n][tile][D][64]
   int n_src;
+  // source 2 (dO) also gives delta[b][n][s] = sum_d dO * O, with O addressed like dO; out null: none
+  const bf16* out;
+  float* delta;
 };
 // chunk c (8 positions) of a transposed row holds the sequence positions
 //   16*(c>>1) + 8*(p>>2) + 4*(c&1) + (p&3),  p = 0..7
 // and is stored at chunk position c ^ ((d>>1)&7) of row d.  Rows past S are zero.
-template <int D>
+// O16: args.out holds fp16 values.
+template <int D, bool O16 = false>
 __global__ __launch_bounds__(256) void attn_timage_kernel(const TImageArgs args, int S, int a) {
   constexpr int PITCH = D + 2;  // bf16 elements; odd number of 32-bit words per row
   __shared__ __attribute__((aligned(16))) bf16 stage[BKV * PITCH];
@@ -167,6 +169,17 @@ __global__ __launch_bounds__(256) void attn_timage_kernel(const TImageArgs args,
     const i32x4 vi = __builtin_bit_cast(i32x4, v);
 #pragma unroll
     for (int e = 0; e < 4; ++e) dstw[e] = (uint32_t)vi[e];
+    if (w == 2 && args.out) {   // (uniform) the row's TPR threads are neighbouring lanes
+      float acc = 0.f;
+      if (s < S) {
+        const bf16x8 o = *reinterpret_cast<const bf16x8*>(args.out + (size_t)b * S * args.ld[2] + (size_t)n * D + (size_t)s * args.ld[2] + cc * 8);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc = fmaf(O16 ? (float)__builtin_bit_cast(f16x8, o)[e] : (float)o[e], (float)v[e], acc);
+      }
+#pragma unroll
+      for (int x = TPR / 2; x > 0; x >>= 1) acc += __shfl_xor(acc, x, 64);
+      if (cc == 0 && s < S) args.delta[((size_t)b * a + n) * S + s] = acc;
+    }
   }
   __syncthreads();
   const int ntile = (S + BKV - 1) / BKV;
@@ -201,8 +214,10 @@ __device__ __forceinline__ bf16x8 lds_frag(const char* p) { return *reinterpret_
 // ---- forward -----------------------------------------------------------------------------
 // grid (heads, batch, query tiles): the heaviest query tiles of all heads start first.
 // F16: qkv, the V image, the probabilities and out are fp16 (same layouts, f16 instructions).
-template <int D, bool F16 = false>
-__global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv,
+// RW x SW waves: RW blocks of 32 queries; with SW = 2 a second wave per block takes the other 32 keys
+// of every tile, and the two running maxima, sums and outputs are merged through LDS at the end.
+template <int D, bool F16, int RW, int SW>
+__global__ __launch_bounds__(64 * RW * SW, 2) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv,
                                                                const bf16* __restrict__ vt_img,
                                                                bf16* __restrict__ out,
                                                                float* __restrict__ lse, int S, int a) {
@@ -210,11 +225,12 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
   constexpr int DB = D / 32;       // 32-row blocks of O^T
   constexpr int ROWB = D * 2;
   constexpr int TILE = BKV * ROWB;  // bytes of one K tile or one V^T image tile
+  constexpr int NW = RW * SW, BQ = 32 * RW, NKB = 2 / SW;        // queries; 32-key blocks of a tile per wave
   __shared__ __attribute__((aligned(1024))) char lds[4 * TILE];  // [stage][K | V^T image]
 
   const int lane = threadIdx.x & 63;
-  const int lane_id = lane;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rw = wave % RW, kb0 = wave / RW * NKB;   // this wave's query block; its first key block of a tile
   const int qt = gridDim.z - 1 - blockIdx.z;
   const int n = blockIdx.x, b = blockIdx.y;
   const int P = a * D;
@@ -224,9 +240,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
   const bf16* vimg = vt_img + ((size_t)b * a + n) * ntile * (size_t)(D * BKV);
   const int q0 = qt * BQ;
   const int ql = lane & 31, h = lane >> 5;
-  const int qrow = q0 + wave * 32 + ql;          // this lane's query
+  const int qrow = q0 + rw * 32 + ql;          // this lane's query
   const int qclamp = qrow < S ? qrow : S - 1;
-  const int qmax_wave = min(q0 + wave * 32 + 31, S - 1);
+  const int qmax_wave = min(q0 + rw * 32 + 31, S - 1);
 
   // Q fragments (B operand: column = query, 8 consecutive d per lane and k-step)
   bf16x8 qf[KSTEPS];
@@ -249,8 +265,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
 
   const int last_key = min(q0 + BQ, S);               // keys [0, last_key) are needed
   const int nkv = (last_key + BKV - 1) / BKV;
-  dma_tile<D, 4>(base + P, ld, 0, S, lds, wave, lane);
-  dma_image<D, 4>(vimg, lds + TILE, wave, lane);
+  dma_tile<D, NW>(base + P, ld, 0, S, lds, wave, lane);
+  dma_image<D, NW>(vimg, lds + TILE, wave, lane);
 
   for (int kt = 0; kt < nkv; ++kt) {
     asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -259,39 +275,40 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
     const char* tV = tK + TILE;
     if (kt + 1 < nkv) {
       char* nK = lds + ((kt + 1) & 1) * 2 * TILE;
-      dma_tile<D, 4>(base + P, ld, k0 + BKV, S, nK, wave, lane);
-      dma_image<D, 4>(vimg + (size_t)(kt + 1) * (D * BKV), nK + TILE, wave, lane);
+      dma_tile<D, NW>(base + P, ld, k0 + BKV, S, nK, wave, lane);
+      dma_image<D, NW>(vimg + (size_t)(kt + 1) * (D * BKV), nK + TILE, wave, lane);
     }
-    if (k0 > qmax_wave) continue;  // every key of this tile is masked for this wave
+    const int kw0 = k0 + kb0 * 32;
+    if (kw0 > qmax_wave) continue;  // every key of this tile is masked for this wave
 
-    // ---- S^T = K Q^T for the two 32-key blocks -------------------------------------
-    f32x16 sacc[2];
+    // ---- S^T = K Q^T for the wave's 32-key blocks ----------------------------------
+    f32x16 sacc[NKB];
     GPTS_PRIO(1);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) sacc[kb][e] = 0.f;
 #pragma unroll
       for (int kk = 0; kk < KSTEPS; ++kk) {
-        const bf16x8 kf = lds_frag(tK + kb * 32 * ROWB + (koff ^ (kk << 5)));
+        const bf16x8 kf = lds_frag(tK + (kb0 + kb) * 32 * ROWB + (koff ^ (kk << 5)));
         sacc[kb] = mma32<F16>(kf, qf[kk], sacc[kb]);
       }
     }
     GPTS_PRIO(0);
     // ---- causal mask (only tiles that reach past the first query of the wave) --------
-    if (k0 + BKV - 1 > q0 + wave * 32) {
+    if (kw0 + NKB * 32 - 1 > q0 + rw * 32) {
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int key = k0 + kb * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
+          const int key = kw0 + kb * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
           if (key > qrow) sacc[kb][e] = -INFINITY;
         }
     }
     // ---- online softmax ------------------------------------------------------------------
     float mx = sacc[0][0];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
       for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[kb][e]);
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
@@ -299,7 +316,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
     const float mc = m_new * c;
     float psum = 0.f;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const float p = __builtin_amdgcn_exp2f(fmaf(sacc[kb][e], c, -mc));
@@ -321,11 +338,11 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
     // ---- O^T += V^T P^T ------------------------------------------------------------------------
     GPTS_PRIO(1);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {           // 16 keys per step
+    for (int ks = 0; ks < 2 * NKB; ++ks) {     // 16 keys per step
       const bf16x8 pf = pack8<F16>(sacc[ks >> 1], (ks & 1) * 8);
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
-        const bf16x8 vf = lds_frag(tV + db * 4096 + (voff ^ (ks << 5)));
+        const bf16x8 vf = lds_frag(tV + db * 4096 + (voff ^ ((kb0 * 2 + ks) << 5)));
         oacc[db] = mma32<F16>(vf, pf, oacc[db]);
       }
     }
@@ -334,7 +351,37 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
   // ---- finish: combine the two key halves' sums, normalise, store ------------------------
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  if constexpr (SW == 2) {
+    // the second wave of a query block hands its state over: outputs in the tile memory (every wave
+    // has left the loop), maximum and sum beside it.  A query's first key lies in a first wave's
+    // block, so the merged maximum is finite; a wave that met no key weighs exp2(-inf) = 0.
+    __shared__ float ml[2][RW][kWave];
+    __syncthreads();
+    f32x4* ex = reinterpret_cast<f32x4*>(lds) + rw * (DB * 4 * kWave) + lane;
+    if (kb0 != 0) {
+#pragma unroll
+      for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) ex[(i * 4 + g) * kWave] = f32x4{oacc[i][g * 4], oacc[i][g * 4 + 1], oacc[i][g * 4 + 2], oacc[i][g * 4 + 3]};
+      ml[0][rw][lane] = m_run;
+      ml[1][rw][lane] = l_tot;
+    }
+    __syncthreads();
+    if (kb0 != 0) return;
+    const float m2 = ml[0][rw][lane], m_new = fmaxf(m_run, m2);
+    const float s1 = __builtin_amdgcn_exp2f((m_run - m_new) * c), s2 = __builtin_amdgcn_exp2f((m2 - m_new) * c);
+    l_tot = l_tot * s1 + ml[1][rw][lane] * s2;
+    m_run = m_new;
+#pragma unroll
+    for (int i = 0; i < DB; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 o2 = ex[(i * 4 + g) * kWave];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) oacc[i][g * 4 + e] = oacc[i][g * 4 + e] * s1 + o2[e] * s2;
+      }
+  }
   if (qrow < S) {
     const float inv = 1.f / l_tot;
     bf16* orow = out + ((size_t)b * S + qrow) * P + (size_t)n * D;
@@ -359,50 +406,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
 }
 
 
-// delta[b,n,i] = sum_d dO[b,i,n*D+d] * O[b,i,n*D+d]; one 16-lane group per (row, head).
-// O16: out holds fp16 values.
-template <int D, bool O16 = false>
-__global__ __launch_bounds__(256) void attn_delta_kernel(const bf16* __restrict__ out,
-                                                         const bf16* __restrict__ dout,
-                                                         float* __restrict__ delta, int S, int a,
-                                                         int total) {
-  constexpr int PER = D / 16;  // elements per lane
-  const int gid = (blockIdx.x * 256 + threadIdx.x) >> 4, sub = threadIdx.x & 15;
-  float acc = 0.f;
-  if (gid < total) {
-    const int n = gid % a;
-    const size_t row = gid / a;  // b*S + i
-    const size_t off = row * (size_t)a * D + (size_t)n * D + sub * PER;
-    if constexpr (PER >= 4) {
-#pragma unroll
-      for (int e = 0; e < PER; e += 4) {
-        const bf16x4 o = *reinterpret_cast<const bf16x4*>(out + off + e);
-        const bf16x4 g = *reinterpret_cast<const bf16x4*>(dout + off + e);
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          acc = fmaf(O16 ? (float)__builtin_bit_cast(f16x4, o)[k] : (float)o[k], (float)g[k], acc);
-      }
-    } else {   // head dimension 32: two elements per lane
-      typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-      typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-      const bf16x2 o = *reinterpret_cast<const bf16x2*>(out + off);
-      const bf16x2 g = *reinterpret_cast<const bf16x2*>(dout + off);
-#pragma unroll
-      for (int k = 0; k < 2; ++k)
-        acc = fmaf(O16 ? (float)__builtin_bit_cast(f16x2, o)[k] : (float)o[k], (float)g[k], acc);
-    }
-  }
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if (gid < total && sub == 0) {
-    const int n = gid % a;
-    const size_t row = gid / a;
-    const size_t b = row / S, i = row % S;
-    delta[(b * a + n) * S + i] = acc;
-  }
-}
-
-// Backward, key side.  A workgroup owns 256 keys (8 waves x 32) and streams the
+// Backward, key side.  A workgroup owns blocks of 32 keys, one or two waves each, and streams the
 // query rows at and after them in tiles of 64: the Q and dO tiles in natural form, their
 // transposed images, lse and delta, all by DMA.  Per wave and 32-query block:
 //   S[q][k]  = Q K^T       (A = Q fragment from LDS, B = K fragment in registers)
@@ -415,15 +419,15 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const bf16* __restrict_
 // F16S: the logits are recomputed from fp16 copies of Q and K (qk16, laid out like qkv) with
 // the f16 instruction -- the operands the forward pass formed them from; everything else
 // (V, the images, dO) is bf16.  Without F16S qk16 == qkv.
-template <int D, bool F16S = false>
-__global__ __launch_bounds__(512) void attn_bwd_dkv_mfma_kernel(
-    const bf16* __restrict__ qkv, const bf16* __restrict__ qk16, const bf16* __restrict__ dout, const bf16* __restrict__ qt_img,
-    const bf16* __restrict__ dot_img, const float* __restrict__ lse, const float* __restrict__ delta,
-    bf16* __restrict__ dqkv, int S, int a) {
-  constexpr int KSTEPS = D / 16, DB = D / 32, ROWB = D * 2, TILE = BKV * ROWB;
-  __shared__ __attribute__((aligned(1024))) char lds[8 * TILE];  // [stage][Q | dO | Q image | dO image]
-  __shared__ __attribute__((aligned(256))) float stat[2][2][BKV];  // [stage][lse | delta][row]
-
+// RW x SW waves: RW blocks of 32 keys; with SW = 2 a second wave per block takes the other 32 queries
+// of every tile and the two sums are added through LDS at the end.
+constexpr int kDkvTiles = 8;   // LDS tiles [stage][Q | dO | Q image | dO image]
+template <int D, bool F16S, int RW, int SW>
+__device__ __forceinline__ void dkv_block(const bf16* __restrict__ qkv, const bf16* __restrict__ qk16, const bf16* __restrict__ dout,
+                                          const bf16* __restrict__ qt_img, const bf16* __restrict__ dot_img,
+                                          const float* __restrict__ lse, const float* __restrict__ delta,
+                                          bf16* __restrict__ dqkv, int S, int a, int blk, char* lds, float (*stat)[2][BKV]) {
+  constexpr int KSTEPS = D / 16, DB = D / 32, ROWB = D * 2, TILE = BKV * ROWB, NW = RW * SW;
   const int lane = threadIdx.x & 63;
   const int lane_id = lane;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -439,8 +443,9 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_mfma_kernel(
   const bf16* doimg = dot_img + img_off;
   const float* lse_h = lse + ((size_t)b * a + n) * S;
   const float* delta_h = delta + ((size_t)b * a + n) * S;
-  const int k0 = blockIdx.z * BW;
-  const int kw0 = k0 + wave * 32;
+  const int rw = wave % RW, half = wave / RW;
+  const int k0 = blk * (32 * RW);
+  const int kw0 = k0 + rw * 32;
   const int ql = lane & 31, h = lane >> 5;
   const int key = kw0 + ql;
   const int kclamp = key < S ? key : S - 1;
@@ -479,10 +484,10 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_mfma_kernel(
     int lane = lane_id;
     asm volatile("" : "+v"(lane));
     char* t = lds + stage * 4 * TILE;
-    dma_tile<D, 8>(base16, ld, qt * BKV, S, t, wave, lane);
-    dma_tile<D, 8>(dobase, (size_t)P, qt * BKV, S, t + TILE, wave, lane);
-    dma_image<D, 8>(qimg + (size_t)qt * (D * BKV), t + 2 * TILE, wave, lane);
-    dma_image<D, 8>(doimg + (size_t)qt * (D * BKV), t + 3 * TILE, wave, lane);
+    dma_tile<D, NW>(base16, ld, qt * BKV, S, t, wave, lane);
+    dma_tile<D, NW>(dobase, (size_t)P, qt * BKV, S, t + TILE, wave, lane);
+    dma_image<D, NW>(qimg + (size_t)qt * (D * BKV), t + 2 * TILE, wave, lane);
+    dma_image<D, NW>(doimg + (size_t)qt * (D * BKV), t + 3 * TILE, wave, lane);
     const int qi = qt * BKV + lane;
     const int qc = qi < S ? qi : S - 1;
     if (wave == 0) dma_floats(lse_h, qc, stat[stage][0]);
@@ -499,7 +504,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_mfma_kernel(
     const char* tOT = tQ + 3 * TILE;
     if (qt > qt0) fetch(qt - 1, stage ^ 1);
 #pragma unroll 1
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qb = SW == 2 ? half : 0; qb < (SW == 2 ? half + 1 : 2); ++qb) {
       const int qmin = qt * BKV + qb * 32;
       if (qmin + 31 < kw0 || qmin >= S) continue;  // block fully masked for this wave
       // S, then P = exp(S/sqrt(D) - lse) rounded to bf16 right away (the fp32 block dies
@@ -571,9 +576,36 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_mfma_kernel(
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
+  const float scale = 1.f / sqrtf((float)D);
+  bf16* drow = dqkv + ((size_t)b * S + key) * ld + (size_t)n * D;
+  if constexpr (SW == 2) {
+    // the first wave of a key block finishes dK, the second dV: each hands the other its share
+    __syncthreads();
+    f32x4* ex = reinterpret_cast<f32x4*>(lds) + rw * (2 * DB * 4 * kWave) + lane;
+    auto finish = [&](f32x16(&keep)[DB], f32x16(&give)[DB], int mine, float sc, size_t off) {
+#pragma unroll
+      for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          ex[((1 - mine) * DB * 4 + i * 4 + g) * kWave] = f32x4{give[i][g * 4], give[i][g * 4 + 1], give[i][g * 4 + 2], give[i][g * 4 + 3]};
+      __syncthreads();
+      if (key >= S) return;
+#pragma unroll
+      for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 other = ex[(mine * DB * 4 + i * 4 + g) * kWave];
+          bf16x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = (bf16)((keep[i][g * 4 + e] + other[e]) * sc);
+          *reinterpret_cast<bf16x4*>(drow + off + i * 32 + g * 8 + h * 4) = o;
+        }
+    };
+    if (half == 0) finish(dk, dv, 0, scale, P);
+    else finish(dv, dk, 1, 1.f, 2 * (size_t)P);
+    return;
+  }
   if (key < S) {
-    const float scale = 1.f / sqrtf((float)D);
-    bf16* drow = dqkv + ((size_t)b * S + key) * ld + (size_t)n * D;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -590,22 +622,22 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_mfma_kernel(
   }
 }
 
-// Backward, query side.  A workgroup owns 256 queries (8 waves x 32) and walks the key
+// Backward, query side.  A workgroup owns blocks of 32 queries and walks the key
 // tiles of 64 up to the diagonal, everything transposed:
 //   S^T = K Q^T,  dP^T = V dO^T  (A = K / V fragments from LDS, B = Q / dO in registers)
 //   dS^T = P^T (dP^T - delta_q),  dQ^T[d][q] += K^T dS^T (A = fragment of the K image).
 // grid (heads, batch, query blocks), heaviest first.
-template <int D, bool F16S = false>
-__global__ __launch_bounds__(512) void attn_bwd_dq_mfma_kernel(
-    const bf16* __restrict__ qkv, const bf16* __restrict__ qk16, const bf16* __restrict__ dout, const bf16* __restrict__ kt_img,
-    const float* __restrict__ lse, const float* __restrict__ delta, bf16* __restrict__ dqkv, int S, int a) {
-  constexpr int KSTEPS = D / 16, DB = D / 32, ROWB = D * 2, TILE = BKV * ROWB;
-  __shared__ __attribute__((aligned(1024))) char lds[6 * TILE];  // [stage][K | V | K image]
-
+// RW x SW waves as above, SW = 2 splitting the keys of a tile.
+constexpr int kDqTiles = 6;    // LDS tiles [stage][K | V | K image]
+template <int D, bool F16S, int RW, int SW>
+__device__ __forceinline__ void dq_block(const bf16* __restrict__ qkv, const bf16* __restrict__ qk16, const bf16* __restrict__ dout,
+                                         const bf16* __restrict__ kt_img, const float* __restrict__ lse,
+                                         const float* __restrict__ delta, bf16* __restrict__ dqkv, int S, int a, int qt, char* lds) {
+  constexpr int KSTEPS = D / 16, DB = D / 32, ROWB = D * 2, TILE = BKV * ROWB, NW = RW * SW, BW = 32 * RW, NKB = 2 / SW;
   const int lane = threadIdx.x & 63;
   const int lane_id = lane;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int qt = gridDim.z - 1 - blockIdx.z;
+  const int rw = wave % RW, kb0 = wave / RW * NKB;   // this wave's query block; its first key block of a tile
   const int n = blockIdx.x, b = blockIdx.y;
   const int P = a * D;
   const size_t ld = 3 * (size_t)P;
@@ -615,9 +647,9 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_mfma_kernel(
   const bf16* kimg = kt_img + ((size_t)b * a + n) * ntile * (size_t)(D * BKV);
   const int q0 = qt * BW;
   const int ql = lane & 31, h = lane >> 5;
-  const int qrow = q0 + wave * 32 + ql;
+  const int qrow = q0 + rw * 32 + ql;
   const int qclamp = qrow < S ? qrow : S - 1;
-  const int qmax_wave = min(q0 + wave * 32 + 31, S - 1);
+  const int qmax_wave = min(q0 + rw * 32 + 31, S - 1);
   const float c = 1.4426950408889634f / sqrtf((float)D);
 
   bf16x8 qf[KSTEPS], dof[KSTEPS];
@@ -650,9 +682,9 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_mfma_kernel(
     int lane = lane_id;  // opaque: recompute the DMA offsets per tile rather than keep them
     asm volatile("" : "+v"(lane));
     char* t = lds + stage * 3 * TILE;
-    dma_tile<D, 8>(base16 + P, ld, kt * BKV, S, t, wave, lane);
-    dma_tile<D, 8>(base + 2 * P, ld, kt * BKV, S, t + TILE, wave, lane);
-    dma_image<D, 8>(kimg + (size_t)kt * (D * BKV), t + 2 * TILE, wave, lane);
+    dma_tile<D, NW>(base16 + P, ld, kt * BKV, S, t, wave, lane);
+    dma_tile<D, NW>(base + 2 * P, ld, kt * BKV, S, t + TILE, wave, lane);
+    dma_image<D, NW>(kimg + (size_t)kt * (D * BKV), t + 2 * TILE, wave, lane);
   };
   fetch(0, 0);
 
@@ -663,34 +695,35 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_mfma_kernel(
     const char* tV = tK + TILE;
     const char* tKT = tK + 2 * TILE;
     if (kt + 1 < nkv) fetch(kt + 1, (kt + 1) & 1);
-    if (k0 > qmax_wave) continue;
-    f32x16 sacc[2], dpacc[2];
+    const int kw0 = k0 + kb0 * 32;
+    if (kw0 > qmax_wave) continue;
+    f32x16 sacc[NKB], dpacc[NKB];
     GPTS_PRIO(1);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) sacc[kb][e] = dpacc[kb][e] = 0.f;
 #pragma unroll
       for (int kk = 0; kk < KSTEPS; ++kk) {
-        const int off = kb * 32 * ROWB + (koff ^ (kk << 5));
+        const int off = (kb0 + kb) * 32 * ROWB + (koff ^ (kk << 5));
         sacc[kb] = mma32<F16S>(lds_frag(tK + off), qf[kk], sacc[kb]);
         dpacc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(tV + off), dof[kk], dpacc[kb], 0, 0, 0);
       }
     }
     GPTS_PRIO(0);
-    if (k0 + BKV - 1 > q0 + wave * 32) {  // tile reaches past the first query of the wave: mask
+    if (kw0 + NKB * 32 - 1 > q0 + rw * 32) {  // tile reaches past the first query of the wave: mask
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           float p = __builtin_amdgcn_exp2f(fmaf(sacc[kb][e], c, -L2));
-          const int key = k0 + kb * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
+          const int key = kw0 + kb * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
           if (key > qrow) p = 0.f;
           dpacc[kb][e] = p * (dpacc[kb][e] - Dl);
         }
     } else {
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const float p = __builtin_amdgcn_exp2f(fmaf(sacc[kb][e], c, -L2));
@@ -699,16 +732,36 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_mfma_kernel(
     }
     GPTS_PRIO(1);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
+    for (int ks = 0; ks < 2 * NKB; ++ks) {
       const bf16x8 dsf = pack8(dpacc[ks >> 1], (ks & 1) * 8);
 #pragma unroll
       for (int db = 0; db < DB; ++db)
-        dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(tKT + db * 4096 + (ioff ^ (ks << 5))), dsf, dq[db], 0, 0, 0);
+        dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(tKT + db * 4096 + (ioff ^ ((kb0 * 2 + ks) << 5))), dsf, dq[db], 0, 0, 0);
     }
     GPTS_PRIO(0);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
+  if constexpr (SW == 2) {
+    __syncthreads();
+    f32x4* ex = reinterpret_cast<f32x4*>(lds) + rw * (DB * 4 * kWave) + lane;
+    if (kb0 != 0) {
+#pragma unroll
+      for (int i = 0; i < DB; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) ex[(i * 4 + g) * kWave] = f32x4{dq[i][g * 4], dq[i][g * 4 + 1], dq[i][g * 4 + 2], dq[i][g * 4 + 3]};
+    }
+    __syncthreads();
+    if (kb0 != 0) return;
+#pragma unroll
+    for (int i = 0; i < DB; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 other = ex[(i * 4 + g) * kWave];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dq[i][g * 4 + e] += other[e];
+      }
+  }
   if (qrow < S) {
     const float scale = 1.f / sqrtf((float)D);
     bf16* drow = dqkv + ((size_t)b * S + qrow) * ld + (size_t)n * D;
@@ -724,15 +777,90 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_mfma_kernel(
   }
 }
 
+struct BwdArgs {
+  const bf16 *qkv, *qk16, *dout, *q_img, *k_img, *do_img;
+  const float *lse, *delta;
+  bf16* dqkv;
+  int S, a;
+};
+// Key side and query side, 256 rows per workgroup, a launch each: the form for many workgroups.
+// (One launch for both, heaviest first, was 2 % slower at 4096 queries of 32 heads.)
+template <int D, bool F16S> __global__ __launch_bounds__(512) void attn_bwd_dkv_mfma_kernel(const BwdArgs p) {
+  __shared__ __attribute__((aligned(1024))) char lds[kDkvTiles * BKV * D * 2];
+  __shared__ __attribute__((aligned(256))) float stat[2][2][BKV];  // [stage][lse | delta][row]
+  dkv_block<D, F16S, 8, 1>(p.qkv, p.qk16, p.dout, p.q_img, p.do_img, p.lse, p.delta, p.dqkv, p.S, p.a, blockIdx.z, lds, stat);
+}
+template <int D, bool F16S> __global__ __launch_bounds__(512) void attn_bwd_dq_mfma_kernel(const BwdArgs p) {
+  __shared__ __attribute__((aligned(1024))) char lds[kDqTiles * BKV * D * 2];
+  dq_block<D, F16S, 8, 1>(p.qkv, p.qk16, p.dout, p.k_img, p.lse, p.delta, p.dqkv, p.S, p.a, gridDim.z - 1 - blockIdx.z, lds);
+}
+// Both sides in one launch, 32 RW rows per workgroup and two waves per block of 32: the form for few
+// workgroups.  Even z: key block z/2; odd z: the query blocks from the last one down (heaviest first).
+template <int D, bool F16S, int RW>
+__global__ __launch_bounds__(128 * RW) void attn_bwd_split_mfma_kernel(const BwdArgs p) {
+  __shared__ __attribute__((aligned(1024))) char lds[kDkvTiles * BKV * D * 2];
+  __shared__ __attribute__((aligned(256))) float stat[2][2][BKV];
+  const int i = blockIdx.z >> 1;
+  if ((blockIdx.z & 1) == 0)
+    dkv_block<D, F16S, RW, 2>(p.qkv, p.qk16, p.dout, p.q_img, p.do_img, p.lse, p.delta, p.dqkv, p.S, p.a, i, lds, stat);
+  else
+    dq_block<D, F16S, RW, 2>(p.qkv, p.qk16, p.dout, p.k_img, p.lse, p.delta, p.dqkv, p.S, p.a, (int)(gridDim.z >> 1) - 1 - i, lds);
+}
+
 size_t image_bytes(int B, int S, int a, int d) {
   return (size_t)B * a * ((S + BKV - 1) / BKV) * (size_t)(d * BKV) * 2;
 }
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-template <int D>
+template <int D, bool O16 = false>
 void launch_timage(const TImageArgs& t, int B, int S, int a, hipStream_t st) {
   dim3 g((S + BKV - 1) / BKV, a, B * t.n_src);
-  hipLaunchKernelGGL(attn_timage_kernel<D>, g, dim3(256), 0, st, t, S, a);
+  hipLaunchKernelGGL((attn_timage_kernel<D, O16>), g, dim3(256), 0, st, t, S, a);
+}
+
+// How the rows go over the workgroups.  A workgroup walks its rows' half of the other side tile by
+// tile, so with few workgroups the time is that chain; fewer rows per workgroup and two waves per 32
+// rows, which share a tile, shorten it, at the price of streaming each tile for fewer rows.
+// Measured (us; forward 128 rows, one wave per 32 | 64 rows, two waves; backward 256 rows, two launches
+// | 128 rows | 64 rows, one launch):
+//   heads S    D    wg    forward       backward           (wg: workgroups of 256 rows)
+//      5  192  64   10    8.1 |  7.7    22.0 | 13.3 | 11.8   (batch 2)
+//     16  512  64   32   13.2 | 11.1    44.0 | 22.0 | 20.4
+//      2 8192 128   64    174 |  126     712 |  249 |  316
+//     16 2048 128  128   55.3 | 45.5     203 | 99.5 |  176
+//     16 1984 128  256   60.4 | 57.3     207 |  172 |  285   (batch 2)
+//     40 2048 128  320   66.3 | 75.3     227 |  228 |  397
+//     12  333  32  384   13.3 | 13.2    41.8 | 32.3 | 31.9   (batch 16)
+//     32 4096 128  512    162 |  191     507 |  604 | 1083
+// So the split forms up to about one workgroup of 256 rows per compute unit (somewhat longer at head
+// dimension 32, whose workgroups share a unit), and 64 rows in backward only where even those leave
+// every workgroup a unit of its own.
+long row_blocks(int B, int S, int a, int rows) { return (long)a * B * ((S + rows - 1) / rows); }
+bool split_fwd(int B, int S, int a) { return row_blocks(B, S, a, 256) <= 256; }
+int split_rows_bwd(int B, int S, int a, int d) {
+  if (2 * row_blocks(B, S, a, 64) <= 256) return 64;
+  return row_blocks(B, S, a, 256) <= (d == 32 ? 448 : 288) ? 128 : 0;
+}
+
+template <int D, bool F16>
+void launch_fwd(const bf16* qkv, const bf16* vimg, bf16* out, float* lse, int B, int S, int a, hipStream_t st) {
+  auto grid = [&](int rows) { return dim3(a, B, (S + rows - 1) / rows); };
+  if (split_fwd(B, S, a)) hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 2, 2>), grid(64), dim3(256), 0, st, qkv, vimg, out, lse, S, a);
+  else hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 4, 1>), grid(128), dim3(256), 0, st, qkv, vimg, out, lse, S, a);
+}
+
+template <int D, bool F16> void launch_bwd(const TImageArgs& t, const BwdArgs& p, int B, hipStream_t st) {
+  launch_timage<D, F16>(t, B, p.S, p.a, st);
+  auto grid = [&](int rows, int sides) { return dim3(p.a, B, sides * ((p.S + rows - 1) / rows)); };
+  const int rows = split_rows_bwd(B, p.S, p.a, D);
+  if (rows == 64) {
+    hipLaunchKernelGGL((attn_bwd_split_mfma_kernel<D, F16, 2>), grid(64, 2), dim3(256), 0, st, p);
+  } else if (rows == 128) {
+    hipLaunchKernelGGL((attn_bwd_split_mfma_kernel<D, F16, 4>), grid(128, 2), dim3(512), 0, st, p);
+  } else {
+    hipLaunchKernelGGL((attn_bwd_dkv_mfma_kernel<D, F16>), grid(256, 1), dim3(512), 0, st, p);
+    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<D, F16>), grid(256, 1), dim3(512), 0, st, p);
+  }
 }
 
 }  // namespace
@@ -761,32 +889,18 @@ hipError_t attention_fwd_mfma(int B, int S, int a, int d, const void* qkv, void*
   t.src[0] = q + 2 * P;
   t.ld[0] = 3 * (size_t)P;
   t.dst[0] = vimg;
-  dim3 g(a, B, (S + BQ - 1) / BQ), blk(256);
   // the image kernel only moves 16-bit values, so it serves fp16 as it serves bf16
-  if (d == 128) {
-    launch_timage<128>(t, B, S, a, st);
-    if (f16) hipLaunchKernelGGL((attn_fwd_mfma_kernel<128, true>), g, blk, 0, st, q, vimg, (bf16*)out, lse, S, a);
-    else hipLaunchKernelGGL((attn_fwd_mfma_kernel<128, false>), g, blk, 0, st, q, vimg, (bf16*)out, lse, S, a);
-  } else if (d == 64) {
-    launch_timage<64>(t, B, S, a, st);
-    if (f16) hipLaunchKernelGGL((attn_fwd_mfma_kernel<64, true>), g, blk, 0, st, q, vimg, (bf16*)out, lse, S, a);
-    else hipLaunchKernelGGL((attn_fwd_mfma_kernel<64, false>), g, blk, 0, st, q, vimg, (bf16*)out, lse, S, a);
-  } else {
-    launch_timage<32>(t, B, S, a, st);
-    if (f16) hipLaunchKernelGGL((attn_fwd_mfma_kernel<32, true>), g, blk, 0, st, q, vimg, (bf16*)out, lse, S, a);
-    else hipLaunchKernelGGL((attn_fwd_mfma_kernel<32, false>), g, blk, 0, st, q, vimg, (bf16*)out, lse, S, a);
-  }
+#define GPTS_FWD(D)                                                                                        \
+  do {                                                                                                     \
+    launch_timage<D>(t, B, S, a, st);                                                                      \
+    if (f16) launch_fwd<D, true>(q, vimg, (bf16*)out, lse, B, S, a, st);                                   \
+    else launch_fwd<D, false>(q, vimg, (bf16*)out, lse, B, S, a, st);                                      \
+  } while (0)
+  if (d == 128) GPTS_FWD(128);
+  else if (d == 64) GPTS_FWD(64);
+  else GPTS_FWD(32);
+#undef GPTS_FWD
   return hipGetLastError();
-}
-
-template <int D, bool F16>
-static void launch_bwd(dim3 gd, dim3 gw, const TImageArgs& t, int B, int S, int a, int total, const bf16* q,
-                const bf16* q16, const bf16* o, const bf16* g, bf16* qimg, bf16* kimg, bf16* doimg,
-                const float* lse, float* delta, bf16* dq, hipStream_t st) {
-  hipLaunchKernelGGL((attn_delta_kernel<D, F16>), gd, dim3(256), 0, st, o, g, delta, S, a, total);
-  launch_timage<D>(t, B, S, a, st);
-  hipLaunchKernelGGL((attn_bwd_dkv_mfma_kernel<D, F16>), gw, dim3(512), 0, st, q, q16, g, qimg, doimg, lse, delta, dq, S, a);
-  hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<D, F16>), gw, dim3(512), 0, st, q, q16, g, kimg, lse, delta, dq, S, a);
 }
 
 hipError_t attention_bwd_mfma(int B, int S, int a, int d, const void* qkv, const void* out,
@@ -801,25 +915,25 @@ hipError_t attention_bwd_mfma(int B, int S, int a, int d, const void* qkv, const
   bf16* kimg = reinterpret_cast<bf16*>(reinterpret_cast<char*>(qimg) + img);
   bf16* doimg = reinterpret_cast<bf16*>(reinterpret_cast<char*>(kimg) + img);
   const bf16* q = (const bf16*)qkv;
-  const bf16* o = (const bf16*)out;
   const bf16* g = (const bf16*)dout;
-  bf16* dq = (bf16*)dqkv;
   TImageArgs t{};
   t.n_src = 3;
   t.src[0] = q;         t.ld[0] = 3 * (size_t)P; t.dst[0] = qimg;
   t.src[1] = q + P;     t.ld[1] = 3 * (size_t)P; t.dst[1] = kimg;
   t.src[2] = g;         t.ld[2] = (size_t)P;     t.dst[2] = doimg;
-  dim3 gd((unsigned)(((size_t)total * 16 + 255) / 256)), gw(a, B, (S + BW - 1) / BW);
-  const bf16* q16 = (const bf16*)qkv_f16;
+  t.out = (const bf16*)out;
+  t.delta = delta;
+  const bool f16 = qkv_f16 != nullptr;
+  const BwdArgs p{q, f16 ? (const bf16*)qkv_f16 : q, g, qimg, kimg, doimg, lse, delta, (bf16*)dqkv, S, a};
   if (d == 128) {
-    if (q16) launch_bwd<128, true>(gd, gw, t, B, S, a, total, q, q16, o, g, qimg, kimg, doimg, lse, delta, dq, st);
-    else launch_bwd<128, false>(gd, gw, t, B, S, a, total, q, q, o, g, qimg, kimg, doimg, lse, delta, dq, st);
+    if (f16) launch_bwd<128, true>(t, p, B, st);
+    else launch_bwd<128, false>(t, p, B, st);
   } else if (d == 64) {
-    if (q16) launch_bwd<64, true>(gd, gw, t, B, S, a, total, q, q16, o, g, qimg, kimg, doimg, lse, delta, dq, st);
-    else launch_bwd<64, false>(gd, gw, t, B, S, a, total, q, q, o, g, qimg, kimg, doimg, lse, delta, dq, st);
+    if (f16) launch_bwd<64, true>(t, p, B, st);
+    else launch_bwd<64, false>(t, p, B, st);
   } else {
-    if (q16) launch_bwd<32, true>(gd, gw, t, B, S, a, total, q, q16, o, g, qimg, kimg, doimg, lse, delta, dq, st);
-    else launch_bwd<32, false>(gd, gw, t, B, S, a, total, q, q, o, g, qimg, kimg, doimg, lse, delta, dq, st);
+    if (f16) launch_bwd<32, true>(t, p, B, st);
+    else launch_bwd<32, false>(t, p, B, st);
   }
   return hipGetLastError();
 }

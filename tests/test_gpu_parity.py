@@ -645,6 +645,39 @@ def _attention_op(dt, Bn, S, a, d, qkv, dout):
     return out, lse, dqkv
 
 
+@pytest.mark.parametrize("Bn,S,a,d", [(1, 1, 1, 32), (1, 31, 2, 64), (2, 33, 3, 128), (1, 65, 3, 32), (1, 97, 2, 64), (1, 129, 2, 128),
+                                      (3, 320, 14, 64), (1, 1000, 9, 128), (1, 257, 130, 32), (1, 260, 150, 64), (1, 130, 300, 128)])
+def test_op_attention_bf16_splits(Bn, S, a, d):
+    """The arrangements of the bf16 attention kernels at the edges of their blocks (32, 64, 128, 256 rows): the
+    first six take 64 rows and two waves per 32 throughout, then backward with 128 rows, and the last two
+    one wave per 32 rows in both directions.  Against fp64 on the same inputs; probabilities, dS and the
+    outputs are rounded to bf16 (2^-9 each), so 2-norm errors stay within 2^-7 and single values within 2^-4
+    of the largest."""
+    print(f"[case] attention splits B={Bn} S={S} a={a} d={d}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(S * a + d)
+    qkv = torch.empty(Bn, S, 3 * a * d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    dout = torch.empty(Bn, S, a * d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    out, dqkv = torch.full_like(dout, 7.0), torch.full_like(qkv, 7.0)
+    lse = torch.full((Bn, a, S), 7.0, dtype=torch.float32, device="cuda")
+    scratch = [torch.empty(max(B.gpt_stage_op_attention_scratch_bytes(B.GPTS_BF16, Bn, S, a, d, ph), 256),
+                           dtype=torch.uint8, device="cuda") for ph in (0, 1)]
+    B.gpt_stage_op_attention_fwd(B.GPTS_BF16, Bn, S, a, d, qkv, out, lse, scratch[0])
+    B.gpt_stage_op_attention_bwd(B.GPTS_BF16, Bn, S, a, d, qkv, out, lse, dout, dqkv, scratch[1])
+    masked = torch.ones(S, S, dtype=torch.bool, device="cuda").triu(1)
+    for b in range(Bn):
+        x = qkv[b].double().requires_grad_()
+        q, k, v = (t.reshape(S, a, d).transpose(0, 1).contiguous() for t in x.split(a * d, dim=1))
+        s = torch.stack([q[n] @ k[n].t() for n in range(a)]) / d ** 0.5
+        s = s.masked_fill(masked, float("-inf"))
+        o = torch.stack([torch.softmax(s[n], -1) @ v[n] for n in range(a)]).transpose(0, 1).reshape(S, a * d)
+        o.backward(dout[b].double())
+        assert (lse[b].double() - torch.logsumexp(s.detach(), -1)).abs().max().item() < 1e-5
+        for got, want in ((out[b].double(), o.detach()), (dqkv[b].double(), x.grad)):
+            assert ((got - want).norm() / want.norm()).item() < 2 ** -7
+            assert (got - want).abs().max().item() < 2 ** -4 * want.abs().max().item()
+
+
 @pytest.mark.parametrize("Bn,S,a,d", [(1, 1, 1, 32), (2, 15, 2, 64), (1, 16, 2, 128), (2, 17, 3, 32), (1, 63, 1, 128),
                                       (1, 65, 2, 64), (2, 130, 2, 32)])
 def test_op_attention_fp32_edges(Bn, S, a, d):
