@@ -1,8 +1,8 @@
 // HBM-bound kernels of the stage: LayerNorm forward/backward (with the residual
 // gradient and the bias gradient of the preceding linear layer folded in), column sums
 // for the other bias gradients, and the fixed-order reduction of per-workgroup partial
-// sums.  One workgroup per token row at a time (256 threads forward, 512 backward),
-// 16-byte loads, the row cached in registers, fp32 statistics.
+// sums.  A token row belongs to one wave where it fits its registers (then without a barrier), else to
+// a whole workgroup; 16-byte loads, the row cached in registers, fp32 statistics.
 #include "../../include/gpt_stage.h"
 
 #include <mutex>
@@ -49,35 +49,65 @@ __device__ __forceinline__ void store8(bf16* p, const float (&v)[8]) {
   *reinterpret_cast<bf16x8*>(p) = a;
 }
 
+// 8 consecutive elements kept as they are stored (half the registers for 16-bit types)
+template <typename T> struct Raw8 {
+  typedef T v8 __attribute__((ext_vector_type(8)));
+  v8 v;
+  __device__ __forceinline__ void load(const T* p) { v = *reinterpret_cast<const v8*>(p); }
+  __device__ __forceinline__ float get(int e) const { return (float)v[e]; }
+};
+template <> struct Raw8<float> {
+  f32x4 a, b;
+  __device__ __forceinline__ void load(const float* p) {
+    a = *reinterpret_cast<const f32x4*>(p);
+    b = *reinterpret_cast<const f32x4*>(p + 4);
+  }
+  __device__ __forceinline__ float get(int e) const { return e < 4 ? a[e] : b[e - 4]; }
+};
+
 // ----------------------------------------------------------------- LN fwd ----
 // Per token: mu = mean(x), var = mean((x-mu)^2), r = 1/sqrt(var+eps),
 // out = (x-mu) r gamma + beta.  TX = type of x (the residual stream, fp32 inside
 // bf16 stages), T = type of gamma/beta, TO = type of out (T, or fp16 when the forward
-// activations of a bf16 stage are kept in fp16).  NCH = 8-element chunks per thread.
-template <typename TX, typename T, typename TO, int NCH>
+// activations of a bf16 stage are kept in fp16).  RW = waves per row (1: four rows per
+// workgroup, no barrier; 4), NCH = 8-element chunks per lane.  xcopy (may be null): x as fp32, the
+// first layer's own copy of the stage input.
+// Bound by HBM from some thousand rows on, by launch and latency below.  With a wave per row instead of a
+// workgroup, whose threads were half idle: 8192 rows of 512 9.7 -> 7.4 us, of 768 10.9 -> 7.7 us,
+// 3968 of 2048 9.7 -> 8.7 us.
+template <typename TX, typename T, typename TO, int NCH, int RW>
 __global__ __launch_bounds__(kLnThreads) void ln_fwd_kernel(
-    const TX* __restrict__ x, const T* __restrict__ gamma, const T* __restrict__ beta,
-    TO* __restrict__ out, float* __restrict__ mean, float* __restrict__ rstd, int H, float eps) {
-  __shared__ float red[2][kLnThreads / kWave];
-  const int row = blockIdx.x;
+    const TX* __restrict__ x, const T* __restrict__ gamma, const T* __restrict__ beta, TO* __restrict__ out,
+    float* __restrict__ mean, float* __restrict__ rstd, float* __restrict__ xcopy, int T_rows, int H, float eps) {
+  constexpr int NWV = kLnThreads / kWave, NT = RW * kWave;   // NT: threads of a row
+  static_assert(RW == 1 || RW == NWV, "a wave or the workgroup per row");
+  __shared__ float red[2][NWV];
+  const int t = threadIdx.x % NT;
+  const int row = blockIdx.x * (NWV / RW) + threadIdx.x / NT;
+  if (RW == 1 && row >= T_rows) return;
   const int nvec = H / 8;
   const TX* xr = x + (size_t)row * H;
   float xv[NCH][8];
   float s = 0.f;
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    const int i = threadIdx.x + c * kLnThreads;
+    const int i = t + c * NT;
+    if (i < nvec) load8(xr + (size_t)i * 8, xv[c]);
+  }
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    const int i = t + c * NT;
     if (i < nvec) {
-      load8(xr + (size_t)i * 8, xv[c]);
+      if (xcopy) store8(xcopy + (size_t)row * H + (size_t)i * 8, xv[c]);
 #pragma unroll
       for (int e = 0; e < 8; ++e) s += xv[c][e];
     }
   }
-  const float mu = block_sum<kLnThreads / kWave>(s, red[0]) / (float)H;
+  const float mu = block_sum<RW>(s, red[0]) / (float)H;
   float q = 0.f;
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    const int i = threadIdx.x + c * kLnThreads;
+    const int i = t + c * NT;
     if (i < nvec) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -86,12 +116,12 @@ __global__ __launch_bounds__(kLnThreads) void ln_fwd_kernel(
       }
     }
   }
-  const float var = block_sum<kLnThreads / kWave>(q, red[1]) / (float)H;
+  const float var = block_sum<RW>(q, red[1]) / (float)H;
   const float r = 1.f / sqrtf(var + eps);
   TO* orow = out + (size_t)row * H;
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    const int i = threadIdx.x + c * kLnThreads;
+    const int i = t + c * NT;
     if (i < nvec) {
       float g[8], b[8], o[8];
       load8(gamma + (size_t)i * 8, g);
@@ -101,7 +131,7 @@ __global__ __launch_bounds__(kLnThreads) void ln_fwd_kernel(
       store8(orow + (size_t)i * 8, o);
     }
   }
-  if (threadIdx.x == 0) {
+  if (t == 0) {
     mean[row] = mu;
     rstd[row] = r;
   }
@@ -110,75 +140,91 @@ __global__ __launch_bounds__(kLnThreads) void ln_fwd_kernel(
 // ----------------------------------------------------------------- LN bwd ----
 // Per token, with xhat = (x-mu) r and g = dout*gamma:
 //   dx = dres + r (g - mean(g) - xhat mean(g xhat)).
-// Each workgroup walks rows blockIdx.x, +gridDim.x, ... and keeps its share of
-// sum_t dout*xhat and sum_t dout in registers; it writes them once to
-// partial[blockIdx.x][0][H] / [1][H] for the fixed-order reduction below.  With DXSUM it
-// also keeps the column sums of dx as stored (partial[blockIdx.x][2][H]): dx is the
+// A workgroup's 8 waves form 8/RW groups of RW waves, a row per group at a time; each group keeps its
+// share of sum_t dout*xhat and sum_t dout in registers, the groups add up through LDS in fixed order
+// at the end, and the workgroup writes partial[blockIdx.x][0][H] / [1][H] for the reduction below.
+// With DXSUM it also keeps the column sums of dx as stored (partial[blockIdx.x][2][H]): dx is the
 // gradient of the output of the linear layer in front of the residual branch, so these
 // are that layer's bias gradient, which then needs no pass of its own over dx.
+// Bound by HBM, and by the partial sums where rows are short.  A wave per row up to 1024 columns (no
+// barrier, no idle threads, an eighth of the partial sums): 4096 rows of 1024 with the reduction
+// 23.1 -> 12.8 us, 8192 of 512 30.4 -> 11.7 us; 3968 of 2048 26.6 -> 20.7 us; 16-bit operands kept
+// packed and rows up to 12288 in three chunks, prefetched: 2048 of 12288 95.5 -> 65.3 us (3.9 TB/s).
 constexpr int kLnBwdThreads = 512;
-// workgroups of the backward kernel (measured at 4096 rows of 4096: 256 -> 42.6 us, 512 -> 39.6,
-// 1024 -> 50.2: more workgroups put more rows in flight but each writes its own partial sums)
-#ifndef GPTS_LN_BWD_BLOCKS
-#define GPTS_LN_BWD_BLOCKS 512
-#endif
-constexpr int kLnBwdMaxBlocks = GPTS_LN_BWD_BLOCKS;
+// Workgroups: 512 for rows of a whole workgroup (measured at 4096 rows of 4096: 256 -> 42.6 us,
+// 512 -> 39.6, 1024 -> 50.2: more workgroups put more rows in flight but each writes its own partial
+// sums), 256 where a workgroup has several rows in flight.
+constexpr int kLnBwdMaxBlocks = 512, kLnBwdMaxBlocksGroups = 256;
+int ln_bwd_row_waves(int H) { return H <= 1024 ? 1 : (H <= 2048 ? 4 : 8); }
+int ln_bwd_blocks(int T_rows, int H) {
+  const int groups = kLnBwdThreads / kWave / ln_bwd_row_waves(H), most = groups == 1 ? kLnBwdMaxBlocks : kLnBwdMaxBlocksGroups;
+  const int need = (T_rows + groups - 1) / groups;
+  return need < most ? need : most;
+}
 
-template <typename TX, typename T, int NCH, bool DXSUM>
+template <typename TX, typename T, int NCH, int RW, bool DXSUM>
 __global__ __launch_bounds__(kLnBwdThreads) void ln_bwd_kernel(
     const T* __restrict__ dout, const TX* __restrict__ x, const float* __restrict__ mean,
     const float* __restrict__ rstd, const T* __restrict__ gamma, const T* __restrict__ dres,
     T* __restrict__ dx, float* __restrict__ partial, int T_rows, int H) {
-  // One barrier per row: the two row sums are reduced together and the LDS slots alternate
+  // At most one barrier per row: the two row sums are reduced together and the LDS slots alternate
   // between rows, so a row's writes cannot overtake the previous row's reads.  The loads of
   // the next row (when the row fits few registers) and of the residual gradient are issued
   // before the barrier, so that memory latency overlaps the reduction.
-  constexpr int NT = kLnBwdThreads, NWV = NT / kWave, NPART = DXSUM ? 3 : 2;
-  constexpr bool PREFETCH = NCH <= 2;
+  constexpr int NWV = kLnBwdThreads / kWave, GR = NWV / RW, NT = RW * kWave, NPART = DXSUM ? 3 : 2;
+  constexpr bool PREFETCH = NCH <= 3;   // 168 registers at three chunks; a fourth would spill
   __shared__ float red[2][2][NWV];
+  __shared__ __attribute__((aligned(16))) float comb[GR > 1 ? GR * NT * NCH * 8 : 1];
   const int nvec = H / 8;
-  const int wv = threadIdx.x / kWave;
-  float dg[NCH][8], db[NCH][8], dc[DXSUM ? NCH : 1][8], gam[NCH][8];
+  const int wv = threadIdx.x / kWave, grp = wv / RW, t = threadIdx.x % NT;
+  float dg[NCH][8], db[NCH][8], dc[DXSUM ? NCH : 1][8];
+  Raw8<T> gam[NCH];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    const int i = threadIdx.x + c * NT;
-    if (i < nvec) load8(gamma + (size_t)i * 8, gam[c]);
+    const int i = t + c * NT;
+    if (i < nvec) gam[c].load(gamma + (size_t)i * 8);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       dg[c][e] = db[c][e] = 0.f;
       if constexpr (DXSUM) dc[c][e] = 0.f;
     }
   }
-  float dv[NCH][8], xh[NCH][8], dvn[PREFETCH ? NCH : 1][8], xn[PREFETCH ? NCH : 1][8];
-  auto load_row = [&](int row, float (&d)[NCH][8], float (&xx)[NCH][8]) {
+  Raw8<T> dv[NCH], dvn[PREFETCH ? NCH : 1];
+  float xh[NCH][8], xn[PREFETCH ? NCH : 1][8];
+  auto load_row = [&](int row, Raw8<T>(&d)[NCH], float (&xx)[NCH][8]) {
     const size_t base = (size_t)row * H;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const int i = threadIdx.x + c * NT;
+      const int i = t + c * NT;
       if (i < nvec) {
-        load8(dout + base + (size_t)i * 8, d[c]);
+        d[c].load(dout + base + (size_t)i * 8);
         load8(x + base + (size_t)i * 8, xx[c]);
       }
     }
   };
+  const int step = gridDim.x * GR;
   if constexpr (PREFETCH) {
-    if ((int)blockIdx.x < T_rows) load_row(blockIdx.x, dv, xh);
+    if ((int)blockIdx.x * GR + grp < T_rows) load_row(blockIdx.x * GR + grp, dv, xh);
   }
   int buf = 0;
-  for (int row = blockIdx.x; row < T_rows; row += gridDim.x, buf ^= 1) {
-    if constexpr (!PREFETCH) load_row(row, dv, xh);
-    const float mu = mean[row], r = rstd[row];
+  for (int first = blockIdx.x * GR; first < T_rows; first += step, buf ^= 1) {
+    const int row = first + grp;
+    const bool on = GR == 1 || row < T_rows;      // the groups of a workgroup meet at the barriers together
+    if constexpr (!PREFETCH) {
+      if (on) load_row(row, dv, xh);
+    }
+    const float mu = on ? mean[row] : 0.f, r = on ? rstd[row] : 0.f;
     const size_t base = (size_t)row * H;
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const int i = threadIdx.x + c * NT;
-      if (i < nvec) {
+      const int i = t + c * NT;
+      if (on && i < nvec) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float d = dv[c][e];
+          const float d = dv[c].get(e);
           xh[c][e] = (xh[c][e] - mu) * r;
-          const float g = d * gam[c][e];
+          const float g = d * gam[c].get(e);
           s1 += g;
           s2 += g * xh[c][e];
           dg[c][e] += d * xh[c][e];
@@ -188,40 +234,43 @@ __global__ __launch_bounds__(kLnBwdThreads) void ln_bwd_kernel(
     }
     s1 = wave_sum(s1);
     s2 = wave_sum(s2);
-    if ((threadIdx.x & (kWave - 1)) == 0) {
+    if (RW > 1 && (threadIdx.x & (kWave - 1)) == 0) {
       red[buf][0][wv] = s1;
       red[buf][1][wv] = s2;
     }
-    float rs[NCH][8];
+    Raw8<T> rs[NCH];
     if (dres) {
 #pragma unroll
       for (int c = 0; c < NCH; ++c) {
-        const int i = threadIdx.x + c * NT;
-        if (i < nvec) load8(dres + base + (size_t)i * 8, rs[c]);
+        const int i = t + c * NT;
+        if (on && i < nvec) rs[c].load(dres + base + (size_t)i * 8);
       }
     }
     if constexpr (PREFETCH) {
-      const int nxt = row + gridDim.x;
+      const int nxt = row + step;
       if (nxt < T_rows) load_row(nxt, dvn, xn);
     }
-    __syncthreads();
-    float m1 = 0.f, m2 = 0.f;
+    float m1 = s1, m2 = s2;
+    if constexpr (RW > 1) {
+      __syncthreads();
+      m1 = m2 = 0.f;
 #pragma unroll
-    for (int i = 0; i < NWV; ++i) {
-      m1 += red[buf][0][i];
-      m2 += red[buf][1][i];
+      for (int i = 0; i < RW; ++i) {
+        m1 += red[buf][0][grp * RW + i];
+        m2 += red[buf][1][grp * RW + i];
+      }
     }
     m1 /= (float)H;
     m2 /= (float)H;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const int i = threadIdx.x + c * NT;
-      if (i < nvec) {
+      const int i = t + c * NT;
+      if (on && i < nvec) {
         float o[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          float v = r * (dv[c][e] * gam[c][e] - m1 - xh[c][e] * m2);
-          if (dres) v += rs[c][e];
+          float v = r * (dv[c].get(e) * gam[c].get(e) - m1 - xh[c][e] * m2);
+          if (dres) v += rs[c].get(e);
           o[e] = v;
           if constexpr (DXSUM) dc[c][e] += (float)(T)v;
         }
@@ -230,60 +279,88 @@ __global__ __launch_bounds__(kLnBwdThreads) void ln_bwd_kernel(
     }
     if constexpr (PREFETCH) {
 #pragma unroll
-      for (int c = 0; c < NCH; ++c)
+      for (int c = 0; c < NCH; ++c) {
+        dv[c] = dvn[c];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          dv[c][e] = dvn[c][e];
-          xh[c][e] = xn[c][e];
-        }
+        for (int e = 0; e < 8; ++e) xh[c][e] = xn[c][e];
+      }
     }
   }
   float* pg = partial + (size_t)blockIdx.x * NPART * H;
+  auto write_part = [&](float (&v)[NCH][8], int part) {
+    if constexpr (GR == 1) {
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int i = threadIdx.x + c * NT;
-    if (i < nvec) {
-      store8(pg + (size_t)i * 8, dg[c]);
-      store8(pg + (size_t)H + (size_t)i * 8, db[c]);
-      if constexpr (DXSUM) store8(pg + (size_t)2 * H + (size_t)i * 8, dc[c]);
+      for (int c = 0; c < NCH; ++c) {
+        const int i = t + c * NT;
+        if (i < nvec) store8(pg + (size_t)part * H + (size_t)i * 8, v[c]);
+      }
+    } else {
+      constexpr int PITCH = NT * NCH * 8;   // floats of a group's sums
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) store8(comb + grp * PITCH + (t + c * NT) * 8, v[c]);
+      __syncthreads();
+      for (int i = threadIdx.x * 4; i < H; i += kLnBwdThreads * 4) {
+        f32x4 a = *reinterpret_cast<const f32x4*>(comb + i);
+#pragma unroll
+        for (int k = 1; k < GR; ++k) a += *reinterpret_cast<const f32x4*>(comb + k * PITCH + i);
+        *reinterpret_cast<f32x4*>(pg + (size_t)part * H + i) = a;
+      }
     }
-  }
+  };
+  write_part(dg, 0);
+  write_part(db, 1);
+  if constexpr (DXSUM) write_part(dc, 2);
 }
 
-// out[i] = (float) in[i]   (stage input -> fp32 residual stream), 8 elements per thread
-__global__ __launch_bounds__(256) void widen_kernel(const bf16* __restrict__ in, float* __restrict__ out,
-                                                    size_t n8) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n8) return;
-  float v[8];
-  load8(in + i * 8, v);
-  store8(out + i * 8, v);
-}
-
-// out[c] += sum_{g<G} partial[g*stride + c], the columns c < N being split at N0 and N1
-// over out0 (c < N0), out1 (N0 <= c < N1) and out2 (N1 <= c).  32 columns x 32 row groups per
-// workgroup; the row groups are combined through LDS in fixed order, so the result is
-// deterministic.
-__global__ __launch_bounds__(1024) void reduce_partials_kernel(const float* __restrict__ partial, int G,
-                                                               size_t stride, int N, float* __restrict__ out0,
-                                                               int N0, float* __restrict__ out1, int N1,
-                                                               float* __restrict__ out2) {
+// For every segment: out[c] += sum_{g<G} partial[g*stride + c], c < N, see ReduceSeg.  32 columns x
+// 32 row groups per workgroup, four columns per load; the row groups are combined through LDS in fixed
+// order, so the result is deterministic.  One launch takes all the bias and LayerNorm gradients of a
+// layer: each is a few microseconds of launch and latency whatever its size (16 rows: 2.4 us).
+struct ReduceArgs {
+  ReduceSeg seg[kMaxReduceSegs];
+  int first[kMaxReduceSegs + 1];   // first workgroup of a segment
+};
+__global__ __launch_bounds__(256) void reduce_partials_kernel(const ReduceArgs args) {
   __shared__ float sm[32][33];
-  const int cx = threadIdx.x & 31, ry = threadIdx.x >> 5;
-  const int c = blockIdx.x * 32 + cx;
-  float s = 0.f;
-  if (c < N)
-    for (int g = ry; g < G; g += 32) s += partial[(size_t)g * stride + c];
-  sm[ry][cx] = s;
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxReduceSegs; ++i)
+    if ((int)blockIdx.x >= args.first[i]) k = i;
+  const ReduceSeg& sg = args.seg[k];
+  const int col0 = (blockIdx.x - args.first[k]) * 32;
+  const int cq = threadIdx.x & 7, ry = threadIdx.x >> 3, c4 = col0 + cq * 4;
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  if (c4 < sg.N) {
+#pragma unroll 4
+    for (int g = ry; g < sg.G; g += 32) s += *reinterpret_cast<const f32x4*>(sg.partial + (size_t)g * sg.stride + c4);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) sm[ry][cq * 4 + e] = s[e];
   __syncthreads();
-  if (ry == 0 && c < N) {
+  const int c = col0 + threadIdx.x;
+  if (threadIdx.x < 32 && c < sg.N) {
     float t = 0.f;
 #pragma unroll
-    for (int i = 0; i < 32; ++i) t += sm[i][cx];
-    if (c < N0) out0[c] += t;
-    else if (c < N1) out1[c - N0] += t;
-    else out2[c - N1] += t;
+    for (int i = 0; i < 32; ++i) t += sm[i][threadIdx.x];
+    if (c < sg.n0) sg.out0[c] += t;
+    else if (c < sg.n1) sg.out1[c - sg.n0] += t;
+    else sg.out2[c - sg.n1] += t;
   }
+}
+
+hipError_t reduce_partials(const ReduceSeg* segs, int n, hipStream_t st) {
+  if (n < 1 || n > kMaxReduceSegs) return hipErrorInvalidValue;
+  ReduceArgs a{};
+  int blocks = 0;
+  for (int i = 0; i < kMaxReduceSegs; ++i) {
+    a.first[i] = i < n ? blocks : 0x7fffffff;      // (never reached)
+    if (i >= n) continue;
+    a.seg[i] = segs[i];
+    blocks += (segs[i].N + 31) / 32;
+  }
+  hipLaunchKernelGGL(reduce_partials_kernel, dim3(blocks), dim3(256), 0, st, a);
+  return hipGetLastError();
 }
 
 // ----------------------------------------------------------------- colsum ----
@@ -322,86 +399,78 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict
 
 // --------------------------------------------------------------- launchers ----
 template <typename TX, typename T, typename TO>
-static hipError_t ln_fwd_t(int T_rows, int H, float eps, const TX* x, const T* gamma, const T* beta,
-                           TO* out, float* mean, float* rstd, hipStream_t st) {
-  const int nch = (H / 8 + kLnThreads - 1) / kLnThreads;
-  dim3 g(T_rows), b(kLnThreads);
-#define GPTS_LN_FWD(N)                                                                           \
-  hipLaunchKernelGGL((ln_fwd_kernel<TX, T, TO, N>), g, b, 0, st, x, gamma, beta, out, mean, rstd, H, eps)
-  if (nch <= 1) GPTS_LN_FWD(1);
-  else if (nch <= 2) GPTS_LN_FWD(2);
-  else if (nch <= 4) GPTS_LN_FWD(4);
-  else GPTS_LN_FWD(8);
+static hipError_t ln_fwd_t(int T_rows, int H, float eps, const void* x, const void* gamma, const void* beta,
+                           void* out, float* mean, float* rstd, float* xcopy, hipStream_t st) {
+#define GPTS_LN_FWD(N, RW)                                                                                        \
+  hipLaunchKernelGGL((ln_fwd_kernel<TX, T, TO, N, RW>), dim3(RW == 1 ? (T_rows + 3) / 4 : T_rows), dim3(kLnThreads), 0, st, \
+                     (const TX*)x, (const T*)gamma, (const T*)beta, (TO*)out, mean, rstd, xcopy, T_rows, H, eps)
+  // a wave per row up to 2048 columns (32 registers a lane), a workgroup beyond
+  if (H <= 512) GPTS_LN_FWD(1, 1);
+  else if (H <= 1024) GPTS_LN_FWD(2, 1);
+  else if (H <= 2048) GPTS_LN_FWD(4, 1);
+  else if (H <= 4096) GPTS_LN_FWD(2, 4);
+  else if (H <= 8192) GPTS_LN_FWD(4, 4);
+  else GPTS_LN_FWD(8, 4);
 #undef GPTS_LN_FWD
   return hipGetLastError();
 }
 
 hipError_t ln_fwd(int dtype, bool x_f32, int T_rows, int H, float eps, const void* x,
                   const void* gamma, const void* beta, void* out, float* mean, float* rstd,
-                  hipStream_t st, bool out_f16) {
+                  hipStream_t st, bool out_f16, float* xcopy) {
   if (dtype == 0) {
     if (out_f16) return hipErrorInvalidValue;
-    return ln_fwd_t<float, float, float>(T_rows, H, eps, (const float*)x, (const float*)gamma,
-                                         (const float*)beta, (float*)out, mean, rstd, st);
+    return ln_fwd_t<float, float, float>(T_rows, H, eps, x, gamma, beta, out, mean, rstd, xcopy, st);
   }
-  if (x_f32) {
-    if (out_f16)
-      return ln_fwd_t<float, bf16, f16>(T_rows, H, eps, (const float*)x, (const bf16*)gamma,
-                                        (const bf16*)beta, (f16*)out, mean, rstd, st);
-    return ln_fwd_t<float, bf16, bf16>(T_rows, H, eps, (const float*)x, (const bf16*)gamma,
-                                       (const bf16*)beta, (bf16*)out, mean, rstd, st);
-  }
-  if (out_f16) return hipErrorInvalidValue;
-  return ln_fwd_t<bf16, bf16, bf16>(T_rows, H, eps, (const bf16*)x, (const bf16*)gamma, (const bf16*)beta,
-                                    (bf16*)out, mean, rstd, st);
+  if (x_f32)
+    return out_f16 ? ln_fwd_t<float, bf16, f16>(T_rows, H, eps, x, gamma, beta, out, mean, rstd, xcopy, st)
+                   : ln_fwd_t<float, bf16, bf16>(T_rows, H, eps, x, gamma, beta, out, mean, rstd, xcopy, st);
+  return out_f16 ? ln_fwd_t<bf16, bf16, f16>(T_rows, H, eps, x, gamma, beta, out, mean, rstd, xcopy, st)
+                 : ln_fwd_t<bf16, bf16, bf16>(T_rows, H, eps, x, gamma, beta, out, mean, rstd, xcopy, st);
 }
 
-int ln_bwd_blocks(int T_rows) { return T_rows < kLnBwdMaxBlocks ? T_rows : kLnBwdMaxBlocks; }
-
 template <typename TX, typename T>
-static hipError_t ln_bwd_t(int T_rows, int H, const T* dout, const TX* x, const float* mean,
-                           const float* rstd, const T* gamma, const T* dres, T* dx, float* dgamma,
-                           float* dbeta, float* dxsum, float* partial, hipStream_t st) {
-  const int nch = (H / 8 + kLnBwdThreads - 1) / kLnBwdThreads;
-  const int G = ln_bwd_blocks(T_rows);
-  dim3 g(G), b(kLnBwdThreads);
-#define GPTS_LN_BWD(N)                                                                                  \
-  do {                                                                                                  \
-    if (dxsum)                                                                                          \
-      hipLaunchKernelGGL((ln_bwd_kernel<TX, T, N, true>), g, b, 0, st, dout, x, mean, rstd, gamma, dres, \
-                         dx, partial, T_rows, H);                                                       \
-    else                                                                                                \
-      hipLaunchKernelGGL((ln_bwd_kernel<TX, T, N, false>), g, b, 0, st, dout, x, mean, rstd, gamma,     \
-                         dres, dx, partial, T_rows, H);                                                 \
+static hipError_t ln_bwd_t(int T_rows, int H, const void* dout, const void* x, const float* mean,
+                           const float* rstd, const void* gamma, const void* dres, void* dx, bool dxsum,
+                           float* partial, hipStream_t st) {
+  const dim3 g(ln_bwd_blocks(T_rows, H)), b(kLnBwdThreads);
+#define GPTS_LN_BWD_(N, RW, SUM)                                                                                  \
+  hipLaunchKernelGGL((ln_bwd_kernel<TX, T, N, RW, SUM>), g, b, 0, st, (const T*)dout, (const TX*)x, mean, rstd,   \
+                     (const T*)gamma, (const T*)dres, (T*)dx, partial, T_rows, H)
+#define GPTS_LN_BWD(N, RW)                  \
+  do {                                      \
+    if (dxsum) GPTS_LN_BWD_(N, RW, true);   \
+    else GPTS_LN_BWD_(N, RW, false);        \
   } while (0)
-  if (nch <= 1) GPTS_LN_BWD(1);
-  else if (nch <= 2) GPTS_LN_BWD(2);
-  else if (nch <= 4) GPTS_LN_BWD(4);
-  else GPTS_LN_BWD(8);
+  if (H <= 512) GPTS_LN_BWD(1, 1);
+  else if (H <= 1024) GPTS_LN_BWD(2, 1);
+  else if (H <= 2048) GPTS_LN_BWD(1, 4);
+  else if (H <= 4096) GPTS_LN_BWD(1, 8);
+  else if (H <= 8192) GPTS_LN_BWD(2, 8);
+  else if (H <= 12288) GPTS_LN_BWD(3, 8);
+  else GPTS_LN_BWD(4, 8);
 #undef GPTS_LN_BWD
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int np = dxsum ? 3 : 2;
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3((np * H + 31) / 32), dim3(1024), 0, st, partial, G,
-                     (size_t)np * H, np * H, dgamma, H, dbeta, 2 * H, dxsum);
+#undef GPTS_LN_BWD_
   return hipGetLastError();
 }
 
+hipError_t ln_bwd_partials(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
+                           const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
+                           float* dgamma, float* dbeta, float* dxsum, float* partial, ReduceSeg* seg, hipStream_t st) {
+  if (H > 4 * 8 * kLnBwdThreads) return hipErrorInvalidValue;
+  const int np = dxsum ? 3 : 2;
+  *seg = ReduceSeg{partial, (size_t)np * H, ln_bwd_blocks(T_rows, H), np * H, H, 2 * H, dgamma, dbeta, dxsum};
+  if (dtype == 0) return ln_bwd_t<float, float>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, st);
+  if (x_f32) return ln_bwd_t<float, bf16>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, st);
+  return ln_bwd_t<bf16, bf16>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, st);
+}
 hipError_t ln_bwd(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
                   const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
                   float* dgamma, float* dbeta, float* dxsum, float* partial, hipStream_t st) {
-  if (H > 8 * 8 * kLnBwdThreads) return hipErrorInvalidValue;
-  if (dtype == 0)
-    return ln_bwd_t<float, float>(T_rows, H, (const float*)dout, (const float*)x, mean, rstd,
-                                  (const float*)gamma, (const float*)dres, (float*)dx, dgamma, dbeta,
-                                  dxsum, partial, st);
-  if (x_f32)
-    return ln_bwd_t<float, bf16>(T_rows, H, (const bf16*)dout, (const float*)x, mean, rstd,
-                                 (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, dgamma, dbeta,
-                                 dxsum, partial, st);
-  return ln_bwd_t<bf16, bf16>(T_rows, H, (const bf16*)dout, (const bf16*)x, mean, rstd,
-                              (const bf16*)gamma, (const bf16*)dres, (bf16*)dx, dgamma, dbeta, dxsum,
-                              partial, st);
+  ReduceSeg seg;
+  const hipError_t e = ln_bwd_partials(dtype, x_f32, T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dgamma, dbeta, dxsum,
+                                       partial, &seg, st);
+  return e != hipSuccess ? e : reduce_partials(&seg, 1, st);
 }
 
 // g[i] = gelu(u[i]), 8 elements per thread (recomputation of the MLP activation)
@@ -450,28 +519,18 @@ hipError_t f16_to_bf16(const void* in, void* out, size_t n, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t widen_to_f32(const void* in, float* out, size_t n, hipStream_t st) {
-  const size_t n8 = n / 8;
-  hipLaunchKernelGGL(widen_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, st, (const bf16*)in,
-                     out, n8);
-  return hipGetLastError();
-}
-
 size_t ln_bwd_scratch_bytes(int T_rows, int H) {
-  return (size_t)ln_bwd_blocks(T_rows) * 3 * H * sizeof(float);
+  return (size_t)ln_bwd_blocks(T_rows, H) * 3 * H * sizeof(float);
 }
 
 int colsum_splits(int M) { return M < 4 * 64 ? (M + 3) / 4 : 64; }
 size_t colsum_scratch_bytes(int M, int N) { return (size_t)colsum_splits(M) * N * sizeof(float); }
 
-hipError_t reduce_colsum_partials(const float* partial, int G, int N, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3((N + 31) / 32), dim3(1024), 0, st, partial, G, (size_t)N, N,
-                     out, N, (float*)nullptr, N, (float*)nullptr);
-  return hipGetLastError();
+ReduceSeg colsum_segment(const float* partial, int G, int N, float* out) {
+  return ReduceSeg{partial, (size_t)N, G, N, N, N, out, nullptr, nullptr};
 }
-
-hipError_t colsum(int dtype, int M, int N, const void* A, float* out, float* partial,
-                  hipStream_t st) {
+hipError_t colsum_partials(int dtype, int M, int N, const void* A, float* out, float* partial, ReduceSeg* seg,
+                           hipStream_t st) {
   const int G = colsum_splits(M);
   const int V = dtype == 0 ? 4 : 8;
   dim3 g((N / V + kWave - 1) / kWave, G), b(256);
@@ -479,11 +538,13 @@ hipError_t colsum(int dtype, int M, int N, const void* A, float* out, float* par
     hipLaunchKernelGGL(colsum_partial_kernel<float>, g, b, 0, st, (const float*)A, partial, M, N);
   else
     hipLaunchKernelGGL(colsum_partial_kernel<bf16>, g, b, 0, st, (const bf16*)A, partial, M, N);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3((N + 31) / 32), dim3(1024), 0, st, partial, G, (size_t)N, N,
-                     out, N, (float*)nullptr, N, (float*)nullptr);
+  *seg = colsum_segment(partial, G, N, out);
   return hipGetLastError();
+}
+hipError_t colsum(int dtype, int M, int N, const void* A, float* out, float* partial, hipStream_t st) {
+  ReduceSeg seg;
+  const hipError_t e = colsum_partials(dtype, M, N, A, out, partial, &seg, st);
+  return e != hipSuccess ? e : reduce_partials(&seg, 1, st);
 }
 
 // ---- column sums for callers that cannot allocate ------------------------------------------

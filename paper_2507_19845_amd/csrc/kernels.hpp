@@ -8,17 +8,32 @@ namespace gpts {
 // dtype: 0 = fp32 storage, 1 = bf16 storage (fp32 arithmetic in both).
 
 // x_f32: the normalised tensor x (the residual stream) is fp32 even when dtype is bf16.
-// out_f16 (bf16 stages with an fp32 x only): out is written as fp16 instead of bf16.
+// out_f16 (bf16 stages only): out is written as fp16 instead of bf16.
+// xcopy (may be null): receives x as fp32.
 hipError_t ln_fwd(int dtype, bool x_f32, int T_rows, int H, float eps, const void* x,
                   const void* gamma, const void* beta, void* out, float* mean, float* rstd,
-                  hipStream_t st, bool out_f16 = false);
+                  hipStream_t st, bool out_f16 = false, float* xcopy = nullptr);
+// Partial column sums waiting to be added up: out[c] += sum_{g<G} partial[g*stride + c], the columns
+// c < N being split at n0 and n1 over out0 (c < n0), out1 (n0 <= c < n1) and out2 (n1 <= c).
+// N, n0, n1 and stride are multiples of 4.
+struct ReduceSeg {
+  const float* partial;
+  size_t stride;
+  int G, N, n0, n1;
+  float *out0, *out1, *out2;
+};
+constexpr int kMaxReduceSegs = 5;
+// adds up n <= kMaxReduceSegs segments in one launch, each in fixed order
+hipError_t reduce_partials(const ReduceSeg* segs, int n, hipStream_t st);
 size_t ln_bwd_scratch_bytes(int T_rows, int H);
-// dxsum (may be null): += column sums of dx as stored
+// dxsum (may be null): += column sums of dx as stored.  ln_bwd_partials leaves the three sums in
+// `partial` (ln_bwd_scratch_bytes()) and describes them in *seg; ln_bwd adds them up as well.
+hipError_t ln_bwd_partials(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
+                           const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
+                           float* dgamma, float* dbeta, float* dxsum, float* partial, ReduceSeg* seg, hipStream_t st);
 hipError_t ln_bwd(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
                   const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
                   float* dgamma, float* dbeta, float* dxsum, float* partial, hipStream_t st);
-// out[i] = (float) in[i] for n bf16 elements (n a multiple of 8)
-hipError_t widen_to_f32(const void* in, float* out, size_t n, hipStream_t st);
 // g = gelu(u) elementwise (kind 0 tanh form, 1 erf form); n a multiple of 8
 // u_f16 (bf16 stages): u is fp16, g is still written as bf16
 hipError_t gelu_fwd(int dtype, int kind, const void* u, void* g, size_t n, hipStream_t st, bool u_f16 = false);
@@ -26,10 +41,12 @@ hipError_t gelu_fwd(int dtype, int kind, const void* u, void* g, size_t n, hipSt
 hipError_t f16_to_bf16(const void* in, void* out, size_t n, hipStream_t st);
 size_t colsum_scratch_bytes(int M, int N);
 int colsum_splits(int M);   // rows of partial sums that colsum_scratch_bytes() provides for
-hipError_t colsum(int dtype, int M, int N, const void* A, float* out, float* partial,
-                  hipStream_t st);
-// out[n] += sum_{g<G} partial[g*N + n], in fixed order
-hipError_t reduce_colsum_partials(const float* partial, int G, int N, float* out, hipStream_t st);
+// out += column sums of A [M,N]; colsum_partials leaves them in `partial`, as above
+hipError_t colsum_partials(int dtype, int M, int N, const void* A, float* out, float* partial, ReduceSeg* seg,
+                           hipStream_t st);
+hipError_t colsum(int dtype, int M, int N, const void* A, float* out, float* partial, hipStream_t st);
+// the segment of G rows of N partial sums each, added to out
+ReduceSeg colsum_segment(const float* partial, int G, int N, float* out);
 
 // Epilogue description shared by all GEMM implementations.
 struct GemmEpilogue {

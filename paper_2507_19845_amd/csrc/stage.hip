@@ -129,7 +129,7 @@ FwdWs fwd_ws(const gpt_stage_cfg& c) {
 }
 size_t fwd_ws_bytes(const gpt_stage_cfg& c) { return fwd_ws(c).end; }
 struct BwdWs {
-  size_t dU, dA, dX1, dC, dQKV, attn, ping, pong, ln_part, cs_part, rA, rG, rstat, end;
+  size_t dU, dA, dX1, dC, dQKV, attn, ping, pong, ln1_part, ln2_part, cs_qkv, cs_fc1, cs_fc2, rA, rG, rstat, end;
   size_t bQKV, bC, bU;   // fwd_fp16: bf16 copies of the fp16 QKV, C and U of the stash
   size_t fwd2;           // recompute == 2: a forward workspace of the backward phase's own
 };
@@ -147,11 +147,12 @@ BwdWs bwd_ws(const gpt_stage_cfg& c) {
   w.attn = take(attention_scratch_bytes(c.dtype, D.B, D.S, D.a, D.d, 1));
   w.ping = take((size_t)D.T * D.H * e);
   w.pong = take((size_t)D.T * D.H * e);
-  w.ln_part = take(ln_bwd_scratch_bytes(D.T, D.H));
-  int maxn = D.H;
-  if (3 * D.P > maxn) maxn = 3 * D.P;
-  if (D.F > maxn) maxn = D.F;
-  w.cs_part = take(colsum_scratch_bytes(D.T, maxn));
+  // partial column sums: they wait for the end of their layer, where one launch adds them all up
+  w.ln1_part = take(ln_bwd_scratch_bytes(D.T, D.H));
+  w.ln2_part = take(ln_bwd_scratch_bytes(D.T, D.H));
+  w.cs_qkv = take(colsum_scratch_bytes(D.T, 3 * D.P));
+  w.cs_fc1 = take(colsum_scratch_bytes(D.T, D.F));
+  w.cs_fc2 = take(colsum_scratch_bytes(D.T, D.H));
   // recomputed LayerNorm output (one buffer, used for A2 and then A), GeLU output, statistics
   const bool rebuild = c.recompute == 1 || c.fwd_fp16;
   w.rA = rebuild ? take((size_t)D.T * D.H * e) : kAbsent;
@@ -324,8 +325,10 @@ int need_prepared(const gpt_stage_params* p) {
 // written here); Yout: the layer's output, or nullptr to stop after the GeLU (the re-run of a
 // layer inside the backward phase needs nothing beyond it); fwk: a forward workspace (fwd_ws
 // layout).  phase: what the tracer records (0 forward phase, 1 backward phase).
+// x_in (may be null): the caller's stage input; the first LayerNorm then reads it and fills X, the
+// stage's own (fp32) copy, so that the backward phase never needs the caller's buffer.
 int fwd_layer(const gpt_stage_params* p, int l, const void* X, char* blk, void* Yout, bool y_f32,
-              char* fwk, hipStream_t st, int phase) {
+              char* fwk, hipStream_t st, int phase, const void* x_in = nullptr) {
   Tracer* tr = static_cast<Tracer*>(p->trace);
   const gpt_stage_cfg& c = p->cfg;
   const Dims D(c);
@@ -362,8 +365,8 @@ int fwd_layer(const gpt_stage_params* p, int l, const void* X, char* blk, void* 
   auto fwd_gemm = [&](int N, int K, const void* Ain, int wid, void* Cout, const GemmEpilogue& ep_) {
     return h16 ? gemm_fwd_f16(D.T, N, K, Ain, ep_.b_image, Cout, ep_, st) : gemm(dt, 0, D.T, N, K, Ain, w(l, wid), Cout, ep_, st);
   };
-  GPTS_OP(top, 0, phase, 0.0, TH * (kResBytes + e), ln_fwd(dt, bf, D.T, D.H, c.ln_eps, X, w(l, GPTS_LN1_G), w(l, GPTS_LN1_B), A, stat1,
-                  stat1 + D.T, st, h16), "ln1 fwd");
+  GPTS_OP(top, 0, phase, 0.0, TH * (kResBytes + e), ln_fwd(dt, bf && !x_in, D.T, D.H, c.ln_eps, x_in ? x_in : X, w(l, GPTS_LN1_G), w(l, GPTS_LN1_B), A,
+                  stat1, stat1 + D.T, st, h16, x_in ? static_cast<float*>(const_cast<void*>(X)) : nullptr), "ln1 fwd");
   GemmEpilogue ep;
   ep.bias = w(l, GPTS_B_QKV);
   ep.b_image = img(l, 0);
@@ -408,11 +411,6 @@ int run_fwd(const gpt_stage_params* p, const void* x, void* act_stash, void* y, 
   const size_t e = esize(c);
   const StashLayer sl = stash_layer(c);
   char* stash = static_cast<char*>(act_stash);
-  // layer 0 keeps its own (fp32) copy of x so the backward phase never needs the caller's buffer
-  if (c.dtype == GPTS_BF16)
-    GPTS_TRY(widen_to_f32(x, reinterpret_cast<float*>(stash + sl.X), (size_t)D.T * D.H, st), "widen x");
-  else
-    GPTS_TRY(hipMemcpyAsync(stash + sl.X, x, (size_t)D.T * D.H * e, hipMemcpyDeviceToDevice, st), "copy x");
   const FwdWs fw = fwd_ws(c);
   char* fwk = static_cast<char*>(p->workspace);
   for (int l = 0; l < D.L; ++l) {
@@ -421,7 +419,7 @@ int run_fwd(const gpt_stage_params* p, const void* x, void* act_stash, void* y, 
     char* blk = c.recompute == 2 ? fwk + fw.blk : s;
     const bool last = l == D.L - 1;
     void* Yout = last ? y : (void*)(s + sl.end + sl.X);
-    rc = fwd_layer(p, l, s + sl.X, blk, Yout, !last, fwk, st, 0);
+    rc = fwd_layer(p, l, s + sl.X, blk, Yout, !last, fwk, st, 0, l == 0 ? x : nullptr);
     if (rc != GPTS_OK) return rc;
   }
   return GPTS_OK;
@@ -456,8 +454,7 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
   float* dP = static_cast<float*>(dparams);
   auto w = [&](int l, int id) { return (const void*)(W + tensor_off(D, l, id) * e); };
   auto g = [&](int l, int id) { return dP + tensor_off(D, l, id); };
-  float* ln_part = reinterpret_cast<float*>(wk + ws.ln_part);
-  float* cs_part = reinterpret_cast<float*>(wk + ws.cs_part);
+  auto part = [&](size_t off) { return reinterpret_cast<float*>(wk + off); };
   void* dU = wk + ws.dU;
   void* dA = wk + ws.dA;
   void* dX1 = wk + ws.dX1;
@@ -523,10 +520,11 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
     // per-tile-row partials, when it runs and they fit the column-sum scratch
     const int cs_rows = (dt == GPTS_BF16 && gemm_mfma_supported(1, D.T, D.F, D.H)) ? gemm_mfma_colsum_rows(D.T, D.F, D.H) : 0;
     const bool fused_b1 = cs_rows > 0 && cs_rows <= colsum_splits(D.T);
-    if (fused_b1) ep.colsum_partial = cs_part;
+    if (fused_b1) ep.colsum_partial = part(ws.cs_fc1);
     GPTS_OP(GPTS_TR_GEMM_DGRAD, 3, 1, gf(D.T, D.F, D.H), gb(D.T, D.F, D.H, 2 * e), gemm(dt, 1, D.T, D.F, D.H, dY, w(l, GPTS_W_FC2), dU, ep, st), "fc2 dgrad");
-    if (fused_b1)
-      GPTS_OP(GPTS_TR_BIAS_GRAD, 2, 1, 0.0, (double)cs_rows * D.F * 4, reduce_colsum_partials(cs_part, cs_rows, D.F, g(l, GPTS_B_FC1), st), "fc1 bias grad (partials from the fc2 dgrad epilogue)");
+    ReduceSeg sums[kMaxReduceSegs];   // the layer's partial column sums, added up at its end
+    int n_sums = 0;
+    if (fused_b1) sums[n_sums++] = colsum_segment(part(ws.cs_fc1), cs_rows, D.F, g(l, GPTS_B_FC1));
     const void* G = s + sl.G;
     if (rebuild && !data_only) {
       GPTS_OP(GPTS_TR_RECOMPUTE, 2, 1, 0.0, (double)D.T * D.F * 2 * e, gelu_fwd(dt, c.gelu, s + sl.U, wk + ws.rG, (size_t)D.T * D.F, st, h16), "gelu recompute");
@@ -537,7 +535,7 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
     // the bias gradient of fc2 is the column sum of the layer's incoming gradient: below the
     // top layer the LayerNorm backward that produced that gradient has summed it already
     if (l == c.n_layers - 1)
-      GPTS_OP(GPTS_TR_BIAS_GRAD, 3, 1, 0.0, TH * e, colsum(dt, D.T, D.H, dY, g(l, GPTS_B_FC2), cs_part, st), "fc2 bias grad");
+      GPTS_OP(GPTS_TR_BIAS_GRAD, 3, 1, 0.0, TH * e, colsum_partials(dt, D.T, D.H, dY, g(l, GPTS_B_FC2), part(ws.cs_fc2), &sums[n_sums++], st), "fc2 bias grad");
     // u = a2 W1^T + b1
     GPTS_OP(GPTS_TR_GEMM_DGRAD, 2, 1, gf(D.T, D.H, D.F), gb(D.T, D.H, D.F, e), gemm(dt, 1, D.T, D.H, D.F, dU, w(l, GPTS_W_FC1), dA, d_fc1, st), "fc1 dgrad");
     const void* A2 = s + sl.A2;
@@ -550,10 +548,10 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
     if (!data_only)
       GPTS_OP(GPTS_TR_GEMM_WGRAD, 2, 1, gf(D.F, D.H, D.T), gb(D.F, D.H, D.T, 8), gemm(dt, 2, D.F, D.H, D.T, dU, A2, g(l, GPTS_W_FC1), none, st), "fc1 wgrad");
     if (!fused_b1)
-      GPTS_OP(GPTS_TR_BIAS_GRAD, 2, 1, 0.0, (double)D.T * D.F * e, colsum(dt, D.T, D.F, dU, g(l, GPTS_B_FC1), cs_part, st), "fc1 bias grad");
+      GPTS_OP(GPTS_TR_BIAS_GRAD, 2, 1, 0.0, (double)D.T * D.F * e, colsum_partials(dt, D.T, D.F, dU, g(l, GPTS_B_FC1), part(ws.cs_fc1), &sums[n_sums++], st), "fc1 bias grad");
     // a2 = LN2(x1), x1 also feeds the residual
-    GPTS_OP(GPTS_TR_LN_BWD, 1, 1, 0.0, TH * (3 * e + kResBytes), ln_bwd(dt, dt == GPTS_BF16, D.T, D.H, dA, s + sl.X1, stat2, stat2 + D.T, w(l, GPTS_LN2_G), dY, dX1,
-                    g(l, GPTS_LN2_G), g(l, GPTS_LN2_B), g(l, GPTS_B_O), ln_part, st), "ln2 bwd (+ out-proj bias grad)");
+    GPTS_OP(GPTS_TR_LN_BWD, 1, 1, 0.0, TH * (3 * e + kResBytes), ln_bwd_partials(dt, dt == GPTS_BF16, D.T, D.H, dA, s + sl.X1, stat2, stat2 + D.T, w(l, GPTS_LN2_G), dY, dX1,
+                    g(l, GPTS_LN2_G), g(l, GPTS_LN2_B), g(l, GPTS_B_O), part(ws.ln2_part), &sums[n_sums++], st), "ln2 bwd (+ out-proj bias grad)");
     // x1 = x + c Wo^T + bo
     GPTS_OP(GPTS_TR_GEMM_DGRAD, 1, 1, gf(D.T, D.P, D.H), gb(D.T, D.P, D.H, e), gemm(dt, 1, D.T, D.P, D.H, dX1, w(l, GPTS_W_O), dC, d_o, st), "out-proj dgrad");
     const void* Cb = s + sl.C;
@@ -582,11 +580,19 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
     }
     if (!data_only)
       GPTS_OP(GPTS_TR_GEMM_WGRAD, 0, 1, gf(3 * D.P, D.H, D.T), gb(3 * D.P, D.H, D.T, 8), gemm(dt, 2, 3 * D.P, D.H, D.T, dQKV, A, g(l, GPTS_W_QKV), none, st), "qkv wgrad");
-    GPTS_OP(GPTS_TR_BIAS_GRAD, 0, 1, 0.0, (double)D.T * 3 * D.P * e, colsum(dt, D.T, 3 * D.P, dQKV, g(l, GPTS_B_QKV), cs_part, st), "qkv bias grad");
+    GPTS_OP(GPTS_TR_BIAS_GRAD, 0, 1, 0.0, (double)D.T * 3 * D.P * e, colsum_partials(dt, D.T, 3 * D.P, dQKV, g(l, GPTS_B_QKV), part(ws.cs_qkv), &sums[n_sums++], st), "qkv bias grad");
     // a = LN1(x), x also feeds the residual
-    GPTS_OP(GPTS_TR_LN_BWD, 0, 1, 0.0, TH * (3 * e + kResBytes), ln_bwd(dt, dt == GPTS_BF16, D.T, D.H, dA, xs, stat1, stat1 + D.T, w(l, GPTS_LN1_G), dX1, dXout,
-                    g(l, GPTS_LN1_G), g(l, GPTS_LN1_B), l > 0 ? g(l - 1, GPTS_B_FC2) : nullptr, ln_part, st),
-            "ln1 bwd (+ fc2 bias grad of the layer below)");
+    auto ln1_bwd = [&]() {
+      const hipError_t err = ln_bwd_partials(dt, dt == GPTS_BF16, D.T, D.H, dA, xs, stat1, stat1 + D.T, w(l, GPTS_LN1_G), dX1, dXout,
+                                             g(l, GPTS_LN1_G), g(l, GPTS_LN1_B), l > 0 ? g(l - 1, GPTS_B_FC2) : nullptr,
+                                             part(ws.ln1_part), &sums[n_sums++], st);
+      return err != hipSuccess || fused_b1 ? err : reduce_partials(sums, n_sums, st);
+    };
+    GPTS_OP(GPTS_TR_LN_BWD, 0, 1, 0.0, TH * (3 * e + kResBytes), ln1_bwd(), "ln1 bwd (+ fc2 bias grad of the layer below)");
+    // the layer's partial sums: the fc1 bias gradient's own operator where its sums came out of the fc2
+    // dgrad, else part of the operator above
+    if (fused_b1)
+      GPTS_OP(GPTS_TR_BIAS_GRAD, 2, 1, 0.0, (double)cs_rows * D.F * 4, reduce_partials(sums, n_sums, st), "fc1 bias grad and the layer's other column sums");
     dY = dXout;
   }
   return GPTS_OK;

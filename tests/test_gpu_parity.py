@@ -479,6 +479,15 @@ def test_op_layernorm(dtype, T, H, x_f32):
     assert max_norm_err(B.to_host(dxs), (rdx + dres).sum(0) + 0.5) <= max(tol * 0.1, 1e-5)
 
 
+@pytest.mark.parametrize("dtype,T,H,x_f32", [("bf16", 5, 504, True), ("bf16", 2061, 512, True), ("fp32", 9, 520, False),
+                                             ("bf16", 4100, 1024, True), ("fp32", 33, 1032, False), ("bf16", 515, 2048, True),
+                                             ("bf16", 5, 2056, False), ("fp32", 513, 4096, False)])
+def test_op_layernorm_row_shapes(dtype, T, H, x_f32):
+    """LayerNorm at the edges of its row shapes: a wave per row up to 1024 (backward) and 2048 (forward)
+    columns, four waves up to 2048, a workgroup beyond; row counts that leave the last workgroup short."""
+    test_op_layernorm(dtype, T, H, x_f32)
+
+
 GEMM_SHAPES = [(64, 64, 64), (200, 136, 72), (256, 256, 256), (320, 448, 192), (512, 1024, 320),
                (1024, 768, 2048),
                (3904, 3392, 192),   # large enough for the 256x256 tiles, ragged last tile in M and N
