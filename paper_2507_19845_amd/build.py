@@ -28,12 +28,12 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=f
 FLAGS += os.environ.get("GPTS_HIPCC_FLAGS", "").split()   # e.g. -DGPTS_BIG_WAVES=8 for experiments
 
 
-# gemm_mi16_kernel<EPI, FORM, F16, MB, NB, ..> keeps its 4 MB NB accumulators in AGPRs a0.. by hand, across
+# gemm_mi16_kernel<EPI, FORM, F16, MB, NB, ..> (and the group kernel) keeps its 4 MB NB accumulators in AGPRs a0.. by hand, across
 # separate inline assembly statements; the compiler only knows them as clobbered.  That is safe as long as the
 # register allocator never needs an AGPR of its own in that kernel, i.e. as long as nothing is
 # spilled.  The build checks the compiler's resource report for every instance and fails
 # otherwise (a change of compiler or flags must not corrupt results silently).
-PINNED_AGPR_KERNEL = "gemm_mi16_kernel"
+PINNED_AGPR_KERNEL = re.compile(r"gemm_mi16_(?:group_)?kernelILi\d+ELi\d+ELb[01]ELi(\d+)ELi(\d+)E")
 
 
 def _check_pinned_accumulators(src: str, remarks: str) -> None:
@@ -41,10 +41,11 @@ def _check_pinned_accumulators(src: str, remarks: str) -> None:
     seen = 0
     for b in blocks:
         name = b.split()[0]
-        if PINNED_AGPR_KERNEL not in name:
+        m = PINNED_AGPR_KERNEL.search(name)
+        if not m:
             continue
         seen += 1
-        mb, nb = map(int, re.search(r"gemm_mi16_kernelILi\d+ELi\d+ELb[01]ELi(\d+)ELi(\d+)E", name).groups())
+        mb, nb = map(int, m.groups())
         val = {k: int(v) for k, v in re.findall(r"remark:\s+([A-Za-z ]+?)(?: \[bytes/lane\])?: (\d+) \[", b)}
         ok = (val.get("AGPRs") == 4 * mb * nb and val.get("ScratchSize") == 0 and val.get("VGPRs Spill") == 0
               and val.get("SGPRs Spill") == 0 and val.get("VGPRs", 999) < 256)
@@ -52,7 +53,7 @@ def _check_pinned_accumulators(src: str, remarks: str) -> None:
             raise RuntimeError(f"{src}: {name} must use exactly its {4 * mb * nb} hand-placed AGPRs and spill nothing; "
                                f"the compiler reports {val}")
     if seen == 0:
-        raise RuntimeError(f"{src}: no resource report found for {PINNED_AGPR_KERNEL}")
+        raise RuntimeError(f"{src}: no resource report found for the kernels with hand-placed accumulators")
 
 
 def _compile(src: str) -> str:

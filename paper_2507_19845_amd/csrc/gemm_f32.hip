@@ -135,20 +135,24 @@ template <int EPI> __device__ __forceinline__ void f32_store4(const F32Args& a, 
   }
 }
 
+// floats of LDS a tile's two stages take
+template <int WM, int WN, int WK, bool A_KM, bool B_KM> constexpr int f32_lds_floats() {
+  constexpr int BK = WK == 1 ? 32 : 64;
+  return 2 * (F32Operand<32 * WM, BK, A_KM>::FLOATS + F32Operand<32 * WN, BK, B_KM>::FLOATS);
+}
 template <int WM, int WN, int WK, bool A_KM, bool B_KM, int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const F32Args a) {
+__device__ __forceinline__ void f32_tile(const F32Args& a, int tile_m, int tile_n, float* const lds) {
   static_assert(WM * WN * WK == 4 && (WK == 1 || (WM == 1 && WN == 1)), "four waves; a split contraction has one tile");
   constexpr int BM = 32 * WM, BN = 32 * WN, BK = WK == 1 ? 32 : 64, KW = BK / WK;
   using OpA = F32Operand<BM, BK, A_KM>;
   using OpB = F32Operand<BN, BK, B_KM>;
   constexpr int STAGE = OpA::FLOATS + OpB::FLOATS;
-  __shared__ __attribute__((aligned(16))) float lds[2 * STAGE];
   static_assert(2 * STAGE >= 4 * 4 * 256, "the four partial tiles fit");
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wk = wave % WK, wn = wave / WK % WN, wm = wave / WK / WN;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
   OpA opA;
   OpB opB;
   opA.init(a.A, m0, a.M, a.K);
@@ -229,6 +233,26 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const F32Args a) {
   }
 }
 
+template <int WM, int WN, int WK, bool A_KM, bool B_KM, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const F32Args a) {
+  __shared__ __attribute__((aligned(16))) float lds[f32_lds_floats<WM, WN, WK, A_KM, B_KM>()];
+  f32_tile<WM, WN, WK, A_KM, B_KM, EPI>(a, blockIdx.y, blockIdx.x, lds);
+}
+// Several weight gradients in one launch.
+struct F32Group {
+  F32Args p[kMaxWgrads];
+  int first[kMaxWgrads];   // first workgroup of a product
+};
+template <int WM, int WN, int WK> __global__ __launch_bounds__(256) void gemm_f32_group_kernel(const F32Group g) {
+  __shared__ __attribute__((aligned(16))) float lds[f32_lds_floats<WM, WN, WK, true, true>()];
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxWgrads; ++i)
+    if ((int)blockIdx.x >= g.first[i]) k = i;
+  const int id = blockIdx.x - g.first[k], tiles_n = (g.p[k].N + 32 * WN - 1) / (32 * WN);
+  f32_tile<WM, WN, WK, true, true, F32_ACCUM>(g.p[k], id / tiles_n, id % tiles_n, lds);
+}
+
 // 64 x 64 tiles where there are at least 320 of them, else 32 x 32 tiles with a split contraction.
 // Measured (64 / 32): 512 tiles (NT 999x2048x512) 22.3 / 25.6 us; 384 tiles (NT 999x1536x512)
 // 22.9 / 22.9; 256 tiles, one per CU and none to hide its latency (TN 2048x512x999) 29.7 / 27.1;
@@ -241,6 +265,18 @@ template <bool A_KM, bool B_KM, int EPI> hipError_t launch_f32(const F32Args& a,
   } else {
     hipLaunchKernelGGL((gemm_f32_kernel<1, 1, 4, A_KM, B_KM, EPI>), dim3((a.N + 31) / 32, (a.M + 31) / 32), dim3(256), 0, st, a);
   }
+  return hipGetLastError();
+}
+
+template <int WM, int WN, int WK> hipError_t launch_f32_group(const F32Args* a, int n, hipStream_t st) {
+  F32Group g;
+  int blocks = 0;
+  for (int i = 0; i < kMaxWgrads; ++i) {
+    g.p[i] = a[i < n ? i : 0];
+    g.first[i] = i < n ? blocks : 0x7fffffff;      // (never reached)
+    if (i < n) blocks += ((a[i].M + 32 * WM - 1) / (32 * WM)) * ((a[i].N + 32 * WN - 1) / (32 * WN));
+  }
+  hipLaunchKernelGGL((gemm_f32_group_kernel<WM, WN, WK>), dim3(blocks), dim3(256), 0, st, g);
   return hipGetLastError();
 }
 
@@ -269,7 +305,26 @@ hipError_t gemm_f32(int form, int M, int N, int K, const void* A, const void* B,
     if (a.dgelu_u) return ep.gelu_kind == 0 ? launch_f32<false, true, F32_DGELU_TANH>(a, st) : launch_f32<false, true, F32_DGELU_ERF>(a, st);
     return launch_f32<false, true, F32_PLAIN>(a, st);
   }
-  return launch_f32<true, true, F32_ACCUM>(a, st);
+  const WgradItem w{M, N, A, B, (float*)C};
+  return gemm_f32_wgrad_group(&w, 1, K, st);
+}
+
+// Each product keeps the tile it has alone (use_wide), so that its bits do not depend on its company.
+hipError_t gemm_f32_wgrad_group(const WgradItem* items, int n, int K, hipStream_t st) {
+  if (n < 1 || n > kMaxWgrads) return hipErrorInvalidValue;
+  F32Args wide[kMaxWgrads], narrow[kMaxWgrads];
+  int n_wide = 0, n_narrow = 0;
+  for (int i = 0; i < n; ++i) {
+    const WgradItem& w = items[i];
+    if (!gemm_f32_supported(2, w.M, w.N, K, w.dout, w.in, w.dw, GemmEpilogue())) return hipErrorInvalidValue;
+    const F32Args a{(const float*)w.dout, (const float*)w.in, w.dw, w.M, w.N, K, nullptr, nullptr, nullptr, nullptr};
+    if (use_wide(w.M, w.N)) wide[n_wide++] = a;
+    else narrow[n_narrow++] = a;
+  }
+  hipError_t e = hipSuccess;
+  if (n_wide > 0) e = launch_f32_group<2, 2, 1>(wide, n_wide, st);
+  if (e == hipSuccess && n_narrow > 0) e = launch_f32_group<1, 1, 4>(narrow, n_narrow, st);
+  return e;
 }
 
 }  // namespace gpts

@@ -62,20 +62,27 @@ constexpr TileInfo kTiles[N_TILES] = {
     {192, 192, 0.83f, 4.5f, 0.84f, 13.f}, {256, 128, 0.78f, 4.f, 0.85f, 12.f}, {128, 128, 0.40f, 5.f, 0.40f, 9.5f},
     {128, 64, 0.27f, 3.6f, 0.27f, 5.2f},  {64, 64, 0.17f, 2.6f, 0.18f, 3.3f},  {64, 32, 0.16f, 2.2f, 0.18f, 2.7f}};
 
-Tile choose_tile(int form, int M, int N, long K) {
+// A smaller tile has to promise 3 %, about what the estimates are good for.
+struct Product { int M, N; };
+Tile choose_tile(int form, const Product* p, int n, long K) {
   Tile best = TILE_256x256;
   float best_us = 0.f;
   for (int t = 0; t < N_TILES; ++t) {
     const TileInfo& i = kTiles[t];
-    const long tiles = (long)((M + i.bm - 1) / i.bm) * ((N + i.bn - 1) / i.bn);
+    long tiles = 0;
+    for (int q = 0; q < n; ++q) tiles += (long)((p[q].M + i.bm - 1) / i.bm) * ((p[q].N + i.bn - 1) / i.bn);
     const float slices = (float)((K + 63) / 64);
     const float us = (float)((tiles + 255) / 256) * (form == 2 ? slices * i.slice_tn + i.fixed_tn : slices * i.slice + i.fixed);
-    if (t == 0 || us < best_us) {
+    if (t == 0 || us < 0.97f * best_us) {
       best = (Tile)t;
       best_us = us;
     }
   }
   return best;
+}
+Tile choose_tile(int form, int M, int N, long K) {
+  const Product p{M, N};
+  return choose_tile(form, &p, 1, K);
 }
 
 }  // namespace
@@ -145,14 +152,11 @@ hipError_t gemm_fwd_f16(int M, int N, int K, const void* A, const void* b_image,
 
 hipError_t gemm_mfma(int form, int M, int N, int K, const void* A, const void* B, void* C,
                      const GemmEpilogue& ep, hipStream_t st) {
-  MfmaArgs a = make_args(M, N, K, A, B, C, ep);
   if (form == 2) {
-    if (ep.k_segments > 1 && !gemm_wgrad_segments_supported(M, N, K, ep.k_segments)) return hipErrorInvalidValue;
-    a.k_segments = ep.k_segments;
-    a.seg_stride_a = ep.seg_stride_a;
-    a.seg_stride_b = ep.seg_stride_b;
-    return launch_gemm_wgrad(choose_tile(2, M, N, (long)K * ep.k_segments), a, st);
+    const WgradItem w{M, N, A, B, (float*)C};
+    return gemm_wgrad_group(&w, 1, K, ep.k_segments, ep.seg_stride_a, ep.seg_stride_b, st);
   }
+  MfmaArgs a = make_args(M, N, K, A, B, C, ep);
   const Tile t = choose_tile(form, M, N, K);
   if (form == 1)
     return launch_gemm_dgrad(t, !ep.dgelu_u ? EPI_PLAIN : (ep.gelu_kind == 0 ? EPI_DGELU_TANH : EPI_DGELU_ERF), a, st);
@@ -161,6 +165,24 @@ hipError_t gemm_mfma(int form, int M, int N, int K, const void* A, const void* B
     a.b_img = 1;
   }
   return launch_gemm_fwd(t, fwd_epilogue(ep), a, st);
+}
+
+hipError_t gemm_wgrad_group(const WgradItem* items, int n, int K, int segments, size_t seg_stride_dout,
+                            size_t seg_stride_in, hipStream_t st) {
+  if (n < 1 || n > kMaxWgrads) return hipErrorInvalidValue;
+  MfmaArgs a[kMaxWgrads];
+  Product p[kMaxWgrads];
+  for (int i = 0; i < n; ++i) {
+    const WgradItem& w = items[i];
+    if (segments > 1 ? !gemm_wgrad_segments_supported(w.M, w.N, K, segments) : !gemm_mfma_supported(2, w.M, w.N, K))
+      return hipErrorInvalidValue;
+    a[i] = make_args(w.M, w.N, K, w.dout, w.in, w.dw, GemmEpilogue());
+    a[i].k_segments = segments;
+    a[i].seg_stride_a = seg_stride_dout;
+    a[i].seg_stride_b = seg_stride_in;
+    p[i] = Product{w.M, w.N};
+  }
+  return launch_gemm_wgrad(choose_tile(2, p, n, (long)K * segments), a, n, st);
 }
 
 }  // namespace gpts

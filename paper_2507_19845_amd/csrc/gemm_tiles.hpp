@@ -80,7 +80,7 @@ enum Tile { TILE_256x256 = 0, TILE_256x192, TILE_256x160, TILE_192x192, TILE_256
 hipError_t launch_gemm_fwd(Tile tile, int epi, const MfmaArgs& a, hipStream_t st);
 hipError_t launch_gemm_fwd_f16(Tile tile, int epi, const MfmaArgs& a, hipStream_t st);
 hipError_t launch_gemm_dgrad(Tile tile, int epi, const MfmaArgs& a, hipStream_t st);
-hipError_t launch_gemm_wgrad(Tile tile, const MfmaArgs& a, hipStream_t st);
+hipError_t launch_gemm_wgrad(Tile tile, const MfmaArgs* a, int n, hipStream_t st);   // n <= kMaxWgrads, one launch
 
 // 16-byte chunk swizzle of a K-contiguous tile row with CPR chunks per row.  Chosen
 // so that 16 consecutive rows read at the same logical chunk hit 16 different
@@ -367,8 +367,10 @@ enum GemmForm { FORM_NT = 0, FORM_NN = 1, FORM_TN = 2 };
 
 // F16: both operands hold fp16 values (A an activation stored in fp16, B the fp16 image of a
 // weight); the f16 form of the matrix instruction is used and the 16-bit outputs are fp16.
+// id: the workgroup's place among the product's tiles; lds: kernel's pipeline memory (gemm_lds_bytes()).
+template <int MB, int NB, int BK, int NS> constexpr int gemm_lds_bytes() { return NS * 32 * (MB + NB) * BK * 2; }
 template <int EPI, int FORM, bool F16, int MB, int NB, int BK, int NS>
-__global__ __launch_bounds__(256) void gemm_mi16_kernel(const MfmaArgs a) {
+__device__ __forceinline__ void gemm_tile(const MfmaArgs& a, int id, char* const lds) {
   constexpr bool A_KM = FORM == FORM_TN, B_KM = FORM != FORM_NT;
   constexpr int NW = 4, WM = 16 * MB, WN = 16 * NB, BM = 2 * WM, BN = 2 * WN, KS = BK / 32;
   using OpA = Operand<BM, BK, A_KM>;
@@ -376,7 +378,7 @@ __global__ __launch_bounds__(256) void gemm_mi16_kernel(const MfmaArgs a) {
   constexpr int A_BYTES = OpA::BYTES, STAGE = A_BYTES + OpB::BYTES, RB = BK * 2, LDS_BYTES = NS * STAGE;
   constexpr int NIA = OpA::NI, N_DMA = NIA + OpB::NI;
   static_assert((KS == 1 || KS == 2) && LDS_BYTES <= 160 * 1024, "shape of the pipeline");
-  __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
+  static_assert(LDS_BYTES == gemm_lds_bytes<MB, NB, BK, NS>(), "pipeline memory");
   const uint32_t lds_base = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)lds;
 
   const int lane = threadIdx.x & 63;
@@ -385,7 +387,6 @@ __global__ __launch_bounds__(256) void gemm_mi16_kernel(const MfmaArgs a) {
 
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
   const int nb = tiles_m * tiles_n;
-  int id = blockIdx.x;
   {   // contiguous range of tiles per XCD (the first nb % 8 of them hold one more)
     const int x = id & 7, q = nb >> 3, r = nb & 7;
     id = x * q + min(x, r) + (id >> 3);
@@ -573,6 +574,28 @@ __global__ __launch_bounds__(256) void gemm_mi16_kernel(const MfmaArgs a) {
 }
 
 template <int EPI, int FORM, bool F16, int MB, int NB, int BK, int NS>
+__global__ __launch_bounds__(256) void gemm_mi16_kernel(const MfmaArgs a) {
+  __shared__ __attribute__((aligned(1024))) char lds[gemm_lds_bytes<MB, NB, BK, NS>()];
+  gemm_tile<EPI, FORM, F16, MB, NB, BK, NS>(a, blockIdx.x, lds);
+}
+
+// Several weight gradients in one launch, one after the other in the order of the workgroups: their
+// last, partly filled rounds of tiles run into the next product's first.
+struct WgradGroup {
+  MfmaArgs p[kMaxWgrads];
+  int first[kMaxWgrads];   // first workgroup of a product
+};
+template <int EPI, int FORM, bool F16, int MB, int NB, int BK, int NS>
+__global__ __launch_bounds__(256) void gemm_mi16_group_kernel(const WgradGroup g) {
+  __shared__ __attribute__((aligned(1024))) char lds[gemm_lds_bytes<MB, NB, BK, NS>()];
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxWgrads; ++i)
+    if ((int)blockIdx.x >= g.first[i]) k = i;
+  gemm_tile<EPI, FORM, F16, MB, NB, BK, NS>(g.p[k], blockIdx.x - g.first[k], lds);
+}
+
+template <int EPI, int FORM, bool F16, int MB, int NB, int BK, int NS>
 hipError_t launch_mi16(const MfmaArgs& a, hipStream_t st) {
   if (a.b_img && BK != kImageK) return hipErrorInvalidValue;
   const int tiles = ((a.M + 32 * MB - 1) / (32 * MB)) * ((a.N + 32 * NB - 1) / (32 * NB));
@@ -580,15 +603,22 @@ hipError_t launch_mi16(const MfmaArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Two K-major operands at 256 columns wide: slices of 32 in four or five stages.  Their rows are whole
-// lines at any depth, and the transposing reads leave no room for a copy as bursty as two stages of
-// 64 (4096^3: 115 against 118 us; 3968x6144x2048 with 192 columns: 109 against 117 us).  With a
-// K-contiguous operand two stages of 64 win (97 against 102 us; 84 against 94 us).
+template <int MB, int NB, int BK, int NS> hipError_t launch_group(const MfmaArgs* a, int n, hipStream_t st) {
+  WgradGroup g;
+  int blocks = 0;
+  for (int i = 0; i < kMaxWgrads; ++i) {
+    g.p[i] = a[i < n ? i : 0];
+    g.first[i] = i < n ? blocks : 0x7fffffff;      // (never reached)
+    if (i < n) blocks += ((a[i].M + 32 * MB - 1) / (32 * MB)) * ((a[i].N + 32 * NB - 1) / (32 * NB));
+  }
+  hipLaunchKernelGGL((gemm_mi16_group_kernel<EPI_ACCUM, FORM_TN, false, MB, NB, BK, NS>), dim3(blocks), dim3(256), 0, st, g);
+  return hipGetLastError();
+}
+
 template <int EPI, int FORM, bool F16 = false> hipError_t launch_tile(Tile tile, const MfmaArgs& a, hipStream_t st) {
-  constexpr bool TN = FORM == FORM_TN;
   switch (tile) {
-    case TILE_256x256: return launch_mi16<EPI, FORM, F16, 8, 8, TN ? 32 : 64, TN ? 4 : 2>(a, st);
-    case TILE_256x192: return launch_mi16<EPI, FORM, F16, 8, 6, TN ? 32 : 64, TN ? 5 : 2>(a, st);
+    case TILE_256x256: return launch_mi16<EPI, FORM, F16, 8, 8, 64, 2>(a, st);
+    case TILE_256x192: return launch_mi16<EPI, FORM, F16, 8, 6, 64, 2>(a, st);
     case TILE_256x160: return launch_mi16<EPI, FORM, F16, 8, 5, 64, 3>(a, st);
     case TILE_192x192: return launch_mi16<EPI, FORM, F16, 6, 6, 64, 3>(a, st);
     case TILE_256x128: return launch_mi16<EPI, FORM, F16, 8, 4, 64, 3>(a, st);
@@ -596,6 +626,24 @@ template <int EPI, int FORM, bool F16 = false> hipError_t launch_tile(Tile tile,
     case TILE_128x64: return launch_mi16<EPI, FORM, F16, 4, 2, 64, 4>(a, st);
     case TILE_64x64: return launch_mi16<EPI, FORM, F16, 2, 2, 64, 4>(a, st);
     case TILE_64x32: return launch_mi16<EPI, FORM, F16, 2, 1, 64, 4>(a, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+// Weight gradients, two K-major operands: the two widest tiles take slices of 32 in four or five stages.
+// Their rows are whole lines at any depth, and the transposing reads leave no room for a copy as
+// bursty as two stages of 64 (4096^3: 115 against 118 us; 3968x6144x2048 with 192 columns: 109 against
+// 117 us).  With a K-contiguous operand two stages of 64 win (97 against 102 us; 84 against 94 us).
+inline hipError_t launch_wgrads(Tile tile, const MfmaArgs* a, int n, hipStream_t st) {
+  switch (tile) {
+    case TILE_256x256: return launch_group<8, 8, 32, 4>(a, n, st);
+    case TILE_256x192: return launch_group<8, 6, 32, 5>(a, n, st);
+    case TILE_256x160: return launch_group<8, 5, 64, 3>(a, n, st);
+    case TILE_192x192: return launch_group<6, 6, 64, 3>(a, n, st);
+    case TILE_256x128: return launch_group<8, 4, 64, 3>(a, n, st);
+    case TILE_128x128: return launch_group<4, 4, 64, 4>(a, n, st);
+    case TILE_128x64: return launch_group<4, 2, 64, 4>(a, n, st);
+    case TILE_64x64: return launch_group<2, 2, 64, 4>(a, n, st);
+    case TILE_64x32: return launch_group<2, 1, 64, 4>(a, n, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -95,6 +95,20 @@ hipError_t gemm_fwd_f16(int M, int N, int K, const void* A, const void* b_image,
                         const GemmEpilogue& ep, hipStream_t st);
 hipError_t gemm_mfma(int form, int M, int N, int K, const void* A, const void* B, void* C,
                      const GemmEpilogue& ep, hipStream_t st);
+// Weight gradients dw[M,N] += dout[K,M]^T in[K,N] of n <= kMaxWgrads linears over the same tokens in one
+// launch, bit for bit what gemm_mfma() gives for each; every shape gemm_mfma_supported(), with segments
+// (see GemmEpilogue) gemm_wgrad_segments_supported().
+struct WgradItem {
+  int M, N;
+  const void* dout;
+  const void* in;
+  float* dw;
+};
+constexpr int kMaxWgrads = 4;
+hipError_t gemm_wgrad_group(const WgradItem* items, int n, int K, int segments, size_t seg_stride_dout,
+                            size_t seg_stride_in, hipStream_t st);
+// the same for fp32 buffers, every shape and buffer gemm_f32_supported()
+hipError_t gemm_f32_wgrad_group(const WgradItem* items, int n, int K, hipStream_t st);
 bool gemm_wgrad_segments_supported(int M, int N, int K, int segments);
 // rows of GemmEpilogue::colsum_partial that gemm_mfma() writes for an [M,N] product
 int gemm_mfma_colsum_rows(int M, int N, int K);

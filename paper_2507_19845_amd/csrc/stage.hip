@@ -129,7 +129,7 @@ FwdWs fwd_ws(const gpt_stage_cfg& c) {
 }
 size_t fwd_ws_bytes(const gpt_stage_cfg& c) { return fwd_ws(c).end; }
 struct BwdWs {
-  size_t dU, dA, dX1, dC, dQKV, attn, ping, pong, ln1_part, ln2_part, cs_qkv, cs_fc1, cs_fc2, rA, rG, rstat, end;
+  size_t dU, dA, dX1, dC, dQKV, attn, ping, pong, ln1_part, ln2_part, cs_qkv, cs_fc1, cs_fc2, rA, rA2, rG, rstat, end;
   size_t bQKV, bC, bU;   // fwd_fp16: bf16 copies of the fp16 QKV, C and U of the stash
   size_t fwd2;           // recompute == 2: a forward workspace of the backward phase's own
 };
@@ -153,9 +153,10 @@ BwdWs bwd_ws(const gpt_stage_cfg& c) {
   w.cs_qkv = take(colsum_scratch_bytes(D.T, 3 * D.P));
   w.cs_fc1 = take(colsum_scratch_bytes(D.T, D.F));
   w.cs_fc2 = take(colsum_scratch_bytes(D.T, D.H));
-  // recomputed LayerNorm output (one buffer, used for A2 and then A), GeLU output, statistics
+  // recomputed LayerNorm outputs, GeLU output, statistics
   const bool rebuild = c.recompute == 1 || c.fwd_fp16;
   w.rA = rebuild ? take((size_t)D.T * D.H * e) : kAbsent;
+  w.rA2 = rebuild ? take((size_t)D.T * D.H * e) : kAbsent;
   w.rG = rebuild ? take((size_t)D.T * D.F * e) : kAbsent;
   w.rstat = rebuild ? take((size_t)2 * D.T * 4) : kAbsent;
   w.bQKV = c.fwd_fp16 ? take((size_t)D.T * 3 * D.P * e) : kAbsent;
@@ -273,6 +274,25 @@ hipError_t gemm(int dtype, int form, int M, int N, int K, const void* A, const v
   if (dtype == GPTS_FP32 && gemm_f32_supported(form, M, N, K, A, B, C, ep))
     return gemm_f32(form, M, N, K, A, B, C, ep, st);
   return gemm_simple(dtype, form, M, N, K, A, B, C, ep, st);
+}
+
+// The weight gradients of a layer's linears, over the same K tokens: one launch where the matrix-core
+// kernels take all of them, else one product each.
+hipError_t wgrads(int dtype, const WgradItem* items, int n, int K, hipStream_t st) {
+  bool bf = dtype == GPTS_BF16, f32 = dtype == GPTS_FP32;
+  for (int i = 0; i < n; ++i) {
+    const WgradItem& w = items[i];
+    bf = bf && gemm_mfma_supported(2, w.M, w.N, K);
+    f32 = f32 && gemm_f32_supported(2, w.M, w.N, K, w.dout, w.in, w.dw, GemmEpilogue());
+  }
+  if (bf) return gemm_wgrad_group(items, n, K, 1, 0, 0, st);
+  if (f32) return gemm_f32_wgrad_group(items, n, K, st);
+  for (int i = 0; i < n; ++i) {
+    const WgradItem& w = items[i];
+    const hipError_t e = gemm(dtype, 2, w.M, w.N, K, w.dout, w.in, w.dw, GemmEpilogue(), st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // Attention: on the matrix cores for bf16 and for aligned fp32 buffers, the plain FMA kernels
@@ -500,7 +520,6 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
       dQKV = g0 + gl.dQKV;
       if (l > 0) dXout = gs + (size_t)(l - 1) * gl.end + gl.dY;   // the layer below reads it as its dY
     }
-    GemmEpilogue none;
     GemmEpilogue d_fc1, d_o, d_qkv;   // plain dgrads (on the raw weights)
     // y = x1 + g W2^T + b2 ;  g = gelu(u)
     const bool h16 = c.fwd_fp16 != 0;            // QKV, C, U of the stash hold fp16 values
@@ -530,8 +549,6 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
       GPTS_OP(GPTS_TR_RECOMPUTE, 2, 1, 0.0, (double)D.T * D.F * 2 * e, gelu_fwd(dt, c.gelu, s + sl.U, wk + ws.rG, (size_t)D.T * D.F, st, h16), "gelu recompute");
       G = wk + ws.rG;
     }
-    if (!data_only)
-      GPTS_OP(GPTS_TR_GEMM_WGRAD, 3, 1, gf(D.H, D.F, D.T), gb(D.H, D.F, D.T, 8), gemm(dt, 2, D.H, D.F, D.T, dY, G, g(l, GPTS_W_FC2), none, st), "fc2 wgrad");
     // the bias gradient of fc2 is the column sum of the layer's incoming gradient: below the
     // top layer the LayerNorm backward that produced that gradient has summed it already
     if (l == c.n_layers - 1)
@@ -542,11 +559,9 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
     if (rebuild && !data_only) {
       float* rs = reinterpret_cast<float*>(wk + ws.rstat);
       GPTS_OP(GPTS_TR_RECOMPUTE, 1, 1, 0.0, TH * (kResBytes + e), ln_fwd(dt, dt == GPTS_BF16, D.T, D.H, c.ln_eps, s + sl.X1, w(l, GPTS_LN2_G), w(l, GPTS_LN2_B),
-                      wk + ws.rA, rs, rs + D.T, st), "ln2 recompute");
-      A2 = wk + ws.rA;
+                      wk + ws.rA2, rs, rs + D.T, st), "ln2 recompute");
+      A2 = wk + ws.rA2;
     }
-    if (!data_only)
-      GPTS_OP(GPTS_TR_GEMM_WGRAD, 2, 1, gf(D.F, D.H, D.T), gb(D.F, D.H, D.T, 8), gemm(dt, 2, D.F, D.H, D.T, dU, A2, g(l, GPTS_W_FC1), none, st), "fc1 wgrad");
     if (!fused_b1)
       GPTS_OP(GPTS_TR_BIAS_GRAD, 2, 1, 0.0, (double)D.T * D.F * e, colsum_partials(dt, D.T, D.F, dU, g(l, GPTS_B_FC1), part(ws.cs_fc1), &sums[n_sums++], st), "fc1 bias grad");
     // a2 = LN2(x1), x1 also feeds the residual
@@ -563,8 +578,6 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
       Cb = wk + ws.bC;
       QKVb = wk + ws.bQKV;
     }
-    if (!data_only)
-      GPTS_OP(GPTS_TR_GEMM_WGRAD, 1, 1, gf(D.H, D.P, D.T), gb(D.H, D.P, D.T, 8), gemm(dt, 2, D.H, D.P, D.T, dX1, Cb, g(l, GPTS_W_O), none, st), "out-proj wgrad");
     // c = attention(qkv)
     GPTS_OP(GPTS_TR_ATTN_BWD, 0, 1, 2.0 * attn_fl, (double)D.T * 9 * D.P * e, attention_bwd(dt, D.B, D.S, D.a, D.d, QKVb, s + sl.C,
                                   reinterpret_cast<const float*>(s + sl.LSE), dC, dQKV, attn_scratch, st, h16 ? s + sl.QKV : nullptr),
@@ -578,8 +591,16 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
                       wk + ws.rA, rs, rs + D.T, st), "ln1 recompute");
       A = wk + ws.rA;
     }
-    if (!data_only)
-      GPTS_OP(GPTS_TR_GEMM_WGRAD, 0, 1, gf(3 * D.P, D.H, D.T), gb(3 * D.P, D.H, D.T, 8), gemm(dt, 2, 3 * D.P, D.H, D.T, dQKV, A, g(l, GPTS_W_QKV), none, st), "qkv wgrad");
+    if (!data_only) {
+      // all four weight gradients together (dY is still whole: dx, which may alias it, is written by
+      // the LayerNorm below); one by one under a tracer, which times each
+      const WgradItem lin[4] = {{D.H, D.F, dY, G, g(l, GPTS_W_FC2)}, {D.F, D.H, dU, A2, g(l, GPTS_W_FC1)},
+                                {D.H, D.P, dX1, Cb, g(l, GPTS_W_O)}, {3 * D.P, D.H, dQKV, A, g(l, GPTS_W_QKV)}};
+      if (!tr) GPTS_TRY(wgrads(dt, lin, 4, D.T, st), "weight gradients");
+      else
+        for (int i = 0; i < 4; ++i)
+          GPTS_OP(GPTS_TR_GEMM_WGRAD, 3 - i, 1, gf(lin[i].M, lin[i].N, D.T), gb(lin[i].M, lin[i].N, D.T, 8), wgrads(dt, &lin[i], 1, D.T, st), "wgrad");
+    }
     GPTS_OP(GPTS_TR_BIAS_GRAD, 0, 1, 0.0, (double)D.T * 3 * D.P * e, colsum_partials(dt, D.T, 3 * D.P, dQKV, g(l, GPTS_B_QKV), part(ws.cs_qkv), &sums[n_sums++], st), "qkv bias grad");
     // a = LN1(x), x also feeds the residual
     auto ln1_bwd = [&]() {
@@ -647,7 +668,20 @@ int run_wgrad_flush(const gpt_stage_params* p, int n, const void* const* act_sta
   struct Lin { int sub, M, N, wid; size_t dout, in; };   // dW[M,N] += dOut[T,M]^T In[T,N]
   const Lin lins[4] = {{3, D.H, D.F, GPTS_W_FC2, gl.dY, sl.G}, {2, D.F, D.H, GPTS_W_FC1, gl.dU, sl.A2},
                        {1, D.H, D.P, GPTS_W_O, gl.dX1, sl.C}, {0, 3 * D.P, D.H, GPTS_W_QKV, gl.dQKV, sl.A}};
+  bool one_launch = spaced && !tr;   // all four linears of a layer (one by one under a tracer)
+  for (const Lin& L : lins)
+    one_launch = one_launch && (n == 1 ? gemm_mfma_supported(2, L.M, L.N, D.T) : gemm_wgrad_segments_supported(L.M, L.N, D.T, n));
   for (int l = D.L - 1; l >= 0; --l) {
+    if (one_launch) {
+      WgradItem it[4];
+      for (int i = 0; i < 4; ++i) {
+        const Lin& L = lins[i];
+        it[i] = WgradItem{L.M, L.N, static_cast<const char*>(grad_stashes[0]) + (size_t)l * gl.end + L.dout,
+                          static_cast<const char*>(act_stashes[0]) + (size_t)l * sl.end + L.in, g(l, L.wid)};
+      }
+      GPTS_TRY(gemm_wgrad_group(it, 4, D.T, n, (size_t)grad_stride / e, (size_t)act_stride / e, st), "weight gradients over all micro-batches");
+      continue;
+    }
     for (const Lin& L : lins) {
       auto dout_of = [&](int m) { return static_cast<const char*>(grad_stashes[m]) + (size_t)l * gl.end + L.dout; };
       if (spaced && (n == 1 || gemm_wgrad_segments_supported(L.M, L.N, D.T, n))) {
