@@ -364,17 +364,28 @@ hipError_t reduce_partials(const ReduceSeg* segs, int n, hipStream_t st) {
 }
 
 // ----------------------------------------------------------------- colsum ----
-// partial[blockIdx.y][n] = sum over this workgroup's rows of A[m][n].
+// For every matrix: partial[blockIdx.y][n] = sum over this workgroup's rows of A[m][n].
 // Lane owns one 16-byte column vector; the 4 waves take interleaved rows and
-// are combined through LDS in fixed order.
+// are combined through LDS in fixed order.  One launch takes all the matrices of a layer (the same M
+// rows): below some MB each is a few microseconds of launch and latency whatever its size.  Three matrices
+// of 128 rows, 128 to 512 columns, in one launch instead of three: 3.7 us of a 74 us step.
+struct ColsumArgs {
+  ColsumMat mat[kMaxColsums];
+  int first[kMaxColsums];   // first blockIdx.x of a matrix
+};
 template <typename T>
-__global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict__ A,
-                                                             float* __restrict__ partial, int M,
-                                                             int N) {
+__global__ __launch_bounds__(256) void colsum_partial_kernel(const ColsumArgs args, int M) {
   constexpr int V = Vec16<T>::N;
   __shared__ float sm[4][kWave * V];
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxColsums; ++i)
+    if ((int)blockIdx.x >= args.first[i]) k = i;
+  const int N = args.mat[k].N;
+  const T* __restrict__ A = static_cast<const T*>(args.mat[k].A);
+  float* __restrict__ partial = args.mat[k].partial;
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  const int col = (blockIdx.x * kWave + lane) * V;
+  const int col = (((int)blockIdx.x - args.first[k]) * kWave + lane) * V;
   float acc[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) acc[e] = 0.f;
@@ -529,21 +540,29 @@ size_t colsum_scratch_bytes(int M, int N) { return (size_t)colsum_splits(M) * N 
 ReduceSeg colsum_segment(const float* partial, int G, int N, float* out) {
   return ReduceSeg{partial, (size_t)N, G, N, N, N, out, nullptr, nullptr};
 }
-hipError_t colsum_partials(int dtype, int M, int N, const void* A, float* out, float* partial, ReduceSeg* seg,
-                           hipStream_t st) {
+hipError_t colsum_partials(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, hipStream_t st) {
+  if (n < 1 || n > kMaxColsums) return hipErrorInvalidValue;
   const int G = colsum_splits(M);
   const int V = dtype == 0 ? 4 : 8;
-  dim3 g((N / V + kWave - 1) / kWave, G), b(256);
+  ColsumArgs a{};
+  int blocks = 0;
+  for (int i = 0; i < kMaxColsums; ++i) {
+    a.first[i] = i < n ? blocks : 0x7fffffff;      // (never reached)
+    if (i >= n) continue;
+    a.mat[i] = mats[i];
+    blocks += (mats[i].N / V + kWave - 1) / kWave;
+    segs[i] = colsum_segment(mats[i].partial, G, mats[i].N, mats[i].out);
+  }
   if (dtype == 0)
-    hipLaunchKernelGGL(colsum_partial_kernel<float>, g, b, 0, st, (const float*)A, partial, M, N);
+    hipLaunchKernelGGL(colsum_partial_kernel<float>, dim3(blocks, G), dim3(256), 0, st, a, M);
   else
-    hipLaunchKernelGGL(colsum_partial_kernel<bf16>, g, b, 0, st, (const bf16*)A, partial, M, N);
-  *seg = colsum_segment(partial, G, N, out);
+    hipLaunchKernelGGL(colsum_partial_kernel<bf16>, dim3(blocks, G), dim3(256), 0, st, a, M);
   return hipGetLastError();
 }
 hipError_t colsum(int dtype, int M, int N, const void* A, float* out, float* partial, hipStream_t st) {
+  const ColsumMat mat{A, N, out, partial};
   ReduceSeg seg;
-  const hipError_t e = colsum_partials(dtype, M, N, A, out, partial, &seg, st);
+  const hipError_t e = colsum_partials(dtype, M, &mat, 1, &seg, st);
   return e != hipSuccess ? e : reduce_partials(&seg, 1, st);
 }
 

@@ -41,9 +41,15 @@ hipError_t gelu_fwd(int dtype, int kind, const void* u, void* g, size_t n, hipSt
 hipError_t f16_to_bf16(const void* in, void* out, size_t n, hipStream_t st);
 size_t colsum_scratch_bytes(int M, int N);
 int colsum_splits(int M);   // rows of partial sums that colsum_scratch_bytes() provides for
-// out += column sums of A [M,N]; colsum_partials leaves them in `partial`, as above
-hipError_t colsum_partials(int dtype, int M, int N, const void* A, float* out, float* partial, ReduceSeg* seg,
-                           hipStream_t st);
+// out += column sums of A [M,N].  colsum_partials takes n <= kMaxColsums matrices of M rows in one launch
+// and leaves their sums in each one's `partial` (colsum_scratch_bytes()) and segs[0 .. n-1], as above
+struct ColsumMat {
+  const void* A;
+  int N;
+  float *out, *partial;
+};
+constexpr int kMaxColsums = 3;
+hipError_t colsum_partials(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, hipStream_t st);
 hipError_t colsum(int dtype, int M, int N, const void* A, float* out, float* partial, hipStream_t st);
 // the segment of G rows of N partial sums each, added to out
 ReduceSeg colsum_segment(const float* partial, int G, int N, float* out);

@@ -542,7 +542,8 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
     if (fused_b1) ep.colsum_partial = part(ws.cs_fc1);
     GPTS_OP(GPTS_TR_GEMM_DGRAD, 3, 1, gf(D.T, D.F, D.H), gb(D.T, D.F, D.H, 2 * e), gemm(dt, 1, D.T, D.F, D.H, dY, w(l, GPTS_W_FC2), dU, ep, st), "fc2 dgrad");
     ReduceSeg sums[kMaxReduceSegs];   // the layer's partial column sums, added up at its end
-    int n_sums = 0;
+    ColsumMat cols[kMaxColsums];      // matrices that a pass of their own sums up, late in the layer
+    int n_sums = 0, n_cols = 0;
     if (fused_b1) sums[n_sums++] = colsum_segment(part(ws.cs_fc1), cs_rows, D.F, g(l, GPTS_B_FC1));
     const void* G = s + sl.G;
     if (rebuild && !data_only) {
@@ -552,7 +553,7 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
     // the bias gradient of fc2 is the column sum of the layer's incoming gradient: below the
     // top layer the LayerNorm backward that produced that gradient has summed it already
     if (l == c.n_layers - 1)
-      GPTS_OP(GPTS_TR_BIAS_GRAD, 3, 1, 0.0, TH * e, colsum_partials(dt, D.T, D.H, dY, g(l, GPTS_B_FC2), part(ws.cs_fc2), &sums[n_sums++], st), "fc2 bias grad");
+      cols[n_cols++] = ColsumMat{dY, D.H, g(l, GPTS_B_FC2), part(ws.cs_fc2)};
     // u = a2 W1^T + b1
     GPTS_OP(GPTS_TR_GEMM_DGRAD, 2, 1, gf(D.T, D.H, D.F), gb(D.T, D.H, D.F, e), gemm(dt, 1, D.T, D.H, D.F, dU, w(l, GPTS_W_FC1), dA, d_fc1, st), "fc1 dgrad");
     const void* A2 = s + sl.A2;
@@ -562,8 +563,7 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
                       wk + ws.rA2, rs, rs + D.T, st), "ln2 recompute");
       A2 = wk + ws.rA2;
     }
-    if (!fused_b1)
-      GPTS_OP(GPTS_TR_BIAS_GRAD, 2, 1, 0.0, (double)D.T * D.F * e, colsum_partials(dt, D.T, D.F, dU, g(l, GPTS_B_FC1), part(ws.cs_fc1), &sums[n_sums++], st), "fc1 bias grad");
+    if (!fused_b1) cols[n_cols++] = ColsumMat{dU, D.F, g(l, GPTS_B_FC1), part(ws.cs_fc1)};
     // a2 = LN2(x1), x1 also feeds the residual
     GPTS_OP(GPTS_TR_LN_BWD, 1, 1, 0.0, TH * (3 * e + kResBytes), ln_bwd_partials(dt, dt == GPTS_BF16, D.T, D.H, dA, s + sl.X1, stat2, stat2 + D.T, w(l, GPTS_LN2_G), dY, dX1,
                     g(l, GPTS_LN2_G), g(l, GPTS_LN2_B), g(l, GPTS_B_O), part(ws.ln2_part), &sums[n_sums++], st), "ln2 bwd (+ out-proj bias grad)");
@@ -601,7 +601,15 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
         for (int i = 0; i < 4; ++i)
           GPTS_OP(GPTS_TR_GEMM_WGRAD, 3 - i, 1, gf(lin[i].M, lin[i].N, D.T), gb(lin[i].M, lin[i].N, D.T, 8), wgrads(dt, &lin[i], 1, D.T, st), "wgrad");
     }
-    GPTS_OP(GPTS_TR_BIAS_GRAD, 0, 1, 0.0, (double)D.T * 3 * D.P * e, colsum_partials(dt, D.T, 3 * D.P, dQKV, g(l, GPTS_B_QKV), part(ws.cs_qkv), &sums[n_sums++], st), "qkv bias grad");
+    // the remaining bias gradients: column sums of dY (top layer), dU and dQKV in one launch, one by one
+    // under a tracer
+    cols[n_cols++] = ColsumMat{dQKV, 3 * D.P, g(l, GPTS_B_QKV), part(ws.cs_qkv)};
+    if (!tr) GPTS_TRY(colsum_partials(dt, D.T, cols, n_cols, sums + n_sums, st), "bias gradients");
+    else
+      for (int i = 0; i < n_cols; ++i)
+        GPTS_OP(GPTS_TR_BIAS_GRAD, cols[i].A == dQKV ? 0 : (cols[i].A == dU ? 2 : 3), 1, 0.0, (double)D.T * cols[i].N * e,
+                colsum_partials(dt, D.T, &cols[i], 1, sums + n_sums + i, st), "bias gradient");
+    n_sums += n_cols;
     // a = LN1(x), x also feeds the residual
     auto ln1_bwd = [&]() {
       const hipError_t err = ln_bwd_partials(dt, dt == GPTS_BF16, D.T, D.H, dA, xs, stat1, stat1 + D.T, w(l, GPTS_LN1_G), dX1, dXout,
