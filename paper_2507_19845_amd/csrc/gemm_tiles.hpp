@@ -615,6 +615,8 @@ template <int MB, int NB, int BK, int NS> hipError_t launch_group(const MfmaArgs
   return hipGetLastError();
 }
 
+// Six stages instead of four gain nothing at 128x64 and 64x32 (two layers of 192 rows, 320 wide: 335
+// against 338 us a step; 512 rows, 1024 wide, four chunks: 4999 against 5008 us).
 template <int EPI, int FORM, bool F16 = false> hipError_t launch_tile(Tile tile, const MfmaArgs& a, hipStream_t st) {
   switch (tile) {
     case TILE_256x256: return launch_mi16<EPI, FORM, F16, 8, 8, 64, 2>(a, st);
