@@ -534,7 +534,7 @@ size_t ln_bwd_scratch_bytes(int T_rows, int H) {
   return (size_t)ln_bwd_blocks(T_rows, H) * 3 * H * sizeof(float);
 }
 
-int colsum_splits(int M) { return M < 4 * 64 ? (M + 3) / 4 : 64; }
+static int colsum_splits(int M) { return M < 4 * 64 ? (M + 3) / 4 : 64; }
 size_t colsum_scratch_bytes(int M, int N) { return (size_t)colsum_splits(M) * N * sizeof(float); }
 
 ReduceSeg colsum_segment(const float* partial, int G, int N, float* out) {

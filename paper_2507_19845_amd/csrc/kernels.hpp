@@ -40,7 +40,6 @@ hipError_t gelu_fwd(int dtype, int kind, const void* u, void* g, size_t n, hipSt
 // out[i] = bf16(in[i]) for n fp16 elements (n a multiple of 8)
 hipError_t f16_to_bf16(const void* in, void* out, size_t n, hipStream_t st);
 size_t colsum_scratch_bytes(int M, int N);
-int colsum_splits(int M);   // rows of partial sums that colsum_scratch_bytes() provides for
 // out += column sums of A [M,N].  colsum_partials takes n <= kMaxColsums matrices of M rows in one launch
 // and leaves their sums in each one's `partial` (colsum_scratch_bytes()) and segs[0 .. n-1], as above
 struct ColsumMat {

@@ -128,6 +128,11 @@ FwdWs fwd_ws(const gpt_stage_cfg& c) {
   return w;
 }
 size_t fwd_ws_bytes(const gpt_stage_cfg& c) { return fwd_ws(c).end; }
+// Rows of partial sums of dU that the fc2 data gradient leaves (the fc1 bias gradient): as many as its
+// tile makes of the tokens, 0 where the product runs outside the matrix-core path and leaves none.
+int fc1_sum_rows(const Dims& D, int dtype) {
+  return dtype == GPTS_BF16 && gemm_mfma_supported(1, D.T, D.F, D.H) ? gemm_mfma_colsum_rows(D.T, D.F, D.H) : 0;
+}
 struct BwdWs {
   size_t dU, dA, dX1, dC, dQKV, attn, ping, pong, ln1_part, ln2_part, cs_qkv, cs_fc1, cs_fc2, rA, rA2, rG, rstat, end;
   size_t bQKV, bC, bU;   // fwd_fp16: bf16 copies of the fp16 QKV, C and U of the stash
@@ -151,7 +156,8 @@ BwdWs bwd_ws(const gpt_stage_cfg& c) {
   w.ln1_part = take(ln_bwd_scratch_bytes(D.T, D.H));
   w.ln2_part = take(ln_bwd_scratch_bytes(D.T, D.H));
   w.cs_qkv = take(colsum_scratch_bytes(D.T, 3 * D.P));
-  w.cs_fc1 = take(colsum_scratch_bytes(D.T, D.F));
+  const int fc1_rows = fc1_sum_rows(D, c.dtype);
+  w.cs_fc1 = take(fc1_rows > 0 ? (size_t)fc1_rows * D.F * sizeof(float) : colsum_scratch_bytes(D.T, D.F));
   w.cs_fc2 = take(colsum_scratch_bytes(D.T, D.H));
   // recomputed LayerNorm outputs, GeLU output, statistics
   const bool rebuild = c.recompute == 1 || c.fwd_fp16;
@@ -536,9 +542,9 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
     ep.dgelu_u = U;
     ep.gelu_kind = c.gelu;
     // the matrix-core product also leaves the column sums of dU (the fc1 bias gradient) as
-    // per-tile-row partials, when it runs and they fit the column-sum scratch
-    const int cs_rows = (dt == GPTS_BF16 && gemm_mfma_supported(1, D.T, D.F, D.H)) ? gemm_mfma_colsum_rows(D.T, D.F, D.H) : 0;
-    const bool fused_b1 = cs_rows > 0 && cs_rows <= colsum_splits(D.T);
+    // per-tile-row partials
+    const int cs_rows = fc1_sum_rows(D, dt);
+    const bool fused_b1 = cs_rows > 0;
     if (fused_b1) ep.colsum_partial = part(ws.cs_fc1);
     GPTS_OP(GPTS_TR_GEMM_DGRAD, 3, 1, gf(D.T, D.F, D.H), gb(D.T, D.F, D.H, 2 * e), gemm(dt, 1, D.T, D.F, D.H, dY, w(l, GPTS_W_FC2), dU, ep, st), "fc2 dgrad");
     ReduceSeg sums[kMaxReduceSegs];   // the layer's partial column sums, added up at its end

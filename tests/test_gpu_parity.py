@@ -238,6 +238,39 @@ def test_operator_tracer_records_every_operator():
     assert len(recs2) == 5 and dropped2 == n_ops - 5
 
 
+@pytest.mark.parametrize("batch,hidden,ffn", [(97, 896, 2688), (130, 512, 2048), (3, 256, 512)])
+def test_fc1_bias_gradient_needs_no_pass_over_du(batch, hidden, ffn):
+    """The fc1 bias gradient comes out of the fc2 data gradient's epilogue however many rows of partial
+    sums its tile makes of the tokens: 66 (192-row tiles of 6208 tokens), 88 and 6.  The operator
+    that adds them up reads those rows and not dU.  Against the column sums of dU as stored: each of its
+    values is rounded to bf16 (2^-9), the summed ones are not."""
+    shape = W[1].with_(name="bf16_fc1_sums", n_layers=1, hidden=hidden, n_heads=1, head_dim=128, ffn=ffn, seq=64,
+                       batch=batch)
+    print(f"[case] fc1 bias sums {shape}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(batch)
+    bufs = B.StageBuffers(shape)
+    bufs.weights.normal_(0.0, 0.02, generator=gen)
+    bufs.alloc_grad_stash(1)
+    x, dy = (bufs.act().normal_(generator=gen) for _ in range(2))
+    y, dx = bufs.act(), bufs.act()
+    B.gpt_stage_fwd(bufs.params(), x, bufs.stash[0], y)
+    tr = B.gpt_stage_trace_create(64)
+    try:
+        bufs.trace = tr
+        B.gpt_stage_bwd_data_only(bufs.params(), bufs.stash[0], dy, dx, bufs.dparams, bufs.grad_stash[0])
+        recs, _ = B.gpt_stage_trace_collect(tr, 64)
+    finally:
+        B.gpt_stage_trace_destroy(tr)
+    T = shape.tokens
+    fc1 = [r for r in recs if r["op"] == "bias_grad" and r["sub"] == 2]
+    assert len(fc1) == 1 and fc1[0]["bytes"] <= T * ffn * 2 / 8      # dU itself is T * ffn * 2 bytes
+    off = (T * hidden * 2 + 255) // 256 * 256                        # grad stash: dY, then dU, 256-byte aligned
+    du = bufs.grad_stash[0][off:off + T * ffn * 2].view(torch.bfloat16).view(T, ffn).double()
+    o, n = B.gpt_stage_param_offset(bufs.cfg, 0, synth.TENSOR_NAMES.index("b_fc1"))
+    assert ((bufs.dparams[o:o + n].double() - du.sum(0)).abs() <= 2.0 ** -8 * du.abs().sum(0)).all()
+
+
 def test_run_to_run_bitwise_determinism():
     shape = W[1].with_(name="bf16_det", n_layers=1, hidden=256, n_heads=4, head_dim=64, ffn=512,
                        seq=256, batch=2)
