@@ -820,32 +820,65 @@ void launch_timage(const TImageArgs& t, int B, int S, int a, hipStream_t st) {
 
 // How the rows go over the workgroups.  A workgroup walks its rows' half of the other side tile by
 // tile, so with few workgroups the time is that chain; fewer rows per workgroup and two waves per 32
-// rows, which share a tile, shorten it, at the price of streaming each tile for fewer rows.
-// Measured (us; forward 128 rows, one wave per 32 | 64 rows, two waves; backward 256 rows, two launches
-// | 128 rows | 64 rows, one launch):
-//   heads S    D    wg    forward       backward           (wg: workgroups of 256 rows)
-//      5  192  64   10    8.1 |  7.7    22.0 | 13.3 | 11.8   (batch 2)
-//     16  512  64   32   13.2 | 11.1    44.0 | 22.0 | 20.4
-//      2 8192 128   64    174 |  126     712 |  249 |  316
-//     16 2048 128  128   55.3 | 45.5     203 | 99.5 |  176
-//     16 1984 128  256   60.4 | 57.3     207 |  172 |  285   (batch 2)
-//     40 2048 128  320   66.3 | 75.3     227 |  228 |  397
-//     12  333  32  384   13.3 | 13.2    41.8 | 32.3 | 31.9   (batch 16)
-//     32 4096 128  512    162 |  191     507 |  604 | 1083
-// So the split forms up to about one workgroup of 256 rows per compute unit (somewhat longer at head
-// dimension 32, whose workgroups share a unit), and 64 rows in backward only where even those leave
-// every workgroup a unit of its own.
+// rows, which share a tile, shorten it, at the price of streaming each tile for fewer rows.  The price
+// shows as soon as the workgroups no longer run at once, and a short sequence has no long chain to
+// shorten: the limits on the workgroups below grow with S.  Limits on 256-row blocks (wg) alone,
+// whatever S, took short sequences of many heads to the split forms at up to 1.4 times the time.
+// Measured in us, both sides of every line (h: heads times batch; n: workgroups of the split form, of
+// one side in backward).
+//   forward, 128 rows and one wave per 32 | 64 rows and two waves:
+//      D=128  S=128   h 128 n 256  12.9 | 12.4    h 160 n 320  13.1 | 14.1
+//             S=256   h 128 n 512  18.6 | 18.6    h 160 n 640  21.5 | 23.8
+//             S=512   h  80 n 640  26.4 | 25.3    h 112 n 896  27.8 | 30.0
+//             S=768   h  53 n 636  33.6 | 32.9    h  85 n1020  40.5 | 57.1
+//             S=1280  h  38 n 760  44.2 | 40.0    h  45 n 900  45.9 | 51.2
+//             S=2048  h  32 n1024  64.0 | 62.9    h  40 n1280  67.8 | 78.3
+//      D=64   S=256   h 160 n 640  13.7 | 13.7    h 224 n 896  15.4 | 16.7
+//             S=768   h  64 n 768  21.9 | 19.2    h  85 n1020  27.6 | 31.1
+//             S=2048  h  32 n1024  43.2 | 38.3    h  48 n1536  50.5 | 53.1
+//      D=32   S=768   h  64 n 768  15.3 | 13.4    h  85 n1020  23.7 | 25.3
+//             S=2048  h  32 n1024  31.0 | 26.6    h  56 n1792  40.5 | 40.7
+//   backward, 256 rows and two launches | 128 rows:
+//      D=128  S=128   h 160 n 160  33.1 | 32.2    h 256 n 256  39.5 | 41.1
+//             S=192   h 128 n 256  42.9 | 38.6    h 160 n 320  45.1 | 48.2
+//             S=256   h 192 n 384  62.5 | 62.0    h 224 n 448  68.1 | 76.1
+//             S=512   h 104 n 416  83.1 | 81.0    h 128 n 512  89.3 | 96.0
+//             S=1024  h  64 n 512   132 |  122    h  72 n 576   135 |  139
+//             S=2048  h  36 n 576   228 |  207    h  48 n 768   247 |  277
+//      D=64   S=160   h 149 n 298  26.8 | 25.1    h 213 n 426  28.1 | 32.5
+//             S=256   h 192 n 384  38.4 | 36.5    h 224 n 448  40.3 | 43.7
+//             S=2048  h  36 n 576   142 |  123    h  48 n 768   153 |  167
+//      D=32   S=160   h 213 n 426  21.1 | 20.5    h 256 n 512  22.5 | 24.0
+//             S=1024  h 112 n 896  78.7 | 70.3    h 128 n1024  79.9 | 82.5
+//   backward, 128 rows | 64 rows:
+//      D=128  S=512   h  16 n 128  34.1 | 33.1    S=1024  h   8 n 128  48.3 | 50.0
+//      D=64   S=1024  h   8 n 128  33.5 | 31.3    S=1024  h  32 n 512  43.2 | 42.9
+// Between 257 blocks of 256 rows, one more than there are compute units, and the limits on wg the
+// two-launch form needs a second round of workgroups, which costs a short sequence (up to 256 rows) more
+// than the split: D=128 S=256 h 288 109 | 96.  At D=32, whose workgroups share a unit, every shape
+// gains up to wg 448 and the first one loses at 512.
 long row_blocks(int B, int S, int a, int rows) { return (long)a * B * ((S + rows - 1) / rows); }
-bool split_fwd(int B, int S, int a) { return row_blocks(B, S, a, 256) <= 256; }
+bool split_fwd(int B, int S, int a, int d) {
+  const long most = d == 128 ? (S <= 128 ? 256 : S < 448 ? 512 : S < 1024 ? 640 : S < 1792 ? 832 : 1024)
+                             : (S <= 192 ? 512 : S < 448 ? 640 : S < 1024 ? 832 : 1024);
+  return row_blocks(B, S, a, 256) <= 256 && row_blocks(B, S, a, 64) <= most;
+}
 int split_rows_bwd(int B, int S, int a, int d) {
-  if (2 * row_blocks(B, S, a, 64) <= 256) return 64;
-  return row_blocks(B, S, a, 256) <= (d == 32 ? 448 : 288) ? 128 : 0;
+  constexpr long kAny = 1l << 40;
+  if (2 * row_blocks(B, S, a, 64) <= 256 && (d < 128 || S <= 512)) return 64;
+  const long wg = row_blocks(B, S, a, 256);
+  if (wg > (d == 32 ? 448 : 288)) return 0;
+  if (wg > 256 && S <= 256) return 128;
+  const long most = d == 128  ? (S <= 128 ? 160 : S <= 192 ? 288 : S <= 256 ? 384 : S <= 512 ? 432 : S <= 1024 ? 544 : kAny)
+                    : d == 64 ? (S <= 128 ? kAny : S <= 192 ? 304 : S <= 256 ? 384 : kAny)
+                              : (S <= 128 ? kAny : S < 256 ? 448 : kAny);
+  return row_blocks(B, S, a, 128) <= most ? 128 : 0;
 }
 
 template <int D, bool F16>
 void launch_fwd(const bf16* qkv, const bf16* vimg, bf16* out, float* lse, int B, int S, int a, hipStream_t st) {
   auto grid = [&](int rows) { return dim3(a, B, (S + rows - 1) / rows); };
-  if (split_fwd(B, S, a)) hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 2, 2>), grid(64), dim3(256), 0, st, qkv, vimg, out, lse, S, a);
+  if (split_fwd(B, S, a, D)) hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 2, 2>), grid(64), dim3(256), 0, st, qkv, vimg, out, lse, S, a);
   else hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 4, 1>), grid(128), dim3(256), 0, st, qkv, vimg, out, lse, S, a);
 }
 
