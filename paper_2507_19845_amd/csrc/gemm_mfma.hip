@@ -59,20 +59,30 @@ struct TileInfo {
 };
 constexpr TileInfo kTiles[N_TILES] = {
     {256, 256, 1.39f, 8.f, 1.45f, 20.f},  {256, 192, 1.20f, 5.f, 1.17f, 17.f}, {256, 160, 0.95f, 4.5f, 0.98f, 14.f},
-    {192, 192, 0.83f, 4.5f, 0.84f, 13.f}, {256, 128, 0.78f, 4.f, 0.85f, 12.f}, {128, 128, 0.40f, 5.f, 0.40f, 9.5f},
+    {192, 192, 0.83f, 4.5f, 0.88f, 13.f}, {256, 128, 0.78f, 4.f, 0.85f, 12.f}, {128, 128, 0.40f, 5.f, 0.40f, 9.5f},
     {128, 64, 0.27f, 3.6f, 0.27f, 5.2f},  {64, 64, 0.17f, 2.6f, 0.18f, 3.3f},  {64, 32, 0.16f, 2.2f, 0.18f, 2.7f}};
 
+// Not bound by the matrix pipe in every tile:
+//  * Weight gradients whose operands no longer stay in the 256 MB cache.  Each XCD reads a patch of 4 x 8
+//    tiles, (4 bm + 8 bn) columns of a slice, and the eight together get 2.65 TB/s: 0.59 us a slice in
+//    128x128.  6144x2048 (192 tiles of 256x256, 768 of 128x128): K = 10240, 168 MB of operands, 230 us in
+//    either; K = 14336, 235 MB, 316 against 344; K = 16384 355 against 468; K = 32768 683 against 961.
+//    2560x2560, K = 32768: 192x192 436, 128x128 614.
 // A smaller tile has to promise 3 %, about what the estimates are good for.
 struct Product { int M, N; };
 Tile choose_tile(int form, const Product* p, int n, long K) {
   Tile best = TILE_256x256;
-  float best_us = 0.f;
+  float best_us = 0.f, operand_bytes = 0.f;
+  for (int q = 0; q < n; ++q) operand_bytes += 2.f * (float)K * ((float)p[q].M + (float)p[q].N);
   for (int t = 0; t < N_TILES; ++t) {
     const TileInfo& i = kTiles[t];
     long tiles = 0;
     for (int q = 0; q < n; ++q) tiles += (long)((p[q].M + i.bm - 1) / i.bm) * ((p[q].N + i.bn - 1) / i.bn);
-    const float slices = (float)((K + 63) / 64);
-    const float us = (float)((tiles + 255) / 256) * (form == 2 ? slices * i.slice_tn + i.fixed_tn : slices * i.slice + i.fixed);
+    const long rounds = (tiles + 255) / 256, slices = (K + 63) / 64;
+    const float fixed = form == 2 ? i.fixed_tn : i.fixed;
+    float slice = form == 2 ? i.slice_tn : i.slice;
+    if (form == 2 && operand_bytes > 200e6f) slice = fmaxf(slice, (float)(4 * i.bm + 8 * i.bn) * (64 * 2 * 8 / 2.65e6f));
+    const float us = (float)rounds * ((float)slices * slice + fixed);
     if (t == 0 || us < 0.97f * best_us) {
       best = (Tile)t;
       best_us = us;

@@ -601,6 +601,21 @@ def test_op_gemm_bf16_tiles(M, N, K):
     assert ((out.double() - want).abs() <= want.abs() * 2.0 ** -8 + 2.0 ** -12 * K ** 0.5).all()
 
 
+@pytest.mark.parametrize("M,N,K", [(520, 1032, 65600), (264, 3000, 32768)])
+def test_op_gemm_bf16_wgrad_large_operands(M, N, K):
+    """Weight gradients whose operands exceed the cache (above 200 MB tiles are chosen by another rate), ragged in
+    both widths.  fp32 sums of K/32 matrix steps: errors of sqrt(K/32) roundings of 2^-24 in the 2-norm, four
+    times that allowed."""
+    print(f"[case] wgrad of large operands M={M} N={N} K={K}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    A, Bn = (torch.empty(K, w, dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for w in (M, N))
+    out = torch.full((M, N), 0.25, dtype=torch.float32, device="cuda")
+    B.gpt_stage_op_gemm(B.GPTS_BF16, 2, M, N, K, A, Bn, out)
+    want = A.double().t().contiguous() @ Bn.double() + 0.25
+    assert ((out.double() - want).norm() / want.norm()).item() <= 4 * (K / 32) ** 0.5 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 4, 4), (33, 36, 60), (32, 32, 64), (31, 100, 68), (65, 60, 132), (4, 4, 1),
                                    (36, 64, 999), (1216, 1032, 40), (1100, 1284, 36), (8, 6, 8), (10, 12, 7)])
 def test_op_gemm_fp32_edges(M, N, K):
