@@ -62,12 +62,14 @@ constexpr TileInfo kTiles[N_TILES] = {
     {192, 192, 0.83f, 4.5f, 0.88f, 13.f}, {256, 128, 0.78f, 4.f, 0.85f, 12.f}, {128, 128, 0.40f, 5.f, 0.40f, 9.5f},
     {128, 64, 0.27f, 3.6f, 0.27f, 5.2f},  {64, 64, 0.17f, 2.6f, 0.18f, 3.3f},  {64, 32, 0.16f, 2.2f, 0.18f, 2.7f}};
 
-// Not bound by the matrix pipe in every tile:
+// Two products are not bound by the matrix pipe in every tile:
 //  * Weight gradients whose operands no longer stay in the 256 MB cache.  Each XCD reads a patch of 4 x 8
 //    tiles, (4 bm + 8 bn) columns of a slice, and the eight together get 2.65 TB/s: 0.59 us a slice in
 //    128x128.  6144x2048 (192 tiles of 256x256, 768 of 128x128): K = 10240, 168 MB of operands, 230 us in
 //    either; K = 14336, 235 MB, 316 against 344; K = 16384 355 against 468; K = 32768 683 against 961.
 //    2560x2560, K = 32768: 192x192 436, 128x128 614.
+//  * One or two slices, several rounds: the stores, 3 TB/s.  32768x4096, K = 64: 256x256 89 us, 256x192 105;
+//    K = 128: 99 and 116; K = 192 (16384x8192): 112 and 131, where the fitted numbers choose 256x256 too.
 // A smaller tile has to promise 3 %, about what the estimates are good for.
 struct Product { int M, N; };
 Tile choose_tile(int form, const Product* p, int n, long K) {
@@ -79,9 +81,9 @@ Tile choose_tile(int form, const Product* p, int n, long K) {
     long tiles = 0;
     for (int q = 0; q < n; ++q) tiles += (long)((p[q].M + i.bm - 1) / i.bm) * ((p[q].N + i.bn - 1) / i.bn);
     const long rounds = (tiles + 255) / 256, slices = (K + 63) / 64;
-    const float fixed = form == 2 ? i.fixed_tn : i.fixed;
-    float slice = form == 2 ? i.slice_tn : i.slice;
+    float slice = form == 2 ? i.slice_tn : i.slice, fixed = form == 2 ? i.fixed_tn : i.fixed;
     if (form == 2 && operand_bytes > 200e6f) slice = fmaxf(slice, (float)(4 * i.bm + 8 * i.bn) * (64 * 2 * 8 / 2.65e6f));
+    if (form != 2 && slices <= 2 && rounds > 1) fixed = fmaxf(fixed, (float)(i.bm * i.bn) * (256 * 2 / 3.0e6f));
     const float us = (float)rounds * ((float)slices * slice + fixed);
     if (t == 0 || us < 0.97f * best_us) {
       best = (Tile)t;

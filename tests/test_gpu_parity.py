@@ -572,10 +572,11 @@ def test_op_gemm_forms(dtype, M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [(72, 1000, 64), (264, 3000, 128), (520, 2056, 192), (1000, 4104, 128), (2040, 4104, 128),
-                                   (2040, 5112, 192), (2040, 6136, 64), (4088, 4088, 320), (264, 1000, 1024)])
+                                   (2040, 5112, 192), (2040, 6136, 64), (4088, 4088, 320), (264, 1000, 1024),
+                                   (8200, 4104, 64)])
 def test_op_gemm_bf16_tiles(M, N, K):
     """Each tile of the bf16 products (64x32, 64x64, 128x64, 256x128, 192x192, 256x160, 256x192, 256x256 for
-    the first forms, 64x32 again with a long contraction) with ragged last tiles, one to sixteen slices, and the
+    the first forms, 64x32 again with a long contraction, 256x256 again for its stores) with ragged last tiles, one to sixteen slices, and the
     fp32 epilogues.  fp32 sums of K products of bf16 values: K eps of the sum of magnitudes."""
     print(f"[case] gemm tiles M={M} N={N} K={K}", flush=True)
     gen = torch.Generator(device="cuda")
