@@ -415,10 +415,17 @@ static hipError_t ln_fwd_t(int T_rows, int H, float eps, const void* x, const vo
 #define GPTS_LN_FWD(N, RW)                                                                                        \
   hipLaunchKernelGGL((ln_fwd_kernel<TX, T, TO, N, RW>), dim3(RW == 1 ? (T_rows + 3) / 4 : T_rows), dim3(kLnThreads), 0, st, \
                      (const TX*)x, (const T*)gamma, (const T*)beta, (TO*)out, mean, rstd, xcopy, T_rows, H, eps)
-  // a wave per row up to 2048 columns (32 registers a lane), a workgroup beyond
+  // A wave per row up to 2048 columns (32 registers a lane), a workgroup beyond -- and for many long rows
+  // too, where a wave's four chunks each wait for memory longer than the barrier costs.  Workgroup | wave,
+  // us: fp32 4096x2048 15.1 | 13.8, 8192x1536 17.4 | 19.1, 16384x2048 42.9 | 46.0, 32768x2048 100 | 113,
+  // 32768x1152 67.1 | 65.0; fp32 in, 16 bits out 16384x2048 31.2 | 30.7, 32768x1792 60.9 | 61.4, 32768x2048
+  // 69.1 | 72.1; 16 bits in and out 65536x2048 105 | 96.
+  const bool wave_row = H <= 1152 || sizeof(TX) == 2 ||
+                        (sizeof(TO) == 4 ? T_rows <= 4096 : (H <= 1792 || T_rows <= 16384));
   if (H <= 512) GPTS_LN_FWD(1, 1);
   else if (H <= 1024) GPTS_LN_FWD(2, 1);
-  else if (H <= 2048) GPTS_LN_FWD(4, 1);
+  else if (H <= 2048 && wave_row) GPTS_LN_FWD(4, 1);
+  else if (H <= 2048) GPTS_LN_FWD(1, 4);
   else if (H <= 4096) GPTS_LN_FWD(2, 4);
   else if (H <= 8192) GPTS_LN_FWD(4, 4);
   else GPTS_LN_FWD(8, 4);
