@@ -515,7 +515,8 @@ def test_op_layernorm(dtype, T, H, x_f32):
 @pytest.mark.parametrize("dtype,T,H,x_f32", [("bf16", 5, 504, True), ("bf16", 2061, 512, True), ("fp32", 9, 520, False),
                                              ("bf16", 4100, 1024, True), ("fp32", 33, 1032, False), ("bf16", 515, 2048, True),
                                              ("bf16", 5, 2056, False), ("fp32", 513, 4096, False),
-                                             ("fp32", 4100, 1160, False), ("fp32", 4097, 2048, False), ("bf16", 16390, 2048, True)])
+                                             ("fp32", 4100, 1160, False), ("fp32", 4097, 2048, False), ("bf16", 16390, 2048, True),
+                                             ("bf16", 520, 12296, True)])
 def test_op_layernorm_row_shapes(dtype, T, H, x_f32):
     """LayerNorm at the edges of its row shapes: a wave per row up to 1024 (backward) and 2048 (forward)
     columns, four waves up to 2048, a workgroup beyond and for many long rows; row counts that leave the last
