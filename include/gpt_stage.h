@@ -220,13 +220,15 @@ int gpt_stage_bwd_only(const gpt_stage_params* p, const void* act_stash, const v
  * gpt_stage_wgrad_flush: the weight phase for n micro-batches at once: for every linear layer
  * dW += sum_m (output gradient of micro-batch m)^T (its input activation), added to dparams.
  * act_stashes / grad_stashes are HOST arrays of n device pointers.  When the n buffers of each
- * kind are equally spaced in memory (e.g. slices of one allocation), the stash holds the
- * activations (no recompute, no fwd_fp16) and the shape suits the 256x256 tiles, each linear
- * is ONE product contracting over all micro-batches' tokens: the fp32 gradient matrix is read
- * and written once instead of n times.  Otherwise it is one accumulating product per
- * micro-batch, as in gpt_stage_bwd.  Same mathematics either way; the fp32 summation order
- * over tokens differs from n separate calls of gpt_stage_bwd.  Needs p->workspace of
- * workspace_bytes(cfg, 1).  Deterministic. */
+ * kind are equally spaced in memory (e.g. slices of one allocation) and the stash holds bf16
+ * activations (no recompute, no fwd_fp16), then from four micro-batches on each linear is ONE
+ * product contracting over all micro-batches' tokens: the fp32 gradient matrix is read and
+ * written once instead of n times.  With two or three that holds only for linears of at least
+ * 100 blocks of 256 x 256 weights and micro-batches of a multiple of 128 tokens.  Otherwise it is
+ * one accumulating product per micro-batch, as in gpt_stage_bwd, with the bits of n calls of
+ * gpt_stage_bwd in the order given.  Same mathematics either way; the ONE product differs from
+ * those in the fp32 summation order over tokens.  Needs p->workspace of workspace_bytes(cfg, 1).
+ * Deterministic. */
 size_t gpt_stage_grad_stash_bytes(const gpt_stage_cfg* cfg);
 int gpt_stage_bwd_data_only(const gpt_stage_params* p, const void* act_stash, const void* dy,
                             void* dx, void* dparams, void* grad_stash, void* stream,
@@ -245,7 +247,9 @@ int gpt_stage_fwd_bwd(const gpt_stage_params* p, const void* x, const void* dy,
  * end event on the stream around each operator and reads the elapsed time later, off
  * the critical path, together with the operator's arguments.  Same scheme here with
  * hipEvents: a traced call only records events; gpt_stage_trace_collect() waits for
- * them and returns one record per operator.  A tracer is a host object owning
+ * them and returns one record per operator.  Operators that an untraced call launches
+ * together -- a layer's weight gradients, and its column sums -- are launched one by one under a
+ * tracer, to be timed each: same results bit for bit, more launches.  A tracer is a host object owning
  * 2*capacity events; it is not thread-safe and must not be shared by calls that
  * run concurrently on the host.  Records beyond capacity are dropped and counted. */
 enum {
@@ -355,7 +359,9 @@ int gpt_stage_op_attention_bwd(int dtype, int B, int S, int n_heads, int head_di
  * A window of W micro-batches runs F(i,0) for its i, then F(i,1), ..., then B(i,C-1) for its
  * i, ..., B(i,0); DFC is W = 1, BFC is W = M.  Inside a chunk micro-batches always run in
  * ascending order, so gradient accumulation order -- and every result bit -- is the same for
- * all three policies. */
+ * all three policies.  (gpt_dpp_run with a grad_pool: the weight matrices' gradients are summed
+ * window by window there, in the order of gpt_stage_wgrad_flush, so their last bits depend on W
+ * where that call contracts over several micro-batches at once; everything else does not.) */
 enum { GPT_DPP_DFC = 0, GPT_DPP_BFC = 1, GPT_DPP_BFC_BEST_EFFORT = 2 };
 enum { GPT_DPP_FWD = 0, GPT_DPP_BWD = 1 };
 typedef struct {

@@ -105,11 +105,16 @@ bool gemm_mfma_supported(int form, int M, int N, int K) {
          (size_t)M * K < (1ull << 31) && (size_t)N * K < (1ull << 31);
 }
 
-// A weight-gradient product whose contraction is split over several buffers runs as one launch
-// (K here is the length of one segment: whole slices, so no slice straddles two buffers) from four
-// micro-batches on: one fp32 read-modify-write and one epilogue instead of four or more.  Two or three
-// micro-batches save less; only matrices of at least 100 tiles of 256x256 with segments of whole 128
-// rows are then worth the changed summation order, all others keep the bits of the unsplit backward.
+// A weight-gradient product whose contraction is split over several buffers can run as one launch
+// (K here is the length of one segment: whole slices, so no slice straddles two buffers): one fp32
+// read-modify-write and one epilogue instead of one per micro-batch, and the four products of a layer in
+// one launch.  It changes the fp32 summation order over the tokens.  It is taken from four micro-batches
+// on, and with two or three only for matrices of at least 100 tiles of 256x256 with segments of whole 128
+// rows; other matrices keep the bits of the unsplit backward there.  That line is one of results and
+// not of speed, one launch being the faster everywhere.  A layer's weight phase, a launch per micro-batch
+// and matrix | one launch, us, 2 / 3 / 4 micro-batches:
+//   hidden 320, 192 tokens   37 | 11    49 | 12    65 | 12      1024, 4096   305 | 242    461 | 353    613 | 466
+//   hidden 1024, 512 tokens  81 | 42   119 | 52   154 | 61      4096, 4096  2769 | 2485  4118 | 3619  5508 | 4775
 bool gemm_wgrad_segments_supported(int M, int N, int K, int segments) {
   if (!gemm_mfma_supported(2, M, N, K)) return false;
   return segments >= 4 || ((long)((M + 255) / 256) * ((N + 255) / 256) >= 100 && K % 128 == 0);
@@ -164,6 +169,7 @@ hipError_t gemm_fwd_f16(int M, int N, int K, const void* A, const void* b_image,
 
 hipError_t gemm_mfma(int form, int M, int N, int K, const void* A, const void* B, void* C,
                      const GemmEpilogue& ep, hipStream_t st) {
+  if (!gemm_mfma_supported(form, M, N, K)) return hipErrorInvalidValue;   // (whole slices of K only)
   if (form == 2) {
     const WgradItem w{M, N, A, B, (float*)C};
     return gemm_wgrad_group(&w, 1, K, ep.k_segments, ep.seg_stride_a, ep.seg_stride_b, st);

@@ -83,7 +83,7 @@ bool gemm_f32_supported(int form, int M, int N, int K, const void* A, const void
                         const GemmEpilogue& ep);
 hipError_t gemm_f32(int form, int M, int N, int K, const void* A, const void* B, void* C,
                     const GemmEpilogue& ep, hipStream_t st);
-// bf16 MFMA path; returns hipErrorNotSupported if the shape does not fit its tiles.
+// bf16 MFMA path, for every shape gemm_mfma_supported(); hipErrorInvalidValue for others, nothing launched.
 bool gemm_mfma_supported(int form, int M, int N, int K);
 // Tiled image of a weight src [N,K] as the B operand of form 0; K % 64 == 0 (else the rest of K is
 // left out).  N any.
