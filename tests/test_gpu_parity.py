@@ -55,6 +55,14 @@ SMALL = [
                seq=200 + 56, batch=1, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
     W[1].with_(name="bf16_fwd16_d64_erf", n_layers=2, hidden=384, n_heads=4, head_dim=64, ffn=896,
                seq=192, batch=2, gelu="erf", bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
+    # the same with so many heads times sequences that attention takes its forms of one wave per 32 rows
+    # in both directions (320 blocks of 256 rows, 512 at head dimension 32), the second block short
+    W[1].with_(name="bf16_fwd16_d128_full_chip", n_layers=1, hidden=256, n_heads=10, head_dim=128, ffn=256,
+               seq=260, batch=16, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
+    W[1].with_(name="bf16_fwd16_d64_full_chip", n_layers=1, hidden=256, n_heads=10, head_dim=64, ffn=256,
+               seq=260, batch=16, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
+    W[1].with_(name="bf16_fwd16_d32_full_chip", n_layers=1, hidden=256, n_heads=16, head_dim=32, ffn=256,
+               seq=260, batch=16, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
 ]
 
 
@@ -114,10 +122,53 @@ def test_split_backward_data_phase_then_one_weight_phase(mode):
     _report(shape.name, compare(shape, split, oracle_run(shape, params, xs, dys)))
 
 
+@pytest.mark.parametrize("n_mb,seq,hidden,heads,ffn", [(4, 64, 128, 1, 256), (5, 192, 192, 5, 2112), (4, 320, 448, 2, 2112),
+                                                       (5, 64, 832, 3, 2112), (5, 320, 832, 5, 2112),
+                                                       (4, 64, 2112, 5, 4160), (5, 192, 2560, 2, 5056)],
+                         ids=["64x32", "128x64", "128x128", "256x128", "192x192", "256x192", "256x256"])
+def test_split_backward_four_or_more_microbatches(n_mb, seq, hidden, heads, ffn):
+    """From four micro-batches on the weight phase contracts over all of them in one launch, whatever the
+    widths: each tile of the products, segments of one, three and five slices of 64 (shorter than the
+    ring of stages, odd) and the two tiles with slices of 32.  The fp32 summation order changes and
+    nothing else: at most 1600 tokens, so up to sqrt(1600) roundings of 2^-24, 2.4e-6, of the largest sum.  The
+    same bits from one launch per linear (which a tracer asks for); micro-batches that are not equally
+    spaced take one product each and keep the bits of the unsplit run."""
+    shape = W[1].with_(name="bf16_split_many", n_layers=1, hidden=hidden, n_heads=heads, head_dim=64, ffn=ffn, seq=seq,
+                       batch=1, bias_std=0.02, ln_jitter=0.1)
+    print(f"[case] split backward, {n_mb} micro-batches {shape}", flush=True)
+    params, xs, dys = _inputs(shape, n_mb=n_mb)
+    whole = gpu_run(shape, params, xs, dys, decoupled=True)
+    split = gpu_run(shape, params, xs, dys, decoupled=True, split_wgrad=True)
+    for a, b in zip(whole[0] + whole[1], split[0] + split[1]):
+        assert np.array_equal(a, b)
+    for k, a in whole[2][0].items():
+        b = split[2][0][k]
+        if k.startswith("w_"):
+            assert not np.array_equal(a, b), f"{k}: expected the one-launch path"
+            assert max_norm_err(b, a) < 2.4e-6, k
+        else:
+            assert np.array_equal(a, b), k
+    tr = B.gpt_stage_trace_create(64 * n_mb)
+    try:
+        traced = gpu_run(shape, params, xs, dys, decoupled=True, split_wgrad=True, trace=tr)
+        recs, _ = B.gpt_stage_trace_collect(tr, 64 * n_mb)
+    finally:
+        B.gpt_stage_trace_destroy(tr)
+    assert len([r for r in recs if r["op"] == "gemm_wgrad"]) == 4
+    bufs = B.StageBuffers(shape, n_stash=n_mb + 1)
+    bufs.load_params(params)
+    del bufs.stash[1]                                    # a gap between the first two
+    apart = gpu_run(shape, params, xs, dys, decoupled=True, split_wgrad=True, bufs=bufs)
+    for k, a in whole[2][0].items():
+        assert np.array_equal(split[2][0][k], traced[2][0][k]) and np.array_equal(a, apart[2][0][k]), k
+    if hidden <= 832:
+        _report(shape.name, compare(shape, split, oracle_run(shape, params, xs, dys)))
+
+
 def test_split_backward_other_paths():
-    """The weight phase where one launch per linear is not possible: tokens per micro-batch not a
-    multiple of 128 (one accumulating product per micro-batch, bit-identical to the unsplit
-    run), and a single micro-batch (one product, nothing to concatenate)."""
+    """The weight phase of fewer than four micro-batches where the segments are not whole multiples of 128
+    tokens: one accumulating product per micro-batch, bit-identical to the unsplit run; and a single
+    micro-batch (one product, nothing to concatenate)."""
     shape = W[1].with_(name="bf16_split_192", n_layers=2, hidden=2048, n_heads=16, head_dim=128, ffn=4096,
                        seq=192, batch=1, bias_std=0.02, ln_jitter=0.1)
     print(f"[case] split backward, fallback paths {shape}", flush=True)
@@ -175,12 +226,25 @@ def test_backward_stream_waits_for_the_forward_event():
 def test_prepared_weights_give_identical_results(ffn):
     """With the weight images of gpt_stage_prepare() the forward products read the same
     numbers through a different layout: every output must be bit-identical to the run on the
-    raw weights.  One layer of the decoupled workload's shape (large
-    enough for the 256x256 tiles the images are made for).  ffn 16320: ragged N, and a
-    contraction length that is not a multiple of 128 (the fc2 forward image then feeds the
-    32x32x16 kernel); ffn 8192: every image-fed product takes the 16x16x32 kernel, as in the
-    benchmark."""
+    raw weights.  One layer of the decoupled workload's shape, all 256x256 tiles.  ffn 16320: an
+    image whose last tile of 256 rows is short, and a contraction of an odd number of slices; ffn 8192:
+    whole tiles, as in the benchmark."""
     shape = W[3].with_(name="bf16_prepared", n_layers=1, ffn=ffn, n_microbatches=1, bias_std=0.02)
+    _check_prepared_weights(shape)
+
+
+@pytest.mark.parametrize("seq,hidden,ffn", [(1984, 5056, 320), (1984, 4160, 320), (1984, 1088, 6080), (448, 832, 3008)],
+                         ids=["256x160", "192x192", "256x192", "128x64_64x32"])
+def test_prepared_weights_give_identical_results_in_every_tile(seq, hidden, ffn):
+    """The same with tiles that do not divide the image's tiles of 256 rows, or are smaller, and widths that
+    leave the last tile of both short: 256x160 and 64x64; 192x192; 256x192, 256x128 and 128x128; 128x64
+    and 64x32."""
+    heads, d = (5, 64) if seq == 448 else (1, 128)
+    _check_prepared_weights(W[1].with_(name="bf16_prepared_tiles", n_layers=1, hidden=hidden, n_heads=heads, head_dim=d,
+                                       ffn=ffn, seq=seq, batch=1, bias_std=0.02))
+
+
+def _check_prepared_weights(shape):
     print(f"[case] prepared weights {shape}", flush=True)
     params, xs, dys = _inputs(shape)
     bufs = B.StageBuffers(shape)
@@ -576,10 +640,10 @@ def test_op_gemm_forms(dtype, M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(72, 1000, 64), (264, 3000, 128), (520, 2056, 192), (1000, 4104, 128), (2040, 4104, 128),
                                    (2040, 5112, 192), (2040, 6136, 64), (4088, 4088, 320), (264, 1000, 1024),
-                                   (8200, 4104, 64)])
+                                   (1000, 2056, 320), (8200, 4104, 64)])
 def test_op_gemm_bf16_tiles(M, N, K):
-    """Each tile of the bf16 products (64x32, 64x64, 128x64, 256x128, 192x192, 256x160, 256x192, 256x256 for
-    the first forms, 64x32 again with a long contraction, 256x256 again for its stores) with ragged last tiles, one to sixteen slices, and the
+    """Each tile of the bf16 products (64x32, 64x64, 128x64, 256x128, 192x192, 256x160, 256x192, 256x256 in
+    all three forms, 64x32 again with a long contraction, 128x128, 256x256 again for its stores) with ragged last tiles, one to sixteen slices, and the
     fp32 epilogues.  fp32 sums of K products of bf16 values: K eps of the sum of magnitudes."""
     print(f"[case] gemm tiles M={M} N={N} K={K}", flush=True)
     gen = torch.Generator(device="cuda")
