@@ -40,6 +40,9 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 #define GPTS_PRIO(p) __builtin_amdgcn_s_setprio(p)
 
 constexpr int BKV = 64;   // rows per streamed tile
+// Stands for "no key seen yet" in the running maximum: no finite logit is smaller, and the difference of
+// two such values is 0 and not NaN.  (A wave's share of a row's keys may have no logit but -inf.)
+constexpr float kNoKey = -3.4028234663852886e38f;
 
 __device__ __forceinline__ int swz16(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
@@ -257,7 +260,7 @@ __global__ __launch_bounds__(64 * RW * SW, 2) void attn_fwd_mfma_kernel(const bf
   for (int i = 0; i < DB; ++i)
 #pragma unroll
     for (int e = 0; e < 16; ++e) oacc[i][e] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kNoKey, l_run = 0.f;
   const float c = 1.4426950408889634f / sqrtf((float)D);  // log2(e)/sqrt(D)
 
   const int koff = natural_frag_off<D>(ql, h);
@@ -354,8 +357,8 @@ __global__ __launch_bounds__(64 * RW * SW, 2) void attn_fwd_mfma_kernel(const bf
   float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   if constexpr (SW == 2) {
     // the second wave of a query block hands its state over: outputs in the tile memory (every wave
-    // has left the loop), maximum and sum beside it.  A query's first key lies in a first wave's
-    // block, so the merged maximum is finite; a wave that met no key weighs exp2(-inf) = 0.
+    // has left the loop), maximum and sum beside it.  A wave that met no key, or no finite
+    // logit, hands over kNoKey and zeros: it weighs 0 beside a finite maximum.
     __shared__ float ml[2][RW][kWave];
     __syncthreads();
     f32x4* ex = reinterpret_cast<f32x4*>(lds) + rw * (DB * 4 * kWave) + lane;

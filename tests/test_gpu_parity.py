@@ -806,6 +806,35 @@ def test_op_attention_bf16_splits(Bn, S, a, d):
             assert (got - want).abs().max().item() < 2 ** -4 * want.abs().max().item()
 
 
+@pytest.mark.parametrize("Bn,S,a,d", [(1, 40, 2, 64), (1, 97, 2, 128), (2, 130, 1, 32), (1, 70, 300, 32)])
+def test_op_attention_bf16_minus_infinite_logits(Bn, S, a, d):
+    """Keys 32 to 63, the second wave's share of the first tile where two waves take a row block (the first
+    three), have logits of -inf for every query: they count as masked keys do, in the output and in lse.
+    Tolerances as in test_op_attention_bf16_splits."""
+    print(f"[case] attention minus infinity B={Bn} S={S} a={a} d={d}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(S * a + d)
+    qkv = torch.empty(Bn, S, 3, a, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    qkv[:, :, 0, :, 0] = -1.0
+    qkv[:, 32:64, 1, :, 0] = float("inf")
+    out = torch.full((Bn, S, a * d), 7.0, dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((Bn, a, S), 7.0, dtype=torch.float32, device="cuda")
+    scratch = torch.empty(max(B.gpt_stage_op_attention_scratch_bytes(B.GPTS_BF16, Bn, S, a, d, 0), 256), dtype=torch.uint8, device="cuda")
+    B.gpt_stage_op_attention_fwd(B.GPTS_BF16, Bn, S, a, d, qkv, out, lse, scratch)
+    x = qkv.cpu().double()
+    x[:, 32:64, 1, :, 0] = 0.0
+    masked = torch.ones(S, S, dtype=torch.bool).triu(1)
+    masked[:, 32:64] = True
+    for b in range(Bn):
+        q, k, v = (t.transpose(0, 1).contiguous() for t in x[b].unbind(1))
+        s = (torch.stack([q[n] @ k[n].t() for n in range(a)]) / d ** 0.5).masked_fill(masked, float("-inf"))
+        want = torch.stack([torch.softmax(s[n], -1) @ v[n] for n in range(a)]).transpose(0, 1).reshape(S, a * d)
+        got = out[b].cpu().double()
+        assert (lse[b].cpu().double() - torch.logsumexp(s, -1)).abs().max().item() < 1e-5
+        assert ((got - want).norm() / want.norm()).item() < 2 ** -7
+        assert (got - want).abs().max().item() < 2 ** -4 * want.abs().max().item()
+
+
 @pytest.mark.parametrize("Bn,S,a,d", [(1, 1, 1, 32), (2, 15, 2, 64), (1, 16, 2, 128), (2, 17, 3, 32), (1, 63, 1, 128),
                                       (1, 65, 2, 64), (2, 130, 2, 32)])
 def test_op_attention_fp32_edges(Bn, S, a, d):
