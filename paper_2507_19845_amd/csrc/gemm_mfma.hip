@@ -62,17 +62,41 @@ constexpr TileInfo kTiles[N_TILES] = {
     {192, 192, 0.83f, 4.5f, 0.88f, 13.f}, {256, 128, 0.78f, 4.f, 0.85f, 12.f}, {128, 128, 0.40f, 5.f, 0.40f, 9.5f},
     {128, 64, 0.27f, 3.6f, 0.27f, 5.2f},  {64, 64, 0.17f, 2.6f, 0.18f, 3.3f},  {64, 32, 0.16f, 2.2f, 0.18f, 2.7f}};
 
-// Two products are not bound by the matrix pipe in every tile:
-//  * Weight gradients whose operands no longer stay in the 256 MB cache.  Each XCD reads a patch of 4 x 8
-//    tiles, (4 bm + 8 bn) columns of a slice, and the eight together get 2.65 TB/s: 0.59 us a slice in
-//    128x128.  6144x2048 (192 tiles of 256x256, 768 of 128x128): K = 10240, 168 MB of operands, 230 us in
-//    either; K = 14336, 235 MB, 316 against 344; K = 16384 355 against 468; K = 32768 683 against 961.
-//    2560x2560, K = 32768: 192x192 436, 128x128 614.
-//  * One or two slices, several rounds: the stores, 3 TB/s.  32768x4096, K = 64: 256x256 89 us, 256x192 105;
-//    K = 128: 99 and 116; K = 192 (16384x8192): 112 and 131, where the fitted numbers choose 256x256 too.
+// Weight gradients whose operands no longer stay in the 256 MB cache are not bound by the matrix pipe in
+// every tile.  Each XCD reads a patch of 4 x 8 tiles, (4 bm + 8 bn) columns of a slice, and the eight
+// together get 2.65 TB/s: 0.59 us a slice in 128x128.  6144x2048 (192 tiles of 256x256, 768 of 128x128):
+// K = 10240, 168 MB of operands, 230 us in either; K = 14336, 235 MB, 316 against 344; K = 16384 355
+// against 468; K = 32768 683 against 961.  2560x2560, K = 32768: 192x192 436, 128x128 614.
+//
+// Short contractions (short_contraction(), forward products and data gradients) are bound by their
+// epilogues as much: they have numbers of their own, fitted to products of 64 ... 768 k (the estimate is
+// within 8 % on average), a factor for what the epilogue does, and two forms with two stages, whose
+// workgroups share a compute unit and need no whole rounds.  256x256 | 256x192 | 128x128 in two stages, us:
+// 7784x9152, K = 256, GeLU' 122 | 135 | 101; 14608x13952, K = 128, bias 155 | 176 | 138; 32768x4096, K = 128,
+// bias 98 | 117 | 98 and GeLU' 4096x2048, K = 512 31 | 28 | 19; 3560x1024, K = 64, GeLU' in 256x128, which the
+// other estimate took, 13.4, in 64x64 8.7.
+//
 // A smaller tile has to promise 3 %, about what the estimates are good for.
+struct ShortInfo { float start, slice, fixed; };
+constexpr ShortInfo kShort[N_TILES] = {{-1.5f, 1.11f, 11.2f}, {-0.9f, 0.87f, 10.2f}, {-0.3f, 0.71f, 7.9f},
+                                       {0.f, 0.67f, 7.9f},    {0.3f, 0.59f, 6.4f},   {0.8f, 0.36f, 3.9f},
+                                       {1.3f, 0.26f, 2.4f},   {2.5f, 0.13f, 0.95f},  {2.5f, 0.11f, 0.54f}};
+constexpr ShortInfo kShortShared128 = {2.75f, 0.37f, 1.87f}, kShortShared64 = {2.73f, 0.235f, 0.94f};
+// what an epilogue moves and computes, over that of a bias or none: alone in a unit, sharing it
+enum Cost { COST_PLAIN, COST_GELU, COST_DGELU, COST_RES32 };
+constexpr float kCostAlone[] = {1.f, 1.55f, 1.75f, 1.5f}, kCostShared[] = {1.f, 1.8f, 2.f, 2.2f};
+
+float short_us(Tile t, long tiles, long slices, Cost cost) {
+  if (two_stages(tiles, slices * 64) && (t == TILE_128x128 || t == TILE_128x64)) {
+    const ShortInfo& i = t == TILE_128x128 ? kShortShared128 : kShortShared64;
+    return i.start + ((float)tiles / 256.f + 0.4f) * ((float)slices * i.slice + i.fixed * kCostShared[cost]);
+  }
+  const ShortInfo& i = kShort[t];
+  return i.start + (float)((tiles + 255) / 256) * ((float)slices * i.slice + i.fixed * kCostAlone[cost]);
+}
+
 struct Product { int M, N; };
-Tile choose_tile(int form, const Product* p, int n, long K) {
+Tile choose_tile(int form, const Product* p, int n, long K, Cost cost) {
   Tile best = TILE_256x256;
   float best_us = 0.f, operand_bytes = 0.f;
   for (int q = 0; q < n; ++q) operand_bytes += 2.f * (float)K * ((float)p[q].M + (float)p[q].N);
@@ -83,8 +107,8 @@ Tile choose_tile(int form, const Product* p, int n, long K) {
     const long rounds = (tiles + 255) / 256, slices = (K + 63) / 64;
     float slice = form == 2 ? i.slice_tn : i.slice, fixed = form == 2 ? i.fixed_tn : i.fixed;
     if (form == 2 && operand_bytes > 200e6f) slice = fmaxf(slice, (float)(4 * i.bm + 8 * i.bn) * (64 * 2 * 8 / 2.65e6f));
-    if (form != 2 && slices <= 2 && rounds > 1) fixed = fmaxf(fixed, (float)(i.bm * i.bn) * (256 * 2 / 3.0e6f));
-    const float us = (float)rounds * ((float)slices * slice + fixed);
+    const float us = form != 2 && short_contraction(K) ? short_us((Tile)t, tiles, slices, cost)
+                                                       : (float)rounds * ((float)slices * slice + fixed);
     if (t == 0 || us < 0.97f * best_us) {
       best = (Tile)t;
       best_us = us;
@@ -92,9 +116,9 @@ Tile choose_tile(int form, const Product* p, int n, long K) {
   }
   return best;
 }
-Tile choose_tile(int form, int M, int N, long K) {
+Tile choose_tile(int form, int M, int N, long K, Cost cost) {
   const Product p{M, N};
-  return choose_tile(form, &p, 1, K);
+  return choose_tile(form, &p, 1, K, cost);
 }
 
 }  // namespace
@@ -121,7 +145,7 @@ bool gemm_wgrad_segments_supported(int M, int N, int K, int segments) {
 }
 
 int gemm_mfma_colsum_rows(int M, int N, int K) {
-  const int bm = kTiles[choose_tile(1, M, N, K)].bm;
+  const int bm = kTiles[choose_tile(1, M, N, K, COST_DGELU)].bm;   // of the product with the GeLU' epilogue
   return 2 * ((M + bm - 1) / bm);
 }
 
@@ -157,6 +181,11 @@ int fwd_epilogue(const GemmEpilogue& ep) {
   if (ep.residual && ep.residual_f32) return ep.out_f32 ? EPI_BIAS_RES32_OUT32 : EPI_BIAS_RES32_OUT16;
   return ep.residual ? EPI_BIAS_RES : EPI_BIAS;
 }
+Cost cost_of(const GemmEpilogue& ep) {
+  if (ep.gelu_out) return COST_GELU;
+  if (ep.dgelu_u) return COST_DGELU;
+  return ep.residual && ep.residual_f32 ? COST_RES32 : COST_PLAIN;
+}
 }  // namespace
 
 hipError_t gemm_fwd_f16(int M, int N, int K, const void* A, const void* b_image, void* C,
@@ -164,7 +193,7 @@ hipError_t gemm_fwd_f16(int M, int N, int K, const void* A, const void* b_image,
   if (!gemm_fwd_f16_supported(M, N, K) || !b_image) return hipErrorInvalidValue;
   MfmaArgs a = make_args(M, N, K, A, b_image, C, ep);
   a.b_img = 1;
-  return launch_gemm_fwd_f16(choose_tile(0, M, N, K), fwd_epilogue(ep), a, st);
+  return launch_gemm_fwd_f16(choose_tile(0, M, N, K, cost_of(ep)), fwd_epilogue(ep), a, st);
 }
 
 hipError_t gemm_mfma(int form, int M, int N, int K, const void* A, const void* B, void* C,
@@ -175,7 +204,7 @@ hipError_t gemm_mfma(int form, int M, int N, int K, const void* A, const void* B
     return gemm_wgrad_group(&w, 1, K, ep.k_segments, ep.seg_stride_a, ep.seg_stride_b, st);
   }
   MfmaArgs a = make_args(M, N, K, A, B, C, ep);
-  const Tile t = choose_tile(form, M, N, K);
+  const Tile t = choose_tile(form, M, N, K, cost_of(ep));
   if (form == 1)
     return launch_gemm_dgrad(t, !ep.dgelu_u ? EPI_PLAIN : (ep.gelu_kind == 0 ? EPI_DGELU_TANH : EPI_DGELU_ERF), a, st);
   if (ep.b_image) {
@@ -200,7 +229,7 @@ hipError_t gemm_wgrad_group(const WgradItem* items, int n, int K, int segments, 
     a[i].seg_stride_b = seg_stride_in;
     p[i] = Product{w.M, w.N};
   }
-  return launch_gemm_wgrad(choose_tile(2, p, n, (long)K * segments), a, n, st);
+  return launch_gemm_wgrad(choose_tile(2, p, n, (long)K * segments, COST_PLAIN), a, n, st);
 }
 
 }  // namespace gpts

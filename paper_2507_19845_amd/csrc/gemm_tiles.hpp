@@ -76,6 +76,18 @@ constexpr int kImageK = 64;   // slice depth of the weight images
 enum Tile { TILE_256x256 = 0, TILE_256x192, TILE_256x160, TILE_192x192, TILE_256x128, TILE_128x128, TILE_128x64,
             TILE_64x64, TILE_64x32, N_TILES };
 
+// Short contractions of forward products and data gradients in more than one tile per compute unit: two
+// stages of the 128x128 and 128x64 tiles, so that two (three) workgroups share a unit and one's stores
+// run under the other's slices.  With four stages a unit holds one, which waits for its first slice and its
+// stores in every round; beyond 768 the deeper ring is worth as much.  Four | two stages, us: GeLU'
+// 7784x9152, K = 256, 128x128 143 | 101; bias 9920x15872, K = 64 156 | 90; GeLU 8192x3072, K = 768 75 | 55;
+// 128x64: GeLU 8040x3328, K = 128 52 | 31; time of two over four stages, 128x128 with 512 to 1024 tiles: K
+// to 256 0.77, to 768 0.91, to 2048 0.98, to 8000 1.05; with at most 256 tiles 0.99 ... 1.05 up to 768, 1.5
+// beyond.
+constexpr int kShortSlices = 12;   // of 64 k
+inline bool short_contraction(long K) { return (K + 63) / 64 <= kShortSlices; }
+inline bool two_stages(long tiles, long K) { return tiles > 256 && short_contraction(K); }
+
 // Launchers, one translation unit each.
 hipError_t launch_gemm_fwd(Tile tile, int epi, const MfmaArgs& a, hipStream_t st);
 hipError_t launch_gemm_fwd_f16(Tile tile, int epi, const MfmaArgs& a, hipStream_t st);
@@ -617,6 +629,10 @@ template <int MB, int NB, int BK, int NS> hipError_t launch_group(const MfmaArgs
   return hipGetLastError();
 }
 
+template <int EPI, int FORM, bool F16, int MB, int NB> hipError_t launch_ring(const MfmaArgs& a, hipStream_t st) {
+  const long tiles = (long)((a.M + 32 * MB - 1) / (32 * MB)) * ((a.N + 32 * NB - 1) / (32 * NB));
+  return two_stages(tiles, a.K) ? launch_mi16<EPI, FORM, F16, MB, NB, 64, 2>(a, st) : launch_mi16<EPI, FORM, F16, MB, NB, 64, 4>(a, st);
+}
 // Six stages instead of four gain nothing at 128x64 and 64x32 (two layers of 192 rows, 320 wide: 335
 // against 338 us a step; 512 rows, 1024 wide, four chunks: 4999 against 5008 us).
 template <int EPI, int FORM, bool F16 = false> hipError_t launch_tile(Tile tile, const MfmaArgs& a, hipStream_t st) {
@@ -626,8 +642,8 @@ template <int EPI, int FORM, bool F16 = false> hipError_t launch_tile(Tile tile,
     case TILE_256x160: return launch_mi16<EPI, FORM, F16, 8, 5, 64, 3>(a, st);
     case TILE_192x192: return launch_mi16<EPI, FORM, F16, 6, 6, 64, 3>(a, st);
     case TILE_256x128: return launch_mi16<EPI, FORM, F16, 8, 4, 64, 3>(a, st);
-    case TILE_128x128: return launch_mi16<EPI, FORM, F16, 4, 4, 64, 4>(a, st);
-    case TILE_128x64: return launch_mi16<EPI, FORM, F16, 4, 2, 64, 4>(a, st);
+    case TILE_128x128: return launch_ring<EPI, FORM, F16, 4, 4>(a, st);
+    case TILE_128x64: return launch_ring<EPI, FORM, F16, 4, 2>(a, st);
     case TILE_64x64: return launch_mi16<EPI, FORM, F16, 2, 2, 64, 4>(a, st);
     case TILE_64x32: return launch_mi16<EPI, FORM, F16, 2, 1, 64, 4>(a, st);
     default: return hipErrorInvalidValue;

@@ -640,11 +640,15 @@ def test_op_gemm_forms(dtype, M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(72, 1000, 64), (264, 3000, 128), (520, 2056, 192), (1000, 4104, 128), (2040, 4104, 128),
                                    (2040, 5112, 192), (2040, 6136, 64), (4088, 4088, 320), (264, 1000, 1024),
-                                   (1000, 2056, 320), (8200, 4104, 64)])
+                                   (1000, 2056, 320), (8200, 4104, 64), (1000, 4104, 832), (2040, 4104, 832),
+                                   (2040, 6136, 832), (1000, 2056, 832), (4088, 1160, 704), (8200, 4104, 768)])
 def test_op_gemm_bf16_tiles(M, N, K):
-    """Each tile of the bf16 products (64x32, 64x64, 128x64, 256x128, 192x192, 256x160, 256x192, 256x256 in
-    all three forms, 64x32 again with a long contraction, 128x128, 256x256 again for its stores) with ragged last tiles, one to sixteen slices, and the
-    fp32 epilogues.  fp32 sums of K products of bf16 values: K eps of the sum of magnitudes."""
+    """Each tile of the bf16 products with ragged last tiles, one to sixteen slices, and the fp32 epilogues:
+    weight gradients in 64x32, 64x64, 128x64, 256x128, 192x192, 256x160, 256x192, 256x256, 64x32 again with a
+    long contraction, 128x128 and 256x192; forward products and data gradients in the same tiles, except
+    that up to 768 k the shapes of more than 256 tiles of 128x64 take 128x64 and 128x128 in two
+    stages; then the tiles passed over for those, with 832 k, and both of the two-stage forms with eleven
+    and twelve slices.  fp32 sums of K products of bf16 values: K eps of the sum of magnitudes."""
     print(f"[case] gemm tiles M={M} N={N} K={K}", flush=True)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(M + N + K)
