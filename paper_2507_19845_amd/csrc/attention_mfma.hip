@@ -831,19 +831,25 @@ void launch_timage(const TImageArgs& t, int B, int S, int a, hipStream_t st) {
 // one side in backward).
 //   forward, 128 rows and one wave per 32 | 64 rows and two waves:
 //      D=128  S=128   h 128 n 256  12.9 | 12.4    h 160 n 320  13.1 | 14.1
-//             S=256   h 128 n 512  18.6 | 18.6    h 160 n 640  21.5 | 23.8
-//             S=512   h  80 n 640  26.4 | 25.3    h 112 n 896  27.8 | 30.0
-//             S=768   h  53 n 636  33.6 | 32.9    h  85 n1020  40.5 | 57.1
-//             S=1280  h  38 n 760  44.2 | 40.0    h  45 n 900  45.9 | 51.2
+//             S=130   h 154 n 462  17.7 | 17.5    S=169   h 184 n 552  17.8 | 20.3
+//             S=206   h  57 n 228  13.6 | 13.3    S=201   h 126 n 504  16.8 | 19.5
+//             S=299   h  95 n 475  21.5 | 20.4    S=286   h 109 n 545  22.8 | 24.3
+//             S=567   h  68 n 612  27.8 | 26.0    S=674   h  66 n 726  30.7 | 32.3
+//             S=978   h  48 n 768  35.8 | 33.3    S=861   h  59 n 826  36.3 | 42.1
+//             S=1835  h  28 n 812  55.1 | 49.6    S=1696  h  31 n 837  52.7 | 56.9
 //             S=2048  h  32 n1024  64.0 | 62.9    h  40 n1280  67.8 | 78.3
-//      D=64   S=256   h 160 n 640  13.7 | 13.7    h 224 n 896  15.4 | 16.7
-//             S=768   h  64 n 768  21.9 | 19.2    h  85 n1020  27.6 | 31.1
+//      D=64   S=256   h 160 n 640  13.7 | 13.7    S=195   h 186 n 744  13.7 | 15.3
+//             S=406   h 100 n 700  17.7 | 16.4    S=448   h 119 n 833  19.3 | 20.0
+//             S=491   h  92 n 736  19.6 | 18.4    S=460   h  97 n 776  18.4 | 19.6
+//             S=677   h  86 n 946  24.6 | 23.3    S=768   h  85 n1020  27.6 | 31.1
 //             S=2048  h  32 n1024  43.2 | 38.3    h  48 n1536  50.5 | 53.1
-//      D=32   S=768   h  64 n 768  15.3 | 13.4    h  85 n1020  23.7 | 25.3
+//      D=32   S=714   h  83 n 996  19.0 | 18.2    S=768   h  85 n1020  23.7 | 25.3
+//             S=1000  h  63 n1008  21.4 | 19.9    S=833   h  73 n1022  19.9 | 21.4 (more than 256 blocks of 256 rows)
 //             S=2048  h  32 n1024  31.0 | 26.6    h  56 n1792  40.5 | 40.7
+// (129 to 192 rows are three blocks of 64 or two of 128, whose second one is half empty: a higher limit.)
 //   backward, 256 rows and two launches | 128 rows:
 //      D=128  S=128   h 160 n 160  33.1 | 32.2    h 256 n 256  39.5 | 41.1
-//             S=192   h 128 n 256  42.9 | 38.6    h 160 n 320  45.1 | 48.2
+//             S=178   h 148 n 296  46.3 | 40.8    S=192   h 160 n 320  45.1 | 48.2
 //             S=256   h 192 n 384  62.5 | 62.0    h 224 n 448  68.1 | 76.1
 //             S=512   h 104 n 416  83.1 | 81.0    h 128 n 512  89.3 | 96.0
 //             S=1024  h  64 n 512   132 |  122    h  72 n 576   135 |  139
@@ -852,18 +858,20 @@ void launch_timage(const TImageArgs& t, int B, int S, int a, hipStream_t st) {
 //             S=256   h 192 n 384  38.4 | 36.5    h 224 n 448  40.3 | 43.7
 //             S=2048  h  36 n 576   142 |  123    h  48 n 768   153 |  167
 //      D=32   S=160   h 213 n 426  21.1 | 20.5    h 256 n 512  22.5 | 24.0
+//             S=226   h 248 n 496  32.2 | 25.6    (no loss up to the limit on wg)
 //             S=1024  h 112 n 896  78.7 | 70.3    h 128 n1024  79.9 | 82.5
 //   backward, 128 rows | 64 rows:
 //      D=128  S=512   h  16 n 128  34.1 | 33.1    S=1024  h   8 n 128  48.3 | 50.0
 //      D=64   S=1024  h   8 n 128  33.5 | 31.3    S=1024  h  32 n 512  43.2 | 42.9
 // Between 257 blocks of 256 rows, one more than there are compute units, and the limits on wg the
-// two-launch form needs a second round of workgroups, which costs a short sequence (up to 256 rows) more
-// than the split: D=128 S=256 h 288 109 | 96.  At D=32, whose workgroups share a unit, every shape
+// two-launch form needs a second round of workgroups, which costs a short sequence (up to 512 rows) more
+// than the split: D=128 S=256 h 288 109 | 96, S=420 h 132 96.3 | 87.9.  At D=32, whose workgroups share a unit, every shape
 // gains up to wg 448 and the first one loses at 512.
 long row_blocks(int B, int S, int a, int rows) { return (long)a * B * ((S + rows - 1) / rows); }
 bool split_fwd(int B, int S, int a, int d) {
-  const long most = d == 128 ? (S <= 128 ? 256 : S < 448 ? 512 : S < 1024 ? 640 : S < 1792 ? 832 : 1024)
-                             : (S <= 192 ? 512 : S < 448 ? 640 : S < 1024 ? 832 : 1024);
+  const long most = d == 128 ? (S <= 128 ? 256 : S <= 192 ? 480 : S <= 256 ? 256 : S <= 448 ? 480 : S <= 512 ? 576
+                                : S <= 768 ? 640 : S < 1024 ? 768 : S < 2048 ? 832 : 1024)
+                             : (S <= 192 ? 512 : S <= 256 ? 640 : S <= 448 ? 704 : S <= 512 ? 736 : S <= 768 ? 992 : 1024);
   return row_blocks(B, S, a, 256) <= 256 && row_blocks(B, S, a, 64) <= most;
 }
 int split_rows_bwd(int B, int S, int a, int d) {
@@ -871,10 +879,10 @@ int split_rows_bwd(int B, int S, int a, int d) {
   if (2 * row_blocks(B, S, a, 64) <= 256 && (d < 128 || S <= 512)) return 64;
   const long wg = row_blocks(B, S, a, 256);
   if (wg > (d == 32 ? 448 : 288)) return 0;
-  if (wg > 256 && S <= 256) return 128;
-  const long most = d == 128  ? (S <= 128 ? 160 : S <= 192 ? 288 : S <= 256 ? 384 : S <= 512 ? 432 : S <= 1024 ? 544 : kAny)
+  if (wg > 256 && S <= 512) return 128;
+  const long most = d == 128  ? (S <= 128 ? 160 : S <= 192 ? 304 : S <= 256 ? 384 : S <= 512 ? 432 : S <= 1024 ? 544 : kAny)
                     : d == 64 ? (S <= 128 ? kAny : S <= 192 ? 304 : S <= 256 ? 384 : kAny)
-                              : (S <= 128 ? kAny : S < 256 ? 448 : kAny);
+                              : (S <= 128 || S > 192 ? kAny : 448);
   return row_blocks(B, S, a, 128) <= most ? 128 : 0;
 }
 

@@ -782,7 +782,7 @@ def test_op_attention_bf16_splits(Bn, S, a, d):
     """The arrangements of the bf16 attention kernels at the edges of their blocks (32, 64, 128, 256 rows): the
     first six take 64 rows and two waves per 32 throughout, then backward with 128 rows, and the next two
     one wave per 32 rows in both directions; then, forward and backward, one wave and one wave (head
-    dimension 32), and the limits of short sequences: one wave and one wave, two and two, two and two, one
+    dimension 32), and the limits of short sequences: one wave and one wave, two and two, one and two, one
     and one, two and two.  Against fp64 on the same inputs; probabilities, dS and the outputs are rounded to bf16
     (2^-9 each), so 2-norm errors stay within 2^-7 and single values within 2^-4 of the largest."""
     print(f"[case] attention splits B={Bn} S={S} a={a} d={d}", flush=True)
