@@ -827,26 +827,46 @@ void launch_timage(const TImageArgs& t, int B, int S, int a, hipStream_t st) {
 // shows as soon as the workgroups no longer run at once, and a short sequence has no long chain to
 // shorten: the limits on the workgroups below grow with S.  Limits on 256-row blocks (wg) alone,
 // whatever S, took short sequences of many heads to the split forms at up to 1.4 times the time.
-// Measured in us, both sides of every line (h: heads times batch; n: workgroups of the split form, of
-// one side in backward).
+// In forward the limits depend on the number of heads too (heads times batch, h): workgroups go to the
+// eight XCDs in turn, the heads first, so all of a head's are on one XCD where h is a multiple of 8, on two of
+// them where it is a multiple of 4, and its K and V come out of that L2.  An odd h spreads every head over all
+// eight, and the split form, which reads them twice as often, pays for that first: MB fetched at S=1792, D=128,
+// one wave per 32 rows | two: h 32 44 | 51, h 28 62 | 79, h 30 112 | 177, h 33 198 | 372.
+// Measured in us, both sides of every line (n: workgroups of the split form, of one side in backward).
 //   forward, 128 rows and one wave per 32 | 64 rows and two waves:
 //      D=128  S=128   h 128 n 256  12.9 | 12.4    h 160 n 320  13.1 | 14.1
 //             S=130   h 154 n 462  17.7 | 17.5    S=169   h 184 n 552  17.8 | 20.3
 //             S=206   h  57 n 228  13.6 | 13.3    S=201   h 126 n 504  16.8 | 19.5
-//             S=299   h  95 n 475  21.5 | 20.4    S=286   h 109 n 545  22.8 | 24.3
-//             S=567   h  68 n 612  27.8 | 26.0    S=674   h  66 n 726  30.7 | 32.3
-//             S=978   h  48 n 768  35.8 | 33.3    S=861   h  59 n 826  36.3 | 42.1
-//             S=1835  h  28 n 812  55.1 | 49.6    S=1696  h  31 n 837  52.7 | 56.9
-//             S=2048  h  32 n1024  64.0 | 62.9    h  40 n1280  67.8 | 78.3
+//       odd   S=299   h  95 n 475  21.5 | 20.4    S=286   h 109 n 545  22.8 | 24.3
+//             S=567   h  68 n 612  27.8 | 26.0    S=768   h  57 n 684   x1.06
+//             S=960   h  35 n 525   x0.89         S=850   h  51 n 714   x1.05
+//             S=1472  h  33 n 759  46.8 | 47.2    S=1344  h  39 n 819  45.3 | 46.1
+//             S=1728  h  27 n 729  51.3 | 49.4    S=1792  h  33 n 924  57.3 | 64.9
+//             S=2048  h  21 n 672   x0.86         S=2048  h  27 n 864  60.8 | 64.3
+//       even  S=420   h  66 n 462   x0.89         S=420   h  90 n 630   x1.03
+//             S=1216  h  42 n 798  41.9 | 40.8    S=1024  h  58 n 928   x1.09
+//             S=1664  h  30 n 780  51.0 | 46.0    S=1408  h  42 n 924  47.2 | 48.7
+//             S=1984  h  30 n 930  59.4 | 59.0    S=2047  h  30 n 960  61.7 | 62.6
+//       of 4  S=384   h  88 n 528   x0.93         S=384   h 104 n 624   x1.02
+//             S=512   h  80 n 640   x0.96         S=512   h  88 n 704   x1.00
+//             S=768   h  56 n 672   x0.90         S=640   h  84 n 840   x1.06
+//             S=960   h  56 n 840   x0.96         S=960   h  60 n 900   x1.03
+//             S=1152  h  48 n 864  41.4 | 39.4    S=1024  h  60 n 960   x1.03
+//             S=1728  h  32 n 864  53.2 | 47.9    S=1984  h  32 n 992  60.9 | 58.0   (no loss from 1216 rows on)
 //      D=64   S=256   h 160 n 640  13.7 | 13.7    S=195   h 186 n 744  13.7 | 15.3
-//             S=406   h 100 n 700  17.7 | 16.4    S=448   h 119 n 833  19.3 | 20.0
-//             S=491   h  92 n 736  19.6 | 18.4    S=460   h  97 n 776  18.4 | 19.6
-//             S=677   h  86 n 946  24.6 | 23.3    S=768   h  85 n1020  27.6 | 31.1
-//             S=2048  h  32 n1024  43.2 | 38.3    h  48 n1536  50.5 | 53.1
-//      D=32   S=714   h  83 n 996  19.0 | 18.2    S=768   h  85 n1020  23.7 | 25.3
+//       odd   S=406   h 100 n 700  17.7 | 16.4    S=384   h 119 n 714   x1.06
+//             S=512   h  63 n 504   x0.95         S=460   h  97 n 776  18.4 | 19.6
+//             S=768   h  61 n 732   x0.91         S=700   h  85 n 935   x1.09
+//       even  S=420   h  90 n 630   x0.94         S=420   h 114 n 798   x1.03
+//             S=768   h  82 n 984   x0.96         (no loss from 513 rows on)
+//       of 4  S=384   h 128 n 768   x0.95         S=512   h 128 n1024   x1.02
+//             S=2048  h  32 n1024  43.2 | 38.3    (more than 256 blocks of 256 rows: h 48 n1536 50.5 | 53.1)
+//      D=32   S=160   h 232 n 696   x0.97         S=256   h 256 n1024   x1.04
+//       of 4  S=512   h 104 n 832   x0.96         S=512   h 114 n 912   x1.12 (even)
 //             S=1000  h  63 n1008  21.4 | 19.9    S=833   h  73 n1022  19.9 | 21.4 (more than 256 blocks of 256 rows)
 //             S=2048  h  32 n1024  31.0 | 26.6    h  56 n1792  40.5 | 40.7
-// (129 to 192 rows are three blocks of 64 or two of 128, whose second one is half empty: a higher limit.)
+// (x: time of the split form over the other's.  129 to 192 rows are three blocks of 64 or two of 128, whose
+// second one is half empty: a higher limit.)
 //   backward, 256 rows and two launches | 128 rows:
 //      D=128  S=128   h 160 n 160  33.1 | 32.2    h 256 n 256  39.5 | 41.1
 //             S=178   h 148 n 296  46.3 | 40.8    S=192   h 160 n 320  45.1 | 48.2
@@ -869,9 +889,15 @@ void launch_timage(const TImageArgs& t, int B, int S, int a, hipStream_t st) {
 // gains up to wg 448 and the first one loses at 512.
 long row_blocks(int B, int S, int a, int rows) { return (long)a * B * ((S + rows - 1) / rows); }
 bool split_fwd(int B, int S, int a, int d) {
-  const long most = d == 128 ? (S <= 128 ? 256 : S <= 192 ? 480 : S <= 256 ? 256 : S <= 448 ? 480 : S <= 512 ? 576
-                                : S <= 768 ? 640 : S < 1024 ? 768 : S < 2048 ? 832 : 1024)
-                             : (S <= 192 ? 512 : S <= 256 ? 640 : S <= 448 ? 704 : S <= 512 ? 736 : S <= 768 ? 992 : 1024);
+  struct Limit { int rows, odd, even, of4; };   // sequences of up to `rows`: most workgroups by heads times batch
+  static constexpr Limit k128[] = {{128, 256, 256, 256},  {192, 480, 480, 480},   {256, 256, 256, 256},   {448, 480, 544, 560},
+                                   {512, 576, 576, 688},  {768, 640, 640, 800},   {1023, 672, 752, 864},  {1215, 768, 832, 912},
+                                   {2047, 768, 912, 1024}, {2999, 832, 960, 1024}, {0x7fffffff, 1024, 1024, 1024}};
+  static constexpr Limit k64[] = {{192, 512, 512, 512}, {256, 640, 640, 640},    {448, 672, 704, 896},
+                                  {512, 704, 736, 928}, {768, 896, 1024, 1024}, {0x7fffffff, 1024, 1024, 1024}};
+  const Limit* l = d == 128 ? k128 : k64;
+  while (S > l->rows) ++l;
+  const long h = (long)a * B, most = d == 32 && S <= 192 ? 768 : h % 4 == 0 ? l->of4 : h % 2 == 0 ? l->even : l->odd;
   return row_blocks(B, S, a, 256) <= 256 && row_blocks(B, S, a, 64) <= most;
 }
 int split_rows_bwd(int B, int S, int a, int d) {

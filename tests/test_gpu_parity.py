@@ -777,13 +777,14 @@ def _attention_op(dt, Bn, S, a, d, qkv, dout):
 @pytest.mark.parametrize("Bn,S,a,d", [(1, 1, 1, 32), (1, 31, 2, 64), (2, 33, 3, 128), (1, 65, 3, 32), (1, 97, 2, 64), (1, 129, 2, 128),
                                       (3, 320, 14, 64), (1, 1000, 9, 128), (1, 257, 130, 32), (1, 260, 150, 64), (1, 130, 300, 128),
                                       (1, 300, 260, 32), (1, 200, 200, 64), (1, 161, 150, 64), (1, 193, 120, 128), (1, 130, 230, 128),
-                                      (1, 520, 60, 128)])
+                                      (1, 520, 60, 128), (1, 520, 84, 128), (1, 520, 83, 128)])
 def test_op_attention_bf16_splits(Bn, S, a, d):
     """The arrangements of the bf16 attention kernels at the edges of their blocks (32, 64, 128, 256 rows): the
     first six take 64 rows and two waves per 32 throughout, then backward with 128 rows, and the next two
     one wave per 32 rows in both directions; then, forward and backward, one wave and one wave (head
     dimension 32), and the limits of short sequences: one wave and one wave, two and two, one and two, one
-    and one, two and two.  Against fp64 on the same inputs; probabilities, dS and the outputs are rounded to bf16
+    and one, two and two; then two and two for a multiple of four heads, one and two for one head less.
+    Against fp64 on the same inputs; probabilities, dS and the outputs are rounded to bf16
     (2^-9 each), so 2-norm errors stay within 2^-7 and single values within 2^-4 of the largest."""
     print(f"[case] attention splits B={Bn} S={S} a={a} d={d}", flush=True)
     gen = torch.Generator(device="cuda")
