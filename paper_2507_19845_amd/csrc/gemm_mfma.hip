@@ -121,6 +121,25 @@ Tile choose_tile(int form, int M, int N, long K, Cost cost) {
   return choose_tile(form, &p, 1, K, cost);
 }
 
+// Whether weight gradients in one launch gain on a launch each.  What they gain is the rounds that their
+// partly filled last ones share.  What they lose is step: the workgroups of an XCD read each slice of an operand
+// once from memory while they walk the contraction together, a new launch lines them up again, and in a long
+// one the rounds drift apart (12 rounds of K = 32768: 35 GiB moved against 19.5).  So not with long contractions
+// where under a sixteenth of the rounds is shared.  One launch | a launch each, us a layer, hidden and ffn:
+//   4096, 16384, no shared round of 12   K = 12288 3557 | 3568   K = 16384 4696 | 4691   K = 32768 9590 | 9187
+//   8192, 32768, none of 48              K = 4096  5304 | 5372   K = 16384 19723 | 18836
+//   6144, 24576, one of 28               K = 8192  5558 | 5635   K = 24576 16542 | 16051
+//   5120, 20480, two of 21               K = 32768 15602 | 16130     3072, 12288, two of 9  K = 49152 8427 | 8440
+bool worth_one_launch(Tile t, const Product* p, int n, long K) {
+  long apart = 0, tiles = 0;
+  for (int q = 0; q < n; ++q) {
+    const long own = (long)((p[q].M + kTiles[t].bm - 1) / kTiles[t].bm) * ((p[q].N + kTiles[t].bn - 1) / kTiles[t].bn);
+    apart += (own + 255) / 256;
+    tiles += own;
+  }
+  return K < 16384 || 16 * (apart - (tiles + 255) / 256) >= apart;
+}
+
 }  // namespace
 
 bool gemm_mfma_supported(int form, int M, int N, int K) {
@@ -132,9 +151,10 @@ bool gemm_mfma_supported(int form, int M, int N, int K) {
 // A weight-gradient product whose contraction is split over several buffers can run as one launch
 // (K here is the length of one segment: whole slices, so no slice straddles two buffers): one fp32
 // read-modify-write and one epilogue instead of one per micro-batch, and the four products of a layer in
-// one launch.  It changes the fp32 summation order over the tokens.  It is taken from four micro-batches
-// on, and with two or three only for matrices of at least 100 tiles of 256x256 with segments of whole 128
-// rows; other matrices keep the bits of the unsplit backward there.  That line is one of results and
+// one launch where that gains (worth_one_launch()).  It changes the fp32 summation order over the
+// tokens.  It is taken from four micro-batches on, and with two or three only for matrices of at least 100
+// tiles of 256x256 with segments of whole 128 rows; other matrices keep the bits of the unsplit backward
+// there.  That line is one of results and
 // not of speed, one launch being the faster everywhere.  A layer's weight phase, a launch per micro-batch
 // and matrix | one launch, us, 2 / 3 / 4 micro-batches:
 //   hidden 320, 192 tokens   37 | 11    49 | 12    65 | 12      1024, 4096   305 | 242    461 | 353    613 | 466
@@ -229,7 +249,14 @@ hipError_t gemm_wgrad_group(const WgradItem* items, int n, int K, int segments, 
     a[i].seg_stride_b = seg_stride_in;
     p[i] = Product{w.M, w.N};
   }
-  return launch_gemm_wgrad(choose_tile(2, p, n, (long)K * segments, COST_PLAIN), a, n, st);
+  const long k_all = (long)K * segments;
+  const Tile t = choose_tile(2, p, n, k_all, COST_PLAIN);
+  if (n == 1 || worth_one_launch(t, p, n, k_all)) return launch_gemm_wgrad(t, a, n, st);
+  for (int i = 0; i < n; ++i) {
+    const hipError_t e = launch_gemm_wgrad(choose_tile(2, p + i, 1, k_all, COST_PLAIN), a + i, 1, st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace gpts

@@ -100,8 +100,8 @@ hipError_t gemm_fwd_f16(int M, int N, int K, const void* A, const void* b_image,
                         const GemmEpilogue& ep, hipStream_t st);
 hipError_t gemm_mfma(int form, int M, int N, int K, const void* A, const void* B, void* C,
                      const GemmEpilogue& ep, hipStream_t st);
-// Weight gradients dw[M,N] += dout[K,M]^T in[K,N] of n <= kMaxWgrads linears over the same tokens in one
-// launch, bit for bit what gemm_mfma() gives for each; every shape gemm_mfma_supported(), with segments
+// Weight gradients dw[M,N] += dout[K,M]^T in[K,N] of n <= kMaxWgrads linears over the same tokens, in one
+// launch where that gains, bit for bit what gemm_mfma() gives for each; every shape gemm_mfma_supported(), with segments
 // (see GemmEpilogue) gemm_wgrad_segments_supported().
 struct WgradItem {
   int M, N;
