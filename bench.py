@@ -32,11 +32,12 @@ if ROOT not in sys.path:
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 # Memory traffic of the matrix-product kernels on the default workload and schedule (one weight
 # phase per step), from two rocprofv3 --pmc passes: FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 averaged
-# over the 272 matrix-product launches of a step (the summary under profiles/ has the commands
-# and the per-kernel figures).  Only reported while the kernel source is the one the counters
-# were taken on.
-GEMM_TRAFFIC = {"workload": "decoupled_bf16", "weight_phase": True, "bytes_per_launch": 1016.6 * 2**20,
-                "source_sha256_16": "369e0b5450094d57"}
+# over the matrix-product launches of a traced pass, 272 a step (the summary under profiles/ has the
+# commands and the per-kernel figures).  Only reported while the sources of the kernel and of the
+# choice of its tiles are the ones the counters were taken on.
+GEMM_SOURCES = ("agpr_ops.hpp", "gemm_tiles.hpp", "gemm_mfma.hip")
+GEMM_TRAFFIC = {"workload": "decoupled_bf16", "weight_phase": True, "bytes_per_launch": 948.8 * 2**20,
+                "source_sha256_16": "9a918cbc8fd7e9f8"}
 PEAK_FP32_TFLOPS = 157.3    # MI355X fp32 vector
 DEFAULT_WORKLOAD = "decoupled_bf16"
 
@@ -111,11 +112,14 @@ def gemm_traffic(shape, weight_phase):
     """Measured HBM bytes per launch of the matrix-product kernel, or None when no counters
     exist for this workload or the kernel source has changed since they were taken."""
     import hashlib
-    src = os.path.join(ROOT, "paper_2507_19845_amd", "csrc", "gemm_mfma.hip")
+    h = hashlib.sha256()
     try:
-        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+        for name in GEMM_SOURCES:
+            with open(os.path.join(ROOT, "paper_2507_19845_amd", "csrc", name), "rb") as f:
+                h.update(f.read())
     except OSError:
         return None
+    sha = h.hexdigest()[:16]
     if (shape.name != GEMM_TRAFFIC["workload"] or sha != GEMM_TRAFFIC["source_sha256_16"]
             or weight_phase != GEMM_TRAFFIC["weight_phase"]):
         return None
@@ -168,7 +172,8 @@ def traced_pass(step, bufs, shape, n_ops, steps, weight_phase):
             "algorithmic_bytes_per_launch": sum(c["bytes"] for c in gemm) / n,
             "launches": n, "launches_per_step": n // steps, "avg_launch_ms": ms / n, "flops_per_launch": fl / n,
             "avg_launch_ms_source": "hipEvent pairs recorded on the launch stream by the library's tracer (not rocprofv3)",
-            "measured": f"hipEvent pairs around every launch, {steps} traced step(s) after the timed region",
+            "measured": f"hipEvent pairs around every launch, {steps} traced step(s) after the timed region; weight "
+                        "gradients and column sums that a step launches together are launched and timed one by one",
             "dropped_records": dropped}
     return roof, table
 

@@ -25,7 +25,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=fast",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
-FLAGS += os.environ.get("GPTS_HIPCC_FLAGS", "").split()   # e.g. -DGPTS_BIG_WAVES=8 for experiments
+FLAGS += os.environ.get("GPTS_HIPCC_FLAGS", "").split()   # more flags, e.g. -Rpass-analysis=kernel-resource-usage
 
 
 # gemm_mi16_kernel<EPI, FORM, F16, MB, NB, ..> (and the group kernel) keeps its 4 MB NB accumulators in AGPRs a0.. by hand, across
