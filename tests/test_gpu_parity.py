@@ -59,6 +59,8 @@ SMALL = [
     # in both directions (320 blocks of 256 rows, 512 at head dimension 32), the second block short
     W[1].with_(name="bf16_fwd16_d128_full_chip", n_layers=1, hidden=256, n_heads=10, head_dim=128, ffn=256,
                seq=260, batch=16, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
+    W[1].with_(name="bf16_fwd16_d128_many", n_layers=1, hidden=128, n_heads=10, head_dim=128, ffn=128,
+               seq=260, batch=48, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
     W[1].with_(name="bf16_fwd16_d64_full_chip", n_layers=1, hidden=256, n_heads=10, head_dim=64, ffn=256,
                seq=260, batch=16, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
     W[1].with_(name="bf16_fwd16_d32_full_chip", n_layers=1, hidden=256, n_heads=16, head_dim=32, ffn=256,
@@ -809,6 +811,33 @@ def test_op_attention_bf16_splits(Bn, S, a, d):
         for got, want in ((out[b].double(), o.detach()), (dqkv[b].double(), x.grad)):
             assert ((got - want).norm() / want.norm()).item() < 2 ** -7
             assert (got - want).abs().max().item() < 2 ** -4 * want.abs().max().item()
+
+
+@pytest.mark.parametrize("Bn,S,a,d", [(1, 130, 90, 128), (1, 100, 150, 64), (2, 70, 200, 32), (1, 130, 600, 128), (2, 70, 430, 64),
+                                      (1, 65, 900, 32), (1, 449, 220, 128)])
+def test_op_attention_bf16_backward_forms(Bn, S, a, d):
+    """One wave per 32 rows in backward: 128 rows and one launch (the first three), 128 rows and a launch for each
+    side (the next three), 256 rows.  Reference and tolerances as in test_op_attention_bf16_splits."""
+    test_op_attention_bf16_splits(Bn, S, a, d)
+
+
+@pytest.mark.parametrize("S,a,d", [(70, 2, 128), (97, 1, 64), (65, 3, 32), (70, 500, 64)])
+def test_op_attention_bf16_rows_past_the_end_count_as_zeros(S, a, d):
+    """The last tile's rows past the sequence's end hold a copy of its last row: with an infinite value there
+    (and in its output gradient) the last query's output is infinite and no NaN, and the last key's dV too."""
+    print(f"[case] attention rows past the end S={S} a={a} d={d}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(S)
+    qkv = torch.empty(1, S, 3, a, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    dout = torch.empty(1, S, a, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    finite = _attention_op(B.GPTS_BF16, 1, S, a, d, qkv, dout)
+    qkv[:, -1, 2] = float("inf")
+    out, lse, _ = _attention_op(B.GPTS_BF16, 1, S, a, d, qkv, dout)
+    assert (out[0, -1] == float("inf")).all() and torch.equal(lse, finite[1])
+    qkv[:, -1, 2] = 1.0
+    dout[:, -1] = float("inf")
+    dv = _attention_op(B.GPTS_BF16, 1, S, a, d, qkv, dout)[2].view(S, 3, a, d)[:, 2]
+    assert (dv[-1] == float("inf")).all()
 
 
 @pytest.mark.parametrize("Bn,S,a,d", [(1, 40, 2, 64), (1, 97, 2, 128), (2, 130, 1, 32), (1, 70, 300, 32)])
