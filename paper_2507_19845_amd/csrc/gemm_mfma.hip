@@ -24,7 +24,7 @@ __global__ __launch_bounds__(256) void prepare_image_kernel(const bf16* __restri
   bf16x8 v[PER];
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const int slot = p * 256 + threadIdx.x, r = slot >> 3, c = (slot & 7) ^ swz_kc<8>(r);
+    const int slot = p * 256 + threadIdx.x, r = slot >> 3, c = (slot & 7) ^ swz_kc(r);
     if (tn * 256 + r < N) v[p] = *reinterpret_cast<const bf16x8*>(src + (size_t)(tn * 256 + r) * K + kt * kImageK + c * 8);
     else for (int e = 0; e < 8; ++e) v[p][e] = (bf16)0.f;
   }

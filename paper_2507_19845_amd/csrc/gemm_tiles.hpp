@@ -94,13 +94,12 @@ hipError_t launch_gemm_fwd_f16(Tile tile, int epi, const MfmaArgs& a, hipStream_
 hipError_t launch_gemm_dgrad(Tile tile, int epi, const MfmaArgs& a, hipStream_t st);
 hipError_t launch_gemm_wgrad(Tile tile, const MfmaArgs* a, int n, hipStream_t st);   // n <= kMaxWgrads, one launch
 
-// 16-byte chunk swizzle of a K-contiguous tile row with CPR chunks per row.  Chosen
-// so that 16 consecutive rows read at the same logical chunk hit 16 different
-// (row parity / quarter, chunk) bank groups, for 64- and for 32-bank layouts.
-template <int CPR> __device__ __forceinline__ int swz_kc(int row) {
-  if constexpr (CPR == 8) return (row & 7) ^ ((row >> 3) & 1);
-  else return ((row >> 1) & 3) ^ ((row >> 3) & 1);
-}
+// 16-byte chunk swizzle of a K-contiguous tile row of eight chunks (BK = 64).  A 16-byte LDS read serves
+// 16 lanes at a time over the 64 banks, lanes {0-3, 12-15, 20-27} of each half wave, then the others, and
+// not 16 in a row: of a fragment (lane: row lane % 16, chunk lane / 16) rows 4-11 of the one chunk come
+// together with rows 0-3 and 12-15 of the chunk before it.  The eighth bit of the row (its half of the 64 banks)
+// and this make the 16 places different.
+__host__ __device__ __forceinline__ int swz_kc(int row) { return (row & 7) ^ ((row >> 2) & 1); }
 
 namespace {
 
@@ -147,7 +146,7 @@ template <int R, int BK, bool KMAJOR> struct Operand {
           const int gr = min(r0 + row, rpad - 16 + (row & 15));
           goff[i] = (uint32_t)(((size_t)(gr / 256) * 256 * ld + (size_t)(gr % 256) * BK + (slot % CPR) * 8) * 2);
         } else {
-          const int chunk = (slot % CPR) ^ swz_kc<CPR>(row);
+          const int chunk = (slot % CPR) ^ swz_kc(row);
           const int gr = min(r0 + row, rtotal - 1);
           goff[i] = (uint32_t)(((size_t)gr * ld + chunk * 8) * 2);
         }
@@ -422,7 +421,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, int id, char* const
   int kc_off[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
-    kc_off[ks] = (lane & 15) * RB + (((4 * ks + (lane >> 4)) ^ swz_kc<BK / 8>(lane & 15)) << 4);
+    kc_off[ks] = (lane & 15) * RB + (((4 * ks + (lane >> 4)) ^ swz_kc(lane & 15)) << 4);
   const char* fragA = lds + (A_KM ? 0 : wm * WM * RB);
   const char* fragB = lds + A_BYTES + (B_KM ? 0 : wn * WN * RB);
   // K-major: transposing read t (0, 1) of block rb fetches k-rows 8*(lane>>4) + 4t + 0..3 of the
