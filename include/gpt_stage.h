@@ -410,7 +410,10 @@ typedef struct {
                                      fp32 gradient matrices.  The stash pool must then hold
                                      n_chunks * W slots (handed out in a fixed, equally spaced
                                      pattern, which the one-launch weight phase needs); a
-                                     stash is released after its chunk's weight phase.      */
+                                     stash is released after its chunk's weight phase.
+                                     Small micro-batches of a window go through a chunk
+                                     together, one launch per operator, with the bits of a
+                                     launch each; the pools' contents are undefined after. */
   size_t grad_pool_bytes;
 } gpt_dpp_job;
 

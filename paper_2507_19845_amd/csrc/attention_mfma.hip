@@ -85,6 +85,13 @@ __device__ __forceinline__ void settle(const bf16x8& v) {
 }
 __device__ __forceinline__ void settle(float v) { asm volatile("" ::"v"(v)); }
 
+template <typename P> __device__ __forceinline__ P* after(P* p, size_t bytes) {
+  return (P*)((const char*)p + bytes);   // (by way of an integer it would no longer count as global memory)
+}
+// blockIdx.y counts the B sequences of every micro-batch; stride 0: there is one (and no division)
+__device__ __forceinline__ int microbatch(int B, size_t stride) {
+  return stride ? __builtin_amdgcn_readfirstlane(blockIdx.y / B) : 0;
+}
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(size_t)(__attribute__((address_space(3))) const char*)p;
 }
@@ -132,8 +139,11 @@ template <int D, int NW> __device__ __forceinline__ void zero_rows(char* tile, i
 
 // delta[b][n][s] = sum_d dO * O: one row of a head per D/8 lanes.
 template <int D, bool O16>
-__global__ __launch_bounds__(256) void attn_delta_kernel(const bf16* __restrict__ out, const bf16* __restrict__ dout,
-                                                         float* __restrict__ delta, int S, int a, int total) {
+__global__ __launch_bounds__(256) void attn_delta_kernel(const bf16* __restrict__ out0, const bf16* __restrict__ dout0,
+                                                         float* __restrict__ delta0, int S, int a, int total, size_t stride) {
+  const bf16* const out = after(out0, blockIdx.y * stride);
+  const bf16* const dout = after(dout0, blockIdx.y * stride);
+  float* const delta = after(delta0, blockIdx.y * stride);
   constexpr int TPR = D / 8;
   const int t = (int)(blockIdx.x * 256 + threadIdx.x);
   const int i = t / TPR, cc = t % TPR;     // i: [b][s][n], as the rows lie in memory
@@ -188,8 +198,8 @@ template <int D> __device__ __forceinline__ bf16x8 natural_frag(const char* tile
 // RW x SW waves: RW blocks of 32 queries; with SW = 2 a second wave per block takes the other 32 keys
 // of every tile, and the two running maxima, sums and outputs are merged through LDS at the end.
 template <int D, bool F16, int RW, int SW>
-__global__ __launch_bounds__(64 * RW * SW, 2) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out,
-                                                               float* __restrict__ lse, int S, int a) {
+__global__ __launch_bounds__(64 * RW * SW, 2) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv0, bf16* __restrict__ out0,
+                                                               float* __restrict__ lse0, int S, int a, int B, size_t stride) {
   constexpr int KSTEPS = D / 16;   // MFMA k-steps over the head dimension
   constexpr int DB = D / 32;       // 32-row blocks of O^T
   constexpr int TILE = BKV * D * 2;  // bytes of one K or V tile
@@ -200,7 +210,10 @@ __global__ __launch_bounds__(64 * RW * SW, 2) void attn_fwd_mfma_kernel(const bf
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rw = wave % RW, kb0 = wave / RW * NKB;   // this wave's query block; its first key block of a tile
   const int qt = gridDim.z - 1 - blockIdx.z;
-  const int n = blockIdx.x, b = blockIdx.y;
+  const int n = blockIdx.x, mb = microbatch(B, stride), b = blockIdx.y - mb * B;   // head; micro-batch, sequence
+  const bf16* __restrict__ qkv = after(qkv0, mb * stride);
+  bf16* __restrict__ out = after(out0, mb * stride);
+  float* __restrict__ lse = after(lse0, mb * stride);
   const int P = a * D;
   const size_t ld = 3 * (size_t)P;
   const bf16* base = qkv + (size_t)b * S * ld + (size_t)n * D;
@@ -376,6 +389,26 @@ __global__ __launch_bounds__(64 * RW * SW, 2) void attn_fwd_mfma_kernel(const bf
 }
 
 
+struct BwdArgs {
+  const bf16 *qkv, *qk16, *dout, *out;   // out: where the query side forms delta, else null
+  const float* lse;
+  float* delta;
+  bf16* dqkv;
+  int S, a, B;           // B sequences per micro-batch
+  size_t act, grad;      // bytes between the micro-batches' dqkv (grad) and everything else (act)
+};
+// the arguments of the workgroup's micro-batch mb
+__device__ __forceinline__ BwdArgs at_microbatch(BwdArgs p, int mb) {
+  p.qkv = after(p.qkv, mb * p.act);
+  p.qk16 = after(p.qk16, mb * p.act);
+  p.dout = after(p.dout, mb * p.act);
+  if (p.out) p.out = after(p.out, mb * p.act);
+  p.lse = after(p.lse, mb * p.act);
+  p.delta = after(p.delta, mb * p.act);
+  p.dqkv = after(p.dqkv, mb * p.grad);
+  return p;
+}
+
 // Backward, key side.  A workgroup owns blocks of 32 keys, one or two waves each, and streams the
 // query rows at and after them in tiles of 64: Q and dO, lse and delta, all by DMA.  Per wave and 32-query block:
 //   S[q][k]  = Q K^T       (A = Q fragment from LDS, B = K fragment in registers)
@@ -392,14 +425,21 @@ __global__ __launch_bounds__(64 * RW * SW, 2) void attn_fwd_mfma_kernel(const bf
 // of every tile and the two sums are added through LDS at the end.
 template <bool F16S> constexpr int kBwdTiles = F16S ? 3 : 2;   // LDS tiles of a stage: [Q | dO | fp16 Q] or [K | V | fp16 K]
 template <int D, bool F16S, int RW, int SW>
-__device__ __forceinline__ void dkv_block(const bf16* __restrict__ qkv, const bf16* __restrict__ qk16, const bf16* __restrict__ dout,
-                                          const float* __restrict__ lse, const float* __restrict__ delta,
-                                          bf16* __restrict__ dqkv, int S, int a, int blk, char* lds, float (*stat)[2][BKV]) {
+__device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* lds, float (*stat)[2][BKV]) {
+  const int mb = microbatch(args.B, args.act);
+  const BwdArgs p = at_microbatch(args, mb);
+  const bf16* const __restrict__ qkv = p.qkv;
+  const bf16* const __restrict__ qk16 = p.qk16;
+  const bf16* const __restrict__ dout = p.dout;
+  const float* const __restrict__ lse = p.lse;
+  const float* const __restrict__ delta = p.delta;
+  bf16* const __restrict__ dqkv = p.dqkv;
+  const int S = p.S, a = p.a;
   constexpr int KSTEPS = D / 16, DB = D / 32, TILE = BKV * D * 2, NW = RW * SW;
   const int lane = threadIdx.x & 63;
   const int lane_id = lane;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = blockIdx.x, b = blockIdx.y;
+  const int n = blockIdx.x, b = blockIdx.y - mb * p.B;
   const int P = a * D;
   const size_t ld = 3 * (size_t)P;
   const bf16* base = qkv + (size_t)b * S * ld + (size_t)n * D;
@@ -594,15 +634,23 @@ __device__ __forceinline__ void dkv_block(const bf16* __restrict__ qkv, const bf
 // out (may be null): the forward output (fp16 with F16S); delta_q = sum_d dO * O is then formed here, where dO is in
 // registers anyway, and written for the key side, which runs after.  Null: delta is there already.
 template <int D, bool F16S, int RW, int SW>
-__device__ __forceinline__ void dq_block(const bf16* __restrict__ qkv, const bf16* __restrict__ qk16, const bf16* __restrict__ dout,
-                                         const bf16* __restrict__ out, const float* __restrict__ lse,
-                                         float* __restrict__ delta, bf16* __restrict__ dqkv, int S, int a, int qt, char* lds) {
+__device__ __forceinline__ void dq_block(const BwdArgs& args, int qt, char* lds) {
+  const int mb = microbatch(args.B, args.act);
+  const BwdArgs p = at_microbatch(args, mb);
+  const bf16* const __restrict__ qkv = p.qkv;
+  const bf16* const __restrict__ qk16 = p.qk16;
+  const bf16* const __restrict__ dout = p.dout;
+  const bf16* const __restrict__ out = p.out;
+  const float* const __restrict__ lse = p.lse;
+  float* const __restrict__ delta = p.delta;
+  bf16* const __restrict__ dqkv = p.dqkv;
+  const int S = p.S, a = p.a;
   constexpr int KSTEPS = D / 16, DB = D / 32, TILE = BKV * D * 2, NW = RW * SW, BW = 32 * RW, NKB = 2 / SW;
   const int lane = threadIdx.x & 63;
   const int lane_id = lane;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rw = wave % RW, kb0 = wave / RW * NKB;   // this wave's query block; its first key block of a tile
-  const int n = blockIdx.x, b = blockIdx.y;
+  const int n = blockIdx.x, b = blockIdx.y - mb * p.B;
   const int P = a * D;
   const size_t ld = 3 * (size_t)P;
   const bf16* base = qkv + (size_t)b * S * ld + (size_t)n * D;
@@ -754,23 +802,16 @@ __device__ __forceinline__ void dq_block(const bf16* __restrict__ qkv, const bf1
   }
 }
 
-struct BwdArgs {
-  const bf16 *qkv, *qk16, *dout, *out;   // out: where the query side forms delta, else null
-  const float* lse;
-  float* delta;
-  bf16* dqkv;
-  int S, a;
-};
 // Key side and query side a launch each, 32 RW rows per workgroup, the query side first (it forms delta): the form for
 // many workgroups.
 template <int D, bool F16S, int RW> __global__ __launch_bounds__(64 * RW) void attn_bwd_dkv_mfma_kernel(const BwdArgs p) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kBwdTiles<F16S> * BKV * D * 2];
   __shared__ __attribute__((aligned(256))) float stat[2][2][BKV];  // [stage][lse | delta][row]
-  dkv_block<D, F16S, RW, 1>(p.qkv, p.qk16, p.dout, p.lse, p.delta, p.dqkv, p.S, p.a, blockIdx.z, lds, stat);
+  dkv_block<D, F16S, RW, 1>(p, blockIdx.z, lds, stat);
 }
 template <int D, bool F16S, int RW> __global__ __launch_bounds__(64 * RW) void attn_bwd_dq_mfma_kernel(const BwdArgs p) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kBwdTiles<F16S> * BKV * D * 2];
-  dq_block<D, F16S, RW, 1>(p.qkv, p.qk16, p.dout, p.out, p.lse, p.delta, p.dqkv, p.S, p.a, gridDim.z - 1 - blockIdx.z, lds);
+  dq_block<D, F16S, RW, 1>(p, gridDim.z - 1 - blockIdx.z, lds);
 }
 // Both sides in one launch, 32 RW rows per workgroup, SW waves per block of 32: the forms for fewer
 // workgroups.  Even z: key block z/2; odd z: the query blocks from the last one down (heaviest first).
@@ -782,9 +823,9 @@ __global__ __launch_bounds__(64 * RW * SW, F16S && D == 128 && RW * SW == 4 ? 1 
   __shared__ __attribute__((aligned(256))) float stat[2][2][BKV];
   const int i = blockIdx.z >> 1;
   if ((blockIdx.z & 1) == 0)
-    dkv_block<D, F16S, RW, SW>(p.qkv, p.qk16, p.dout, p.lse, p.delta, p.dqkv, p.S, p.a, i, lds, stat);
+    dkv_block<D, F16S, RW, SW>(p, i, lds, stat);
   else
-    dq_block<D, F16S, RW, SW>(p.qkv, p.qk16, p.dout, nullptr, p.lse, p.delta, p.dqkv, p.S, p.a, (int)(gridDim.z >> 1) - 1 - i, lds);
+    dq_block<D, F16S, RW, SW>(p, (int)(gridDim.z >> 1) - 1 - i, lds);
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -849,18 +890,19 @@ BwdForm bwd_form(int B, int S, int a, int d) {
 }
 
 template <int D, bool F16>
-void launch_fwd(const bf16* qkv, bf16* out, float* lse, int B, int S, int a, hipStream_t st) {
-  auto grid = [&](int rows) { return dim3(a, B, (S + rows - 1) / rows); };
-  if (split_fwd(B, S, a, D)) hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 2, 2>), grid(64), dim3(256), 0, st, qkv, out, lse, S, a);
-  else hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 4, 1>), grid(128), dim3(256), 0, st, qkv, out, lse, S, a);
+void launch_fwd(const bf16* qkv, bf16* out, float* lse, int B, int S, int a, int n, size_t stride, hipStream_t st) {
+  auto grid = [&](int rows) { return dim3(a, B * n, (S + rows - 1) / rows); };
+  if (split_fwd(B, S, a, D)) hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 2, 2>), grid(64), dim3(256), 0, st, qkv, out, lse, S, a, B, stride);
+  else hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 4, 1>), grid(128), dim3(256), 0, st, qkv, out, lse, S, a, B, stride);
 }
 
-template <int D, bool F16> void launch_bwd(const bf16* out, BwdArgs p, int B, hipStream_t st) {
-  auto grid = [&](int rows, int sides) { return dim3(p.a, B, sides * ((p.S + rows - 1) / rows)); };
+template <int D, bool F16> void launch_bwd(const bf16* out, BwdArgs p, int n, hipStream_t st) {
+  const int B = p.B;
+  auto grid = [&](int rows, int sides) { return dim3(p.a, B * n, sides * ((p.S + rows - 1) / rows)); };
   auto both = [&](auto rw_c, auto sw_c) {   // delta beforehand
     constexpr int RW = decltype(rw_c)::value, SW = decltype(sw_c)::value;
     const int total = B * p.S * p.a;
-    hipLaunchKernelGGL((attn_delta_kernel<D, F16>), dim3((total + 2048 / D - 1) / (2048 / D)), dim3(256), 0, st, out, p.dout, p.delta, p.S, p.a, total);
+    hipLaunchKernelGGL((attn_delta_kernel<D, F16>), dim3((total + 2048 / D - 1) / (2048 / D), n), dim3(256), 0, st, out, p.dout, p.delta, p.S, p.a, total, p.act);
     hipLaunchKernelGGL((attn_bwd_both_mfma_kernel<D, F16, RW, SW>), grid(32 * RW, 2), dim3(64 * RW * SW), 0, st, p);
   };
   auto each = [&](auto rw_c) {
@@ -899,13 +941,14 @@ size_t attention_mfma_scratch_bytes(int B, int S, int a, int d, int phase) {
 }
 
 hipError_t attention_fwd_mfma(int B, int S, int a, int d, const void* qkv, void* out, float* lse,
-                              void* scratch, hipStream_t st, bool f16) {
-  if (!attention_mfma_supported(B, S, a, d)) return hipErrorInvalidValue;
+                              void* scratch, hipStream_t st, bool f16, int n, size_t stride) {
+  (void)scratch;
+  if (!attention_mfma_supported(B, S, a, d) || n < 1 || (long)B * n > 65535) return hipErrorInvalidValue;
   const bf16* q = (const bf16*)qkv;
 #define GPTS_FWD(D)                                                    \
   do {                                                                 \
-    if (f16) launch_fwd<D, true>(q, (bf16*)out, lse, B, S, a, st);     \
-    else launch_fwd<D, false>(q, (bf16*)out, lse, B, S, a, st);        \
+    if (f16) launch_fwd<D, true>(q, (bf16*)out, lse, B, S, a, n, stride, st);     \
+    else launch_fwd<D, false>(q, (bf16*)out, lse, B, S, a, n, stride, st);        \
   } while (0)
   if (d == 128) GPTS_FWD(128);
   else if (d == 64) GPTS_FWD(64);
@@ -916,16 +959,16 @@ hipError_t attention_fwd_mfma(int B, int S, int a, int d, const void* qkv, void*
 
 hipError_t attention_bwd_mfma(int B, int S, int a, int d, const void* qkv, const void* out,
                               const float* lse, const void* dout, void* dqkv, void* scratch,
-                              hipStream_t st, const void* qkv_f16) {
-  if (!attention_mfma_supported(B, S, a, d)) return hipErrorInvalidValue;
+                              hipStream_t st, const void* qkv_f16, int n, size_t act, size_t grad) {
+  if (!attention_mfma_supported(B, S, a, d) || n < 1 || (long)B * n > 65535) return hipErrorInvalidValue;
   const bf16* q = (const bf16*)qkv;
   const bf16* o = (const bf16*)out;
   const bool f16 = qkv_f16 != nullptr;
-  const BwdArgs p{q, f16 ? (const bf16*)qkv_f16 : q, (const bf16*)dout, nullptr, lse, static_cast<float*>(scratch), (bf16*)dqkv, S, a};
+  const BwdArgs p{q, f16 ? (const bf16*)qkv_f16 : q, (const bf16*)dout, nullptr, lse, static_cast<float*>(scratch), (bf16*)dqkv, S, a, B, act, grad};
 #define GPTS_BWD(D)                             \
   do {                                          \
-    if (f16) launch_bwd<D, true>(o, p, B, st);  \
-    else launch_bwd<D, false>(o, p, B, st);     \
+    if (f16) launch_bwd<D, true>(o, p, n, st);  \
+    else launch_bwd<D, false>(o, p, n, st);     \
   } while (0)
   if (d == 128) GPTS_BWD(128);
   else if (d == 64) GPTS_BWD(64);

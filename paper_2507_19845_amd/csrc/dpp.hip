@@ -141,6 +141,83 @@ struct TaskIssuer {
         bwd_buf(j->n_microbatches, -1), left(j->n_chunks, j->n_microbatches), stash_slot_bytes(stash_slot) {}
   void* stash_at(int i, int j) { return static_cast<char*>(job->stash_pool) + (size_t)(j * W + i % W) * stash_slot_bytes; }
   void* grad_at(int i) { return static_cast<char*>(job->grad_pool) + (size_t)(i % W) * grad_slot_bytes; }
+  // Micro-batches i .. i+n-1 of a window as one pass over chunk j (with a weight phase per window; n from
+  // pass_size()).  A boundary buffer that goes in comes out: a pass reads it before it writes it.
+  int issue_pass(int phase, int i, int n, int j) {
+    const int C = job->n_chunks;
+    const bool fwd = phase == GPT_DPP_FWD, first = j == (fwd ? 0 : C - 1), last = j == (fwd ? C - 1 : 0);
+    std::vector<int>& buf = fwd ? fwd_buf : bwd_buf;
+    const void* in[gpts::kMaxWindow];
+    void* out[gpts::kMaxWindow];
+    for (int m = 0; m < n; ++m) {
+      in[m] = first ? (fwd ? job->x : job->dy)[i + m] : act.at(buf[i + m]);
+      if (first && !last) {
+        if (act.free_ids.empty()) return set_error(GPTS_ENOMEM, "dpp: boundary-activation pool exhausted");
+        buf[i + m] = act.take();
+      }
+      out[m] = last ? (fwd ? job->y : job->dx)[i + m] : act.at(buf[i + m]);
+    }
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    int rc;
+    if (fwd) {
+      live_fixed += n;
+      if (live_fixed > peak_fixed) peak_fixed = live_fixed;
+      rc = gpts::stage_fwd_window(&job->chunks[j], n, in, stash_at(i, j), stash_slot_bytes, out, grad_at(i), grad_slot_bytes, st);
+    } else {
+      rc = gpts::stage_bwd_window(&job->chunks[j], n, stash_at(i, j), stash_slot_bytes, in, out, job->dparams[j], grad_at(i),
+                                  grad_slot_bytes, st);
+    }
+    if (rc != GPTS_OK) return rc;
+    if (last && !first)
+      for (int m = n - 1; m >= 0; --m) {   // (the next to be taken lie in order again)
+        act.give(buf[i + m]);
+        buf[i + m] = -1;
+      }
+    return fwd ? GPTS_OK : after_bwd(i + n - 1, j, n);
+  }
+  // How many micro-batches from i on a pass over chunk j takes, at most n: 1 where the callers' buffers it writes
+  // overlap each other or what another micro-batch of it reads (one by one they would see each other's results), or
+  // where a call on them would be refused.
+  int pass_size(int phase, int i, int n, int j) const {
+    const int C = job->n_chunks;
+    const bool fwd = phase == GPT_DPP_FWD, first = j == (fwd ? 0 : C - 1), last = j == (fwd ? C - 1 : 0);
+    const size_t bytes = gpt_dpp_act_slot_bytes(&job->chunks[j].cfg);
+    auto at = [](const void* q) { return reinterpret_cast<uintptr_t>(q); };
+    auto apart = [&](const void* p, const void* q) { return at(p) + bytes <= at(q) || at(q) + bytes <= at(p); };
+    for (int m = 0; m < n; ++m) {
+      if (at(job->x[i + m]) % 16 || at(job->y[i + m]) % 16 || at(job->dy[i + m]) % 16 || at(job->dx[i + m]) % 16) return 1;
+      for (int k = 0; k < n && last; ++k) {
+        const void* out = (fwd ? job->y : job->dx)[i + m];
+        if (k != m && !apart(out, (fwd ? job->y : job->dx)[i + k])) return 1;
+        if (first && (k != m || fwd) && !apart(out, (fwd ? job->x : job->dy)[i + k])) return 1;
+      }
+    }
+    return at(job->dparams[j]) % 16 || at(job->stash_pool) % 16 || at(job->grad_pool) % 16 || at(job->act_pool) % 16 ? 1 : n;
+  }
+  // n micro-batches up to i have been through chunk j's backward data phase (weight phase per window)
+  int after_bwd(int i, int j, int n) {
+    const int M = job->n_microbatches;
+    if (i % W == W - 1 || i == M - 1) {
+      // the chunk has seen every micro-batch of the window: one weight phase over them
+      const int w0 = i / W * W, nw = i - w0 + 1;
+      std::vector<const void*> as(nw), gs(nw);
+      for (int m = 0; m < nw; ++m) {
+        as[m] = stash_at(w0 + m, j);
+        gs[m] = grad_at(w0 + m);
+      }
+      const int rc = gpt_stage_wgrad_flush(&job->chunks[j], nw, as.data(), gs.data(), job->dparams[j], stream);
+      if (rc != GPTS_OK) return rc;
+      live_fixed -= nw;
+    }
+    return count_bwd(j, n);
+  }
+  int count_bwd(int j, int n) {
+    if ((left[j] -= n) == 0 && job->grad_ready && job->grad_ready[j]) {
+      const hipError_t e = hipEventRecord(static_cast<hipEvent_t>(job->grad_ready[j]), static_cast<hipStream_t>(stream));
+      if (e != hipSuccess) return set_error(GPTS_EHIP, "dpp: recording a grad_ready event failed");
+    }
+    return GPTS_OK;
+  }
   int issue(const gpt_dpp_task& k) {
     const int C = job->n_chunks, i = k.microbatch, j = k.chunk;
     if (k.phase == GPT_DPP_FWD) {
@@ -176,21 +253,8 @@ struct TaskIssuer {
         dout = act.at(out_id);
       }
       if (W > 0) {
-        int rc = gpt_stage_bwd_data_only(&job->chunks[j], stash_at(i, j), din, dout, job->dparams[j], grad_at(i), stream, nullptr);
+        const int rc = gpt_stage_bwd_data_only(&job->chunks[j], stash_at(i, j), din, dout, job->dparams[j], grad_at(i), stream, nullptr);
         if (rc != GPTS_OK) return rc;
-        const int M = job->n_microbatches;
-        if (i % W == W - 1 || i == M - 1) {
-          // the chunk has seen every micro-batch of the window: one weight phase over them
-          const int w0 = i / W * W, n = i - w0 + 1;
-          std::vector<const void*> as(n), gs(n);
-          for (int m = 0; m < n; ++m) {
-            as[m] = stash_at(w0 + m, j);
-            gs[m] = grad_at(w0 + m);
-          }
-          rc = gpt_stage_wgrad_flush(&job->chunks[j], n, as.data(), gs.data(), job->dparams[j], stream);
-          if (rc != GPTS_OK) return rc;
-          live_fixed -= n;
-        }
       } else {
         const int s = slot_of[(size_t)i * C + j];
         const int rc = gpt_stage_bwd_only(&job->chunks[j], stash.at(s), din, dout, job->dparams[j], stream, nullptr);
@@ -199,10 +263,7 @@ struct TaskIssuer {
       }
       if (j != C - 1) act.give(bwd_buf[i]);
       bwd_buf[i] = out_id;
-      if (--left[j] == 0 && job->grad_ready && job->grad_ready[j]) {
-        const hipError_t e = hipEventRecord(static_cast<hipEvent_t>(job->grad_ready[j]), static_cast<hipStream_t>(stream));
-        if (e != hipSuccess) return set_error(GPTS_EHIP, "dpp: recording a grad_ready event failed");
-      }
+      return W > 0 ? after_bwd(i, j, 1) : count_bwd(j, 1);
     }
     return GPTS_OK;
   }
@@ -392,8 +453,9 @@ int gpt_dpp_run(const gpt_dpp_job* job, void* stream, gpt_dpp_report* report) {
   }
 
   // dry run of the pool usage, so that nothing is enqueued when a pool is too small
+  int peak_act = 0;
   {
-    int live_act = 0, peak_act = 0;
+    int live_act = 0;
     for (int t = 0; t < n; ++t) {
       const gpt_dpp_task& k = plan[t];
       const bool edge = (k.phase == GPT_DPP_FWD) ? (k.chunk == C - 1) : (k.chunk == 0);   // writes y / dx
@@ -404,14 +466,25 @@ int gpt_dpp_run(const gpt_dpp_job* job, void* stream, gpt_dpp_report* report) {
     if (!issuer.W && (size_t)peak_stash > issuer.stash.free_ids.size()) return set_error(GPTS_ENOMEM, "dpp_run: stash pool too small for this policy");
     if ((size_t)peak_act > issuer.act.free_ids.size()) return set_error(GPTS_ENOMEM, "dpp_run: boundary-activation pool too small for this policy");
   }
-  for (int t = 0; t < n; ++t) {
-    rc = issuer.issue(plan[t]);
+  // a chunk's micro-batches of a window follow each other in the plan: as passes where there is a weight phase per
+  // window (the stash slots are equally spaced then)
+  std::vector<int> most(C, 1);
+  for (int j = 0; j < C && issuer.W > 1; ++j) most[j] = gpts::stage_window(&job->chunks[j], issuer.W);
+  for (int t = 0; t < n;) {
+    const gpt_dpp_task& k = plan[t];
+    int run = 1;
+    while (run < most[k.chunk] && t + run < n && plan[t + run].phase == k.phase && plan[t + run].chunk == k.chunk &&
+           plan[t + run].microbatch == k.microbatch + run && (k.microbatch + run) % issuer.W != 0)
+      ++run;
+    if (run > 1) run = issuer.pass_size(k.phase, k.microbatch, run, k.chunk);
+    rc = run > 1 ? issuer.issue_pass(k.phase, k.microbatch, run, k.chunk) : issuer.issue(k);
     if (rc != GPTS_OK) return rc;
+    t += run;
   }
   if (report) {
     report->n_tasks = n;
     report->peak_live_stash = issuer.W ? issuer.peak_fixed : issuer.stash.peak;
-    report->peak_live_act = issuer.act.peak;
+    report->peak_live_act = peak_act;
     report->stash_slot_bytes = stash_slot;
     report->act_slot_bytes = act_slot;
   }

@@ -83,10 +83,20 @@ template <> struct Raw8<float> {
 // Bound by HBM from some thousand rows on, by launch and latency below.  With a wave per row instead of a
 // workgroup, whose threads were half idle: 8192 rows of 512 9.7 -> 7.4 us, of 768 10.9 -> 7.7 us,
 // 3968 of 2048 9.7 -> 8.7 us.
+// blockIdx.y: the micro-batch; strides between them in units of 16 bytes
+template <typename P> __device__ __forceinline__ P* at_mb(P* p, uint32_t stride16, uint32_t mb) {
+  return (P*)((const char*)p + (size_t)stride16 * 16 * mb);   // (by way of an integer it would no longer count as global memory)
+}
 template <typename TX, typename T, typename TO, int NCH, int RW>
 __global__ __launch_bounds__(kLnThreads) void ln_fwd_kernel(
-    const TX* __restrict__ x, const T* __restrict__ gamma, const T* __restrict__ beta, TO* __restrict__ out,
-    float* __restrict__ mean, float* __restrict__ rstd, float* __restrict__ xcopy, int T_rows, int H, float eps) {
+    const TX* __restrict__ x0, const T* __restrict__ gamma, const T* __restrict__ beta, TO* __restrict__ out0,
+    float* __restrict__ mean0, float* __restrict__ rstd0, float* __restrict__ xcopy0, int T_rows, int H, float eps,
+    uint32_t stride16, uint32_t x_stride16) {
+  const TX* __restrict__ x = at_mb(x0, x_stride16, blockIdx.y);
+  TO* __restrict__ out = at_mb(out0, stride16, blockIdx.y);
+  float* __restrict__ mean = at_mb(mean0, stride16, blockIdx.y);
+  float* __restrict__ rstd = at_mb(rstd0, stride16, blockIdx.y);
+  float* __restrict__ xcopy = xcopy0 ? at_mb(xcopy0, stride16, blockIdx.y) : nullptr;
   constexpr int NWV = kLnThreads / kWave, NT = RW * kWave;   // NT: threads of a row
   static_assert(RW == 1 || RW == NWV, "a wave or the workgroup per row");
   __shared__ float red[2][NWV];
@@ -172,9 +182,16 @@ int ln_bwd_blocks(int T_rows, int H) {
 
 template <typename TX, typename T, int NCH, int RW, bool DXSUM>
 __global__ __launch_bounds__(kLnBwdThreads) void ln_bwd_kernel(
-    const T* __restrict__ dout, const TX* __restrict__ x, const float* __restrict__ mean,
-    const float* __restrict__ rstd, const T* __restrict__ gamma, const T* __restrict__ dres,
-    T* __restrict__ dx, float* __restrict__ partial, int T_rows, int H) {
+    const T* __restrict__ dout0, const TX* __restrict__ x0, const float* __restrict__ mean0,
+    const float* __restrict__ rstd0, const T* __restrict__ gamma, const T* __restrict__ dres0,
+    T* __restrict__ dx0, float* __restrict__ partial0, int T_rows, int H, uint32_t act16, uint32_t dres16, uint32_t dx16) {
+  const T* __restrict__ dout = at_mb(dout0, act16, blockIdx.y);
+  const TX* __restrict__ x = at_mb(x0, act16, blockIdx.y);
+  const float* __restrict__ mean = at_mb(mean0, act16, blockIdx.y);
+  const float* __restrict__ rstd = at_mb(rstd0, act16, blockIdx.y);
+  const T* __restrict__ dres = dres0 ? at_mb(dres0, dres16, blockIdx.y) : nullptr;
+  T* __restrict__ dx = at_mb(dx0, dx16, blockIdx.y);
+  float* __restrict__ partial = partial0 + (size_t)blockIdx.y * gridDim.x * (DXSUM ? 3 : 2) * H;
   // At most one barrier per row: the two row sums are reduced together and the LDS slots alternate
   // between rows, so a row's writes cannot overtake the previous row's reads.  The loads of
   // the next row (when the row fits few registers) and of the residual gradient are issued
@@ -349,23 +366,29 @@ template <int NS> __global__ __launch_bounds__(256) void reduce_partials_kernel(
   const ReduceSeg& sg = args.seg[k];
   const int col0 = (blockIdx.x - args.first[k]) * 32;
   const int cq = threadIdx.x & 7, ry = threadIdx.x >> 3, c4 = col0 + cq * 4;
-  f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  if (c4 < sg.N) {
-#pragma unroll 4
-    for (int g = ry; g < sg.G; g += 32) s += *reinterpret_cast<const f32x4*>(sg.partial + (size_t)g * sg.stride + c4);
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) sm[ry][cq * 4 + e] = s[e];
-  __syncthreads();
   const int c = col0 + threadIdx.x;
-  if (threadIdx.x < 32 && c < sg.N) {
-    float t = 0.f;
+  const bool sums = threadIdx.x < 32 && c < sg.N;
+  float* const out = c < sg.n0 ? sg.out0 + c : (c < sg.n1 ? sg.out1 + (c - sg.n0) : sg.out2 + (c - sg.n1));
+  float total = sums ? *out : 0.f;
+  for (int b = 0; b < sg.batch; ++b) {
+    const float* const p = sg.partial + (size_t)b * sg.G * sg.stride + c4;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    if (c4 < sg.N) {
+#pragma unroll 4
+      for (int g = ry; g < sg.G; g += 32) s += *reinterpret_cast<const f32x4*>(p + (size_t)g * sg.stride);
+    }
+    if (b > 0) __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 32; ++i) t += sm[i][threadIdx.x];
-    if (c < sg.n0) sg.out0[c] += t;
-    else if (c < sg.n1) sg.out1[c - sg.n0] += t;
-    else sg.out2[c - sg.n1] += t;
+    for (int e = 0; e < 4; ++e) sm[ry][cq * 4 + e] = s[e];
+    __syncthreads();
+    if (sums) {
+      float t = 0.f;
+#pragma unroll
+      for (int i = 0; i < 32; ++i) t += sm[i][threadIdx.x];
+      total += t;
+    }
   }
+  if (sums) *out = total;
 }
 
 template <int NS> static hipError_t launch_reduce(const ReduceSeg* segs, int n, hipStream_t st) {
@@ -392,9 +415,11 @@ hipError_t reduce_partials(const ReduceSeg* segs, int n, hipStream_t st) {
 // rows): below some MB each is a few microseconds of launch and latency whatever its size.  Three matrices
 // of 128 rows, 128 to 512 columns, in one launch instead of three: 3.7 us of a 74 us step.
 // NM: matrices there is room for; one alone has a form of its own, as above.
+// blockIdx.z: the micro-batch.
 template <int NM> struct ColsumArgs {
   ColsumMat mat[NM];
   int first[NM];   // first blockIdx.x of a matrix
+  uint32_t stride16;
 };
 template <typename T, int NM>
 __global__ __launch_bounds__(256) void colsum_partial_kernel(const ColsumArgs<NM> args, int M) {
@@ -405,8 +430,8 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const ColsumArgs<NM
   for (int i = 1; i < NM; ++i)
     if ((int)blockIdx.x >= args.first[i]) k = i;
   const int N = args.mat[k].N;
-  const T* __restrict__ A = static_cast<const T*>(args.mat[k].A);
-  float* __restrict__ partial = args.mat[k].partial;
+  const T* __restrict__ A = at_mb(static_cast<const T*>(args.mat[k].A), args.stride16, blockIdx.z);
+  float* __restrict__ partial = args.mat[k].partial + (size_t)blockIdx.z * gridDim.y * N;
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
   const int col = (((int)blockIdx.x - args.first[k]) * kWave + lane) * V;
   float acc[V];
@@ -434,10 +459,13 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const ColsumArgs<NM
 // --------------------------------------------------------------- launchers ----
 template <typename TX, typename T, typename TO>
 static hipError_t ln_fwd_t(int T_rows, int H, float eps, const void* x, const void* gamma, const void* beta,
-                           void* out, float* mean, float* rstd, float* xcopy, hipStream_t st) {
+                           void* out, float* mean, float* rstd, float* xcopy, hipStream_t st, int n, size_t stride,
+                           size_t x_stride) {
+  if (n < 1 || n > kMaxWindow) return hipErrorInvalidValue;
 #define GPTS_LN_FWD(N, RW)                                                                                        \
-  hipLaunchKernelGGL((ln_fwd_kernel<TX, T, TO, N, RW>), dim3(RW == 1 ? (T_rows + 3) / 4 : T_rows), dim3(kLnThreads), 0, st, \
-                     (const TX*)x, (const T*)gamma, (const T*)beta, (TO*)out, mean, rstd, xcopy, T_rows, H, eps)
+  hipLaunchKernelGGL((ln_fwd_kernel<TX, T, TO, N, RW>), dim3(RW == 1 ? (T_rows + 3) / 4 : T_rows, n), dim3(kLnThreads), 0, st, \
+                     (const TX*)x, (const T*)gamma, (const T*)beta, (TO*)out, mean, rstd, xcopy, T_rows, H, eps,    \
+                     (uint32_t)(stride / 16), (uint32_t)(x_stride / 16))
   // A wave per row up to 2048 columns (32 registers a lane), a workgroup beyond -- and for many long rows
   // too, where a wave's four chunks each wait for memory longer than the barrier costs.  Workgroup | wave,
   // us: fp32 4096x2048 15.1 | 13.8, 8192x1536 17.4 | 19.1, 16384x2048 42.9 | 46.0, 32768x2048 100 | 113,
@@ -458,26 +486,23 @@ static hipError_t ln_fwd_t(int T_rows, int H, float eps, const void* x, const vo
 
 hipError_t ln_fwd(int dtype, bool x_f32, int T_rows, int H, float eps, const void* x,
                   const void* gamma, const void* beta, void* out, float* mean, float* rstd,
-                  hipStream_t st, bool out_f16, float* xcopy) {
-  if (dtype == 0) {
-    if (out_f16) return hipErrorInvalidValue;
-    return ln_fwd_t<float, float, float>(T_rows, H, eps, x, gamma, beta, out, mean, rstd, xcopy, st);
-  }
-  if (x_f32)
-    return out_f16 ? ln_fwd_t<float, bf16, f16>(T_rows, H, eps, x, gamma, beta, out, mean, rstd, xcopy, st)
-                   : ln_fwd_t<float, bf16, bf16>(T_rows, H, eps, x, gamma, beta, out, mean, rstd, xcopy, st);
-  return out_f16 ? ln_fwd_t<bf16, bf16, f16>(T_rows, H, eps, x, gamma, beta, out, mean, rstd, xcopy, st)
-                 : ln_fwd_t<bf16, bf16, bf16>(T_rows, H, eps, x, gamma, beta, out, mean, rstd, xcopy, st);
+                  hipStream_t st, bool out_f16, float* xcopy, int n, size_t stride, size_t x_stride) {
+#define GPTS_LN(TX, T, TO) ln_fwd_t<TX, T, TO>(T_rows, H, eps, x, gamma, beta, out, mean, rstd, xcopy, st, n, stride, x_stride)
+  if (dtype == 0) return out_f16 ? hipErrorInvalidValue : GPTS_LN(float, float, float);
+  if (x_f32) return out_f16 ? GPTS_LN(float, bf16, f16) : GPTS_LN(float, bf16, bf16);
+  return out_f16 ? GPTS_LN(bf16, bf16, f16) : GPTS_LN(bf16, bf16, bf16);
+#undef GPTS_LN
 }
 
 template <typename TX, typename T>
 static hipError_t ln_bwd_t(int T_rows, int H, const void* dout, const void* x, const float* mean,
                            const float* rstd, const void* gamma, const void* dres, void* dx, bool dxsum,
-                           float* partial, hipStream_t st) {
-  const dim3 g(ln_bwd_blocks(T_rows, H)), b(kLnBwdThreads);
+                           float* partial, const LnBwdWindow& win, hipStream_t st) {
+  const dim3 g(ln_bwd_blocks(T_rows, H), win.n), b(kLnBwdThreads);
 #define GPTS_LN_BWD_(N, RW, SUM)                                                                                  \
   hipLaunchKernelGGL((ln_bwd_kernel<TX, T, N, RW, SUM>), g, b, 0, st, (const T*)dout, (const TX*)x, mean, rstd,   \
-                     (const T*)gamma, (const T*)dres, (T*)dx, partial, T_rows, H)
+                     (const T*)gamma, (const T*)dres, (T*)dx, partial, T_rows, H, (uint32_t)(win.act / 16),         \
+                     (uint32_t)(win.dres / 16), (uint32_t)(win.dx / 16))
 #define GPTS_LN_BWD(N, RW)                  \
   do {                                      \
     if (dxsum) GPTS_LN_BWD_(N, RW, true);   \
@@ -497,13 +522,15 @@ static hipError_t ln_bwd_t(int T_rows, int H, const void* dout, const void* x, c
 
 hipError_t ln_bwd_partials(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
                            const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
-                           float* dgamma, float* dbeta, float* dxsum, float* partial, ReduceSeg* seg, hipStream_t st) {
-  if (H > 4 * 8 * kLnBwdThreads) return hipErrorInvalidValue;
+                           float* dgamma, float* dbeta, float* dxsum, float* partial, ReduceSeg* seg, hipStream_t st,
+                           const LnBwdWindow* win) {
+  if (H > 4 * 8 * kLnBwdThreads || (win && (win->n < 1 || win->n > kMaxWindow))) return hipErrorInvalidValue;
   const int np = dxsum ? 3 : 2;
-  *seg = ReduceSeg{partial, (size_t)np * H, ln_bwd_blocks(T_rows, H), np * H, H, 2 * H, dgamma, dbeta, dxsum};
-  if (dtype == 0) return ln_bwd_t<float, float>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, st);
-  if (x_f32) return ln_bwd_t<float, bf16>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, st);
-  return ln_bwd_t<bf16, bf16>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, st);
+  const LnBwdWindow w = win ? *win : LnBwdWindow();
+  *seg = ReduceSeg{partial, (size_t)np * H, ln_bwd_blocks(T_rows, H), np * H, H, 2 * H, dgamma, dbeta, dxsum, w.n};
+  if (dtype == 0) return ln_bwd_t<float, float>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, w, st);
+  if (x_f32) return ln_bwd_t<float, bf16>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, w, st);
+  return ln_bwd_t<bf16, bf16>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, w, st);
 }
 hipError_t ln_bwd(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
                   const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
@@ -568,10 +595,11 @@ static int colsum_splits(int M) { return M < 4 * 64 ? (M + 3) / 4 : 64; }
 size_t colsum_scratch_bytes(int M, int N) { return (size_t)colsum_splits(M) * N * sizeof(float); }
 
 ReduceSeg colsum_segment(const float* partial, int G, int N, float* out) {
-  return ReduceSeg{partial, (size_t)N, G, N, N, N, out, nullptr, nullptr};
+  return ReduceSeg{partial, (size_t)N, G, N, N, N, out, nullptr, nullptr, 1};
 }
 template <int NM>
-static hipError_t launch_colsum(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, hipStream_t st) {
+static hipError_t launch_colsum(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, hipStream_t st, int batch,
+                                size_t stride) {
   const int G = colsum_splits(M);
   const int V = dtype == 0 ? 4 : 8;
   ColsumArgs<NM> a{};
@@ -582,16 +610,40 @@ static hipError_t launch_colsum(int dtype, int M, const ColsumMat* mats, int n, 
     a.mat[i] = mats[i];
     blocks += (mats[i].N / V + kWave - 1) / kWave;
     segs[i] = colsum_segment(mats[i].partial, G, mats[i].N, mats[i].out);
+    segs[i].batch = batch;
   }
-  if (dtype == 0)
-    hipLaunchKernelGGL((colsum_partial_kernel<float, NM>), dim3(blocks, G), dim3(256), 0, st, a, M);
-  else
-    hipLaunchKernelGGL((colsum_partial_kernel<bf16, NM>), dim3(blocks, G), dim3(256), 0, st, a, M);
+  a.stride16 = (uint32_t)(stride / 16);
+  const dim3 g(blocks, G, batch);
+  if (dtype == 0) hipLaunchKernelGGL((colsum_partial_kernel<float, NM>), g, dim3(256), 0, st, a, M);
+  else hipLaunchKernelGGL((colsum_partial_kernel<bf16, NM>), g, dim3(256), 0, st, a, M);
   return hipGetLastError();
 }
-hipError_t colsum_partials(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, hipStream_t st) {
-  if (n < 1 || n > kMaxColsums) return hipErrorInvalidValue;
-  return n == 1 ? launch_colsum<1>(dtype, M, mats, n, segs, st) : launch_colsum<kMaxColsums>(dtype, M, mats, n, segs, st);
+hipError_t colsum_partials(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, hipStream_t st, int batch,
+                           size_t stride) {
+  if (n < 1 || n > kMaxColsums || batch < 1) return hipErrorInvalidValue;
+  return n == 1 ? launch_colsum<1>(dtype, M, mats, n, segs, st, batch, stride)
+                : launch_colsum<kMaxColsums>(dtype, M, mats, n, segs, st, batch, stride);
+}
+
+struct CopyTable {
+  const void* src[kMaxWindow];
+  void* dst[kMaxWindow];
+};
+__global__ __launch_bounds__(256) void window_copy_kernel(const CopyTable t, size_t n16) {
+  const f32x4* const s = static_cast<const f32x4*>(t.src[blockIdx.y]);
+  f32x4* const d = static_cast<f32x4*>(t.dst[blockIdx.y]);
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (size_t)gridDim.x * 256) d[i] = s[i];
+}
+hipError_t window_copy(int n, const void* const* src, void* const* dst, size_t bytes, hipStream_t st) {
+  if (n < 1 || n > kMaxWindow || bytes % 16) return hipErrorInvalidValue;
+  CopyTable t;
+  for (int m = 0; m < kMaxWindow; ++m) {
+    t.src[m] = src[m < n ? m : 0];
+    t.dst[m] = dst[m < n ? m : 0];
+  }
+  const size_t n16 = bytes / 16, blocks = (n16 + 1023) / 1024;   // up to four vectors a thread, then more
+  hipLaunchKernelGGL(window_copy_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048), n), dim3(256), 0, st, t, n16);
+  return hipGetLastError();
 }
 hipError_t colsum(int dtype, int M, int N, const void* A, float* out, float* partial, hipStream_t st) {
   const ColsumMat mat{A, N, out, partial};

@@ -96,14 +96,15 @@ float short_us(Tile t, long tiles, long slices, Cost cost) {
 }
 
 struct Product { int M, N; };
-Tile choose_tile(int form, const Product* p, int n, long K, Cost cost) {
+// batch: products in one launch whose tile rows follow on
+Tile choose_tile(int form, const Product* p, int n, long K, Cost cost, int batch = 1) {
   Tile best = TILE_256x256;
   float best_us = 0.f, operand_bytes = 0.f;
   for (int q = 0; q < n; ++q) operand_bytes += 2.f * (float)K * ((float)p[q].M + (float)p[q].N);
   for (int t = 0; t < N_TILES; ++t) {
     const TileInfo& i = kTiles[t];
     long tiles = 0;
-    for (int q = 0; q < n; ++q) tiles += (long)((p[q].M + i.bm - 1) / i.bm) * ((p[q].N + i.bn - 1) / i.bn);
+    for (int q = 0; q < n; ++q) tiles += (long)batch * ((p[q].M + i.bm - 1) / i.bm) * ((p[q].N + i.bn - 1) / i.bn);
     const long rounds = (tiles + 255) / 256, slices = (K + 63) / 64;
     float slice = form == 2 ? i.slice_tn : i.slice, fixed = form == 2 ? i.fixed_tn : i.fixed;
     if (form == 2 && operand_bytes > 200e6f) slice = fmaxf(slice, (float)(4 * i.bm + 8 * i.bn) * (64 * 2 * 8 / 2.65e6f));
@@ -116,9 +117,9 @@ Tile choose_tile(int form, const Product* p, int n, long K, Cost cost) {
   }
   return best;
 }
-Tile choose_tile(int form, int M, int N, long K, Cost cost) {
+Tile choose_tile(int form, int M, int N, long K, Cost cost, int batch = 1) {
   const Product p{M, N};
-  return choose_tile(form, &p, 1, K, cost);
+  return choose_tile(form, &p, 1, K, cost, batch);
 }
 
 // Whether weight gradients in one launch gain on a launch each.  What they gain is the rounds that their
@@ -224,7 +225,13 @@ hipError_t gemm_mfma(int form, int M, int N, int K, const void* A, const void* B
     return gemm_wgrad_group(&w, 1, K, ep.k_segments, ep.seg_stride_a, ep.seg_stride_b, st);
   }
   MfmaArgs a = make_args(M, N, K, A, B, C, ep);
-  const Tile t = choose_tile(form, M, N, K, cost_of(ep));
+  if (ep.batch < 1 || ep.batch > kMaxWindow) return hipErrorInvalidValue;
+  a.batch = ep.batch;
+  a.stride_a = ep.stride_a;
+  a.stride_b = ep.stride_c;
+  a.stride_r = (uint32_t)(ep.stride_r / 16);
+  // (the order in which the rows of a column are summed is the tile's: a product that leaves column sums keeps it)
+  const Tile t = choose_tile(form, M, N, K, cost_of(ep), a.colsum ? 1 : ep.batch);
   if (form == 1)
     return launch_gemm_dgrad(t, !ep.dgelu_u ? EPI_PLAIN : (ep.gelu_kind == 0 ? EPI_DGELU_TANH : EPI_DGELU_ERF), a, st);
   if (ep.b_image) {
@@ -244,9 +251,9 @@ hipError_t gemm_wgrad_group(const WgradItem* items, int n, int K, int segments, 
     if (segments > 1 ? !gemm_wgrad_segments_supported(w.M, w.N, K, segments) : !gemm_mfma_supported(2, w.M, w.N, K))
       return hipErrorInvalidValue;
     a[i] = make_args(w.M, w.N, K, w.dout, w.in, w.dw, GemmEpilogue());
-    a[i].k_segments = segments;
-    a[i].seg_stride_a = seg_stride_dout;
-    a[i].seg_stride_b = seg_stride_in;
+    a[i].batch = segments;
+    a[i].stride_a = seg_stride_dout;
+    a[i].stride_b = seg_stride_in;
     p[i] = Product{w.M, w.N};
   }
   const long k_all = (long)K * segments;

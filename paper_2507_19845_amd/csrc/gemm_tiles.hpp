@@ -63,11 +63,15 @@ struct MfmaArgs {
   const bf16* dgelu_u;
   float* colsum;   // GeLU' epilogue only, may be null: column sums of C per group of tile rows
   int b_img = 0;   // B is the weight's tiled image (tiles of 256 rows, slices of kImageK): kernels with BK = kImageK only
-  // K-major products only (weight gradients): the contraction runs over `k_segments` pieces of
-  // K rows each (K is then the length of ONE piece), piece s of A starting seg_stride_a elements
-  // after piece s-1, likewise B: the tokens of several micro-batches, each in its own buffer.
-  int k_segments = 1;
-  size_t seg_stride_a = 0, seg_stride_b = 0;
+  // The tokens of several micro-batches, each in its own buffer.
+  // K-major products (weight gradients): the contraction runs over `batch` pieces of
+  // K rows each (K is then the length of ONE piece), piece s of A starting stride_a elements
+  // after piece s-1, likewise B and stride_b.
+  // The others: `batch` products with the same B, whose tile rows follow on, the next A, C, residual or dgelu_u
+  // stride_a, stride_b, 16 stride_r bytes on (see GemmEpilogue).
+  int batch = 1;
+  uint32_t stride_r = 0;
+  size_t stride_a = 0, stride_b = 0;
 };
 
 constexpr int kImageK = 64;   // slice depth of the weight images
@@ -380,8 +384,11 @@ enum GemmForm { FORM_NT = 0, FORM_NN = 1, FORM_TN = 2 };
 // weight); the f16 form of the matrix instruction is used and the 16-bit outputs are fp16.
 // id: the workgroup's place among the product's tiles; lds: kernel's pipeline memory (gemm_lds_bytes()).
 template <int MB, int NB, int BK, int NS> constexpr int gemm_lds_bytes() { return NS * 32 * (MB + NB) * BK * 2; }
+template <typename P> __device__ __forceinline__ P* after(P* p, size_t bytes) {
+  return (P*)((const char*)p + bytes);   // (by way of an integer it would no longer count as global memory)
+}
 template <int EPI, int FORM, bool F16, int MB, int NB, int BK, int NS>
-__device__ __forceinline__ void gemm_tile(const MfmaArgs& a, int id, char* const lds) {
+__device__ __forceinline__ void gemm_tile(MfmaArgs a, int id, char* const lds) {
   constexpr bool A_KM = FORM == FORM_TN, B_KM = FORM != FORM_NT;
   constexpr int NW = 4, WM = 16 * MB, WN = 16 * NB, BM = 2 * WM, BN = 2 * WN, KS = BK / 32;
   using OpA = Operand<BM, BK, A_KM>;
@@ -396,7 +403,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, int id, char* const
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / 2, wn = wave % 2;
 
-  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
+  const int tiles_m1 = (a.M + BM - 1) / BM, tiles_m = tiles_m1 * (FORM == FORM_TN ? 1 : a.batch), tiles_n = (a.N + BN - 1) / BN;
   const int nb = tiles_m * tiles_n;
   {   // contiguous range of tiles per XCD (the first nb % 8 of them hold one more)
     const int x = id & 7, q = nb >> 3, r = nb & 7;
@@ -407,8 +414,20 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, int id, char* const
   const int grp = id / per_group, first_m = grp * GROUP;
   const int gsz = min(tiles_m - first_m, GROUP);
   const int tm_i = first_m + (id % per_group) % gsz, tn_i = (id % per_group) / gsz;
-  const int m0 = tm_i * BM, n0 = tn_i * BN;
-  const int sps = a.K / BK, nk = sps * a.k_segments;     // slices per K segment, in all
+  int tm = tm_i;   // tile row in its product
+  if constexpr (FORM != FORM_TN) {
+    if (a.batch > 1) {
+      const int mb = __builtin_amdgcn_readfirstlane(tm_i / tiles_m1);
+      tm = tm_i - mb * tiles_m1;
+      a.A = after(a.A, mb * a.stride_a);
+      a.C = after(static_cast<char*>(a.C), mb * a.stride_b);
+      a.gelu_out = after(a.gelu_out, mb * a.stride_b);
+      a.residual = after(static_cast<const char*>(a.residual), mb * (size_t)a.stride_r * 16);
+      a.dgelu_u = after(a.dgelu_u, mb * (size_t)a.stride_r * 16);
+    }
+  }
+  const int m0 = tm * BM, n0 = tn_i * BN;
+  const int sps = a.K / BK, nk = sps * (FORM == FORM_TN ? a.batch : 1);     // slices per K segment, in all
 
   const size_t lda = A_KM ? (size_t)a.M : (size_t)a.K, ldb = B_KM ? (size_t)a.N : (size_t)a.K;
   OpA opA;
@@ -473,8 +492,8 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, int id, char* const
       if constexpr (A_KM) {
         if (++fill_in_seg == sps) {
           fill_in_seg = 0;
-          fill_a += a.seg_stride_a - sps * step_a;
-          fill_b += a.seg_stride_b - sps * step_b;
+          fill_a += a.stride_a - sps * step_a;
+          fill_b += a.stride_b - sps * step_b;
         }
       }
     }
@@ -609,7 +628,7 @@ __global__ __launch_bounds__(256) void gemm_mi16_group_kernel(const WgradGroup g
 template <int EPI, int FORM, bool F16, int MB, int NB, int BK, int NS>
 hipError_t launch_mi16(const MfmaArgs& a, hipStream_t st) {
   if (a.b_img && BK != kImageK) return hipErrorInvalidValue;
-  const int tiles = ((a.M + 32 * MB - 1) / (32 * MB)) * ((a.N + 32 * NB - 1) / (32 * NB));
+  const int tiles = (FORM == FORM_TN ? 1 : a.batch) * ((a.M + 32 * MB - 1) / (32 * MB)) * ((a.N + 32 * NB - 1) / (32 * NB));
   hipLaunchKernelGGL((gemm_mi16_kernel<EPI, FORM, F16, MB, NB, BK, NS>), dim3(tiles), dim3(256), 0, st, a);
   return hipGetLastError();
 }
@@ -629,7 +648,7 @@ template <int MB, int NB, int BK, int NS> hipError_t launch_group(const MfmaArgs
 }
 
 template <int EPI, int FORM, bool F16, int MB, int NB> hipError_t launch_ring(const MfmaArgs& a, hipStream_t st) {
-  const long tiles = (long)((a.M + 32 * MB - 1) / (32 * MB)) * ((a.N + 32 * NB - 1) / (32 * NB));
+  const long tiles = (long)a.batch * ((a.M + 32 * MB - 1) / (32 * MB)) * ((a.N + 32 * NB - 1) / (32 * NB));
   return two_stages(tiles, a.K) ? launch_mi16<EPI, FORM, F16, MB, NB, 64, 2>(a, st) : launch_mi16<EPI, FORM, F16, MB, NB, 64, 4>(a, st);
 }
 // Six stages instead of four gain nothing at 128x64 and 64x32 (two layers of 192 rows, 320 wide: 335

@@ -1,36 +1,51 @@
 // Internal launcher interface between the stage orchestrator and the kernels.
 // Every launcher only enqueues on `st` and returns hipGetLastError().
 #pragma once
+#include "../../include/gpt_stage.h"
 #include "common.hpp"
 
 namespace gpts {
 
 // dtype: 0 = fp32 storage, 1 = bf16 storage (fp32 arithmetic in both).
 
+// Several micro-batches in one launch (a window of them): the operators below take the tensors of the first
+// one and how far those of the next one lie, in bytes (a multiple of 16, below 64 GB).  A micro-batch's share is computed
+// as by a launch of its own, bit for bit.
+constexpr int kMaxWindow = 8;
+
 // x_f32: the normalised tensor x (the residual stream) is fp32 even when dtype is bf16.
 // out_f16 (bf16 stages only): out is written as fp16 instead of bf16.
 // xcopy (may be null): receives x as fp32.
+// n micro-batches: out, mean, rstd, xcopy lie `stride` apart, x `x_stride`.
 hipError_t ln_fwd(int dtype, bool x_f32, int T_rows, int H, float eps, const void* x,
                   const void* gamma, const void* beta, void* out, float* mean, float* rstd,
-                  hipStream_t st, bool out_f16 = false, float* xcopy = nullptr);
+                  hipStream_t st, bool out_f16 = false, float* xcopy = nullptr, int n = 1, size_t stride = 0,
+                  size_t x_stride = 0);
 // Partial column sums waiting to be added up: out[c] += sum_{g<G} partial[g*stride + c], the columns
 // c < N being split at n0 and n1 over out0 (c < n0), out1 (n0 <= c < n1) and out2 (n1 <= c).
-// N, n0, n1 and stride are multiples of 4.
+// N, n0, n1 and stride are multiples of 4.  batch > 1: as many groups of G rows, one after the other in memory, each
+// added up as above and then to out, in order.
 struct ReduceSeg {
   const float* partial;
   size_t stride;
   int G, N, n0, n1;
   float *out0, *out1, *out2;
+  int batch = 1;
 };
 constexpr int kMaxReduceSegs = 5;
 // adds up n <= kMaxReduceSegs segments in one launch, each in fixed order
 hipError_t reduce_partials(const ReduceSeg* segs, int n, hipStream_t st);
 size_t ln_bwd_scratch_bytes(int T_rows, int H);
 // dxsum (may be null): += column sums of dx as stored.  ln_bwd_partials leaves the three sums in
-// `partial` (ln_bwd_scratch_bytes()) and describes them in *seg; ln_bwd adds them up as well.
+// `partial` (ln_bwd_scratch_bytes(), for each micro-batch) and describes them in *seg; ln_bwd adds them up as well.
+struct LnBwdWindow {
+  int n = 1;
+  size_t act = 0, dres = 0, dx = 0;   // strides of dout, x, mean and rstd; of dres; of dx
+};
 hipError_t ln_bwd_partials(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
                            const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
-                           float* dgamma, float* dbeta, float* dxsum, float* partial, ReduceSeg* seg, hipStream_t st);
+                           float* dgamma, float* dbeta, float* dxsum, float* partial, ReduceSeg* seg, hipStream_t st,
+                           const LnBwdWindow* win = nullptr);
 hipError_t ln_bwd(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
                   const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
                   float* dgamma, float* dbeta, float* dxsum, float* partial, hipStream_t st);
@@ -41,14 +56,18 @@ hipError_t gelu_fwd(int dtype, int kind, const void* u, void* g, size_t n, hipSt
 hipError_t f16_to_bf16(const void* in, void* out, size_t n, hipStream_t st);
 size_t colsum_scratch_bytes(int M, int N);
 // out += column sums of A [M,N].  colsum_partials takes n <= kMaxColsums matrices of M rows in one launch
-// and leaves their sums in each one's `partial` (colsum_scratch_bytes()) and segs[0 .. n-1], as above
+// and leaves their sums in each one's `partial` (colsum_scratch_bytes(), for each micro-batch) and segs[0 .. n-1],
+// as above.  A's of `batch` micro-batches lie `stride` bytes apart.
 struct ColsumMat {
   const void* A;
   int N;
   float *out, *partial;
 };
 constexpr int kMaxColsums = 3;
-hipError_t colsum_partials(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, hipStream_t st);
+hipError_t colsum_partials(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, hipStream_t st, int batch = 1,
+                           size_t stride = 0);
+// dst[m] = src[m] for n buffers of `bytes` (a multiple of 16) each
+hipError_t window_copy(int n, const void* const* src, void* const* dst, size_t bytes, hipStream_t st);
 hipError_t colsum(int dtype, int M, int N, const void* A, float* out, float* partial, hipStream_t st);
 // the segment of G rows of N partial sums each, added to out
 ReduceSeg colsum_segment(const float* partial, int G, int N, float* out);
@@ -72,6 +91,10 @@ struct GemmEpilogue {
   // ELEMENTS after piece s-1.  One launch, one read-modify-write of C.
   int k_segments = 1;
   size_t seg_stride_a = 0, seg_stride_b = 0;
+  // forms 0 and 1, bf16 MFMA path only: `batch` products of M rows each with the same B.  A's lie stride_a bytes
+  // apart, C's and gelu_out's stride_c, residuals or dgelu_u's stride_r; the rows of colsum_partial follow on.
+  int batch = 1;
+  size_t stride_a = 0, stride_c = 0, stride_r = 0;
 };
 // form 0: C[M,N] = A[M,K] B[N,K]^T ; form 1: C[M,N] = A[M,K] B[K,N] ;
 // form 2: Cf32[M,N] += A[K,M]^T B[K,N].
@@ -136,14 +159,28 @@ hipError_t attention_bwd_f32(int B, int S, int a, int d, const void* qkv, const 
 bool attention_mfma_supported(int B, int S, int a, int d);   // head_dim 32/64/128 and index ranges
 size_t attention_mfma_scratch_bytes(int B, int S, int a, int d, int phase);
 // f16: qkv and out are fp16 (forward activations kept in fp16); lse is fp32 either way.
+// n micro-batches of B sequences: qkv, out and lse lie `stride` bytes apart.
 hipError_t attention_fwd_mfma(int B, int S, int a, int d, const void* qkv, void* out, float* lse,
-                              void* scratch, hipStream_t st, bool f16 = false);
+                              void* scratch, hipStream_t st, bool f16 = false, int n = 1, size_t stride = 0);
 // qkv_f16 (optional): the fp16 qkv of an fp16 forward pass; the logits are then recomputed from
 // its Q and K, `out` is that pass's fp16 output (it only enters delta = rowsum(dO * O)), and
 // qkv is the bf16 copy that every other product reads.
+// n micro-batches: qkv, out, lse, dout and scratch lie `act` bytes apart, dqkv `grad`.
 hipError_t attention_bwd_mfma(int B, int S, int a, int d, const void* qkv, const void* out,
                               const float* lse, const void* dout, void* dqkv, void* scratch,
-                              hipStream_t st, const void* qkv_f16 = nullptr);
+                              hipStream_t st, const void* qkv_f16 = nullptr, int n = 1, size_t act = 0, size_t grad = 0);
+
+// ---- a chunk's window of micro-batches as one pass per operator (stage.hip, for dpp.hip) ----
+// How many of a window of W micro-batches a pass takes; 1: none, they go one by one.
+int stage_window(const gpt_stage_params* p, int W);
+// The forward phase of n micro-batches, their stashes `act_stride` and `grad_stride` bytes apart.  y[m] may be x[m].  The
+// gradient stashes only lend room: buffers that are not equally spaced go through it.
+int stage_fwd_window(const gpt_stage_params* p, int n, const void* const* x, void* act_stash, size_t act_stride,
+                     void* const* y, void* grad_stash, size_t grad_stride, hipStream_t st);
+// Their backward data phase.  It overwrites the parts of the activation stashes that the weight phase does not read.
+// dx[m] may be dy[m].
+int stage_bwd_window(const gpt_stage_params* p, int n, void* act_stash, size_t act_stride, const void* const* dy,
+                     void* const* dx, void* dparams, void* grad_stash, size_t grad_stride, hipStream_t st);
 
 // Records the thread's error text and returns `code` (for sources outside stage.hip).
 int set_error(int code, const char* msg);

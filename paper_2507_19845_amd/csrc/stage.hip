@@ -313,9 +313,9 @@ size_t attention_scratch_bytes(int dtype, int B, int S, int a, int d, int phase)
 }
 // f16 / qkv_f16: the fp16 forward-activation variants (matrix-core path only)
 hipError_t attention_fwd(int dtype, int B, int S, int a, int d, const void* qkv, void* out,
-                         float* lse, void* scratch, hipStream_t st, bool f16 = false) {
-  if (attention_uses_mfma(dtype, B, S, a, d)) return attention_fwd_mfma(B, S, a, d, qkv, out, lse, scratch, st, f16);
-  if (f16) return hipErrorInvalidValue;
+                         float* lse, void* scratch, hipStream_t st, bool f16 = false, int n = 1, size_t stride = 0) {
+  if (attention_uses_mfma(dtype, B, S, a, d)) return attention_fwd_mfma(B, S, a, d, qkv, out, lse, scratch, st, f16, n, stride);
+  if (f16 || n != 1) return hipErrorInvalidValue;
   if (dtype == GPTS_FP32 && attention_f32_supported(qkv, out, nullptr, nullptr))
     return attention_fwd_f32(B, S, a, d, qkv, out, lse, st);
   return attention_fwd_simple(dtype, B, S, a, d, qkv, out, lse, st);
@@ -353,8 +353,14 @@ int need_prepared(const gpt_stage_params* p) {
 // layout).  phase: what the tracer records (0 forward phase, 1 backward phase).
 // x_in (may be null): the caller's stage input; the first LayerNorm then reads it and fills X, the
 // stage's own (fp32) copy, so that the backward phase never needs the caller's buffer.
+// win (may be null): X and blk are those of the first of win->n micro-batches (stage_window()), the others' lie
+// win->stride bytes apart, their x_in's and, in the last layer (y_f32 false), Yout's win->x_stride and win->y_stride.
+struct FwdWindow {
+  int n;
+  size_t stride, x_stride, y_stride;
+};
 int fwd_layer(const gpt_stage_params* p, int l, const void* X, char* blk, void* Yout, bool y_f32,
-              char* fwk, hipStream_t st, int phase, const void* x_in = nullptr) {
+              char* fwk, hipStream_t st, int phase, const void* x_in = nullptr, const FwdWindow* win = nullptr) {
   Tracer* tr = static_cast<Tracer*>(p->trace);
   const gpt_stage_cfg& c = p->cfg;
   const Dims D(c);
@@ -388,17 +394,22 @@ int fwd_layer(const gpt_stage_params* p, int l, const void* X, char* blk, void* 
   void* A2 = transient ? fwk + fw.A : s + sl.A2;
   void* G = transient ? fwk + fw.G : s + sl.G;
   // one forward product: fp16 operands through the weight's fp16 image, or the bf16 paths
-  auto fwd_gemm = [&](int N, int K, const void* Ain, int wid, void* Cout, const GemmEpilogue& ep_) {
+  const int n_mb = win ? win->n : 1;
+  const size_t stride = win ? win->stride : 0;
+  auto fwd_gemm = [&](int N, int K, const void* Ain, int wid, void* Cout, GemmEpilogue ep_) {
+    ep_.batch = n_mb;
+    ep_.stride_a = ep_.stride_r = stride;
+    ep_.stride_c = win && Cout == Yout && !y_f32 ? win->y_stride : stride;
     return h16 ? gemm_fwd_f16(D.T, N, K, Ain, ep_.b_image, Cout, ep_, st) : gemm(dt, 0, D.T, N, K, Ain, w(l, wid), Cout, ep_, st);
   };
   GPTS_OP(top, 0, phase, 0.0, TH * (kResBytes + e), ln_fwd(dt, bf && !x_in, D.T, D.H, c.ln_eps, x_in ? x_in : X, w(l, GPTS_LN1_G), w(l, GPTS_LN1_B), A,
-                  stat1, stat1 + D.T, st, h16, x_in ? static_cast<float*>(const_cast<void*>(X)) : nullptr), "ln1 fwd");
+                  stat1, stat1 + D.T, st, h16, x_in ? static_cast<float*>(const_cast<void*>(X)) : nullptr, n_mb, stride, win && x_in ? win->x_stride : stride), "ln1 fwd");
   GemmEpilogue ep;
   ep.bias = w(l, GPTS_B_QKV);
   ep.b_image = img(l, 0);
   GPTS_OP(top_gemm, 0, phase, gf(D.T, 3 * D.P, D.H), gb(D.T, 3 * D.P, D.H, e), fwd_gemm(3 * D.P, D.H, A, GPTS_W_QKV, s + sl.QKV, ep), "qkv gemm");
   GPTS_OP(top_attn, 0, phase, attn_fl, (double)D.T * 4 * D.P * e, attention_fwd(dt, D.B, D.S, D.a, D.d, s + sl.QKV, s + sl.C,
-                                reinterpret_cast<float*>(s + sl.LSE), fwk + fw.attn, st, h16), "attention fwd");
+                                reinterpret_cast<float*>(s + sl.LSE), fwk + fw.attn, st, h16, n_mb, stride), "attention fwd");
   ep = GemmEpilogue();
   ep.bias = w(l, GPTS_B_O);
   ep.residual = X;
@@ -406,7 +417,7 @@ int fwd_layer(const gpt_stage_params* p, int l, const void* X, char* blk, void* 
   ep.b_image = img(l, 1);
   GPTS_OP(top_gemm, 1, phase, gf(D.T, D.H, D.P), gb(D.T, D.H, D.P, 2 * kResBytes), fwd_gemm(D.H, D.P, s + sl.C, GPTS_W_O, s + sl.X1, ep), "out-proj gemm");
   GPTS_OP(top, 1, phase, 0.0, TH * (kResBytes + e), ln_fwd(dt, bf, D.T, D.H, c.ln_eps, s + sl.X1, w(l, GPTS_LN2_G), w(l, GPTS_LN2_B), A2,
-                  stat2, stat2 + D.T, st, h16), "ln2 fwd");
+                  stat2, stat2 + D.T, st, h16, nullptr, n_mb, stride, stride), "ln2 fwd");
   ep = GemmEpilogue();
   ep.bias = w(l, GPTS_B_FC1);
   ep.gelu_out = G;
@@ -739,10 +750,170 @@ int run_wgrad_flush(const gpt_stage_params* p, int n, const void* const* act_sta
   return GPTS_OK;
 }
 
+// Where a pass over a window keeps what a backward call keeps in its workspace: the tensors of a micro-batch in its
+// own activation stash, whose U is dead once the fc2 data gradient has read it and X1 once the second LayerNorm's
+// backward has; the partial sums of all of them in the workspace, where the tensors would be.
+struct WindowSums {
+  size_t fc1, ln2, qkv, fc2, end;   // fc1 and ln2, then qkv and fc2, then ln1 at offset 0: each lot added up before the next
+};
+WindowSums window_sums(const Dims& D, int n) {
+  WindowSums w;
+  const size_t ln = align_up(n * ln_bwd_scratch_bytes(D.T, D.H), 256);
+  w.fc1 = 0;
+  w.ln2 = align_up((size_t)n * fc1_sum_rows(D, GPTS_BF16) * D.F * sizeof(float), 256);
+  w.qkv = 0;
+  w.fc2 = align_up(n * colsum_scratch_bytes(D.T, 3 * D.P), 256);
+  const size_t late = w.fc2 + align_up(n * colsum_scratch_bytes(D.T, D.H), 256);
+  w.end = w.ln2 + ln > late ? w.ln2 + ln : late;
+  return w;
+}
+// Buffers in order and equally spaced: how far, else 0.
+size_t spacing(const void* const* p, int n) {
+  auto at = [&](int m) { return reinterpret_cast<uintptr_t>(p[m]); };
+  const size_t d = at(1) > at(0) ? at(1) - at(0) : 0;
+  for (int m = 2; m < n; ++m)
+    if (at(m) - at(m - 1) != d) return 0;
+  return d % 16 == 0 && d < ((size_t)1 << 36) ? d : 0;
+}
+// Elements of a [tokens, hidden] tensor of a pass.  Small micro-batches leave most of the chip idle and are chains of
+// launches; beyond this many elements one alone fills it, and a pass's tensors leave the cache before the next
+// operator reads them.  Time of a traversal in passes over that one by one (hidden, tokens x micro-batches), up to
+// 4 | 8 | 16 | 32 thousand tokens a pass: 256, 128 x 8 0.32; 512, 512 x 4 0.44; 1024, 512 x 8 0.48; 1024, 2048 x 4 0.81 |
+// 0.72; 1024, 4096 x 4 1 | 0.92 | 0.91 | 0.92; 512, 8192 x 4 1 | 1 | 0.90 | 0.88; 2048, 1024 x 4 0.77; 2048, 2048 x 8 0.88 |
+// 0.86 | 0.87 | 0.87; 4096, 1024 x 4 0.84; 4096, 2048 x 4 0.94 | 0.94 | 0.94.
+constexpr size_t kWindowElems = (size_t)1 << 24;
+
 }  // namespace
 
 namespace gpts {
 int set_error(int code, const char* msg) { return fail(code, msg); }
+
+int stage_window(const gpt_stage_params* p, int W) {
+  if (check_call(p) != GPTS_OK || !p->workspace || p->trace) return 1;
+  const gpt_stage_cfg& c = p->cfg;
+  if (c.dtype != GPTS_BF16 || c.recompute || c.fwd_fp16) return 1;
+  const Dims D(c);
+  const int widest = D.H > D.P ? D.H : D.P;
+  bool ok = attention_mfma_supported(D.B, D.S, D.a, D.d) && D.F >= widest && fc1_sum_rows(D, c.dtype) > 0 &&
+            (size_t)D.T * D.a * 4 <= (size_t)D.T * D.H * kResBytes;
+  LinDims L[4];
+  linears(D, L);
+  for (const LinDims& lin : L)
+    ok = ok && gemm_mfma_supported(0, D.T, lin.out, lin.in) && gemm_mfma_supported(1, D.T, lin.in, lin.out);
+  const size_t room = bwd_ws(c).end - fwd_ws_bytes(c);
+  int n = W < kMaxWindow ? W : kMaxWindow;
+  while (n > 1 && (!ok || (size_t)n * D.T * D.H > kWindowElems || window_sums(D, n).end > room || (long)n * D.B > 65535)) --n;
+  if (n < 2) return 1;
+  const int passes = (W + n - 1) / n;
+  return (W + passes - 1) / passes;   // passes of like size
+}
+
+int stage_fwd_window(const gpt_stage_params* p, int n, const void* const* x, void* act_stash, size_t act_stride,
+                     void* const* y, void* grad_stash, size_t grad_stride, hipStream_t st) {
+  const Dims D(p->cfg);
+  const StashLayer sl = stash_layer(p->cfg);
+  const GradStashLayer gl = grad_stash_layer(p->cfg);
+  const size_t bytes = (size_t)D.T * D.H * esize(p->cfg);
+  void* room[kMaxWindow];
+  for (int m = 0; m < n; ++m) room[m] = static_cast<char*>(grad_stash) + m * grad_stride + (size_t)(D.L - 1) * gl.end + gl.dY;
+  FwdWindow win{n, act_stride, spacing(x, n), spacing(y, n)};
+  const void* x0 = x[0];
+  void* y0 = y[0];
+  if (!win.x_stride) {
+    GPTS_TRY(window_copy(n, x, room, bytes, st), "copy x");
+    x0 = room[0];
+    win.x_stride = grad_stride;
+  }
+  const bool copy_y = !win.y_stride;
+  if (copy_y) {
+    y0 = room[0];
+    win.y_stride = grad_stride;
+  }
+  for (int l = 0; l < D.L; ++l) {
+    char* s = static_cast<char*>(act_stash) + (size_t)l * sl.end;
+    const bool last = l == D.L - 1;
+    const int rc = fwd_layer(p, l, s + sl.X, s, last ? y0 : (void*)(s + sl.end + sl.X), !last, static_cast<char*>(p->workspace),
+                             st, 0, l == 0 ? x0 : nullptr, &win);
+    if (rc != GPTS_OK) return rc;
+  }
+  if (copy_y) GPTS_TRY(window_copy(n, room, y, bytes, st), "copy y");
+  return GPTS_OK;
+}
+
+int stage_bwd_window(const gpt_stage_params* p, int n, void* act_stash, size_t act_stride, const void* const* dy,
+                     void* const* dx, void* dparams, void* grad_stash, size_t grad_stride, hipStream_t st) {
+  const gpt_stage_cfg& c = p->cfg;
+  const Dims D(c);
+  const size_t e = esize(c);
+  const int dt = c.dtype;
+  const StashLayer sl = stash_layer(c);
+  const GradStashLayer gl = grad_stash_layer(c);
+  const char* W = static_cast<const char*>(p->weights);
+  float* dP = static_cast<float*>(dparams);
+  char* const sums = static_cast<char*>(p->workspace) + fwd_ws_bytes(c);
+  const WindowSums ws = window_sums(D, n);
+  auto part = [&](size_t off) { return reinterpret_cast<float*>(sums + off); };
+  const size_t bytes = (size_t)D.T * D.H * e;
+  void* top[kMaxWindow];
+  for (int m = 0; m < n; ++m) top[m] = static_cast<char*>(grad_stash) + m * grad_stride + (size_t)(D.L - 1) * gl.end + gl.dY;
+  GPTS_TRY(window_copy(n, dy, top, bytes, st), "copy dy");
+  const size_t dx_stride = spacing(dx, n);
+  for (int l = D.L - 1; l >= 0; --l) {
+    char* const s = static_cast<char*>(act_stash) + (size_t)l * sl.end;
+    char* const g0 = static_cast<char*>(grad_stash) + (size_t)l * gl.end;
+    auto w = [&](int id) { return (const void*)(W + tensor_off(D, l, id) * e); };
+    auto g = [&](int layer, int id) { return dP + tensor_off(D, layer, id); };
+    const float* stat1 = reinterpret_cast<const float*>(s + sl.stat1);
+    const float* stat2 = reinterpret_cast<const float*>(s + sl.stat2);
+    void *const dY = g0 + gl.dY, *const dU = g0 + gl.dU, *const dX1 = g0 + gl.dX1, *const dQKV = g0 + gl.dQKV;
+    void* const tmp = s + sl.U;        // dA2, then dC, then dA
+    void* const delta = s + sl.X1;
+    auto dgrad = [&](int N, int K, const void* A, int wid, void* C, size_t c_stride, GemmEpilogue ep) {
+      ep.batch = n;
+      ep.stride_a = grad_stride;
+      ep.stride_c = c_stride;
+      ep.stride_r = act_stride;
+      return gemm(dt, 1, D.T, N, K, A, w(wid), C, ep, st);
+    };
+    LnBwdWindow ln;
+    ln.n = n;
+    ln.act = act_stride;
+    ln.dres = ln.dx = grad_stride;
+    ReduceSeg seg[2];
+    GemmEpilogue ep;
+    ep.dgelu_u = s + sl.U;
+    ep.gelu_kind = c.gelu;
+    ep.colsum_partial = part(ws.fc1);
+    GPTS_TRY(dgrad(D.F, D.H, dY, GPTS_W_FC2, dU, grad_stride, ep), "fc2 dgrad");
+    seg[0] = colsum_segment(part(ws.fc1), fc1_sum_rows(D, dt), D.F, g(l, GPTS_B_FC1));
+    seg[0].batch = n;
+    GPTS_TRY(dgrad(D.H, D.F, dU, GPTS_W_FC1, tmp, act_stride, GemmEpilogue()), "fc1 dgrad");
+    GPTS_TRY(ln_bwd_partials(dt, true, D.T, D.H, tmp, s + sl.X1, stat2, stat2 + D.T, w(GPTS_LN2_G), dY, dX1, g(l, GPTS_LN2_G),
+                             g(l, GPTS_LN2_B), g(l, GPTS_B_O), part(ws.ln2), &seg[1], st, &ln), "ln2 bwd");
+    GPTS_TRY(reduce_partials(seg, 2, st), "fc1 bias and ln2 gradients");
+    GPTS_TRY(dgrad(D.P, D.H, dX1, GPTS_W_O, tmp, act_stride, GemmEpilogue()), "out-proj dgrad");
+    GPTS_TRY(attention_bwd_mfma(D.B, D.S, D.a, D.d, s + sl.QKV, s + sl.C, reinterpret_cast<const float*>(s + sl.LSE), tmp, dQKV,
+                                delta, st, nullptr, n, act_stride, grad_stride), "attention bwd");
+    GPTS_TRY(dgrad(D.H, 3 * D.P, dQKV, GPTS_W_QKV, tmp, act_stride, GemmEpilogue()), "qkv dgrad");
+    const ColsumMat cols[2] = {{dQKV, 3 * D.P, g(l, GPTS_B_QKV), part(ws.qkv)}, {dY, D.H, g(l, GPTS_B_FC2), part(ws.fc2)}};
+    const int n_cols = l == D.L - 1 ? 2 : 1;   // (below the top layer the LayerNorm of the layer above has summed dY)
+    GPTS_TRY(colsum_partials(dt, D.T, cols, n_cols, seg, st, n, grad_stride), "bias gradients");
+    GPTS_TRY(reduce_partials(seg, n_cols, st), "bias gradients");
+    // dx: the layer below reads it as its dY; the bottom layer's is the caller's, by way of the dead X1 where those
+    // are not equally spaced
+    void* dxout = l > 0 ? g0 - gl.end + gl.dY : (dx_stride ? dx[0] : s + sl.X1);
+    if (l == 0) ln.dx = dx_stride ? dx_stride : act_stride;
+    GPTS_TRY(ln_bwd_partials(dt, true, D.T, D.H, tmp, s + sl.X, stat1, stat1 + D.T, w(GPTS_LN1_G), dX1, dxout, g(l, GPTS_LN1_G),
+                             g(l, GPTS_LN1_B), l > 0 ? g(l - 1, GPTS_B_FC2) : nullptr, part(0), &seg[0], st, &ln), "ln1 bwd");
+    GPTS_TRY(reduce_partials(seg, 1, st), "ln1 gradients");
+  }
+  if (!dx_stride) {
+    const void* from[kMaxWindow];
+    for (int m = 0; m < n; ++m) from[m] = static_cast<const char*>(act_stash) + m * act_stride + sl.X1;
+    GPTS_TRY(window_copy(n, from, dx, bytes, st), "copy dx");
+  }
+  return GPTS_OK;
+}
 }  // namespace gpts
 
 extern "C" {

@@ -457,3 +457,78 @@ def test_dpp_weight_phase_per_chunk_and_window():
     with pytest.raises(B.GptStageError) as e:
         B.gpt_dpp_run(B.GPT_DPP_BFC, chunks, t, t, t, t, dps, stash, act, grad_pool=gp)
     assert e.value.code == B.GPTS_ENOMEM
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hidden,heads,d,ffn,seq,batch,layers,M,W,spaced", [
+    (128, 2, 64, 256, 64, 1, 1, 4, 4, True), (192, 4, 32, 320, 192, 3, 2, 7, 3, False), (320, 2, 128, 448, 320, 1, 1, 5, 5, False),
+    (1024, 16, 64, 4096, 512, 1, 1, 8, 8, False), (2048, 4, 128, 2112, 64, 2, 2, 3, 2, True)])
+def test_dpp_passes_over_a_window_keep_every_bit(hidden, heads, d, ffn, seq, batch, layers, M, W, spaced):
+    """A chunk's micro-batches of a window run as one pass per operator; under a tracer they run one by one.  The
+    same bits in every output, with the callers' buffers equally spaced or not, dx in place of dy, gradients that
+    are not zero to begin with, boundary buffers just enough for the plan, and the last window shorter."""
+    import torch
+    C = 3
+    shape = synth.StageShape(name="dpp_pass", n_layers=layers, hidden=hidden, n_heads=heads, head_dim=d, ffn=ffn, seq=seq,
+                             batch=batch, dtype="bf16", n_microbatches=M)
+    print(f"[case] passes over a window {shape} M={M} W={W}", flush=True)
+    cfg = B.make_cfg(shape)
+    n = B.gpt_stage_param_count(cfg)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(hidden + M)
+    tok = (batch, seq, hidden)
+    ws = torch.empty(B.gpt_stage_workspace_bytes(cfg, 1), dtype=torch.uint8, device="cuda")
+    weights = [torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0, 0.03, generator=gen) for _ in range(C)]
+    x0 = torch.empty(M, *tok, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    dy0 = torch.empty(M, *tok, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    order = list(range(M)) if spaced else [(2 * m) % M if M % 2 else (M - 1 - m) for m in range(M)]
+    got = []
+    for traced in (True, False):
+        tr = B.gpt_stage_trace_create(4096) if traced else None
+        chunks = [B.gpt_stage_params(cfg=cfg, weights=w.data_ptr(), workspace=ws.data_ptr(), prepared=None, trace=tr) for w in weights]
+        slot = lambda t: [t[order[m]] for m in range(M)]                     # noqa: E731
+        xs, dys, ys = slot(x0.clone()), slot(dy0.clone()), slot(torch.full_like(x0, 7.0))
+        dps = [torch.ones(n, dtype=torch.float32, device="cuda") for _ in range(C)]
+        stash = torch.empty(B.gpt_dpp_stash_slot_bytes(chunks) * C * W, dtype=torch.uint8, device="cuda")
+        act = torch.empty(B.gpt_dpp_act_slot_bytes(cfg) * (W + 1), dtype=torch.uint8, device="cuda")
+        pool = torch.empty(B.gpt_dpp_grad_slot_bytes(chunks) * W, dtype=torch.uint8, device="cuda")
+        B.gpt_dpp_run(B.GPT_DPP_BFC_BEST_EFFORT, chunks, xs, dys, ys, dys, dps, stash, act, max_live_stash=C * W, grad_pool=pool)
+        torch.cuda.synchronize()
+        if traced:
+            B.gpt_stage_trace_destroy(tr)
+        assert torch.equal(torch.stack([x0[order[m]] for m in range(M)]), torch.stack(xs))
+        got.append(ys + dys + dps)
+    for i, (a, b) in enumerate(zip(*got)):
+        assert torch.isfinite(a.float()).all() and torch.equal(a, b), i
+
+
+@pytest.mark.gpu
+def test_dpp_passes_leave_overlapping_buffers_to_single_calls():
+    """One chunk: y of micro-batch 0 is x of micro-batch 1, and every dx the same buffer.  One by one each sees what
+    the one before it wrote, so no pass may take them together."""
+    import torch
+    shape = synth.StageShape(name="dpp_overlap", n_layers=1, hidden=128, n_heads=2, head_dim=64, ffn=256, seq=64,
+                             batch=1, dtype="bf16", n_microbatches=2)
+    cfg = B.make_cfg(shape)
+    n = B.gpt_stage_param_count(cfg)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    w = torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(0, 0.03, generator=gen)
+    ws = torch.empty(B.gpt_stage_workspace_bytes(cfg, 1), dtype=torch.uint8, device="cuda")
+    data = torch.empty(4, 1, 64, 128, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    got = []
+    for traced in (True, False):
+        tr = B.gpt_stage_trace_create(4096) if traced else None
+        chunks = [B.gpt_stage_params(cfg=cfg, weights=w.data_ptr(), workspace=ws.data_ptr(), prepared=None, trace=tr)]
+        x0, x1, dy0, dy1 = data.clone()
+        y1, dx = torch.empty_like(x0), torch.empty_like(x0)
+        dp = torch.zeros(n, dtype=torch.float32, device="cuda")
+        stash = torch.empty(B.gpt_dpp_stash_slot_bytes(chunks) * 2, dtype=torch.uint8, device="cuda")
+        pool = torch.empty(B.gpt_dpp_grad_slot_bytes(chunks) * 2, dtype=torch.uint8, device="cuda")
+        B.gpt_dpp_run(B.GPT_DPP_BFC, chunks, [x0, x1], [dy0, dy1], [x1, y1], [dx, dx], [dp], stash, stash, grad_pool=pool)
+        torch.cuda.synchronize()
+        if traced:
+            B.gpt_stage_trace_destroy(tr)
+        got.append([x1, y1, dx, dp])
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
