@@ -640,6 +640,34 @@ def test_op_gemm_forms(dtype, M, N, K):
     assert max_norm_err(B.to_host(Cf), ref) <= (1e-5 if dtype == "fp32" else 1e-4)
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 8, 4), (33, 36, 28), (31, 64, 124), (65, 100, 128), (32, 32, 132), (100, 516, 252),
+                                   (64, 28, 260), (129, 260, 512), (999, 512, 516), (999, 1280, 260), (1030, 1540, 36),
+                                   (1500, 2052, 100)])
+def test_op_gemm_fp32_slices(M, N, K):
+    """Both fp32 tiles with ragged edges, and contractions that end at, just before and just behind a slice of 32, 64
+    or 128 k, of one slice and of more than the slices ahead.  What lies behind the operands is NaN.  A sum of K fp32
+    products in any order is off by at most K eps of the sum of magnitudes."""
+    print(f"[case] gemm fp32 slices M={M} N={N} K={K}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+
+    def rnd(r, c):
+        t = torch.full((r * c + 4096,), float("nan"), device="cuda")
+        t[:r * c].normal_(generator=gen)
+        return t[:r * c].view(r, c)
+
+    for form in (0, 1, 2):
+        m = (M + 3) // 4 * 4 if form == 2 else M
+        A, Bm = (rnd(K, m) if form == 2 else rnd(m, K)), (rnd(N, K) if form == 0 else rnd(K, N))
+        out = torch.full((m + 1, N), 0.25, device="cuda")
+        B.gpt_stage_op_gemm(B.GPTS_FP32, form, m, N, K, A, Bm, out[:m])
+        a, b = (A.double().t() if form == 2 else A.double()), (Bm.double().t() if form == 0 else Bm.double())
+        ref = a @ b + (0.25 if form == 2 else 0.0)
+        bound = (K + 1) * 2.0 ** -24 * (a.abs() @ b.abs() + 0.25)
+        assert ((out[:m].double() - ref).abs() <= bound).all(), form
+        assert (out[m] == 0.25).all(), form
+
+
 @pytest.mark.parametrize("M,N,K", [(72, 1000, 64), (264, 3000, 128), (520, 2056, 192), (1000, 4104, 128), (2040, 4104, 128),
                                    (2040, 5112, 192), (2040, 6136, 64), (4088, 4088, 320), (264, 1000, 1024),
                                    (1000, 2056, 320), (8200, 4104, 64), (1000, 4104, 832), (2040, 4104, 832),
