@@ -58,8 +58,8 @@ struct TileInfo {
   float slice_tn, fixed_tn;
 };
 constexpr TileInfo kTiles[N_TILES] = {
-    {256, 256, 1.39f, 8.f, 1.45f, 20.f},  {256, 192, 1.20f, 5.f, 1.17f, 17.f}, {256, 160, 0.95f, 4.5f, 0.98f, 14.f},
-    {192, 192, 0.83f, 4.5f, 0.88f, 13.f}, {256, 128, 0.78f, 4.f, 0.85f, 12.f}, {128, 128, 0.40f, 5.f, 0.40f, 9.5f},
+    {256, 256, 1.39f, 8.f, 1.45f, 21.4f},  {256, 192, 1.20f, 5.f, 1.17f, 17.f}, {256, 160, 0.95f, 4.5f, 0.98f, 14.f},
+    {192, 192, 0.83f, 4.5f, 0.88f, 13.f}, {256, 128, 0.78f, 4.f, 0.66f, 11.f}, {128, 128, 0.40f, 5.f, 0.40f, 9.5f},
     {128, 64, 0.27f, 3.6f, 0.27f, 5.2f},  {64, 64, 0.17f, 2.6f, 0.18f, 3.3f},  {64, 32, 0.16f, 2.2f, 0.18f, 2.7f}};
 
 // Weight gradients whose operands no longer stay in the 256 MB cache are not bound by the matrix pipe in
@@ -67,6 +67,13 @@ constexpr TileInfo kTiles[N_TILES] = {
 // together get 2.65 TB/s: 0.59 us a slice in 128x128.  6144x2048 (192 tiles of 256x256, 768 of 128x128):
 // K = 10240, 168 MB of operands, 230 us in either; K = 14336, 235 MB, 316 against 344; K = 16384 355
 // against 468; K = 32768 683 against 961.  2560x2560, K = 32768: 192x192 436, 128x128 614.
+//
+// Weight gradients in 256x128 and 128x128 share a unit in pairs (launch_wgrads()): beyond 256 tiles they go at the rate
+// of kSharedTn a tile and unit, and a round that is not full costs a share (`lack`) of what is missing in it.  In step up to
+// some 6000 k an XCD reads a patch of 4 x 16 of them for 64; beyond they drift apart and a slice takes an eighth longer.
+// 256x256 | 256x128, us: 16384x4096, K = 2048 271 | 260, 4096 456 | 449, 8192 832 | 846, 32768 3137 | 3380; 6144x4096,
+// K = 4096 200 | 165; 4096x4096, K = 512 33.5 | 38.8; layers of 4800 and 3456 tiles of 256x256, K = 2048 1285 | 1239
+// and 931 | 880.
 //
 // Short contractions (short_contraction(), forward products and data gradients) are bound by their
 // epilogues as much: they have numbers of their own, fitted to products of 64 ... 768 k (the estimate is
@@ -95,6 +102,19 @@ float short_us(Tile t, long tiles, long slices, Cost cost) {
   return i.start + (float)((tiles + 255) / 256) * ((float)slices * i.slice + i.fixed * kCostAlone[cost]);
 }
 
+struct SharedInfo { float start, slice, fixed, lack; };
+constexpr SharedInfo kSharedTn256x128 = {5.1f, 0.72f, 8.3f, 0.42f}, kSharedTn128x128 = {3.0f, 0.41f, 4.3f, 0.47f};
+constexpr long kInStep = 6144;   // k
+// of a weight gradient's tiles, more than 256 of them, whose operands hold so many bytes
+float shared_tn_us(Tile t, long tiles, long K, float operand_bytes) {
+  const SharedInfo& i = t == TILE_256x128 ? kSharedTn256x128 : kSharedTn128x128;
+  const float patch = (float)((K <= kInStep ? 2 : 4) * kTiles[t].bm + 8 * kTiles[t].bn);
+  float slice = K <= kInStep ? i.slice : 1.125f * i.slice;
+  if (operand_bytes > 200e6f) slice = fmaxf(slice, patch * (64 * 2 * 8 / 2.65e6f));
+  const float rounds = (float)tiles / 256.f;
+  return i.start + (rounds + i.lack * (ceilf(rounds) - rounds)) * ((float)((K + 63) / 64) * slice + i.fixed);
+}
+
 struct Product { int M, N; };
 // batch: products in one launch whose tile rows follow on
 Tile choose_tile(int form, const Product* p, int n, long K, Cost cost, int batch = 1) {
@@ -108,8 +128,9 @@ Tile choose_tile(int form, const Product* p, int n, long K, Cost cost, int batch
     const long rounds = (tiles + 255) / 256, slices = (K + 63) / 64;
     float slice = form == 2 ? i.slice_tn : i.slice, fixed = form == 2 ? i.fixed_tn : i.fixed;
     if (form == 2 && operand_bytes > 200e6f) slice = fmaxf(slice, (float)(4 * i.bm + 8 * i.bn) * (64 * 2 * 8 / 2.65e6f));
-    const float us = form != 2 && short_contraction(K) ? short_us((Tile)t, tiles, slices, cost)
-                                                       : (float)rounds * ((float)slices * slice + fixed);
+    float us = (float)rounds * ((float)slices * slice + fixed);
+    if (form != 2 && short_contraction(K)) us = short_us((Tile)t, tiles, slices, cost);
+    if (form == 2 && tiles > 256 && (t == TILE_256x128 || t == TILE_128x128)) us = shared_tn_us((Tile)t, tiles, K, operand_bytes);
     if (t == 0 || us < 0.97f * best_us) {
       best = (Tile)t;
       best_us = us;

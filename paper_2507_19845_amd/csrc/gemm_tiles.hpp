@@ -603,8 +603,14 @@ __device__ __forceinline__ void gemm_tile(MfmaArgs a, int id, char* const lds) {
   }
 }
 
+// Waves per SIMD the registers have to allow: two where half of the LDS holds a ring of the largest tile that two
+// workgroups in a unit can have (256x128: 128 accumulators and at most 128 other registers); the smaller ones
+// need no limit.
+template <int MB, int NB, int BK, int NS> constexpr int gemm_waves() {
+  return MB * NB >= 32 && gemm_lds_bytes<MB, NB, BK, NS>() <= 80 * 1024 ? 2 : 1;
+}
 template <int EPI, int FORM, bool F16, int MB, int NB, int BK, int NS>
-__global__ __launch_bounds__(256) void gemm_mi16_kernel(const MfmaArgs a) {
+__global__ __launch_bounds__(256, (gemm_waves<MB, NB, BK, NS>())) void gemm_mi16_kernel(const MfmaArgs a) {
   __shared__ __attribute__((aligned(1024))) char lds[gemm_lds_bytes<MB, NB, BK, NS>()];
   gemm_tile<EPI, FORM, F16, MB, NB, BK, NS>(a, blockIdx.x, lds);
 }
@@ -616,7 +622,7 @@ struct WgradGroup {
   int first[kMaxWgrads];   // first workgroup of a product
 };
 template <int EPI, int FORM, bool F16, int MB, int NB, int BK, int NS>
-__global__ __launch_bounds__(256) void gemm_mi16_group_kernel(const WgradGroup g) {
+__global__ __launch_bounds__(256, (gemm_waves<MB, NB, BK, NS>())) void gemm_mi16_group_kernel(const WgradGroup g) {
   __shared__ __attribute__((aligned(1024))) char lds[gemm_lds_bytes<MB, NB, BK, NS>()];
   int k = 0;
 #pragma unroll
@@ -671,14 +677,19 @@ template <int EPI, int FORM, bool F16 = false> hipError_t launch_tile(Tile tile,
 // Their rows are whole lines at any depth, and the transposing reads leave no room for a copy as
 // bursty as two stages of 64 (4096^3: 115 against 118 us; 3968x6144x2048 with 192 columns: 109 against
 // 117 us).  With a K-contiguous operand two stages of 64 win (97 against 102 us; 84 against 94 us).
+// 256x128 and 128x128 take slices of 32 in half of the LDS: two workgroups share a unit, and one's read-modify-write
+// of the fp32 matrix, a fifth of a lone workgroup's time, runs under the other's slices.  In slices of 64 and all
+// of the LDS | this, us: 256x128 6144x4096, K = 2048 113 | 98, 4096x2048 (one round of 256) 37.1 | 36.6, 3072x3072,
+// K = 4096 106 | 89; 128x128 4096x4096, K = 1024 57 | 45, 3072x2048, K = 4096 62 | 56, 4096x1024 (one round)
+// 37.1 | 36.5; 128x128 with two slices of 64: 4 % slower than with four of 64, five of 32: within 2 % of four.
 inline hipError_t launch_wgrads(Tile tile, const MfmaArgs* a, int n, hipStream_t st) {
   switch (tile) {
     case TILE_256x256: return launch_group<8, 8, 32, 4>(a, n, st);
     case TILE_256x192: return launch_group<8, 6, 32, 5>(a, n, st);
     case TILE_256x160: return launch_group<8, 5, 64, 3>(a, n, st);
     case TILE_192x192: return launch_group<6, 6, 64, 3>(a, n, st);
-    case TILE_256x128: return launch_group<8, 4, 64, 3>(a, n, st);
-    case TILE_128x128: return launch_group<4, 4, 64, 4>(a, n, st);
+    case TILE_256x128: return launch_group<8, 4, 32, 3>(a, n, st);
+    case TILE_128x128: return launch_group<4, 4, 32, 4>(a, n, st);
     case TILE_128x64: return launch_group<4, 2, 64, 4>(a, n, st);
     case TILE_64x64: return launch_group<2, 2, 64, 4>(a, n, st);
     case TILE_64x32: return launch_group<2, 1, 64, 4>(a, n, st);

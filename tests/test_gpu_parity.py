@@ -126,12 +126,15 @@ def test_split_backward_data_phase_then_one_weight_phase(mode):
 
 @pytest.mark.parametrize("n_mb,seq,hidden,heads,ffn", [(4, 64, 128, 1, 256), (5, 192, 192, 5, 2112), (4, 320, 448, 2, 2112),
                                                        (5, 64, 832, 3, 2112), (5, 320, 832, 5, 2112),
-                                                       (4, 64, 2112, 5, 4160), (5, 192, 2560, 2, 5056)],
-                         ids=["64x32", "128x64", "128x128", "256x128", "192x192", "256x192", "256x256"])
+                                                       (4, 64, 2112, 5, 4160), (5, 192, 2560, 2, 5056),
+                                                       (4, 192, 960, 16, 2112), (4, 192, 1024, 16, 2112),
+                                                       (4, 192, 1728, 5, 2752), (5, 192, 1472, 16, 3200)],
+                         ids=["64x32", "128x64", "128x128", "128x128_short", "128x128_five", "256x128_shared",
+                              "256x128_shared_five", "192x192", "256x160", "256x192", "256x256"])
 def test_split_backward_four_or_more_microbatches(n_mb, seq, hidden, heads, ffn):
     """From four micro-batches on the weight phase contracts over all of them in one launch, whatever the
     widths: each tile of the products, segments of one, three and five slices of 64 (shorter than the
-    ring of stages, odd) and the two tiles with slices of 32.  The fp32 summation order changes and
+    ring of stages, odd) and the tiles with slices of 32.  The fp32 summation order changes and
     nothing else: at most 1600 tokens, so up to sqrt(1600) roundings of 2^-24, 2.4e-6, of the largest sum.  The
     same bits from one launch per linear (which a tracer asks for); micro-batches that are not equally
     spaced take one product each and keep the bits of the unsplit run."""
@@ -671,11 +674,12 @@ def test_op_gemm_fp32_slices(M, N, K):
 @pytest.mark.parametrize("M,N,K", [(72, 1000, 64), (264, 3000, 128), (520, 2056, 192), (1000, 4104, 128), (2040, 4104, 128),
                                    (2040, 5112, 192), (2040, 6136, 64), (4088, 4088, 320), (264, 1000, 1024),
                                    (1000, 2056, 320), (8200, 4104, 64), (1000, 4104, 832), (2040, 4104, 832),
-                                   (2040, 6136, 832), (1000, 2056, 832), (4088, 1160, 704), (8200, 4104, 768)])
+                                   (2040, 6136, 832), (1000, 2056, 832), (4088, 1160, 704), (8200, 4104, 768),
+                                   (2568, 2056, 1088)])
 def test_op_gemm_bf16_tiles(M, N, K):
     """Each tile of the bf16 products with ragged last tiles, one to sixteen slices, and the fp32 epilogues:
-    weight gradients in 64x32, 64x64, 128x64, 256x128, 192x192, 256x160, 256x192, 256x256, 64x32 again with a
-    long contraction, 128x128 and 256x192; forward products and data gradients in the same tiles, except
+    weight gradients in 64x32, 64x64, 128x64, 192x192, 256x160, 256x256, 64x32 again with a long contraction,
+    256x192, 128x128 on at most one a unit and on more, which share it, and 256x128 likewise; forward products and data gradients in the same tiles, except
     that up to 768 k the shapes of more than 256 tiles of 128x64 take 128x64 and 128x128 in two
     stages; then the tiles passed over for those, with 832 k, and both of the two-stage forms with eleven
     and twelve slices.  fp32 sums of K products of bf16 values: K eps of the sum of magnitudes."""
