@@ -80,17 +80,16 @@ constexpr int kImageK = 64;   // slice depth of the weight images
 enum Tile { TILE_256x256 = 0, TILE_256x192, TILE_256x160, TILE_192x192, TILE_256x128, TILE_128x128, TILE_128x64,
             TILE_64x64, TILE_64x32, N_TILES };
 
-// Short contractions of forward products and data gradients in more than one tile per compute unit: two
-// stages of the 128x128 and 128x64 tiles, so that two (three) workgroups share a unit and one's stores
-// run under the other's slices.  With four stages a unit holds one, which waits for its first slice and its
-// stores in every round; beyond 768 the deeper ring is worth as much.  Four | two stages, us: GeLU'
-// 7784x9152, K = 256, 128x128 143 | 101; bias 9920x15872, K = 64 156 | 90; GeLU 8192x3072, K = 768 75 | 55;
-// 128x64: GeLU 8040x3328, K = 128 52 | 31; time of two over four stages, 128x128 with 512 to 1024 tiles: K
-// to 256 0.77, to 768 0.91, to 2048 0.98, to 8000 1.05; with at most 256 tiles 0.99 ... 1.05 up to 768, 1.5
-// beyond.
-constexpr int kShortSlices = 12;   // of 64 k
+// Forward products and data gradients in more than one tile of 128x128 or 128x64 per compute unit: two stages, so
+// that two (three) workgroups share a unit and one's stores run under the other's slices.  With four stages a
+// unit holds one, which waits for its first slice and its stores in every round.  Four | two stages, us: GeLU'
+// 7784x9152, K = 256, 128x128 143 | 101; bias 9920x15872, K = 64 156 | 90; GeLU 8192x3072, K = 768 75 | 55; GeLU'
+// 4096x4096, K = 1024 in 128x64 84 | 64, 128x128 58 | 45; bias 3968x2048, K = 2048 37 | 32.  Time of two over four
+// stages, 288 to 1536 tiles: 128x128 K to 256 0.77, to 768 0.91, to 1536 0.82, to 3072 0.87; 128x64 K = 832 0.83, to 3072
+// 0.92; with at most 256 tiles 0.99 ... 1.05 up to 768, 1.1 at 1024 to 1.5 beyond.
+constexpr int kShortSlices = 12, kSharedSlices = 64;   // of 64 k
 inline bool short_contraction(long K) { return (K + 63) / 64 <= kShortSlices; }
-inline bool two_stages(long tiles, long K) { return tiles > 256 && short_contraction(K); }
+inline bool two_stages(long tiles, long K) { return tiles > 256 && (K + 63) / 64 <= kSharedSlices; }
 
 // Launchers, one translation unit each.
 hipError_t launch_gemm_fwd(Tile tile, int epi, const MfmaArgs& a, hipStream_t st);
