@@ -155,6 +155,52 @@ __global__ __launch_bounds__(kLnThreads) void ln_fwd_kernel(
   }
 }
 
+// For every matrix: partial[slice][n] = sum over the slice's rows (4 slice + w, then every 4 slices) of A[m][n].
+// Lane owns one 16-byte column vector; four waves (w) take interleaved rows and are combined through their LDS `sm`
+// in fixed order.  One launch takes all the matrices of a layer (the same M rows): below some MB each is a few
+// microseconds of launch and latency whatever its size.  Three matrices of 128 rows, 128 to 512 columns, in one
+// launch instead of three: 3.7 us of a 74 us step.
+// NM: matrices there is room for; one alone has a form of its own, without the search.
+template <int NM> struct ColsumArgs {
+  ColsumMat mat[NM];
+  int first[NM];   // first x of a matrix
+  uint32_t stride16;
+};
+template <typename T, int NM>
+__device__ __forceinline__ void colsum_partial(const ColsumArgs<NM>& args, int M, int x, int slice, int slices, int mb, int w,
+                                               float* sm) {
+  constexpr int V = Vec16<T>::N;
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < NM; ++i)
+    if (x >= args.first[i]) k = i;
+  const int N = args.mat[k].N;
+  const T* __restrict__ A = at_mb(static_cast<const T*>(args.mat[k].A), args.stride16, mb);
+  float* __restrict__ partial = args.mat[k].partial + (size_t)mb * slices * N;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int col = ((x - args.first[k]) * kWave + lane) * V;
+  float acc[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) acc[e] = 0.f;
+  if (col < N) {
+    for (int m = slice * 4 + w; m < M; m += slices * 4) {
+      const Vec16<T> v = load16(A + (size_t)m * N + col);
+#pragma unroll
+      for (int e = 0; e < V; ++e) acc[e] += v.get(e);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < V; ++e) sm[w * kWave * V + lane * V + e] = acc[e];
+  __syncthreads();
+  if (w == 0 && col < N && slice < slices) {
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const int i = lane * V + e;
+      partial[(size_t)slice * N + col + e] = sm[i] + sm[kWave * V + i] + sm[2 * kWave * V + i] + sm[3 * kWave * V + i];
+    }
+  }
+}
+
 // ----------------------------------------------------------------- LN bwd ----
 // Per token, with xhat = (x-mu) r and g = dout*gamma:
 //   dx = dres + r (g - mean(g) - xhat mean(g xhat)).
@@ -180,26 +226,45 @@ int ln_bwd_blocks(int T_rows, int H) {
   return need < most ? need : most;
 }
 
-template <typename TX, typename T, int NCH, int RW, bool DXSUM>
+// NM > 0: the workgroups from `tail.blocks` on take the column sums of up to NM matrices of the same rows, two slices
+// each (see ln_bwd_takes_colsums()).
+template <int NM> struct LnBwdTail {
+  ColsumArgs<NM> cols;
+  int blocks, nx, slices;   // workgroups of the LayerNorm; x and slices of the column sums
+};
+template <> struct LnBwdTail<0> {};
+template <typename TX, typename T, int NCH, int RW, bool DXSUM, int NM>
 __global__ __launch_bounds__(kLnBwdThreads) void ln_bwd_kernel(
     const T* __restrict__ dout0, const TX* __restrict__ x0, const float* __restrict__ mean0,
     const float* __restrict__ rstd0, const T* __restrict__ gamma, const T* __restrict__ dres0,
-    T* __restrict__ dx0, float* __restrict__ partial0, int T_rows, int H, uint32_t act16, uint32_t dres16, uint32_t dx16) {
+    T* __restrict__ dx0, float* __restrict__ partial0, int T_rows, int H, uint32_t act16, uint32_t dres16, uint32_t dx16,
+    const LnBwdTail<NM> tail) {
+  constexpr int NWV = kLnBwdThreads / kWave, GR = NWV / RW, NT = RW * kWave, NPART = DXSUM ? 3 : 2;
+  constexpr int COMB = GR > 1 ? GR * NT * NCH * 8 : 4, SUMS = NM > 0 ? NWV * kWave * Vec16<T>::N : 4;
+  __shared__ __attribute__((aligned(16))) float comb[COMB > SUMS ? COMB : SUMS];
+  int n_blocks = gridDim.x;
+  if constexpr (NM > 0) {
+    n_blocks = tail.blocks;
+    if ((int)blockIdx.x >= n_blocks) {
+      const int r = blockIdx.x - n_blocks, half = threadIdx.x / (4 * kWave);   // (four waves a slice)
+      colsum_partial<T>(tail.cols, T_rows, r % tail.nx, r / tail.nx * 2 + half, tail.slices, 0, threadIdx.x / kWave % 4,
+                        comb + half * (4 * kWave * Vec16<T>::N));
+      return;
+    }
+  }
   const T* __restrict__ dout = at_mb(dout0, act16, blockIdx.y);
   const TX* __restrict__ x = at_mb(x0, act16, blockIdx.y);
   const float* __restrict__ mean = at_mb(mean0, act16, blockIdx.y);
   const float* __restrict__ rstd = at_mb(rstd0, act16, blockIdx.y);
   const T* __restrict__ dres = dres0 ? at_mb(dres0, dres16, blockIdx.y) : nullptr;
   T* __restrict__ dx = at_mb(dx0, dx16, blockIdx.y);
-  float* __restrict__ partial = partial0 + (size_t)blockIdx.y * gridDim.x * (DXSUM ? 3 : 2) * H;
+  float* __restrict__ partial = partial0 + (size_t)blockIdx.y * n_blocks * (DXSUM ? 3 : 2) * H;
   // At most one barrier per row: the two row sums are reduced together and the LDS slots alternate
   // between rows, so a row's writes cannot overtake the previous row's reads.  The loads of
   // the next row (when the row fits few registers) and of the residual gradient are issued
   // before the barrier, so that memory latency overlaps the reduction.
-  constexpr int NWV = kLnBwdThreads / kWave, GR = NWV / RW, NT = RW * kWave, NPART = DXSUM ? 3 : 2;
   constexpr bool PREFETCH = NCH <= 3;   // 168 registers at three chunks; a fourth would spill
   __shared__ float red[2][2][NWV];
-  __shared__ __attribute__((aligned(16))) float comb[GR > 1 ? GR * NT * NCH * 8 : 1];
   const int nvec = H / 8;
   const int wv = threadIdx.x / kWave, grp = wv / RW, t = threadIdx.x % NT;
   float dg[NCH][8], db[NCH][8], dc[DXSUM ? NCH : 1][8];
@@ -227,7 +292,7 @@ __global__ __launch_bounds__(kLnBwdThreads) void ln_bwd_kernel(
       }
     }
   };
-  const int step = gridDim.x * GR;
+  const int step = n_blocks * GR;
   if constexpr (PREFETCH) {
     if ((int)blockIdx.x * GR + grp < T_rows) load_row(blockIdx.x * GR + grp, dv, xh);
   }
@@ -377,12 +442,13 @@ template <int NS, int NB> __global__ __launch_bounds__(256) void reduce_partials
   float total = adds ? *out : 0.f;
   const int n = NB == 1 ? 1 : sg.batch;
   const size_t next = (size_t)sg.G * sg.stride;      // between micro-batches
+  constexpr int UNROLL = NB == 1 ? 4 : 2;
   f32x4 s[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (c4 < sg.N) {
     const float* const p = sg.partial + c4;
-#pragma unroll(NB == 1 ? 4 : 2)
+#pragma unroll UNROLL
     for (int g = ry; g < sg.G; g += 32) {
       f32x4 v[NB];
 #pragma unroll
@@ -438,51 +504,11 @@ hipError_t reduce_partials(const ReduceSeg* segs, int n, hipStream_t st) {
 }
 
 // ----------------------------------------------------------------- colsum ----
-// For every matrix: partial[blockIdx.y][n] = sum over this workgroup's rows of A[m][n].
-// Lane owns one 16-byte column vector; the 4 waves take interleaved rows and
-// are combined through LDS in fixed order.  One launch takes all the matrices of a layer (the same M
-// rows): below some MB each is a few microseconds of launch and latency whatever its size.  Three matrices
-// of 128 rows, 128 to 512 columns, in one launch instead of three: 3.7 us of a 74 us step.
-// NM: matrices there is room for; one alone has a form of its own, as above.
-// blockIdx.z: the micro-batch.
-template <int NM> struct ColsumArgs {
-  ColsumMat mat[NM];
-  int first[NM];   // first blockIdx.x of a matrix
-  uint32_t stride16;
-};
+// In a launch of its own; blockIdx.z: the micro-batch.
 template <typename T, int NM>
 __global__ __launch_bounds__(256) void colsum_partial_kernel(const ColsumArgs<NM> args, int M) {
-  constexpr int V = Vec16<T>::N;
-  __shared__ float sm[4][kWave * V];
-  int k = 0;
-#pragma unroll
-  for (int i = 1; i < NM; ++i)
-    if ((int)blockIdx.x >= args.first[i]) k = i;
-  const int N = args.mat[k].N;
-  const T* __restrict__ A = at_mb(static_cast<const T*>(args.mat[k].A), args.stride16, blockIdx.z);
-  float* __restrict__ partial = args.mat[k].partial + (size_t)blockIdx.z * gridDim.y * N;
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  const int col = (((int)blockIdx.x - args.first[k]) * kWave + lane) * V;
-  float acc[V];
-#pragma unroll
-  for (int e = 0; e < V; ++e) acc[e] = 0.f;
-  if (col < N) {
-    for (int m = blockIdx.y * 4 + w; m < M; m += gridDim.y * 4) {
-      const Vec16<T> v = load16(A + (size_t)m * N + col);
-#pragma unroll
-      for (int e = 0; e < V; ++e) acc[e] += v.get(e);
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < V; ++e) sm[w][lane * V + e] = acc[e];
-  __syncthreads();
-  if (w == 0 && col < N) {
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      const int i = lane * V + e;
-      partial[(size_t)blockIdx.y * N + col + e] = sm[0][i] + sm[1][i] + sm[2][i] + sm[3][i];
-    }
-  }
+  __shared__ float sm[4 * kWave * Vec16<T>::N];
+  colsum_partial<T>(args, M, blockIdx.x, blockIdx.y, gridDim.y, blockIdx.z, threadIdx.x / kWave, sm);
 }
 
 // --------------------------------------------------------------- launchers ----
@@ -523,15 +549,33 @@ hipError_t ln_fwd(int dtype, bool x_f32, int T_rows, int H, float eps, const voi
 #undef GPTS_LN
 }
 
-template <typename TX, typename T>
+static int colsum_splits(int M) { return M < 4 * 64 ? (M + 3) / 4 : 64; }
+// the matrices' places in a launch and the sums they leave; returns how many x there are
+template <int NM>
+static int colsum_layout(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, int batch, size_t stride, ColsumArgs<NM>* a) {
+  const int V = dtype == 0 ? 4 : 8;
+  int blocks = 0;
+  for (int i = 0; i < NM; ++i) {
+    a->first[i] = i < n ? blocks : 0x7fffffff;      // (never reached)
+    if (i >= n) continue;
+    a->mat[i] = mats[i];
+    blocks += (mats[i].N / V + kWave - 1) / kWave;
+    segs[i] = colsum_segment(mats[i].partial, colsum_splits(M), mats[i].N, mats[i].out);
+    segs[i].batch = batch;
+  }
+  a->stride16 = (uint32_t)(stride / 16);
+  return blocks;
+}
+
+template <typename TX, typename T, int NM>
 static hipError_t ln_bwd_t(int T_rows, int H, const void* dout, const void* x, const float* mean,
                            const float* rstd, const void* gamma, const void* dres, void* dx, bool dxsum,
-                           float* partial, const LnBwdWindow& win, hipStream_t st) {
-  const dim3 g(ln_bwd_blocks(T_rows, H), win.n), b(kLnBwdThreads);
+                           float* partial, const LnBwdWindow& win, const LnBwdTail<NM>& tail, int tail_blocks, hipStream_t st) {
+  const dim3 g(ln_bwd_blocks(T_rows, H) + tail_blocks, win.n), b(kLnBwdThreads);
 #define GPTS_LN_BWD_(N, RW, SUM)                                                                                  \
-  hipLaunchKernelGGL((ln_bwd_kernel<TX, T, N, RW, SUM>), g, b, 0, st, (const T*)dout, (const TX*)x, mean, rstd,   \
+  hipLaunchKernelGGL((ln_bwd_kernel<TX, T, N, RW, SUM, NM>), g, b, 0, st, (const T*)dout, (const TX*)x, mean, rstd,   \
                      (const T*)gamma, (const T*)dres, (T*)dx, partial, T_rows, H, (uint32_t)(win.act / 16),         \
-                     (uint32_t)(win.dres / 16), (uint32_t)(win.dx / 16))
+                     (uint32_t)(win.dres / 16), (uint32_t)(win.dx / 16), tail)
 #define GPTS_LN_BWD(N, RW)                  \
   do {                                      \
     if (dxsum) GPTS_LN_BWD_(N, RW, true);   \
@@ -540,6 +584,7 @@ static hipError_t ln_bwd_t(int T_rows, int H, const void* dout, const void* x, c
   if (H <= 512) GPTS_LN_BWD(1, 1);
   else if (H <= 1024) GPTS_LN_BWD(2, 1);
   else if (H <= 2048) GPTS_LN_BWD(1, 4);
+  else if constexpr (NM > 0) return hipErrorInvalidValue;
   else if (H <= 4096) GPTS_LN_BWD(1, 8);
   else if (H <= 8192) GPTS_LN_BWD(2, 8);
   else if (H <= 12288) GPTS_LN_BWD(3, 8);
@@ -549,17 +594,44 @@ static hipError_t ln_bwd_t(int T_rows, int H, const void* dout, const void* x, c
   return hipGetLastError();
 }
 
+// Whether the column sums go into the LayerNorm's launch.  Small ones are a launch that leaves most of the chip idle,
+// and run beside it; large ones fill it alone in smaller workgroups, of which a unit holds more than of those with
+// the LayerNorm's registers, and long rows leave a unit one workgroup.  Apart | together, us, bf16, rows x hidden and
+// the matrices' columns: 384x320 and 960 7.6 | 4.9; 2048x2048 and 6144 19.9 | 15.7, 8192 22.1 | 20.0; 4096x1024 and
+// 3072 20.4 | 18.7, 4096 20.9 | 20.6; 2048x5120 and 15360 41 | 50, 20480 49 | 61; 2048x12288 and 4608 74 | 72, 16896
+// 84 | 92.
+bool ln_bwd_takes_colsums(int dtype, int T_rows, int H, const ColsumMat* cols, int n) {
+  size_t bytes = 0;
+  for (int i = 0; i < n; ++i) bytes += (size_t)T_rows * cols[i].N * (dtype == 0 ? 4 : 2);
+  return H <= 2048 && bytes <= (size_t)32 << 20;
+}
+template <int NM>
+static hipError_t ln_bwd_any(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x, const float* mean,
+                             const float* rstd, const void* gamma, const void* dres, void* dx, bool dxsum, float* partial,
+                             const LnBwdWindow& w, const LnBwdTail<NM>& tail, int tail_blocks, hipStream_t st) {
+#define GPTS_LN_BWD(TX, T) ln_bwd_t<TX, T, NM>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, w, tail, tail_blocks, st)
+  if (dtype == 0) return GPTS_LN_BWD(float, float);
+  return x_f32 ? GPTS_LN_BWD(float, bf16) : GPTS_LN_BWD(bf16, bf16);
+#undef GPTS_LN_BWD
+}
 hipError_t ln_bwd_partials(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
                            const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
                            float* dgamma, float* dbeta, float* dxsum, float* partial, ReduceSeg* seg, hipStream_t st,
-                           const LnBwdWindow* win) {
+                           const LnBwdWindow* win, const ColsumMat* cols, int n_cols, ReduceSeg* col_segs) {
   if (H > 4 * 8 * kLnBwdThreads || (win && (win->n < 1 || win->n > kMaxWindow))) return hipErrorInvalidValue;
+  if (n_cols < 0 || n_cols > kMaxColsums || (win && n_cols)) return hipErrorInvalidValue;
   const int np = dxsum ? 3 : 2;
   const LnBwdWindow w = win ? *win : LnBwdWindow();
-  *seg = ReduceSeg{partial, (size_t)np * H, ln_bwd_blocks(T_rows, H), np * H, H, 2 * H, dgamma, dbeta, dxsum, w.n};
-  if (dtype == 0) return ln_bwd_t<float, float>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, w, st);
-  if (x_f32) return ln_bwd_t<float, bf16>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, w, st);
-  return ln_bwd_t<bf16, bf16>(T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, w, st);
+  const int blocks = ln_bwd_blocks(T_rows, H);
+  *seg = ReduceSeg{partial, (size_t)np * H, blocks, np * H, H, 2 * H, dgamma, dbeta, dxsum, w.n};
+  if (!n_cols)
+    return ln_bwd_any<0>(dtype, x_f32, T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, w, LnBwdTail<0>(), 0, st);
+  LnBwdTail<kMaxColsums> tail{};
+  tail.nx = colsum_layout(dtype, T_rows, cols, n_cols, col_segs, 1, 0, &tail.cols);
+  tail.blocks = blocks;
+  tail.slices = colsum_splits(T_rows);
+  return ln_bwd_any<kMaxColsums>(dtype, x_f32, T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, w, tail,
+                                 tail.nx * ((tail.slices + 1) / 2), st);
 }
 hipError_t ln_bwd(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
                   const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
@@ -620,7 +692,6 @@ size_t ln_bwd_scratch_bytes(int T_rows, int H) {
   return (size_t)ln_bwd_blocks(T_rows, H) * 3 * H * sizeof(float);
 }
 
-static int colsum_splits(int M) { return M < 4 * 64 ? (M + 3) / 4 : 64; }
 size_t colsum_scratch_bytes(int M, int N) { return (size_t)colsum_splits(M) * N * sizeof(float); }
 
 ReduceSeg colsum_segment(const float* partial, int G, int N, float* out) {
@@ -629,20 +700,9 @@ ReduceSeg colsum_segment(const float* partial, int G, int N, float* out) {
 template <int NM>
 static hipError_t launch_colsum(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, hipStream_t st, int batch,
                                 size_t stride) {
-  const int G = colsum_splits(M);
-  const int V = dtype == 0 ? 4 : 8;
   ColsumArgs<NM> a{};
-  int blocks = 0;
-  for (int i = 0; i < NM; ++i) {
-    a.first[i] = i < n ? blocks : 0x7fffffff;      // (never reached)
-    if (i >= n) continue;
-    a.mat[i] = mats[i];
-    blocks += (mats[i].N / V + kWave - 1) / kWave;
-    segs[i] = colsum_segment(mats[i].partial, G, mats[i].N, mats[i].out);
-    segs[i].batch = batch;
-  }
-  a.stride16 = (uint32_t)(stride / 16);
-  const dim3 g(blocks, G, batch);
+  const int blocks = colsum_layout(dtype, M, mats, n, segs, batch, stride, &a);
+  const dim3 g(blocks, colsum_splits(M), batch);
   if (dtype == 0) hipLaunchKernelGGL((colsum_partial_kernel<float, NM>), g, dim3(256), 0, st, a, M);
   else hipLaunchKernelGGL((colsum_partial_kernel<bf16, NM>), g, dim3(256), 0, st, a, M);
   return hipGetLastError();

@@ -36,8 +36,18 @@ constexpr int kMaxReduceSegs = 5;
 // adds up n <= kMaxReduceSegs segments in one launch, each in fixed order
 hipError_t reduce_partials(const ReduceSeg* segs, int n, hipStream_t st);
 size_t ln_bwd_scratch_bytes(int T_rows, int H);
+// a matrix whose columns are summed, see colsum_partials()
+struct ColsumMat {
+  const void* A;
+  int N;
+  float *out, *partial;
+};
+constexpr int kMaxColsums = 3;
 // dxsum (may be null): += column sums of dx as stored.  ln_bwd_partials leaves the three sums in
 // `partial` (ln_bwd_scratch_bytes(), for each micro-batch) and describes them in *seg; ln_bwd adds them up as well.
+// cols, n_cols, col_segs: what colsum_partials would do for n_cols <= kMaxColsums matrices of as many rows, in the same
+// launch (not with a window, and only where ln_bwd_takes_colsums()).  dx must not overlap them.
+bool ln_bwd_takes_colsums(int dtype, int T_rows, int H, const ColsumMat* cols, int n);
 struct LnBwdWindow {
   int n = 1;
   size_t act = 0, dres = 0, dx = 0;   // strides of dout, x, mean and rstd; of dres; of dx
@@ -45,7 +55,8 @@ struct LnBwdWindow {
 hipError_t ln_bwd_partials(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
                            const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
                            float* dgamma, float* dbeta, float* dxsum, float* partial, ReduceSeg* seg, hipStream_t st,
-                           const LnBwdWindow* win = nullptr);
+                           const LnBwdWindow* win = nullptr, const ColsumMat* cols = nullptr, int n_cols = 0,
+                           ReduceSeg* col_segs = nullptr);
 hipError_t ln_bwd(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
                   const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
                   float* dgamma, float* dbeta, float* dxsum, float* partial, hipStream_t st);
@@ -58,12 +69,6 @@ size_t colsum_scratch_bytes(int M, int N);
 // out += column sums of A [M,N].  colsum_partials takes n <= kMaxColsums matrices of M rows in one launch
 // and leaves their sums in each one's `partial` (colsum_scratch_bytes(), for each micro-batch) and segs[0 .. n-1],
 // as above.  A's of `batch` micro-batches lie `stride` bytes apart.
-struct ColsumMat {
-  const void* A;
-  int N;
-  float *out, *partial;
-};
-constexpr int kMaxColsums = 3;
 hipError_t colsum_partials(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, hipStream_t st, int batch = 1,
                            size_t stride = 0);
 // dst[m] = src[m] for n buffers of `bytes` (a multiple of 16) each

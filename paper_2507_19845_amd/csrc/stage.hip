@@ -618,20 +618,25 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
         for (int i = 0; i < 4; ++i)
           GPTS_OP(GPTS_TR_GEMM_WGRAD, 3 - i, 1, gf(lin[i].M, lin[i].N, D.T), gb(lin[i].M, lin[i].N, D.T, 8), wgrads(dt, &lin[i], 1, D.T, st), "wgrad");
     }
-    // the remaining bias gradients: column sums of dY (top layer), dU and dQKV in one launch, one by one
-    // under a tracer
+    // the remaining bias gradients: column sums of dY (top layer), dU and dQKV in the launch of the LayerNorm
+    // below where they are small, or one of their own, also where its dx lies on dY (a single layer whose caller lets
+    // dx replace dy); one by one under a tracer
     cols[n_cols++] = ColsumMat{dQKV, 3 * D.P, g(l, GPTS_B_QKV), part(ws.cs_qkv)};
-    if (!tr) GPTS_TRY(colsum_partials(dt, D.T, cols, n_cols, sums + n_sums, st), "bias gradients");
-    else
+    const char *const y0 = static_cast<const char*>(dY), *const x0 = static_cast<const char*>(dXout);
+    const bool with_ln = !tr && ln_bwd_takes_colsums(dt, D.T, D.H, cols, n_cols) &&
+                         (l < D.L - 1 || x0 + (size_t)D.T * D.H * e <= y0 || y0 + (size_t)D.T * D.H * e <= x0);
+    if (!tr && !with_ln) GPTS_TRY(colsum_partials(dt, D.T, cols, n_cols, sums + n_sums, st), "bias gradients");
+    if (tr)
       for (int i = 0; i < n_cols; ++i)
         GPTS_OP(GPTS_TR_BIAS_GRAD, cols[i].A == dQKV ? 0 : (cols[i].A == dU ? 2 : 3), 1, 0.0, (double)D.T * cols[i].N * e,
                 colsum_partials(dt, D.T, &cols[i], 1, sums + n_sums + i, st), "bias gradient");
+    ReduceSeg* const col_sums = sums + n_sums;
     n_sums += n_cols;
     // a = LN1(x), x also feeds the residual
     auto ln1_bwd = [&]() {
       const hipError_t err = ln_bwd_partials(dt, dt == GPTS_BF16, D.T, D.H, dA, xs, stat1, stat1 + D.T, w(l, GPTS_LN1_G), dX1, dXout,
                                              g(l, GPTS_LN1_G), g(l, GPTS_LN1_B), l > 0 ? g(l - 1, GPTS_B_FC2) : nullptr,
-                                             part(ws.ln1_part), &sums[n_sums++], st);
+                                             part(ws.ln1_part), &sums[n_sums++], st, nullptr, cols, with_ln ? n_cols : 0, col_sums);
       return err != hipSuccess || fused_b1 ? err : reduce_partials(sums, n_sums, st);
     };
     GPTS_OP(GPTS_TR_LN_BWD, 0, 1, 0.0, TH * (3 * e + kResBytes), ln1_bwd(), "ln1 bwd (+ fc2 bias grad of the layer below)");

@@ -533,6 +533,36 @@ def test_boundary_contracts_dx_may_alias_dy_and_backward_keeps_the_stash():
     assert torch.equal(alias, dx1) and torch.equal(g1, bufs.dparams)
 
 
+@pytest.mark.parametrize("dtype,hidden,ffn,seq,batch,layers", [("fp32", 128, 512, 3, 1, 1), ("fp32", 136, 200, 37, 7, 2),
+                                                               ("bf16", 320, 832, 192, 2, 2), ("bf16", 1024, 1024, 64, 5, 1),
+                                                               ("bf16", 1088, 1088, 320, 1, 1), ("bf16", 2048, 2048, 64, 1, 2)])
+def test_bias_gradients_beside_the_layernorm(dtype, hidden, ffn, seq, batch, layers):
+    """The column sums of a layer in the launch of its first LayerNorm's backward: each form of that kernel, one and
+    several matrices, numbers of slices even and odd.  The same bits as from a launch of their own, which they have
+    under a tracer and where a single layer's dx replaces dy."""
+    shape = W[1].with_(name="bias_beside_ln", dtype=dtype, n_layers=layers, hidden=hidden, n_heads=2, head_dim=64, ffn=ffn,
+                       seq=seq, batch=batch, bias_std=0.02, ln_jitter=0.1)
+    print(f"[case] bias gradients beside the LayerNorm {shape}", flush=True)
+    params, xs, dys = _inputs(shape)
+    bufs = B.StageBuffers(shape)
+    bufs.load_params(params)
+    x, dy = B.to_device(xs[0], dtype), B.to_device(dys[0], dtype)
+    y, dx = bufs.act(), bufs.act()
+    B.gpt_stage_fwd(bufs.params(), x, bufs.stash[0], y)
+    bufs.dparams.zero_()
+    B.gpt_stage_bwd(bufs.params(), bufs.stash[0], dy, dx, bufs.dparams)
+    together = bufs.dparams.clone()
+    for traced in (False, True):
+        bufs.trace = B.gpt_stage_trace_create(64) if traced else None
+        over = dy.clone()
+        bufs.dparams.zero_()
+        B.gpt_stage_bwd(bufs.params(), bufs.stash[0], over, over, bufs.dparams)
+        torch.cuda.synchronize()
+        if traced:
+            B.gpt_stage_trace_destroy(bufs.trace)
+        assert torch.equal(over, dx) and torch.equal(bufs.dparams, together), traced
+
+
 # ------------------------------------------------------- single operations ----
 @pytest.mark.parametrize("dtype,T,H,x_f32", [("fp32", 37, 128, False), ("fp32", 5, 4104, False),
                                              ("bf16", 130, 1024, False), ("bf16", 64, 12288, True),
