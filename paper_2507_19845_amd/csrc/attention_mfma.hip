@@ -670,14 +670,20 @@ __device__ __forceinline__ void dq_block(const BwdArgs& args, int qt, char* lds)
   }
   const float L2 = lse[((size_t)b * a + n) * S + qclamp] * 1.4426950408889634f;
   float Dl = 0.f;
-  if (out) {
+  if (out) {   // (summed in attn_delta_kernel's order: a row's gradients do not depend on the form)
+    float part[KSTEPS];
 #pragma unroll
     for (int kk = 0; kk < KSTEPS; ++kk) {
       const bf16x8 o = *reinterpret_cast<const bf16x8*>(out + ((size_t)b * S + qclamp) * P + (size_t)n * D + kk * 16 + h * 8);
+      part[kk] = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) Dl = fmaf(F16S ? (float)__builtin_bit_cast(f16x8, o)[e] : (float)o[e], (float)dof[kk][e], Dl);
+      for (int e = 0; e < 8; ++e) part[kk] = fmaf(F16S ? (float)__builtin_bit_cast(f16x8, o)[e] : (float)o[e], (float)dof[kk][e], part[kk]);
     }
-    Dl += __shfl_xor(Dl, 32, 64);
+#pragma unroll
+    for (int x = KSTEPS / 2; x > 0; x >>= 1)
+#pragma unroll
+      for (int kk = 0; kk < x; ++kk) part[kk] += part[kk + x];
+    Dl = part[0] + __shfl_xor(part[0], 32, 64);
     if (kb0 == 0 && h == 0 && qrow < S) delta[((size_t)b * a + n) * S + qrow] = Dl;
   } else {
     Dl = delta[((size_t)b * a + n) * S + qclamp];

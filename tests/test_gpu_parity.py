@@ -883,6 +883,22 @@ def test_op_attention_bf16_backward_forms(Bn, S, a, d):
     test_op_attention_bf16_splits(Bn, S, a, d)
 
 
+@pytest.mark.parametrize("S,few,many,d", [(130, 56, 60, 32), (130, 56, 60, 64), (130, 56, 60, 128), (449, 21, 22, 128)])
+def test_op_attention_bf16_forms_with_one_wave_agree_bit_for_bit(S, few, many, d):
+    """A sequence's results do not depend on how many others there are, while one wave takes 32 rows: backward in one
+    launch and in a launch for each side, 128 rows (the first three) and 256."""
+    print(f"[case] attention forms agree S={S} sequences={few},{many} d={d}", flush=True)
+    a = 10
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(S)
+    qkv = torch.empty(many, S, 3 * a * d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    dout = torch.empty(many, S, a * d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    want = _attention_op(B.GPTS_BF16, few, S, a, d, qkv[:few], dout[:few])
+    got = _attention_op(B.GPTS_BF16, many, S, a, d, qkv, dout)
+    for name, x, y in zip(("out", "lse", "dqkv"), got, want):
+        assert torch.equal(x[:few], y), name
+
+
 @pytest.mark.parametrize("S,a,d", [(70, 2, 128), (97, 1, 64), (65, 3, 32), (70, 500, 64)])
 def test_op_attention_bf16_rows_past_the_end_count_as_zeros(S, a, d):
     """The last tile's rows past the sequence's end hold a copy of its last row: with an infinite value there
