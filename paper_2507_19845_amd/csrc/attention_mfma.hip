@@ -941,6 +941,9 @@ bool attention_mfma_supported(int B, int S, int a, int d) {
          (size_t)B * S * a < (1ull << 27);
 }
 
+// (the sequences of a single call are left to the launch, which takes 65536 of them)
+static bool microbatches_fit(int B, int n) { return n == 1 || (n > 1 && (long)B * n <= 65535); }
+
 size_t attention_mfma_scratch_bytes(int B, int S, int a, int d, int phase) {
   // forward uses none; the least amount keeps a null scratch refused, as where it does
   return phase == 0 ? 256 : align256((size_t)B * a * S * sizeof(float));   // delta
@@ -949,7 +952,7 @@ size_t attention_mfma_scratch_bytes(int B, int S, int a, int d, int phase) {
 hipError_t attention_fwd_mfma(int B, int S, int a, int d, const void* qkv, void* out, float* lse,
                               void* scratch, hipStream_t st, bool f16, int n, size_t stride) {
   (void)scratch;
-  if (!attention_mfma_supported(B, S, a, d) || n < 1 || (long)B * n > 65535) return hipErrorInvalidValue;
+  if (!attention_mfma_supported(B, S, a, d) || !microbatches_fit(B, n)) return hipErrorInvalidValue;
   const bf16* q = (const bf16*)qkv;
 #define GPTS_FWD(D)                                                    \
   do {                                                                 \
@@ -966,7 +969,7 @@ hipError_t attention_fwd_mfma(int B, int S, int a, int d, const void* qkv, void*
 hipError_t attention_bwd_mfma(int B, int S, int a, int d, const void* qkv, const void* out,
                               const float* lse, const void* dout, void* dqkv, void* scratch,
                               hipStream_t st, const void* qkv_f16, int n, size_t act, size_t grad) {
-  if (!attention_mfma_supported(B, S, a, d) || n < 1 || (long)B * n > 65535) return hipErrorInvalidValue;
+  if (!attention_mfma_supported(B, S, a, d) || !microbatches_fit(B, n)) return hipErrorInvalidValue;
   const bf16* q = (const bf16*)qkv;
   const bf16* o = (const bf16*)out;
   const bool f16 = qkv_f16 != nullptr;

@@ -883,6 +883,23 @@ def test_op_attention_bf16_backward_forms(Bn, S, a, d):
     test_op_attention_bf16_splits(Bn, S, a, d)
 
 
+def test_op_attention_bf16_as_many_sequences_as_a_launch_takes():
+    """65536 sequences of one token: its probability is 1, so out is v, dV is dO, and dS, which is 0, is what two orders of a sum of
+    32 products of about 1 differ by, at most 32 eps times them."""
+    Bn, d = 65536, 32
+    print(f"[case] attention sequences={Bn}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9)
+    qkv = torch.empty(Bn, 1, 3 * d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    dout = torch.empty(Bn, 1, d, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    out, lse, dqkv = _attention_op(B.GPTS_BF16, Bn, 1, 1, d, qkv, dout)
+    q, k, v = qkv.float().split(d, dim=2)
+    assert torch.equal(out.float(), v) and torch.equal(dqkv[..., 2 * d:], dout)
+    assert ((q * k).sum(2).view(-1) / d ** 0.5 - lse.view(-1)).abs().max().item() < 1e-5
+    ds = 32 * 2.0 ** -23 * (dout.float() * v).abs().sum(2, keepdim=True) + 2.0 ** -126
+    assert (dqkv[..., :d].float().abs() <= ds * k.abs()).all() and (dqkv[..., d:2 * d].float().abs() <= ds * q.abs()).all()
+
+
 @pytest.mark.parametrize("S,few,many,d", [(130, 56, 60, 32), (130, 56, 60, 64), (130, 56, 60, 128), (449, 21, 22, 128)])
 def test_op_attention_bf16_forms_with_one_wave_agree_bit_for_bit(S, few, many, d):
     """A sequence's results do not depend on how many others there are, while one wave takes 32 rows: backward in one
