@@ -469,7 +469,7 @@ int gpt_dpp_run(const gpt_dpp_job* job, void* stream, gpt_dpp_report* report) {
   // a chunk's micro-batches of a window follow each other in the plan: as passes where there is a weight phase per
   // window (the stash slots are equally spaced then)
   std::vector<int> most(C, 1);
-  for (int j = 0; j < C && issuer.W > 1; ++j) most[j] = gpts::stage_window(&job->chunks[j], issuer.W);
+  for (int j = 0; j < C && issuer.W > 1; ++j) most[j] = gpts::stage_window(&job->chunks[j], issuer.W, stash_slot, issuer.grad_slot_bytes);
   for (int t = 0; t < n;) {
     const gpt_dpp_task& k = plan[t];
     int run = 1;

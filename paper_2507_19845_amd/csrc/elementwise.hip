@@ -516,7 +516,7 @@ template <typename TX, typename T, typename TO>
 static hipError_t ln_fwd_t(int T_rows, int H, float eps, const void* x, const void* gamma, const void* beta,
                            void* out, float* mean, float* rstd, float* xcopy, hipStream_t st, int n, size_t stride,
                            size_t x_stride) {
-  if (n < 1 || n > kMaxWindow) return hipErrorInvalidValue;
+  if (n < 1 || n > kMaxWindow || !window_stride_ok(stride) || !window_stride_ok(x_stride)) return hipErrorInvalidValue;
 #define GPTS_LN_FWD(N, RW)                                                                                        \
   hipLaunchKernelGGL((ln_fwd_kernel<TX, T, TO, N, RW>), dim3(RW == 1 ? (T_rows + 3) / 4 : T_rows, n), dim3(kLnThreads), 0, st, \
                      (const TX*)x, (const T*)gamma, (const T*)beta, (TO*)out, mean, rstd, xcopy, T_rows, H, eps,    \
@@ -622,6 +622,7 @@ hipError_t ln_bwd_partials(int dtype, bool x_f32, int T_rows, int H, const void*
   if (n_cols < 0 || n_cols > kMaxColsums || (win && n_cols)) return hipErrorInvalidValue;
   const int np = dxsum ? 3 : 2;
   const LnBwdWindow w = win ? *win : LnBwdWindow();
+  if (!window_stride_ok(w.act) || !window_stride_ok(w.dres) || !window_stride_ok(w.dx)) return hipErrorInvalidValue;
   const int blocks = ln_bwd_blocks(T_rows, H);
   *seg = ReduceSeg{partial, (size_t)np * H, blocks, np * H, H, 2 * H, dgamma, dbeta, dxsum, w.n};
   if (!n_cols)
@@ -709,7 +710,7 @@ static hipError_t launch_colsum(int dtype, int M, const ColsumMat* mats, int n, 
 }
 hipError_t colsum_partials(int dtype, int M, const ColsumMat* mats, int n, ReduceSeg* segs, hipStream_t st, int batch,
                            size_t stride) {
-  if (n < 1 || n > kMaxColsums || batch < 1) return hipErrorInvalidValue;
+  if (n < 1 || n > kMaxColsums || batch < 1 || !window_stride_ok(stride)) return hipErrorInvalidValue;
   return n == 1 ? launch_colsum<1>(dtype, M, mats, n, segs, st, batch, stride)
                 : launch_colsum<kMaxColsums>(dtype, M, mats, n, segs, st, batch, stride);
 }

@@ -246,7 +246,7 @@ hipError_t gemm_mfma(int form, int M, int N, int K, const void* A, const void* B
     return gemm_wgrad_group(&w, 1, K, ep.k_segments, ep.seg_stride_a, ep.seg_stride_b, st);
   }
   MfmaArgs a = make_args(M, N, K, A, B, C, ep);
-  if (ep.batch < 1 || ep.batch > kMaxWindow) return hipErrorInvalidValue;
+  if (ep.batch < 1 || ep.batch > kMaxWindow || !window_stride_ok(ep.stride_r)) return hipErrorInvalidValue;
   a.batch = ep.batch;
   a.stride_a = ep.stride_a;
   a.stride_b = ep.stride_c;

@@ -9,9 +9,10 @@ namespace gpts {
 // dtype: 0 = fp32 storage, 1 = bf16 storage (fp32 arithmetic in both).
 
 // Several micro-batches in one launch (a window of them): the operators below take the tensors of the first
-// one and how far those of the next one lie, in bytes (a multiple of 16, below 64 GB).  A micro-batch's share is computed
-// as by a launch of its own, bit for bit.
+// one and how far those of the next one lie, in bytes: a multiple of 16 below 64 GiB, which some kernels are told in 32 bits.
+// A micro-batch's share is computed as by a launch of its own, bit for bit.
 constexpr int kMaxWindow = 8;
+inline bool window_stride_ok(size_t s) { return s % 16 == 0 && s < ((size_t)1 << 36); }
 
 // x_f32: the normalised tensor x (the residual stream) is fp32 even when dtype is bf16.
 // out_f16 (bf16 stages only): out is written as fp16 instead of bf16.
@@ -176,8 +177,9 @@ hipError_t attention_bwd_mfma(int B, int S, int a, int d, const void* qkv, const
                               hipStream_t st, const void* qkv_f16 = nullptr, int n = 1, size_t act = 0, size_t grad = 0);
 
 // ---- a chunk's window of micro-batches as one pass per operator (stage.hip, for dpp.hip) ----
-// How many of a window of W micro-batches a pass takes; 1: none, they go one by one.
-int stage_window(const gpt_stage_params* p, int W);
+// How many of a window of W micro-batches, their stashes `act_stride` and `grad_stride` bytes apart, a pass takes; 1:
+// none, they go one by one.
+int stage_window(const gpt_stage_params* p, int W, size_t act_stride, size_t grad_stride);
 // The forward phase of n micro-batches, their stashes `act_stride` and `grad_stride` bytes apart.  y[m] may be x[m].  The
 // gradient stashes only lend room: buffers that are not equally spaced go through it.
 int stage_fwd_window(const gpt_stage_params* p, int n, const void* const* x, void* act_stash, size_t act_stride,

@@ -778,7 +778,7 @@ size_t spacing(const void* const* p, int n) {
   const size_t d = at(1) > at(0) ? at(1) - at(0) : 0;
   for (int m = 2; m < n; ++m)
     if (at(m) - at(m - 1) != d) return 0;
-  return d % 16 == 0 && d < ((size_t)1 << 36) ? d : 0;
+  return window_stride_ok(d) ? d : 0;
 }
 // Elements of a [tokens, hidden] tensor of a pass.  Small micro-batches leave most of the chip idle and are chains of
 // launches; beyond this many elements one alone fills it, and a pass's tensors leave the cache before the next
@@ -793,10 +793,11 @@ constexpr size_t kWindowElems = (size_t)1 << 24;
 namespace gpts {
 int set_error(int code, const char* msg) { return fail(code, msg); }
 
-int stage_window(const gpt_stage_params* p, int W) {
+int stage_window(const gpt_stage_params* p, int W, size_t act_stride, size_t grad_stride) {
   if (check_call(p) != GPTS_OK || !p->workspace || p->trace) return 1;
   const gpt_stage_cfg& c = p->cfg;
   if (c.dtype != GPTS_BF16 || c.recompute || c.fwd_fp16) return 1;
+  if (!window_stride_ok(act_stride) || !window_stride_ok(grad_stride)) return 1;
   const Dims D(c);
   const int widest = D.H > D.P ? D.H : D.P;
   bool ok = attention_mfma_supported(D.B, D.S, D.a, D.d) && D.F >= widest && fc1_sum_rows(D, c.dtype) > 0 &&

@@ -29,6 +29,26 @@ def test_library_exports_every_declared_symbol():
     assert sorted(B.EXPORTS) == names, "binding and header disagree on the entry points"
 
 
+def test_stashes_too_far_apart_for_a_pass_go_one_by_one():
+    """Passes over a window tell some kernels the distance between two stashes in units of 16 bytes and 32 bits: a chunk takes
+    none where its own stash slot, or the slot of a larger chunk beside it, reaches 64 GiB, or the gradients' does."""
+    window = getattr(ctypes.CDLL(B.LIB_PATH), "_ZN4gpts12stage_windowEPK16gpt_stage_paramsimm")     # gpts::stage_window
+    window.argtypes = [ctypes.POINTER(B.gpt_stage_params), ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
+
+    def passes(layers, act=None, grad=None):
+        shape = synth.StageShape(name="far", n_layers=layers, hidden=1024, n_heads=16, head_dim=64, ffn=4096, seq=4096, batch=2,
+                                 dtype="bf16", n_microbatches=2)
+        p = B.gpt_stage_params(cfg=B.make_cfg(shape), weights=1 << 20, workspace=1 << 21, prepared=None, trace=None)
+        act = act or B.gpt_dpp_stash_slot_bytes([p])
+        return window(ctypes.byref(p), 2, act, grad or B.gpt_dpp_grad_slot_bytes([p])), act
+
+    assert passes(1)[0] == 2
+    n, far = passes(230)
+    assert n == 1 and far > 1 << 36
+    assert passes(1, act=(1 << 36) - 256)[0] == 2 and passes(1, act=1 << 36)[0] == 1
+    assert passes(1, grad=(1 << 36) - 256)[0] == 2 and passes(1, grad=1 << 36)[0] == 1
+
+
 def test_binding_has_a_function_per_entry_point():
     for n in _declared():
         assert callable(getattr(B, n)), n
