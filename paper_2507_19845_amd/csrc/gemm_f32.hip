@@ -53,6 +53,8 @@ template <int R, int BK, bool KMAJOR, int NT> struct F32Operand {
   static constexpr int PITCH = KMAJOR ? R + 8 : BK;
   static constexpr int FLOATS = (KMAJOR ? BK : R) * PITCH;
   static_assert(R * BK / 4 % NT == 0, "whole pieces per thread");
+  // longest row (elements) for which the 32-bit byte offsets below hold: a slice is BK rows (K-major) or R of them
+  static constexpr int MAX_ROW = (1 << 30) / (KMAJOR ? BK : R);
 
   const float* base;       // the tile's first row, slice 0 (wave-uniform)
   uint32_t off[PER];       // bytes from there to this thread's pieces
@@ -165,6 +167,7 @@ template <int WM, int WN, int WK, bool A_KM, bool B_KM> struct F32Shape {
   static constexpr int STAGE = OpA::FLOATS + OpB::FLOATS, LDS_FLOATS = 2 * STAGE;
   static_assert(WK == 1 || LDS_FLOATS >= WK * BM * BN, "the partial tiles fit");
 };
+constexpr int kMaxRow = 1 << 24;   // rows of A and B are shorter (gemm_f32_supported())
 template <int WM, int WN, int WK, bool A_KM, bool B_KM, int EPI>
 __device__ __forceinline__ void f32_tile(const F32Args& a, int tile_m, int tile_n, float* const lds) {
   using Shape = F32Shape<WM, WN, WK, A_KM, B_KM>;
@@ -303,7 +306,11 @@ bool use_wide(int form, int M, int N, int K) {
 }
 
 template <bool A_KM, bool B_KM, int EPI> hipError_t launch_f32(const F32Args& a, hipStream_t st) {
-  if (use_wide(B_KM ? 1 : 0, a.M, a.N, a.K)) {
+  using Wide = F32Shape<2, 2, 1, A_KM, B_KM>;
+  using Narrow = F32Shape<1, 1, 8, A_KM, B_KM>;
+  static_assert(!A_KM && Wide::OpA::MAX_ROW >= kMaxRow && Wide::OpB::MAX_ROW >= kMaxRow && Narrow::OpA::MAX_ROW >= kMaxRow, "offsets fit");
+  // (the narrow tile's slices of a K-major B are 128 rows: 2^23 columns)
+  if ((B_KM ? a.N : a.K) > Narrow::OpB::MAX_ROW || use_wide(B_KM ? 1 : 0, a.M, a.N, a.K)) {
     hipLaunchKernelGGL((gemm_f32_kernel<2, 2, 1, A_KM, B_KM, EPI>), dim3((a.N + 63) / 64, (a.M + 63) / 64), dim3(256), 0, st, a);
   } else {
     hipLaunchKernelGGL((gemm_f32_kernel<1, 1, 8, A_KM, B_KM, EPI>), dim3((a.N + 31) / 32, (a.M + 31) / 32), dim3(512), 0, st, a);
@@ -313,6 +320,7 @@ template <bool A_KM, bool B_KM, int EPI> hipError_t launch_f32(const F32Args& a,
 
 template <int WM, int WN, int WK> hipError_t launch_f32_group(const F32Args* a, int n, hipStream_t st) {
   using Shape = F32Shape<WM, WN, WK, true, true>;
+  static_assert(Shape::OpA::MAX_ROW >= kMaxRow && Shape::OpB::MAX_ROW >= kMaxRow, "offsets fit");
   F32Group g;
   int blocks = 0;
   for (int i = 0; i < kMaxWgrads; ++i) {
@@ -329,10 +337,9 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 }  // namespace
 
 // 16-byte pieces: every contiguous dimension a multiple of 4, every pointer 16-byte aligned; the
-// grid's y dimension holds at most 65535 tile rows; offsets within a slice of a tile are 32 bits (64 rows).
+// grid's y dimension holds at most 65535 tile rows; offsets within a slice of a tile are 32 bits.
 bool gemm_f32_supported(int form, int M, int N, int K, const void* A, const void* B, const void* C,
                         const GemmEpilogue& ep) {
-  constexpr int kMaxRow = 1 << 24;
   if (N >= kMaxRow || (form == 2 ? M : K) >= kMaxRow) return false;
   return N % 4 == 0 && (form == 2 ? M % 4 == 0 : K % 4 == 0) && M <= 32 * 65535 && aligned16(A) && aligned16(B) &&
          aligned16(C) && aligned16(ep.bias) && aligned16(ep.residual) && aligned16(ep.gelu_out) && aligned16(ep.dgelu_u);

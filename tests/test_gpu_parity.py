@@ -701,6 +701,21 @@ def test_op_gemm_fp32_slices(M, N, K):
         assert (out[m] == 0.25).all(), form
 
 
+def test_op_gemm_fp32_rows_of_more_than_32_bits_a_slice():
+    """B's rows are so long that 128 of them, a slice of the narrow tile, are 4 GiB and 2 KiB: the product takes the
+    other tile, whose slices are shorter.  Bound as above, on columns from the start, the middle and the end."""
+    M, N, K = 4, (1 << 23) + 4, 132
+    print(f"[case] gemm fp32 long rows M={M} N={N} K={K}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    A, Bm = (torch.empty(r, c, device="cuda").normal_(generator=gen) for r, c in ((M, K), (K, N)))
+    out = torch.full((M, N), 7.0, device="cuda")
+    B.gpt_stage_op_gemm(B.GPTS_FP32, 1, M, N, K, A, Bm, out)
+    for c0 in (0, N // 2, N - 4096):
+        a, b = A.double(), Bm[:, c0:c0 + 4096].double()
+        assert ((out[:, c0:c0 + 4096].double() - a @ b).abs() <= (K + 1) * 2.0 ** -24 * (a.abs() @ b.abs())).all(), c0
+
+
 @pytest.mark.parametrize("M,N,K", [(72, 1000, 64), (264, 3000, 128), (520, 2056, 192), (1000, 4104, 128), (2040, 4104, 128),
                                    (2040, 5112, 192), (2040, 6136, 64), (4088, 4088, 320), (264, 1000, 1024),
                                    (1000, 2056, 320), (8200, 4104, 64), (1000, 4104, 832), (2040, 4104, 832),
