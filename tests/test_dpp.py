@@ -462,11 +462,16 @@ def test_dpp_weight_phase_per_chunk_and_window():
 @pytest.mark.gpu
 @pytest.mark.parametrize("hidden,heads,d,ffn,seq,batch,layers,M,W,spaced", [
     (128, 2, 64, 256, 64, 1, 1, 4, 4, True), (192, 4, 32, 320, 192, 3, 2, 7, 3, False), (320, 2, 128, 448, 320, 1, 1, 5, 5, False),
-    (1024, 16, 64, 4096, 512, 1, 1, 8, 8, False), (2048, 4, 128, 2112, 64, 2, 2, 3, 2, True)])
+    (1024, 16, 64, 4096, 512, 1, 1, 8, 8, False), (2048, 4, 128, 2112, 64, 2, 2, 3, 2, True),
+    (512, 8, 64, 512, 1216, 1, 1, 8, 8, True), (768, 12, 64, 3072, 576, 1, 1, 8, 8, False),
+    (1024, 16, 64, 4096, 960, 1, 1, 8, 8, True), (1280, 20, 64, 5120, 1088, 1, 1, 8, 8, False)])
 def test_dpp_passes_over_a_window_keep_every_bit(hidden, heads, d, ffn, seq, batch, layers, M, W, spaced):
     """A chunk's micro-batches of a window run as one pass per operator; under a tracer they run one by one.  The
     same bits in every output, with the callers' buffers equally spaced or not, dx in place of dy, gradients that
-    are not zero to begin with, boundary buffers just enough for the plan, and the last window shorter."""
+    are not zero to begin with, boundary buffers just enough for the plan, and the last window shorter.  The last
+    four have products of at most 256 tiles a micro-batch and more in a pass, most with ragged rows: 512 k in 128x128 and
+    128x64 with two stages; 768 k in 128x128, and GeLU' in 128x64 with four stages alone and two in a pass; 256x192, 256x256,
+    and GeLU' in 128x128 with four and two stages; 192x192, 256x160, 256x128, and 128x128 with two stages (3840 k) and four (5120)."""
     import torch
     C = 3
     shape = synth.StageShape(name="dpp_pass", n_layers=layers, hidden=hidden, n_heads=heads, head_dim=d, ffn=ffn, seq=seq,

@@ -55,12 +55,17 @@ SMALL = [
                seq=200 + 56, batch=1, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
     W[1].with_(name="bf16_fwd16_d64_erf", n_layers=2, hidden=384, n_heads=4, head_dim=64, ffn=896,
                seq=192, batch=2, gelu="erf", bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
-    # the same with so many heads times sequences that attention takes its forms of one wave per 32 rows
-    # in both directions (320 blocks of 256 rows, 512 at head dimension 32), the second block short
+    # the same with so many heads times sequences that attention takes its form of one wave per 32 rows in
+    # forward and one launch in backward (800 and 1280 blocks of 64 rows; one wave per 32 rows at head dimensions 32
+    # and 64), then, in the "many" shapes (over 1700 blocks), a launch for each side; the last block short
     W[1].with_(name="bf16_fwd16_d128_full_chip", n_layers=1, hidden=256, n_heads=10, head_dim=128, ffn=256,
                seq=260, batch=16, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
     W[1].with_(name="bf16_fwd16_d128_many", n_layers=1, hidden=128, n_heads=10, head_dim=128, ffn=128,
                seq=260, batch=48, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
+    W[1].with_(name="bf16_fwd16_d64_many", n_layers=1, hidden=128, n_heads=10, head_dim=64, ffn=128,
+               seq=260, batch=48, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
+    W[1].with_(name="bf16_fwd16_d32_many", n_layers=1, hidden=128, n_heads=12, head_dim=32, ffn=128,
+               seq=260, batch=32, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
     W[1].with_(name="bf16_fwd16_d64_full_chip", n_layers=1, hidden=256, n_heads=10, head_dim=64, ffn=256,
                seq=260, batch=16, bias_std=0.02, ln_jitter=0.1, fwd_fp16=True),
     W[1].with_(name="bf16_fwd16_d32_full_chip", n_layers=1, hidden=256, n_heads=16, head_dim=32, ffn=256,
@@ -675,10 +680,12 @@ def test_op_gemm_forms(dtype, M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(1, 8, 4), (33, 36, 28), (31, 64, 124), (65, 100, 128), (32, 32, 132), (100, 516, 252),
                                    (64, 28, 260), (129, 260, 512), (999, 512, 516), (999, 1280, 260), (1030, 1540, 36),
-                                   (1500, 2052, 100)])
+                                   (1500, 2052, 100), (1500, 2052, 164), (1500, 2052, 292), (1500, 2052, 163)])
 def test_op_gemm_fp32_slices(M, N, K):
     """Both fp32 tiles with ragged edges, and contractions that end at, just before and just behind a slice of 32, 64
-    or 128 k, of one slice and of more than the slices ahead.  What lies behind the operands is NaN.  A sum of K fp32
+    or 128 k, of one slice and of more than the slices ahead: the narrow tile up to 1280 columns, the 64 x 64 tile with two and
+    four slices of 32, then six and ten, the last one short (163: the weight gradient's; the other two forms take whole
+    fours of k, and other products the plain kernel).  What lies behind the operands is NaN.  A sum of K fp32
     products in any order is off by at most K eps of the sum of magnitudes."""
     print(f"[case] gemm fp32 slices M={M} N={N} K={K}", flush=True)
     gen = torch.Generator(device="cuda")
