@@ -16,9 +16,9 @@
 // Every product that contracts over the sequence index (O^T = V^T P^T, and in the
 // backward pass dV^T = dO^T P, dK^T = Q^T dS, dQ^T = K^T dS^T) needs its A operand
 // with the sequence index running fastest.  The transposing LDS read (ds_read_b64_tr_b16) delivers that from the
-// same row-major tile the other products read: per byte it occupies the LDS no longer than a plain 16-byte
-// read.  What these kernels wait for is the tiles' way from the L2 and the softmax arithmetic beside the matrix
-// pipe, so a tile is copied once and read both ways.  (Transposed copies of V, Q, K and dO, written to memory by
+// same row-major tile the other products read.  At D = 64 and 128 it has two-way bank conflicts (swz16()), and these
+// are 0.21 to 0.33 of the LDS's active time, but the LDS is active for at most 0.41 of a kernel's: a tile is copied once and
+// read both ways.  (Transposed copies of V, Q, K and dO, written to memory by
 // a kernel of their own and streamed beside the row-major tiles, were the form before: B x S x heads x D,
 // forward and backward, us: 1x8191x16x128 297 + 942, now 287 + 858; 1x2048x16x128 44.5 + 97, now 38 + 86;
 // 16x333x12x32 12.5 + 32.9, now 7.9 + 24.6.)
@@ -45,7 +45,10 @@ constexpr float kNoKey = -3.4028234663852886e38f;
 // A [64][D] tile lies in LDS as panels of up to 64 columns, [64][PW] each (constant offsets between them, and fewer
 // addresses to keep), with the 16-byte chunks of a panel row XOR-swizzled with the row.  A 16-byte LDS read serves 16
 // lanes at a time over the 64 banks, lanes {0-3, 12-15, 20-27} of a half wave, then its others; a half wave
-// reads one chunk of 32 rows, and the rows of each such group land in 16 different places.
+// reads one chunk of 32 rows, and the rows of each such group land in 16 different places.  A transposing read serves a
+// half wave at a time, four chunks of four rows r .. r+3: at D = 32, rows of 64 bytes, in different banks; in rows of 128
+// bytes r and r+2 start at the same bank, and the swizzle moves chunks 0-3 of both within the same 64 bytes, so half of the
+// banks are used twice.
 template <int D> constexpr int kPanel = D < 64 ? D : 64;            // columns of a panel
 template <int D> constexpr int kPanelBytes = BKV * kPanel<D> * 2;
 template <int D> __device__ __forceinline__ int swz16(int row) { return D == 32 ? (row >> 2) & 3 : (row >> 1) & 7; }
@@ -950,8 +953,7 @@ size_t attention_mfma_scratch_bytes(int B, int S, int a, int d, int phase) {
 }
 
 hipError_t attention_fwd_mfma(int B, int S, int a, int d, const void* qkv, void* out, float* lse,
-                              void* scratch, hipStream_t st, bool f16, int n, size_t stride) {
-  (void)scratch;
+                              hipStream_t st, bool f16, int n, size_t stride) {
   if (!attention_mfma_supported(B, S, a, d) || !microbatches_fit(B, n)) return hipErrorInvalidValue;
   const bf16* q = (const bf16*)qkv;
 #define GPTS_FWD(D)                                                    \

@@ -47,7 +47,10 @@ __global__ __launch_bounds__(256) void prepare_image_kernel(const bf16* __restri
 // after the other, each ceil(K / 64) * slice + fixed microseconds.  The two numbers of a tile are
 // fitted to measured products that fill whole rounds (random bf16 operands from HBM, M, N in
 // 384 ... 20480, K in 320 ... 16384; the estimate is within 10 % of those); `fixed` is the first slice's
-// arrival and the epilogue, which reads and writes fp32 in the weight gradients.
+// arrival and the epilogue, which reads and writes fp32 in the weight gradients.  The line knows no
+// costlier epilogue beyond 768 k (below), and takes 128x128 and 128x64 for lone workgroups of four stages also where
+// they run with two (two_stages()).  Estimated | measured within steps, us: 4096x4096, K = 1024 in 256x256 30 | GeLU 46.9,
+// GeLU' 51.6; 4096x3072, K = 1024 in 256x192 24 | 33.4; 2048x1536, K = 12288 in 128x128 82 | 121.
 // What the choice is about: 2048x5120 is 160 tiles of 256x256 and 256 of 256x160 (K = 5120: 104 against
 // 81 us), 2048x6144 is 192 and 256 of 256x192 (K = 12288: 279 against 266, weight gradient 253
 // against 235 us), 4096x1024 is 64 and 256 of 128x128 (K = 4096: 76 against 30 us), 512x4096 is 256 of
@@ -73,7 +76,7 @@ constexpr TileInfo kTiles[N_TILES] = {
 // some 6000 k an XCD reads a patch of 4 x 16 of them for 64; beyond they drift apart and a slice takes an eighth longer.
 // 256x256 | 256x128, us: 16384x4096, K = 2048 271 | 260, 4096 456 | 449, 8192 832 | 846, 32768 3137 | 3380; 6144x4096,
 // K = 4096 200 | 165; 4096x4096, K = 512 33.5 | 38.8; layers of 4800 and 3456 tiles of 256x256, K = 2048 1285 | 1239
-// and 931 | 880.
+// and 931 | 880 (these two set `fixed_tn` of 256x256, too).
 //
 // Short contractions (short_contraction(), forward products and data gradients) are bound by their
 // epilogues as much: they have numbers of their own, fitted to products of 64 ... 768 k (the estimate is

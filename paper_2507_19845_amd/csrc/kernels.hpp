@@ -160,14 +160,14 @@ hipError_t attention_fwd_f32(int B, int S, int a, int d, const void* qkv, void* 
 hipError_t attention_bwd_f32(int B, int S, int a, int d, const void* qkv, const void* out, const float* lse,
                              const void* dout, void* dqkv, hipStream_t st);
 
-// bf16 MFMA attention (head_dim 32, 64 or 128).  scratch: device memory of
-// attention_mfma_scratch_bytes(B, S, a, d, phase) bytes (phase 0 forward: not used; phase 1 backward: delta).
+// bf16 MFMA attention (head_dim 32, 64 or 128).  scratch (backward: delta): device memory of
+// attention_mfma_scratch_bytes(B, S, a, d, 1) bytes; phase 0: what the forward entry points ask for, see there.
 bool attention_mfma_supported(int B, int S, int a, int d);   // head_dim 32/64/128 and index ranges
 size_t attention_mfma_scratch_bytes(int B, int S, int a, int d, int phase);
 // f16: qkv and out are fp16 (forward activations kept in fp16); lse is fp32 either way.
 // n micro-batches of B sequences: qkv, out and lse lie `stride` bytes apart.
 hipError_t attention_fwd_mfma(int B, int S, int a, int d, const void* qkv, void* out, float* lse,
-                              void* scratch, hipStream_t st, bool f16 = false, int n = 1, size_t stride = 0);
+                              hipStream_t st, bool f16 = false, int n = 1, size_t stride = 0);
 // qkv_f16 (optional): the fp16 qkv of an fp16 forward pass; the logits are then recomputed from
 // its Q and K, `out` is that pass's fp16 output (it only enters delta = rowsum(dO * O)), and
 // qkv is the bf16 copy that every other product reads.

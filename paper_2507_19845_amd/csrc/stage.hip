@@ -106,11 +106,11 @@ StashLayer stash_layer(const gpt_stage_cfg& c) {
 
 // ---- workspace ---------------------------------------------------------------------
 // [forward region | backward region]: a forward and a backward call on different streams
-// may share one workspace, their regions are disjoint.  The forward region is the
-// attention kernels' scratch; offsets in BwdWs are relative to the whole workspace.
+// may share one workspace, their regions are disjoint.  Offsets in BwdWs are relative to the
+// whole workspace.
 size_t attention_scratch_bytes(int dtype, int B, int S, int a, int d, int phase);
 struct FwdWs {
-  size_t attn, A, G, blk, end;   // A (shared by both LayerNorm outputs) and G only where they are
+  size_t A, G, blk, end;         // A (shared by both LayerNorm outputs) and G only where they are
                                  // not kept; blk: the layer block with recompute == 2
 };
 FwdWs fwd_ws(const gpt_stage_cfg& c) {
@@ -119,7 +119,7 @@ FwdWs fwd_ws(const gpt_stage_cfg& c) {
   FwdWs w;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o = align_up(o + bytes, 256); return r; };
-  w.attn = take(attention_scratch_bytes(c.dtype, D.B, D.S, D.a, D.d, 0));
+  take(attention_scratch_bytes(c.dtype, D.B, D.S, D.a, D.d, 0));   // (not used: a bf16 forward call is refused without a workspace)
   const bool transient = c.recompute == 1 || c.fwd_fp16;
   w.A = transient ? take((size_t)D.T * D.H * e) : kAbsent;
   w.G = transient ? take((size_t)D.T * D.F * e) : kAbsent;
@@ -303,7 +303,7 @@ hipError_t wgrads(int dtype, const WgradItem* items, int n, int K, hipStream_t s
 
 // Attention: on the matrix cores for bf16 and for aligned fp32 buffers, the plain FMA kernels
 // otherwise.
-// scratch: attention_scratch_bytes(.., phase) bytes of device memory.
+// scratch (backward): attention_scratch_bytes(.., 1) bytes of device memory.
 bool attention_uses_mfma(int dtype, int B, int S, int a, int d) {
   return dtype == GPTS_BF16 && attention_mfma_supported(B, S, a, d);
 }
@@ -313,8 +313,8 @@ size_t attention_scratch_bytes(int dtype, int B, int S, int a, int d, int phase)
 }
 // f16 / qkv_f16: the fp16 forward-activation variants (matrix-core path only)
 hipError_t attention_fwd(int dtype, int B, int S, int a, int d, const void* qkv, void* out,
-                         float* lse, void* scratch, hipStream_t st, bool f16 = false, int n = 1, size_t stride = 0) {
-  if (attention_uses_mfma(dtype, B, S, a, d)) return attention_fwd_mfma(B, S, a, d, qkv, out, lse, scratch, st, f16, n, stride);
+                         float* lse, hipStream_t st, bool f16 = false, int n = 1, size_t stride = 0) {
+  if (attention_uses_mfma(dtype, B, S, a, d)) return attention_fwd_mfma(B, S, a, d, qkv, out, lse, st, f16, n, stride);
   if (f16 || n != 1) return hipErrorInvalidValue;
   if (dtype == GPTS_FP32 && attention_f32_supported(qkv, out, nullptr, nullptr))
     return attention_fwd_f32(B, S, a, d, qkv, out, lse, st);
@@ -409,7 +409,7 @@ int fwd_layer(const gpt_stage_params* p, int l, const void* X, char* blk, void* 
   ep.b_image = img(l, 0);
   GPTS_OP(top_gemm, 0, phase, gf(D.T, 3 * D.P, D.H), gb(D.T, 3 * D.P, D.H, e), fwd_gemm(3 * D.P, D.H, A, GPTS_W_QKV, s + sl.QKV, ep), "qkv gemm");
   GPTS_OP(top_attn, 0, phase, attn_fl, (double)D.T * 4 * D.P * e, attention_fwd(dt, D.B, D.S, D.a, D.d, s + sl.QKV, s + sl.C,
-                                reinterpret_cast<float*>(s + sl.LSE), fwk + fw.attn, st, h16, n_mb, stride), "attention fwd");
+                                reinterpret_cast<float*>(s + sl.LSE), st, h16, n_mb, stride), "attention fwd");
   ep = GemmEpilogue();
   ep.bias = w(l, GPTS_B_O);
   ep.residual = X;
@@ -1202,7 +1202,7 @@ int gpt_stage_op_attention_fwd(int dtype, int B, int S, int n_heads, int head_di
     return fail(GPTS_ESHAPE, "attention_fwd: head_dim must be 32, 64 or 128");
   if (!scratch && attention_scratch_bytes(dtype, B, S, n_heads, head_dim, 0) > 0)
     return fail(GPTS_EINVAL, "attention_fwd: scratch is NULL");
-  GPTS_TRY(attention_fwd(dtype, B, S, n_heads, head_dim, qkv, out, lse, scratch, static_cast<hipStream_t>(stream)), "attention_fwd");
+  GPTS_TRY(attention_fwd(dtype, B, S, n_heads, head_dim, qkv, out, lse, static_cast<hipStream_t>(stream)), "attention_fwd");
   return GPTS_OK;
 }
 int gpt_stage_op_attention_bwd(int dtype, int B, int S, int n_heads, int head_dim, const void* qkv,

@@ -865,11 +865,9 @@ def _attention_op(dt, Bn, S, a, d, qkv, dout):
                                       (1, 300, 260, 32), (1, 200, 200, 64), (1, 161, 150, 64), (1, 193, 120, 128), (1, 130, 230, 128),
                                       (1, 520, 60, 128), (1, 520, 84, 128), (1, 520, 83, 128)])
 def test_op_attention_bf16_splits(Bn, S, a, d):
-    """The arrangements of the bf16 attention kernels at the edges of their blocks (32, 64, 128, 256 rows): the
-    first six take 64 rows and two waves per 32 throughout, then backward with 128 rows, and the next two
-    one wave per 32 rows in both directions; then, forward and backward, one wave and one wave (head
-    dimension 32), and the limits of short sequences: one wave and one wave, two and two, one and two, one
-    and one, two and two; then two and two for a multiple of four heads, one and two for one head less.
+    """The arrangements of the bf16 attention kernels at the edges of their blocks (32, 64, 128, 256 rows): waves
+    per 32 rows in forward and backward, in order: two and one, twice one and one, five times two and two, two and
+    one, four times one and one, twice two and one, one and one, two and one, twice one and one.
     Against fp64 on the same inputs; probabilities, dS and the outputs are rounded to bf16
     (2^-9 each), so 2-norm errors stay within 2^-7 and single values within 2^-4 of the largest."""
     print(f"[case] attention splits B={Bn} S={S} a={a} d={d}", flush=True)
@@ -957,10 +955,10 @@ def test_op_attention_bf16_rows_past_the_end_count_as_zeros(S, a, d):
     assert (dv[-1] == float("inf")).all()
 
 
-@pytest.mark.parametrize("Bn,S,a,d", [(1, 40, 2, 64), (1, 97, 2, 128), (2, 130, 1, 32), (1, 70, 300, 32)])
+@pytest.mark.parametrize("Bn,S,a,d", [(1, 40, 2, 64), (1, 97, 2, 128), (2, 130, 1, 32), (1, 70, 300, 32), (1, 97, 3, 64)])
 def test_op_attention_bf16_minus_infinite_logits(Bn, S, a, d):
-    """Keys 32 to 63, the second wave's share of the first tile where two waves take a row block (the first
-    three), have logits of -inf for every query: they count as masked keys do, in the output and in lse.
+    """Keys 32 to 63, the second wave's share of the first tile where two waves take a row block (all but the
+    first), have logits of -inf for every query: they count as masked keys do, in the output and in lse.
     Tolerances as in test_op_attention_bf16_splits."""
     print(f"[case] attention minus infinity B={Bn} S={S} a={a} d={d}", flush=True)
     gen = torch.Generator(device="cuda")
