@@ -212,6 +212,12 @@ bool gemm_fwd_f16_supported(int M, int N, int K) {
 }
 
 namespace {
+// MfmaArgs::once: from the 32 MB of the L2s on.  A smaller matrix may still be there from the call before, or be read
+// from there by the next.  Cached | non-temporal, us a step.  Accumulated: 4096 tokens 1024 wide 2005 | 1986, 2048 tokens
+// 5120 wide 7579 | 7457, 12288 wide in 12 heads 6342 | 6259, backward of 2048 tokens 2048 wide 1245 | 1215; 512 tokens 832
+// wide (24 MB a layer) 123.8 | 125.5, 192 tokens 320 wide 298.7 | 299.9.  u on top: 4096 tokens 1024 wide 1997 | 1973, forward
+// of 3968 tokens 2048 wide 888 | 882, 8 x 4096 tokens 4096 wide 141.9 | 141.2 ms.
+constexpr size_t kOnceBytes = (size_t)32 << 20;
 MfmaArgs make_args(int M, int N, int K, const void* A, const void* B, void* C, const GemmEpilogue& ep) {
   MfmaArgs a;
   a.A = (const bf16*)A; a.B = (const bf16*)B; a.C = C;
@@ -219,6 +225,7 @@ MfmaArgs make_args(int M, int N, int K, const void* A, const void* B, void* C, c
   a.bias = (const bf16*)ep.bias; a.residual = ep.residual;
   a.gelu_out = (bf16*)ep.gelu_out; a.dgelu_u = (const bf16*)ep.dgelu_u;
   a.colsum = ep.dgelu_u ? ep.colsum_partial : nullptr;
+  a.once = (ep.gelu_out || ep.dgelu_u) && (size_t)2 * ep.batch * M * N >= kOnceBytes;
   return a;
 }
 int fwd_epilogue(const GemmEpilogue& ep) {
@@ -270,6 +277,7 @@ hipError_t gemm_wgrad_group(const WgradItem* items, int n, int K, int segments, 
   if (n < 1 || n > kMaxWgrads) return hipErrorInvalidValue;
   MfmaArgs a[kMaxWgrads];
   Product p[kMaxWgrads];
+  size_t matrices = 0;   // bytes
   for (int i = 0; i < n; ++i) {
     const WgradItem& w = items[i];
     if (segments > 1 ? !gemm_wgrad_segments_supported(w.M, w.N, K, segments) : !gemm_mfma_supported(2, w.M, w.N, K))
@@ -279,7 +287,9 @@ hipError_t gemm_wgrad_group(const WgradItem* items, int n, int K, int segments, 
     a[i].stride_a = seg_stride_dout;
     a[i].stride_b = seg_stride_in;
     p[i] = Product{w.M, w.N};
+    matrices += sizeof(float) * w.M * w.N;
   }
+  for (int i = 0; i < n; ++i) a[i].once = matrices >= kOnceBytes;
   const long k_all = (long)K * segments;
   const Tile t = choose_tile(2, p, n, k_all, COST_PLAIN);
   if (n == 1 || worth_one_launch(t, p, n, k_all)) return launch_gemm_wgrad(t, a, n, st);

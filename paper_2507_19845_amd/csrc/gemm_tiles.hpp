@@ -50,7 +50,8 @@ namespace gpts {
 // epilogue kinds
 // (RES32: the residual is fp32; OUT32: C is written as fp32 -- the residual stream of a bf16 stage)
 enum { EPI_BIAS_RES = 0, EPI_GELU_TANH, EPI_GELU_ERF, EPI_PLAIN, EPI_DGELU_TANH, EPI_DGELU_ERF, EPI_ACCUM,
-       EPI_BIAS_RES32_OUT32, EPI_BIAS_RES32_OUT16, EPI_BIAS /* bias only: no residual operand */ };
+       EPI_BIAS_RES32_OUT32, EPI_BIAS_RES32_OUT16, EPI_BIAS /* bias only: no residual operand */,
+       EPI_ONCE = 16 /* added to a kind: see MfmaArgs::once */ };
 
 struct MfmaArgs {
   const bf16* A;
@@ -62,6 +63,9 @@ struct MfmaArgs {
   bf16* gelu_out;
   const bf16* dgelu_u;
   float* colsum;   // GeLU' epilogue only, may be null: column sums of C per group of tile rows
+  // The accumulated matrix, or the pre-activation u that a GeLU epilogue writes and a GeLU' epilogue reads for the last
+  // time, is met again only after more has passed than the caches hold: non-temporal, it pushes no operand out of them.
+  int once = 0;
   int b_img = 0;   // B is the weight's tiled image (tiles of 256 rows, slices of kImageK): kernels with BK = kImageK only
   // The tokens of several micro-batches, each in its own buffer.
   // K-major products (weight gradients): the contraction runs over `batch` pieces of
@@ -211,6 +215,16 @@ template <int WN> struct Staged {
   }
 };
 
+// Accesses to what nobody reads again soon (MfmaArgs::once): non-temporal.
+template <bool NT, typename V> __device__ __forceinline__ V load_once(const V* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NT, typename V> __device__ __forceinline__ void store_once(V* p, const V& v) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
 // The accumulators hold a lane-per-row layout, which would store 16-byte pieces scattered over 16
 // rows.  Each wave instead stages its rows through LDS in passes of RP rows (write_pass(pass)) and
 // reads them back row-major: CW lanes cover one row of the WN columns, so every global load and
@@ -220,9 +234,11 @@ template <int WN> struct Staged {
 //   cs      GeLU' epilogue: on return, lanes < WN/4 hold the column sums of their four columns
 // OUT16: the 16-bit outputs (C of the bias-only epilogue; C and the GeLU output of the GeLU
 // epilogues) are written as fp16 instead of bf16 (forward activations kept in fp16).
-template <int EPI, bool OUT16, int WM, int WN, int RP, class StageWriter>
+template <int KIND, bool OUT16, int WM, int WN, int RP, class StageWriter>
 __device__ __forceinline__ void gemm_epilogue(StageWriter&& write_pass, const MfmaArgs& a, const float* stage,
                                               int m_first, int n_first, float (&cs)[4], int lane) {
+  constexpr int EPI = KIND & ~EPI_ONCE;
+  constexpr bool ONCE = (KIND & EPI_ONCE) != 0;
   static_assert(!OUT16 || EPI == EPI_BIAS || EPI == EPI_GELU_TANH || EPI == EPI_GELU_ERF ||
                     EPI == EPI_BIAS_RES32_OUT32 || EPI == EPI_BIAS_RES32_OUT16,
                 "fp16 outputs exist for the forward epilogues only");
@@ -267,9 +283,9 @@ __device__ __forceinline__ void gemm_epilogue(StageWriter&& write_pass, const Mf
       const int m = m_first + pass * RP + row;
       t.ok[u] = m < a.M && n_ok && (EXACT || row < RP);
       t.o[u] = t.ok[u] ? (size_t)m * a.N + n : 0;  // element 0 is always a valid address
-      if constexpr (EPI == EPI_ACCUM) t.in32[u] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(a.C) + t.o[u]);
+      if constexpr (EPI == EPI_ACCUM) t.in32[u] = load_once<ONCE>(reinterpret_cast<const f32x4*>(static_cast<const float*>(a.C) + t.o[u]));
       if constexpr (RES32) t.in32[u] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(a.residual) + t.o[u]);
-      if constexpr (DGELU) t.in16[u] = *reinterpret_cast<const bf16x4*>(a.dgelu_u + t.o[u]);
+      if constexpr (DGELU) t.in16[u] = load_once<ONCE>(reinterpret_cast<const bf16x4*>(a.dgelu_u + t.o[u]));
       if constexpr (EPI == EPI_BIAS_RES) t.in16[u] = *reinterpret_cast<const bf16x4*>(static_cast<const bf16*>(a.residual) + t.o[u]);
     }
   };
@@ -292,7 +308,7 @@ __device__ __forceinline__ void gemm_epilogue(StageWriter&& write_pass, const Mf
         f32x4 c;
 #pragma unroll
         for (int e = 0; e < 4; ++e) c[e] = t.in32[u][e] + v[e];
-        *reinterpret_cast<f32x4*>(static_cast<float*>(a.C) + t.o[u]) = c;
+        store_once<ONCE>(reinterpret_cast<f32x4*>(static_cast<float*>(a.C) + t.o[u]), c);
       } else if constexpr (GELU) {
         using T16 = std::conditional_t<OUT16, f16, bf16>;
         typedef T16 t16x4 __attribute__((ext_vector_type(4)));
@@ -304,7 +320,7 @@ __device__ __forceinline__ void gemm_epilogue(StageWriter&& write_pass, const Mf
           // the stashed u gets the same bits
           gq[e] = from_f32<T16>(gelu_f<EPI == EPI_GELU_TANH ? 0 : 1>((float)uq[e]));
         }
-        *reinterpret_cast<t16x4*>(static_cast<T16*>(a.C) + t.o[u]) = uq;
+        store_once<ONCE>(reinterpret_cast<t16x4*>(static_cast<T16*>(a.C) + t.o[u]), uq);
         *reinterpret_cast<t16x4*>(reinterpret_cast<T16*>(a.gelu_out) + t.o[u]) = gq;
       } else {
         if constexpr (DGELU) {
@@ -591,7 +607,7 @@ __device__ __forceinline__ void gemm_tile(MfmaArgs a, int id, char* const lds) {
   float* const stg = reinterpret_cast<float*>(lds) + wave * (RP * PITCH);
   gemm_epilogue<EPI, F16, WM, WN, RP>([&](auto pass_c) { stage_rows(pass_c, std::integral_constant<int, RP>{}, stg); }, a,
                                       stg, m0 + wm * WM, n0 + wn * WN, cs, lane);
-  if constexpr (EPI == EPI_DGELU_TANH || EPI == EPI_DGELU_ERF) {
+  if constexpr ((EPI & ~EPI_ONCE) == EPI_DGELU_TANH || (EPI & ~EPI_ONCE) == EPI_DGELU_ERF) {
     const int n = n0 + wn * WN + lane * 4;
     if (a.colsum && lane < WN / 4 && n < a.N) {
       f32x4 out;
@@ -630,8 +646,15 @@ __global__ __launch_bounds__(256, (gemm_waves<MB, NB, BK, NS>())) void gemm_mi16
   gemm_tile<EPI, FORM, F16, MB, NB, BK, NS>(g.p[k], blockIdx.x - g.first[k], lds);
 }
 
+// The kinds and tiles that have a form for MfmaArgs::once (tiles below 128x128 are for matrices that fit the caches).
+template <int EPI, int MB, int NB> constexpr bool has_once() {
+  return MB * NB >= 16 && (EPI == EPI_ACCUM || EPI == EPI_GELU_TANH || EPI == EPI_GELU_ERF || EPI == EPI_DGELU_TANH || EPI == EPI_DGELU_ERF);
+}
 template <int EPI, int FORM, bool F16, int MB, int NB, int BK, int NS>
 hipError_t launch_mi16(const MfmaArgs& a, hipStream_t st) {
+  if constexpr (has_once<EPI, MB, NB>()) {
+    if (a.once) return launch_mi16<EPI | EPI_ONCE, FORM, F16, MB, NB, BK, NS>(a, st);
+  }
   if (a.b_img && BK != kImageK) return hipErrorInvalidValue;
   const int tiles = (FORM == FORM_TN ? 1 : a.batch) * ((a.M + 32 * MB - 1) / (32 * MB)) * ((a.N + 32 * NB - 1) / (32 * NB));
   hipLaunchKernelGGL((gemm_mi16_kernel<EPI, FORM, F16, MB, NB, BK, NS>), dim3(tiles), dim3(256), 0, st, a);
@@ -647,6 +670,12 @@ template <int MB, int NB, int BK, int NS> hipError_t launch_group(const MfmaArgs
     g.p[i] = a[i < n ? i : 0];
     g.first[i] = i < n ? blocks : 0x7fffffff;      // (never reached)
     if (i < n) blocks += ((a[i].M + 32 * MB - 1) / (32 * MB)) * ((a[i].N + 32 * NB - 1) / (32 * NB));
+  }
+  if constexpr (has_once<EPI_ACCUM, MB, NB>()) {
+    if (a[0].once) {
+      hipLaunchKernelGGL((gemm_mi16_group_kernel<EPI_ACCUM | EPI_ONCE, FORM_TN, false, MB, NB, BK, NS>), dim3(blocks), dim3(256), 0, st, g);
+      return hipGetLastError();
+    }
   }
   hipLaunchKernelGGL((gemm_mi16_group_kernel<EPI_ACCUM, FORM_TN, false, MB, NB, BK, NS>), dim3(blocks), dim3(256), 0, st, g);
   return hipGetLastError();

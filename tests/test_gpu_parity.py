@@ -759,6 +759,40 @@ def test_op_gemm_bf16_tiles(M, N, K):
     assert ((out.double() - want).abs() <= want.abs() * 2.0 ** -8 + 2.0 ** -12 * K ** 0.5).all()
 
 
+@pytest.mark.parametrize("gelu", ["tanh", "erf"])
+@pytest.mark.parametrize("M,N,K", [(2040, 4104, 64), (2056, 4088, 128), (4088, 4096, 64), (4104, 4096, 64), (4088, 4112, 320),
+                                   (8200, 2056, 832), (2568, 8200, 1088)])
+def test_op_gemm_bf16_matrices_around_the_size_of_the_caches(M, N, K, gelu):
+    """Accumulated fp32 matrices and pre-activations on both sides of 32 MB, from which on their accesses are
+    non-temporal.  u and the gradient through GeLU' are rounded once to bf16 (2^-9 of the value), g = gelu(u as stored) likewise."""
+    print(f"[case] once M={M} N={N} K={K} {gelu}", flush=True)
+    kind = B.GPTS_GELU_TANH if gelu == "tanh" else B.GPTS_GELU_ERF
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    rnd = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    A, Bt, U, bias = rnd(M, K), rnd(N, K), rnd(M, N), rnd(N)
+    u, g = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda"), torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    B.gpt_stage_op_gemm(B.GPTS_BF16, 0, M, N, K, A, Bt, u, bias=bias, C2=g, gelu_kind=kind)
+    ref = A.double() @ Bt.double().T
+    slack = 2.0 ** -12 * K ** 0.5
+    assert ((u.double() - ref - bias.double()).abs() <= (ref + bias.double()).abs() * 2.0 ** -8 + slack).all()
+    want = torch.nn.functional.gelu(u.double(), approximate="tanh" if gelu == "tanh" else "none")
+    assert ((g.double() - want).abs() <= want.abs() * 2.0 ** -8 + 1e-5).all()
+    out = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    Bn = Bt.T.contiguous()
+    B.gpt_stage_op_gemm(B.GPTS_BF16, 1, M, N, K, A, Bn, out, dgelu_u=U, gelu_kind=kind)
+    v = U.double().requires_grad_()
+    torch.nn.functional.gelu(v, approximate="tanh" if gelu == "tanh" else "none").sum().backward()
+    want = ref * v.grad
+    assert ((out.double() - want).abs() <= want.abs() * 2.0 ** -8 + slack).all()
+    At = A.T.contiguous()
+    acc = torch.full((M, N), 0.25, dtype=torch.float32, device="cuda")
+    B.gpt_stage_op_gemm(B.GPTS_BF16, 2, M, N, K, At, Bn, acc)
+    B.gpt_stage_op_gemm(B.GPTS_BF16, 2, M, N, K, At, Bn, acc)      # reads what the first call wrote
+    bound = 4 * K ** 0.5 * K * 2.0 ** -24 + 1e-6
+    assert (acc.double() - (2 * ref + 0.25)).abs().max().item() <= 2 * bound + 2.0 ** -21 * K ** 0.5
+
+
 @pytest.mark.parametrize("M,N,K", [(520, 1032, 65600), (264, 3000, 32768)])
 def test_op_gemm_bf16_wgrad_large_operands(M, N, K):
     """Weight gradients whose operands exceed the cache (above 200 MB tiles are chosen by another rate), ragged in
