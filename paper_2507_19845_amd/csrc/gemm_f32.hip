@@ -26,7 +26,7 @@
 // columns over 999 tokens 77 | 71.  Four of the eight waves' slices ahead: 27.4 and 21.9, 10.2; weight gradients in
 // 64 x 64 tiles of four waves that split the contraction: 71.  Against gemm_simple_kernel (64 x 64 x 16, fp32 FMA):
 // NN 999x512x2048 243 us, NT 128x128x128 11.6.
-#include "kernels.hpp"
+#include "reduce.hpp"
 
 namespace gpts {
 namespace {
@@ -275,10 +275,17 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_f32_kernel(const F32Ar
 struct F32Group {
   F32Args p[kMaxWgrads];
   int first[kMaxWgrads];   // first workgroup of a product
+  int blocks;              // of the products; those from here on add up partial column sums
+  ReduceArgs<kMaxReduceSegs> sums;
 };
 template <int WM, int WN, int WK> __global__ __launch_bounds__(256) void gemm_f32_group_kernel(const F32Group g) {
   using Shape = F32Shape<WM, WN, WK, true, true>;
   __shared__ __attribute__((aligned(16))) float lds[Shape::LDS_FLOATS];
+  if ((int)blockIdx.x >= g.blocks) {
+    static_assert(Shape::LDS_FLOATS >= 32 * 33, "room for the sums");
+    reduce_columns<kMaxReduceSegs, 1>(g.sums, blockIdx.x - g.blocks, reinterpret_cast<float(*)[32][33]>(lds));
+    return;
+  }
   int k = 0;
 #pragma unroll
   for (int i = 1; i < kMaxWgrads; ++i)
@@ -318,16 +325,19 @@ template <bool A_KM, bool B_KM, int EPI> hipError_t launch_f32(const F32Args& a,
   return hipGetLastError();
 }
 
-template <int WM, int WN, int WK> hipError_t launch_f32_group(const F32Args* a, int n, hipStream_t st) {
+template <int WM, int WN, int WK>
+hipError_t launch_f32_group(const F32Args* a, int n, const ReduceSeg* sums, int n_sums, hipStream_t st) {
   using Shape = F32Shape<WM, WN, WK, true, true>;
   static_assert(Shape::OpA::MAX_ROW >= kMaxRow && Shape::OpB::MAX_ROW >= kMaxRow, "offsets fit");
-  F32Group g;
+  F32Group g{};
   int blocks = 0;
   for (int i = 0; i < kMaxWgrads; ++i) {
     g.p[i] = a[i < n ? i : 0];
     g.first[i] = i < n ? blocks : 0x7fffffff;      // (never reached)
     if (i < n) blocks += ((a[i].M + Shape::BM - 1) / Shape::BM) * ((a[i].N + Shape::BN - 1) / Shape::BN);
   }
+  g.blocks = blocks;
+  blocks += reduce_layout<kMaxReduceSegs>(sums, n_sums, &g.sums);
   hipLaunchKernelGGL((gemm_f32_group_kernel<WM, WN, WK>), dim3(blocks), dim3(256), 0, st, g);
   return hipGetLastError();
 }
@@ -363,8 +373,8 @@ hipError_t gemm_f32(int form, int M, int N, int K, const void* A, const void* B,
 }
 
 // Each product keeps the tile it has alone (use_wide), so that its bits do not depend on its company.
-hipError_t gemm_f32_wgrad_group(const WgradItem* items, int n, int K, hipStream_t st) {
-  if (n < 1 || n > kMaxWgrads) return hipErrorInvalidValue;
+hipError_t gemm_f32_wgrad_group(const WgradItem* items, int n, int K, hipStream_t st, const ReduceSeg* sums, int n_sums) {
+  if (n < 1 || n > kMaxWgrads || !few_sums(sums, n_sums)) return hipErrorInvalidValue;
   F32Args wide[kMaxWgrads], narrow[kMaxWgrads];
   int n_wide = 0, n_narrow = 0;
   for (int i = 0; i < n; ++i) {
@@ -375,8 +385,9 @@ hipError_t gemm_f32_wgrad_group(const WgradItem* items, int n, int K, hipStream_
     else narrow[n_narrow++] = a;
   }
   hipError_t e = hipSuccess;
-  if (n_wide > 0) e = launch_f32_group<2, 2, 1>(wide, n_wide, st);
-  if (e == hipSuccess && n_narrow > 0) e = launch_f32_group<1, 1, 4>(narrow, n_narrow, st);
+  // (the sums go with the last launch)
+  if (n_wide > 0) e = launch_f32_group<2, 2, 1>(wide, n_wide, sums, n_narrow > 0 ? 0 : n_sums, st);
+  if (e == hipSuccess && n_narrow > 0) e = launch_f32_group<1, 1, 4>(narrow, n_narrow, sums, n_sums, st);
   return e;
 }
 

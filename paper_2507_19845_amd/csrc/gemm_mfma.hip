@@ -273,8 +273,8 @@ hipError_t gemm_mfma(int form, int M, int N, int K, const void* A, const void* B
 }
 
 hipError_t gemm_wgrad_group(const WgradItem* items, int n, int K, int segments, size_t seg_stride_dout,
-                            size_t seg_stride_in, hipStream_t st) {
-  if (n < 1 || n > kMaxWgrads) return hipErrorInvalidValue;
+                            size_t seg_stride_in, hipStream_t st, const ReduceSeg* sums, int n_sums) {
+  if (n < 1 || n > kMaxWgrads || !few_sums(sums, n_sums)) return hipErrorInvalidValue;
   MfmaArgs a[kMaxWgrads];
   Product p[kMaxWgrads];
   size_t matrices = 0;   // bytes
@@ -292,12 +292,12 @@ hipError_t gemm_wgrad_group(const WgradItem* items, int n, int K, int segments, 
   for (int i = 0; i < n; ++i) a[i].once = matrices >= kOnceBytes;
   const long k_all = (long)K * segments;
   const Tile t = choose_tile(2, p, n, k_all, COST_PLAIN);
-  if (n == 1 || worth_one_launch(t, p, n, k_all)) return launch_gemm_wgrad(t, a, n, st);
+  if (n == 1 || worth_one_launch(t, p, n, k_all)) return launch_gemm_wgrad(t, a, n, sums, n_sums, st);
   for (int i = 0; i < n; ++i) {
-    const hipError_t e = launch_gemm_wgrad(choose_tile(2, p + i, 1, k_all, COST_PLAIN), a + i, 1, st);
+    const hipError_t e = launch_gemm_wgrad(choose_tile(2, p + i, 1, k_all, COST_PLAIN), a + i, 1, nullptr, 0, st);
     if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  return n_sums == 0 ? hipSuccess : reduce_partials(sums, n_sums, st);
 }
 
 }  // namespace gpts

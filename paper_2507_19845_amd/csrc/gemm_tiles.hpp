@@ -43,7 +43,7 @@
 #include <utility>
 
 #include "agpr_ops.hpp"
-#include "kernels.hpp"
+#include "reduce.hpp"
 
 namespace gpts {
 
@@ -99,7 +99,8 @@ inline bool two_stages(long tiles, long K) { return tiles > 256 && (K + 63) / 64
 hipError_t launch_gemm_fwd(Tile tile, int epi, const MfmaArgs& a, hipStream_t st);
 hipError_t launch_gemm_fwd_f16(Tile tile, int epi, const MfmaArgs& a, hipStream_t st);
 hipError_t launch_gemm_dgrad(Tile tile, int epi, const MfmaArgs& a, hipStream_t st);
-hipError_t launch_gemm_wgrad(Tile tile, const MfmaArgs* a, int n, hipStream_t st);   // n <= kMaxWgrads, one launch
+// n <= kMaxWgrads products and n_sums <= kMaxReduceSegs partial sums, one launch
+hipError_t launch_gemm_wgrad(Tile tile, const MfmaArgs* a, int n, const ReduceSeg* sums, int n_sums, hipStream_t st);
 
 // 16-byte chunk swizzle of a K-contiguous tile row of eight chunks (BK = 64).  A 16-byte LDS read serves
 // 16 lanes at a time over the 64 banks, lanes {0-3, 12-15, 20-27} of each half wave, then the others, and
@@ -632,13 +633,24 @@ __global__ __launch_bounds__(256, (gemm_waves<MB, NB, BK, NS>())) void gemm_mi16
 
 // Several weight gradients in one launch, one after the other in the order of the workgroups: their
 // last, partly filled rounds of tiles run into the next product's first.
+// The workgroups from `blocks` on add up partial column sums: alone these are a launch of some microseconds whatever
+// their size, here they fill units that the last round of tiles leaves idle.  In a launch of their own | here, us a step:
+// 128 fp32 tokens 128 wide 67.3 | 64.8, 192 tokens 320 wide 299.7 | 290.3, 4096 tokens 1024 wide 1987 | 1970, 2048 tokens
+// 5120 wide (2080 workgroups of sums) no difference.
 struct WgradGroup {
   MfmaArgs p[kMaxWgrads];
   int first[kMaxWgrads];   // first workgroup of a product
+  int blocks;              // of the products
+  ReduceArgs<kMaxReduceSegs> sums;
 };
 template <int EPI, int FORM, bool F16, int MB, int NB, int BK, int NS>
 __global__ __launch_bounds__(256, (gemm_waves<MB, NB, BK, NS>())) void gemm_mi16_group_kernel(const WgradGroup g) {
   __shared__ __attribute__((aligned(1024))) char lds[gemm_lds_bytes<MB, NB, BK, NS>()];
+  if ((int)blockIdx.x >= g.blocks) {
+    static_assert(sizeof(float[1][32][33]) <= sizeof(lds), "room for the sums");
+    reduce_columns<kMaxReduceSegs, 1>(g.sums, blockIdx.x - g.blocks, reinterpret_cast<float(*)[32][33]>(lds));
+    return;
+  }
   int k = 0;
 #pragma unroll
   for (int i = 1; i < kMaxWgrads; ++i)
@@ -662,15 +674,18 @@ hipError_t launch_mi16(const MfmaArgs& a, hipStream_t st) {
 }
 
 // One product alone takes the plain kernel: a quarter of the arguments, 0.4 us less to launch.
-template <int MB, int NB, int BK, int NS> hipError_t launch_group(const MfmaArgs* a, int n, hipStream_t st) {
-  if (n == 1) return launch_mi16<EPI_ACCUM, FORM_TN, false, MB, NB, BK, NS>(a[0], st);
-  WgradGroup g;
+template <int MB, int NB, int BK, int NS>
+hipError_t launch_group(const MfmaArgs* a, int n, const ReduceSeg* sums, int n_sums, hipStream_t st) {
+  if (n == 1 && n_sums == 0) return launch_mi16<EPI_ACCUM, FORM_TN, false, MB, NB, BK, NS>(a[0], st);
+  WgradGroup g{};
   int blocks = 0;
   for (int i = 0; i < kMaxWgrads; ++i) {
     g.p[i] = a[i < n ? i : 0];
     g.first[i] = i < n ? blocks : 0x7fffffff;      // (never reached)
     if (i < n) blocks += ((a[i].M + 32 * MB - 1) / (32 * MB)) * ((a[i].N + 32 * NB - 1) / (32 * NB));
   }
+  g.blocks = blocks;
+  blocks += reduce_layout<kMaxReduceSegs>(sums, n_sums, &g.sums);
   if constexpr (has_once<EPI_ACCUM, MB, NB>()) {
     if (a[0].once) {
       hipLaunchKernelGGL((gemm_mi16_group_kernel<EPI_ACCUM | EPI_ONCE, FORM_TN, false, MB, NB, BK, NS>), dim3(blocks), dim3(256), 0, st, g);
@@ -710,17 +725,17 @@ template <int EPI, int FORM, bool F16 = false> hipError_t launch_tile(Tile tile,
 // of the LDS | this, us: 256x128 6144x4096, K = 2048 113 | 98, 4096x2048 (one round of 256) 37.1 | 36.6, 3072x3072,
 // K = 4096 106 | 89; 128x128 4096x4096, K = 1024 57 | 45, 3072x2048, K = 4096 62 | 56, 4096x1024 (one round)
 // 37.1 | 36.5; 128x128 with two slices of 64: 4 % slower than with four of 64, five of 32: within 2 % of four.
-inline hipError_t launch_wgrads(Tile tile, const MfmaArgs* a, int n, hipStream_t st) {
+inline hipError_t launch_wgrads(Tile tile, const MfmaArgs* a, int n, const ReduceSeg* sums, int n_sums, hipStream_t st) {
   switch (tile) {
-    case TILE_256x256: return launch_group<8, 8, 32, 4>(a, n, st);
-    case TILE_256x192: return launch_group<8, 6, 32, 5>(a, n, st);
-    case TILE_256x160: return launch_group<8, 5, 64, 3>(a, n, st);
-    case TILE_192x192: return launch_group<6, 6, 64, 3>(a, n, st);
-    case TILE_256x128: return launch_group<8, 4, 32, 3>(a, n, st);
-    case TILE_128x128: return launch_group<4, 4, 32, 4>(a, n, st);
-    case TILE_128x64: return launch_group<4, 2, 64, 4>(a, n, st);
-    case TILE_64x64: return launch_group<2, 2, 64, 4>(a, n, st);
-    case TILE_64x32: return launch_group<2, 1, 64, 4>(a, n, st);
+    case TILE_256x256: return launch_group<8, 8, 32, 4>(a, n, sums, n_sums, st);
+    case TILE_256x192: return launch_group<8, 6, 32, 5>(a, n, sums, n_sums, st);
+    case TILE_256x160: return launch_group<8, 5, 64, 3>(a, n, sums, n_sums, st);
+    case TILE_192x192: return launch_group<6, 6, 64, 3>(a, n, sums, n_sums, st);
+    case TILE_256x128: return launch_group<8, 4, 32, 3>(a, n, sums, n_sums, st);
+    case TILE_128x128: return launch_group<4, 4, 32, 4>(a, n, sums, n_sums, st);
+    case TILE_128x64: return launch_group<4, 2, 64, 4>(a, n, sums, n_sums, st);
+    case TILE_64x64: return launch_group<2, 2, 64, 4>(a, n, sums, n_sums, st);
+    case TILE_64x32: return launch_group<2, 1, 64, 4>(a, n, sums, n_sums, st);
     default: return hipErrorInvalidValue;
   }
 }

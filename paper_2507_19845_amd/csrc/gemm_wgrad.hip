@@ -4,6 +4,8 @@
 
 namespace gpts {
 
-hipError_t launch_gemm_wgrad(Tile tile, const MfmaArgs* a, int n, hipStream_t st) { return launch_wgrads(tile, a, n, st); }
+hipError_t launch_gemm_wgrad(Tile tile, const MfmaArgs* a, int n, const ReduceSeg* sums, int n_sums, hipStream_t st) {
+  return launch_wgrads(tile, a, n, sums, n_sums, st);
+}
 
 }  // namespace gpts

@@ -283,22 +283,22 @@ hipError_t gemm(int dtype, int form, int M, int N, int K, const void* A, const v
 }
 
 // The weight gradients of a layer's linears, over the same K tokens: one launch where the matrix-core
-// kernels take all of them, else one product each.
-hipError_t wgrads(int dtype, const WgradItem* items, int n, int K, hipStream_t st) {
+// kernels take all of them, else one product each.  sums: partial sums to be added up as well.
+hipError_t wgrads(int dtype, const WgradItem* items, int n, int K, hipStream_t st, const ReduceSeg* sums = nullptr, int n_sums = 0) {
   bool bf = dtype == GPTS_BF16, f32 = dtype == GPTS_FP32;
   for (int i = 0; i < n; ++i) {
     const WgradItem& w = items[i];
     bf = bf && gemm_mfma_supported(2, w.M, w.N, K);
     f32 = f32 && gemm_f32_supported(2, w.M, w.N, K, w.dout, w.in, w.dw, GemmEpilogue());
   }
-  if (bf) return gemm_wgrad_group(items, n, K, 1, 0, 0, st);
-  if (f32) return gemm_f32_wgrad_group(items, n, K, st);
+  if (bf) return gemm_wgrad_group(items, n, K, 1, 0, 0, st, sums, n_sums);
+  if (f32) return gemm_f32_wgrad_group(items, n, K, st, sums, n_sums);
   for (int i = 0; i < n; ++i) {
     const WgradItem& w = items[i];
     const hipError_t e = gemm(dtype, 2, w.M, w.N, K, w.dout, w.in, w.dw, GemmEpilogue(), st);
     if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  return n_sums == 0 ? hipSuccess : reduce_partials(sums, n_sums, st);
 }
 
 // Attention: on the matrix cores for bf16 and for aligned fp32 buffers, the plain FMA kernels
@@ -608,11 +608,15 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
                       wk + ws.rA, rs, rs + D.T, st), "ln1 recompute");
       A = wk + ws.rA;
     }
-    if (!data_only) {
-      // all four weight gradients together (dY is still whole: dx, which may alias it, is written by
-      // the LayerNorm below); one by one under a tracer, which times each
-      const WgradItem lin[4] = {{D.H, D.F, dY, G, g(l, GPTS_W_FC2)}, {D.F, D.H, dU, A2, g(l, GPTS_W_FC1)},
-                                {D.H, D.P, dX1, Cb, g(l, GPTS_W_O)}, {3 * D.P, D.H, dQKV, A, g(l, GPTS_W_QKV)}};
+    // all four weight gradients together; one by one under a tracer, which times each
+    const WgradItem lin[4] = {{D.H, D.F, dY, G, g(l, GPTS_W_FC2)}, {D.F, D.H, dU, A2, g(l, GPTS_W_FC1)},
+                              {D.H, D.P, dX1, Cb, g(l, GPTS_W_O)}, {3 * D.P, D.H, dQKV, A, g(l, GPTS_W_QKV)}};
+    // The LayerNorm below replaces dY where the caller lets dx lie on dy and the layer is both first and last: then the
+    // weight gradients go before it.  Else they follow it, and add up the layer's partial sums in the same launch.
+    const char *const y0 = static_cast<const char*>(dY), *const x0 = static_cast<const char*>(dXout);
+    const bool apart = l < D.L - 1 || x0 + (size_t)D.T * D.H * e <= y0 || y0 + (size_t)D.T * D.H * e <= x0;
+    const bool wgrads_last = !data_only && !tr && apart;
+    if (!data_only && !wgrads_last) {
       if (!tr) GPTS_TRY(wgrads(dt, lin, 4, D.T, st), "weight gradients");
       else
         for (int i = 0; i < 4; ++i)
@@ -622,9 +626,7 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
     // below where they are small, or one of their own, also where its dx lies on dY (a single layer whose caller lets
     // dx replace dy); one by one under a tracer
     cols[n_cols++] = ColsumMat{dQKV, 3 * D.P, g(l, GPTS_B_QKV), part(ws.cs_qkv)};
-    const char *const y0 = static_cast<const char*>(dY), *const x0 = static_cast<const char*>(dXout);
-    const bool with_ln = !tr && ln_bwd_takes_colsums(dt, D.T, D.H, cols, n_cols) &&
-                         (l < D.L - 1 || x0 + (size_t)D.T * D.H * e <= y0 || y0 + (size_t)D.T * D.H * e <= x0);
+    const bool with_ln = !tr && ln_bwd_takes_colsums(dt, D.T, D.H, cols, n_cols) && apart;
     if (!tr && !with_ln) GPTS_TRY(colsum_partials(dt, D.T, cols, n_cols, sums + n_sums, st), "bias gradients");
     if (tr)
       for (int i = 0; i < n_cols; ++i)
@@ -637,12 +639,13 @@ int run_bwd(const gpt_stage_params* p, const void* act_stash, const void* dy, vo
       const hipError_t err = ln_bwd_partials(dt, dt == GPTS_BF16, D.T, D.H, dA, xs, stat1, stat1 + D.T, w(l, GPTS_LN1_G), dX1, dXout,
                                              g(l, GPTS_LN1_G), g(l, GPTS_LN1_B), l > 0 ? g(l - 1, GPTS_B_FC2) : nullptr,
                                              part(ws.ln1_part), &sums[n_sums++], st, nullptr, cols, with_ln ? n_cols : 0, col_sums);
-      return err != hipSuccess || fused_b1 ? err : reduce_partials(sums, n_sums, st);
+      return err != hipSuccess || fused_b1 || wgrads_last ? err : reduce_partials(sums, n_sums, st);
     };
     GPTS_OP(GPTS_TR_LN_BWD, 0, 1, 0.0, TH * (3 * e + kResBytes), ln1_bwd(), "ln1 bwd (+ fc2 bias grad of the layer below)");
     // the layer's partial sums: the fc1 bias gradient's own operator where its sums came out of the fc2
     // dgrad, else part of the operator above
-    if (fused_b1)
+    if (wgrads_last) GPTS_TRY(wgrads(dt, lin, 4, D.T, st, sums, n_sums), "weight gradients and column sums");
+    else if (fused_b1)
       GPTS_OP(GPTS_TR_BIAS_GRAD, 2, 1, 0.0, (double)cs_rows * D.F * 4, reduce_partials(sums, n_sums, st), "fc1 bias grad and the layer's other column sums");
     dY = dXout;
   }

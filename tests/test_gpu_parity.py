@@ -569,6 +569,36 @@ def test_bias_gradients_beside_the_layernorm(dtype, hidden, ffn, seq, batch, lay
 
 
 # ------------------------------------------------------- single operations ----
+@pytest.mark.parametrize("dtype,layers,hidden,heads,ffn,seq,batch", [("fp32", 1, 128, 4, 512, 33, 2), ("fp32", 2, 136, 2, 200, 37, 3),
+                                                                    ("bf16", 1, 320, 5, 832, 64, 1), ("bf16", 2, 192, 3, 2112, 96, 2),
+                                                                    ("bf16", 3, 1024, 16, 4096, 320, 1), ("bf16", 2, 64, 1, 128, 64, 1)])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_partial_sums_beside_the_weight_gradients(dtype, layers, hidden, heads, ffn, seq, batch, in_place):
+    """A layer's partial column sums are added up in the launch of its weight gradients, in one of their own under a tracer and
+    where a single layer's dx lies on dy: every output bit for bit the same either way, on widths that the matrix cores take in
+    different tiles and on some that they do not take."""
+    print(f"[case] sums beside wgrads {dtype} L={layers} H={hidden} F={ffn} T={seq * batch} {in_place}", flush=True)
+    shape = synth.WORKLOADS[0].with_(name="sums_beside_wgrads", dtype=dtype, n_layers=layers, hidden=hidden, n_heads=heads,
+                                     head_dim=64 if dtype == "bf16" else 32, ffn=ffn, seq=seq, batch=batch, bias_std=0.02, ln_jitter=0.1)
+    bufs = B.StageBuffers(shape)
+    bufs.load_params(synth.make_params(shape, 3))
+    x, dy = B.to_device(synth.make_x(shape, 3), dtype), B.to_device(synth.make_dy(shape, 3), dtype)
+    got = []
+    for tracer in (None, B.gpt_stage_trace_create(4096)):
+        bufs.trace = tracer
+        bufs.dparams.fill_(0.125)
+        y, g = bufs.act(), dy.clone()
+        dx = g if in_place else bufs.act()
+        B.gpt_stage_fwd(bufs.params(), x, bufs.stash[0], y)
+        B.gpt_stage_bwd(bufs.params(), bufs.stash[0], g, dx, bufs.dparams)
+        torch.cuda.synchronize()
+        got.append((y, dx.clone(), bufs.dparams.clone()))
+    bufs.trace = None
+    B.gpt_stage_trace_destroy(tracer)
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dtype,T,H,x_f32", [("fp32", 37, 128, False), ("fp32", 5, 4104, False),
                                              ("bf16", 130, 1024, False), ("bf16", 64, 12288, True),
                                              ("bf16", 3, 8, False), ("fp32", 600, 16384, False),
