@@ -230,53 +230,54 @@ template <bool NT, typename V> __device__ __forceinline__ void store_once(V* p, 
 // rows.  Each wave instead stages its rows through LDS in passes of RP rows (write_pass(pass)) and
 // reads them back row-major: CW lanes cover one row of the WN columns, so every global load and
 // store touches whole cache lines.
-//   stage   the wave's staged rows, pass by pass at the same place
-//   m_first, n_first   output row and column of the wave's first staged element; WM rows in all
-//   cs      GeLU' epilogue: on return, lanes < WN/4 hold the column sums of their four columns
 // OUT16: the 16-bit outputs (C of the bias-only epilogue; C and the GeLU output of the GeLU
 // epilogues) are written as fp16 instead of bf16 (forward activations kept in fp16).
-template <int KIND, bool OUT16, int WM, int WN, int RP, class StageWriter>
-__device__ __forceinline__ void gemm_epilogue(StageWriter&& write_pass, const MfmaArgs& a, const float* stage,
-                                              int m_first, int n_first, float (&cs)[4], int lane) {
-  constexpr int EPI = KIND & ~EPI_ONCE;
-  constexpr bool ONCE = (KIND & EPI_ONCE) != 0;
+//
+// What an epilogue reads that depends on addresses only (the bias, and the first batch of the fp32 tile that an
+// accumulating product adds to, of a residual, of u for GeLU') is asked for by begin(): in tiles up to 128x64 in front of the
+// slices (EARLY), so that no memory latency follows the last one, else after them.  After | in front, us a step: 192
+// tokens 320 wide (64x32 and 64x64 tiles, five slices) 290.3 | 282.7; in 128x128, whose products are long enough to lose
+// more by the later slices and the registers, 4096 tokens 1024 wide 1935 | 1950, backward of 2048 tokens 2048 wide 1207 | 1220.
+template <int KIND, bool OUT16, int WM, int WN, int RP> struct GemmEpi {
+  static constexpr int EPI = KIND & ~EPI_ONCE;
+  static constexpr bool ONCE = (KIND & EPI_ONCE) != 0;
   static_assert(!OUT16 || EPI == EPI_BIAS || EPI == EPI_GELU_TANH || EPI == EPI_GELU_ERF ||
                     EPI == EPI_BIAS_RES32_OUT32 || EPI == EPI_BIAS_RES32_OUT16,
                 "fp16 outputs exist for the forward epilogues only");
-  constexpr int CW = Staged<WN>::CW, RPI = 64 / CW;          // chunks per row, rows per read instruction
-  constexpr bool FULL = 64 % CW == 0;                        // no idle lanes
-  const int rd_chunk = lane % CW, rd_row = lane / CW;
-  const int n = n_first + rd_chunk * 4;
-  const bool n_ok = n < a.N && (FULL || rd_row < RPI);
-  constexpr bool RES32 = EPI == EPI_BIAS_RES32_OUT32 || EPI == EPI_BIAS_RES32_OUT16;
-  constexpr bool GELU = EPI == EPI_GELU_TANH || EPI == EPI_GELU_ERF;
-  constexpr bool DGELU = EPI == EPI_DGELU_TANH || EPI == EPI_DGELU_ERF;
-  float bias_v[4] = {0.f, 0.f, 0.f, 0.f};
-  if constexpr (EPI == EPI_BIAS_RES || EPI == EPI_BIAS || RES32 || GELU) {
-    if (a.bias && n_ok) {
-      const bf16x4 b = *reinterpret_cast<const bf16x4*>(a.bias + n);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) bias_v[e] = (float)b[e];
-    }
-  }
-  // The readback goes in batches of UB row instructions.  The global loads of a batch (the
-  // fp32 tile an accumulating product adds to, a residual, u for GeLU') depend on addresses
-  // only, so they are issued one batch ahead -- the first before the tile is even staged --
+  static constexpr bool EARLY = WM * WN <= 64 * 32;
+  static constexpr int CW = Staged<WN>::CW, RPI = 64 / CW;          // chunks per row, rows per read instruction
+  static constexpr bool FULL = 64 % CW == 0;                        // no idle lanes
+  static constexpr bool RES32 = EPI == EPI_BIAS_RES32_OUT32 || EPI == EPI_BIAS_RES32_OUT16;
+  static constexpr bool GELU = EPI == EPI_GELU_TANH || EPI == EPI_GELU_ERF;
+  static constexpr bool DGELU = EPI == EPI_DGELU_TANH || EPI == EPI_DGELU_ERF;
+  static constexpr bool BIAS = EPI == EPI_BIAS_RES || EPI == EPI_BIAS || RES32 || GELU;
+  // The readback goes in batches of UB row instructions.  The global loads of a batch are issued one batch ahead,
   // and a batch's memory latency overlaps the staging and the arithmetic and stores of the
   // batch before it.
-  constexpr int ITS = (RP + RPI - 1) / RPI, UB = ITS % 8 == 0 || ITS > 16 ? 8 : 4;
-  constexpr int NPASS = WM / RP, BPP = (ITS + UB - 1) / UB, NBATCH = NPASS * BPP;
-  constexpr bool EXACT = BPP * UB * RPI == RP && FULL;        // no row past the pass's last
+  static constexpr int ITS = (RP + RPI - 1) / RPI, UB = ITS < 4 ? ITS : (ITS % 8 == 0 || ITS > 16 ? 8 : 4);
+  static constexpr int NPASS = WM / RP, BPP = (ITS + UB - 1) / UB, NBATCH = NPASS * BPP;
+  static constexpr bool EXACT = BPP * UB * RPI == RP && FULL;        // no row past the pass's last
   static_assert(WM % RP == 0, "whole passes");
-  constexpr bool HAS_LOADS = EPI == EPI_ACCUM || RES32 || DGELU || EPI == EPI_BIAS_RES;
+  static constexpr bool HAS_LOADS = EPI == EPI_ACCUM || RES32 || DGELU || EPI == EPI_BIAS_RES;
   struct Batch {
     f32x4 in32[UB];
     bf16x4 in16[UB];
     bool ok[UB];
     size_t o[UB];
-  } bt[2];
-  auto issue = [&](auto idx_c) {
-    constexpr int idx = decltype(idx_c)::value, pass = idx / BPP, it0 = (idx % BPP) * UB;
+  };
+  const MfmaArgs a;   // (a copy: by reference the arguments would live in memory)
+  const int m_first, rd_chunk, rd_row, n;
+  const bool n_ok;
+  bf16x4 bias;
+  Batch bt[2];
+
+  // m_first, n_first: output row and column of the wave's first element; WM rows in all
+  __device__ __forceinline__ GemmEpi(const MfmaArgs& a_, int m_first_, int n_first, int lane)
+      : a(a_), m_first(m_first_), rd_chunk(lane % CW), rd_row(lane / CW), n(n_first + lane % CW * 4),
+        n_ok(n_first + lane % CW * 4 < a_.N && (FULL || lane / CW < RPI)) {}
+
+  template <int idx> __device__ __forceinline__ void issue() {
+    constexpr int pass = idx / BPP, it0 = (idx % BPP) * UB;
     Batch& t = bt[idx & 1];
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
@@ -289,9 +290,18 @@ __device__ __forceinline__ void gemm_epilogue(StageWriter&& write_pass, const Mf
       if constexpr (DGELU) t.in16[u] = load_once<ONCE>(reinterpret_cast<const bf16x4*>(a.dgelu_u + t.o[u]));
       if constexpr (EPI == EPI_BIAS_RES) t.in16[u] = *reinterpret_cast<const bf16x4*>(static_cast<const bf16*>(a.residual) + t.o[u]);
     }
-  };
-  auto finish = [&](auto idx_c) {
-    constexpr int idx = decltype(idx_c)::value, it0 = (idx % BPP) * UB;
+  }
+  __device__ __forceinline__ void begin() {
+    if constexpr (BIAS) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bias[e] = (bf16)0.f;
+      if (a.bias && n_ok) bias = *reinterpret_cast<const bf16x4*>(a.bias + n);
+    }
+    if constexpr (HAS_LOADS) issue<0>();
+    asm volatile("" ::: "memory");   // (not put off behind the slices)
+  }
+  template <int idx> __device__ __forceinline__ void finish(const float* stage, const float (&bias_v)[4], float (&cs)[4]) {
+    constexpr int it0 = (idx % BPP) * UB;
     Batch& t = bt[idx & 1];
     f32x4 sv[UB];
 #pragma unroll
@@ -358,41 +368,49 @@ __device__ __forceinline__ void gemm_epilogue(StageWriter&& write_pass, const Mf
         }
       }
     }
-  };
-  if constexpr (HAS_LOADS) issue(std::integral_constant<int, 0>{});
-  static_for<NBATCH>([&](auto idx_c) {
-    constexpr int idx = decltype(idx_c)::value;
-    if constexpr (idx % BPP == 0) {
-      write_pass(std::integral_constant<int, idx / BPP>{});
-      // LDS operations of one wave complete in order: no wait is needed between the
-      // writes above and the reads below, only that the compiler keeps their order
-      asm volatile("" ::: "memory");
+  }
+  // stage: the wave's staged rows, pass by pass at the same place (write_pass(pass))
+  // cs: GeLU' epilogue: on return, lanes < WN/4 hold the column sums of their four columns
+  template <class StageWriter> __device__ __forceinline__ void run(StageWriter&& write_pass, const float* stage, float (&cs)[4], int lane) {
+    float bias_v[4] = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (BIAS) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bias_v[e] = (float)bias[e];
     }
-    if constexpr (HAS_LOADS) {
-      if constexpr (idx + 1 < NBATCH) issue(std::integral_constant<int, idx + 1>{});
-    } else {
-      issue(idx_c);
-    }
-    finish(idx_c);
-  });
-  if constexpr (DGELU) {
-    // lanes CW apart hold the same columns of different rows
-    if constexpr (FULL) {
+    static_for<NBATCH>([&](auto idx_c) {
+      constexpr int idx = decltype(idx_c)::value;
+      if constexpr (idx % BPP == 0) {
+        write_pass(std::integral_constant<int, idx / BPP>{});
+        // LDS operations of one wave complete in order: no wait is needed between the
+        // writes above and the reads below, only that the compiler keeps their order
+        asm volatile("" ::: "memory");
+      }
+      if constexpr (HAS_LOADS) {
+        if constexpr (idx + 1 < NBATCH) issue<idx + 1>();
+      } else {
+        issue<idx>();
+      }
+      finish<idx>(stage, bias_v, cs);
+    });
+    if constexpr (DGELU) {
+      // lanes CW apart hold the same columns of different rows
+      if constexpr (FULL) {
 #pragma unroll
-      for (int off = CW; off < 64; off <<= 1)
+        for (int off = CW; off < 64; off <<= 1)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) cs[e] += __shfl_xor(cs[e], off);
-    } else {
+          for (int e = 0; e < 4; ++e) cs[e] += __shfl_xor(cs[e], off);
+      } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float s = cs[e];
+        for (int e = 0; e < 4; ++e) {
+          float s = cs[e];
 #pragma unroll
-        for (int r = 1; r < RPI; ++r) s += __shfl(cs[e], (lane + r * CW) & 63);
-        cs[e] = s;   // valid in lanes < CW
+          for (int r = 1; r < RPI; ++r) s += __shfl(cs[e], (lane + r * CW) & 63);
+          cs[e] = s;   // valid in lanes < CW
+        }
       }
     }
   }
-}
+};
 
 enum GemmForm { FORM_NT = 0, FORM_NN = 1, FORM_TN = 2 };
 
@@ -443,6 +461,13 @@ __device__ __forceinline__ void gemm_tile(MfmaArgs a, int id, char* const lds) {
     }
   }
   const int m0 = tm * BM, n0 = tn_i * BN;
+  constexpr int PITCH = Staged<WN>::PITCH;
+  constexpr int FIT = LDS_BYTES / NW / (PITCH * 4);        // rows of the wave's block that fit its LDS share
+  constexpr int RP = FIT >= WM ? WM : (FIT >= 64 && WM % 64 == 0 ? 64 : 32);
+  static_assert(FIT >= RP && WM % RP == 0, "epilogue staging does not fit");
+  using Epi = GemmEpi<EPI, F16, WM, WN, RP>;
+  Epi epi(a, m0 + wm * WM, n0 + wn * WN, lane);
+  if constexpr (Epi::EARLY) epi.begin();
   const int sps = a.K / BK, nk = sps * (FORM == FORM_TN ? a.batch : 1);     // slices per K segment, in all
 
   const size_t lda = A_KM ? (size_t)a.M : (size_t)a.K, ldb = B_KM ? (size_t)a.N : (size_t)a.K;
@@ -584,7 +609,6 @@ __device__ __forceinline__ void gemm_tile(MfmaArgs a, int id, char* const lds) {
   asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
   __syncthreads();
 
-  constexpr int PITCH = Staged<WN>::PITCH;
   // rows [pass*RP, +RP) of the wave's block -> its staging area
   auto stage_rows = [&](auto pass_c, auto rp_c, float* stg) {
     constexpr int pass = decltype(pass_c)::value, BI = decltype(rp_c)::value / 16;   // block rows per pass
@@ -602,12 +626,9 @@ __device__ __forceinline__ void gemm_tile(MfmaArgs a, int id, char* const lds) {
   // GeLU' epilogue: the lane's share of the column sums of C, before rounding to bf16 (the bias
   // gradient of the linear layer whose output gradient this product forms)
   float cs[4] = {0.f, 0.f, 0.f, 0.f};
-  constexpr int FIT = LDS_BYTES / NW / (PITCH * 4);        // rows of the wave's block that fit its LDS share
-  constexpr int RP = FIT >= WM ? WM : (FIT >= 64 && WM % 64 == 0 ? 64 : 32);
-  static_assert(FIT >= RP && WM % RP == 0, "epilogue staging does not fit");
   float* const stg = reinterpret_cast<float*>(lds) + wave * (RP * PITCH);
-  gemm_epilogue<EPI, F16, WM, WN, RP>([&](auto pass_c) { stage_rows(pass_c, std::integral_constant<int, RP>{}, stg); }, a,
-                                      stg, m0 + wm * WM, n0 + wn * WN, cs, lane);
+  if constexpr (!Epi::EARLY) epi.begin();
+  epi.run([&](auto pass_c) { stage_rows(pass_c, std::integral_constant<int, RP>{}, stg); }, stg, cs, lane);
   if constexpr ((EPI & ~EPI_ONCE) == EPI_DGELU_TANH || (EPI & ~EPI_ONCE) == EPI_DGELU_ERF) {
     const int n = n0 + wn * WN + lane * 4;
     if (a.colsum && lane < WN / 4 && n < a.N) {
