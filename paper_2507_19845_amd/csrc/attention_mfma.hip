@@ -427,7 +427,7 @@ __device__ __forceinline__ BwdArgs at_microbatch(BwdArgs p, int mb) {
 // RW x SW waves: RW blocks of 32 keys; with SW = 2 a second wave per block takes the other 32 queries
 // of every tile and the two sums are added through LDS at the end.
 template <bool F16S> constexpr int kBwdTiles = F16S ? 3 : 2;   // LDS tiles of a stage: [Q | dO | fp16 Q] or [K | V | fp16 K]
-// SCALED: the query side ran before and has left -lse log2(e), so that the exponent is one multiply-add.  That is 1 % of both
+// SCALED: the query side ran before and has left -lse log2(e), else that is formed here (the same bits).  That is 1 % of both
 // sides at 1x8191x16x128, dP beginning at -delta 1 % (943 -> 925 us together) and 1.5 % at 4x1024x16x64 (55.9 -> 55.0).  Left
 // to attn_delta_kernel, whose lanes have one head each, its scattered second array costs more than it gives (16x333x12x32
 // 21.7 -> 22.4 us).
@@ -460,7 +460,7 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
   const int ql = lane & 31, h = lane >> 5;
   const int key = kw0 + ql;
   const int kclamp = key < S ? key : S - 1;
-  const float rsd = 1.f / sqrtf((float)D), c = 1.4426950408889634f / sqrtf((float)D);
+  const float c = 1.4426950408889634f / sqrtf((float)D);  // log2(e)/sqrt(D)
 
   bf16x8 kfr[KSTEPS], vfr[KSTEPS];
 #pragma unroll
@@ -542,7 +542,7 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
           const f32x4 L = *reinterpret_cast<const f32x4*>(Ls + g * 8);
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            sacc[g * 4 + e] = __builtin_amdgcn_exp2f(SCALED ? fmaf(sacc[g * 4 + e], c, L[e]) : fmaf(sacc[g * 4 + e], rsd, -L[e]) * 1.4426950408889634f);
+            sacc[g * 4 + e] = __builtin_amdgcn_exp2f(fmaf(sacc[g * 4 + e], c, SCALED ? L[e] : L[e] * -1.4426950408889634f));
         }
         if (masked) {
 #pragma unroll
