@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kLnBwdThreads) void ln_bwd_kernel(
     n_blocks = tail.blocks;
     if ((int)blockIdx.x >= n_blocks) {
       const int r = blockIdx.x - n_blocks, half = threadIdx.x / (4 * kWave);   // (four waves a slice)
-      colsum_partial<T>(tail.cols, T_rows, r % tail.nx, r / tail.nx * 2 + half, tail.slices, 0, threadIdx.x / kWave % 4,
+      colsum_partial<T>(tail.cols, T_rows, r % tail.nx, r / tail.nx * 2 + half, tail.slices, blockIdx.y, threadIdx.x / kWave % 4,
                         comb + half * (4 * kWave * Vec16<T>::N));
       return;
     }
@@ -550,16 +550,16 @@ hipError_t ln_bwd_partials(int dtype, bool x_f32, int T_rows, int H, const void*
                            float* dgamma, float* dbeta, float* dxsum, float* partial, ReduceSeg* seg, hipStream_t st,
                            const LnBwdWindow* win, const ColsumMat* cols, int n_cols, ReduceSeg* col_segs) {
   if (H > 4 * 8 * kLnBwdThreads || (win && (win->n < 1 || win->n > kMaxWindow))) return hipErrorInvalidValue;
-  if (n_cols < 0 || n_cols > kMaxColsums || (win && n_cols)) return hipErrorInvalidValue;
+  if (n_cols < 0 || n_cols > kMaxColsums) return hipErrorInvalidValue;
   const int np = dxsum ? 3 : 2;
   const LnBwdWindow w = win ? *win : LnBwdWindow();
-  if (!window_stride_ok(w.act) || !window_stride_ok(w.dres) || !window_stride_ok(w.dx)) return hipErrorInvalidValue;
+  if (!window_stride_ok(w.act) || !window_stride_ok(w.dres) || !window_stride_ok(w.dx) || !window_stride_ok(w.cols)) return hipErrorInvalidValue;
   const int blocks = ln_bwd_blocks(T_rows, H);
   *seg = ReduceSeg{partial, (size_t)np * H, blocks, np * H, H, 2 * H, dgamma, dbeta, dxsum, w.n};
   if (!n_cols)
     return ln_bwd_any<0>(dtype, x_f32, T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, w, LnBwdTail<0>(), 0, st);
   LnBwdTail<kMaxColsums> tail{};
-  tail.nx = colsum_layout(dtype, T_rows, cols, n_cols, col_segs, 1, 0, &tail.cols);
+  tail.nx = colsum_layout(dtype, T_rows, cols, n_cols, col_segs, w.n, w.cols, &tail.cols);
   tail.blocks = blocks;
   tail.slices = colsum_splits(T_rows);
   return ln_bwd_any<kMaxColsums>(dtype, x_f32, T_rows, H, dout, x, mean, rstd, gamma, dres, dx, dxsum, partial, w, tail,

@@ -47,11 +47,11 @@ constexpr int kMaxColsums = 3;
 // dxsum (may be null): += column sums of dx as stored.  ln_bwd_partials leaves the three sums in
 // `partial` (ln_bwd_scratch_bytes(), for each micro-batch) and describes them in *seg; ln_bwd adds them up as well.
 // cols, n_cols, col_segs: what colsum_partials would do for n_cols <= kMaxColsums matrices of as many rows, in the same
-// launch (not with a window, and only where ln_bwd_takes_colsums()).  dx must not overlap them.
+// launch (only where ln_bwd_takes_colsums(), of the rows of all micro-batches).  dx must not overlap them.
 bool ln_bwd_takes_colsums(int dtype, int T_rows, int H, const ColsumMat* cols, int n);
 struct LnBwdWindow {
   int n = 1;
-  size_t act = 0, dres = 0, dx = 0;   // strides of dout, x, mean and rstd; of dres; of dx
+  size_t act = 0, dres = 0, dx = 0, cols = 0;   // strides of dout, x, mean and rstd; of dres; of dx; of the matrices `cols`
 };
 hipError_t ln_bwd_partials(int dtype, bool x_f32, int T_rows, int H, const void* dout, const void* x,
                            const float* mean, const float* rstd, const void* gamma, const void* dres, void* dx,
