@@ -195,10 +195,34 @@ template <int D> __device__ __forceinline__ bf16x8 natural_frag(const char* tile
   return *reinterpret_cast<const bf16x8*>(tile + kk / KP * kPanelBytes<D> + rb * 32 * (kPanel<D> * 2) + (off ^ (kk % KP << 5)));
 }
 
+// the larger of a lane's value and that of lane ^ 32
+__device__ __forceinline__ float max_of_halves(float v) {
+  const unsigned x = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  const unsigned lo = r[0], hi = r[1];   // (a bit cast of r[1] itself gives r[0]'s)
+  return fmaxf(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi));
+}
+// The order asked of the compiler for N matrix instructions and what goes between them: LDS reads (NL for each) AHEAD
+// instructions before their use, NV vector instructions after each of the first LEAD and then NW with one or two exponentials.
+template <int N, int NL, int AHEAD, int LEAD, int NV, int NW, int I = 0> __device__ __forceinline__ void interleave() {
+  if constexpr (I == 0) __builtin_amdgcn_sched_group_barrier(0x100, AHEAD * NL, 0);
+  if constexpr (I < N) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    if constexpr (I + AHEAD < N) __builtin_amdgcn_sched_group_barrier(0x100, NL, 0);
+    if constexpr (I < LEAD) {
+      __builtin_amdgcn_sched_group_barrier(0x002, NV, 0);
+    } else {
+      __builtin_amdgcn_sched_group_barrier(0x002, NW, 0);
+      __builtin_amdgcn_sched_group_barrier(0x400, 1 + (I & 1), 0);
+    }
+    interleave<N, NL, AHEAD, LEAD, NV, NW, I + 1>();
+  }
+}
+
 // ---- forward -----------------------------------------------------------------------------
 // grid (heads, batch, query tiles): the heaviest query tiles of all heads start first.
 // F16: qkv, the probabilities and out are fp16 (same layouts, f16 instructions).
-// RW x SW waves: RW blocks of 32 queries; with SW = 2 a second wave per block takes the other 32 keys
+// RW x SW waves: RW blocks of 32 queries (4, 8 for many long sequences); with SW = 2 a second wave per block takes the other 32 keys
 // of every tile, and the two running maxima, sums and outputs are merged through LDS at the end.
 template <int D, bool F16, int RW, int SW>
 __global__ __launch_bounds__(64 * RW * SW, 2) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv0, bf16* __restrict__ out0,
@@ -247,92 +271,197 @@ __global__ __launch_bounds__(64 * RW * SW, 2) void attn_fwd_mfma_kernel(const bf
 
   const int last_key = min(q0 + BQ, S);               // keys [0, last_key) are needed
   const int nkv = (last_key + BKV - 1) / BKV;
-  dma_tile<D, NW>(base + P, ld, 0, S, lds, wave, lane);
-  dma_tile<D, NW>(base + 2 * P, ld, 0, S, lds + TILE, wave, lane);
-
-  for (int kt = 0; kt < nkv; ++kt) {
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    const int k0 = kt * BKV;
-    const char* tK = lds + (kt & 1) * 2 * TILE;
-    const char* tV = tK + TILE;
-    if (kt + 1 < nkv) {
-      char* nK = lds + ((kt + 1) & 1) * 2 * TILE;
-      dma_tile<D, NW>(base + P, ld, k0 + BKV, S, nK, wave, lane);
-      dma_tile<D, NW>(base + 2 * P, ld, k0 + BKV, S, nK + TILE, wave, lane);
-    }
-    if (k0 + BKV > S) {   // (uniform) keys past the last one: p = 0 has to meet v = 0
-      zero_rows<D, NW>(lds + (kt & 1) * 2 * TILE + TILE, S - k0, wave, lane);
-      __syncthreads();
-    }
-    const int kw0 = k0 + kb0 * 32;
-    if (kw0 > qmax_wave) continue;  // every key of this tile is masked for this wave
-
-    // ---- S^T = K Q^T for the wave's 32-key blocks ----------------------------------
-    f32x16 sacc[NKB];
-    if constexpr (SW == 1) GPTS_PRIO(1);
+  if constexpr (RW == 8) {
+    // The logits of tile kt + 1 are formed while the softmax of tile kt is computed, matrix and vector instructions
+    // alternating within the wave, and K runs a tile ahead of V: with eight waves behind one barrier a SIMD's two waves are in
+    // the same phase, and one after the other the phases left its pipes idle in turn (1x8191x16x128 292 | 281 us; in
+    // four waves, whose workgroups drift apart, it gains nothing: 300 | 308).
+    f32x16 sacc[2][NKB];
+    auto kbuf = [&](int i) -> char* { return lds + i * 2 * TILE; };
+    auto vbuf = [&](int i) -> char* { return lds + i * 2 * TILE + TILE; };
+    auto logits = [&](f32x16(&s)[NKB], const char* tK) {   // S^T = K Q^T for the wave's 32-key blocks
 #pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
+      for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) sacc[kb][e] = 0.f;
+        for (int e = 0; e < 16; ++e) s[kb][e] = 0.f;
 #pragma unroll
-      for (int kk = 0; kk < KSTEPS; ++kk) {
-        const bf16x8 kf = natural_frag<D>(tK, koff, kb0 + kb, kk);
-        sacc[kb] = mma32<F16>(kf, qf[kk], sacc[kb]);
+        for (int kk = 0; kk < KSTEPS; ++kk) s[kb] = mma32<F16>(natural_frag<D>(tK, koff, kb0 + kb, kk), qf[kk], s[kb]);
       }
+    };
+    dma_tile<D, NW>(base + P, ld, 0, S, kbuf(0), wave, lane);
+    dma_tile<D, NW>(base + 2 * P, ld, 0, S, vbuf(0), wave, lane);
+    if (nkv > 1) dma_tile<D, NW>(base + P, ld, BKV, S, kbuf(1), wave, lane);
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    if (kb0 * 32 <= qmax_wave) logits(sacc[0], kbuf(0));
+
+    auto tile = [&](auto cur_c, int kt) {
+      constexpr int cur = decltype(cur_c)::value, nxt = cur ^ 1;
+      f32x16(&s)[NKB] = sacc[cur];
+      // K(kt + 1) and V(kt) have landed; K(kt) and V(kt - 1) are done with
+      asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      const int k0 = kt * BKV;
+      if (kt + 2 < nkv) dma_tile<D, NW>(base + P, ld, k0 + 2 * BKV, S, kbuf(cur), wave, lane);
+      if (kt + 1 < nkv) dma_tile<D, NW>(base + 2 * P, ld, k0 + BKV, S, vbuf(nxt), wave, lane);
+      if (k0 + BKV > S) {   // (uniform) keys past the last one: p = 0 has to meet v = 0
+        zero_rows<D, NW>(vbuf(cur), S - k0, wave, lane);
+        __syncthreads();
+      }
+      const int kw0 = k0 + kb0 * 32;
+      if (kw0 > qmax_wave) return;  // every key of this tile is masked for this wave
+      float m_new, mc, psum = 0.f;
+      auto maximum = [&]() {
+        float mx = s[0][0];
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[kb][e]);
+        m_new = fmaxf(m_run, max_of_halves(mx));
+        mc = m_new * c;
+      };
+      bf16x8 pf[2 * NKB];
+      auto probabilities = [&](int ks) {     // 16 keys
+#pragma unroll
+        for (int e = (ks & 1) * 8; e < (ks & 1) * 8 + 8; ++e) {
+          const float p = __builtin_amdgcn_exp2f(fmaf(s[ks >> 1][e], c, -mc));
+          s[ks >> 1][e] = p;
+          psum += p;
+        }
+        pf[ks] = pack8<F16>(s[ks >> 1], (ks & 1) * 8);
+      };
+      // (a tile that the diagonal crosses is the wave's last: blocks of 32 queries, keys at multiples of 32)
+      if (kt + 1 < nkv && kw0 + BKV <= qmax_wave) {
+        logits(sacc[nxt], kbuf(nxt));
+        maximum();
+#pragma unroll
+        for (int ks = 0; ks < NKB; ++ks) probabilities(ks);
+        interleave<NKB * KSTEPS, 1, 1, KSTEPS / 2, 5, 4>();
+      } else {
+        if (kw0 + NKB * 32 - 1 > q0 + rw * 32) {
+#pragma unroll
+          for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              const int key = kw0 + kb * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
+              if (key > qrow) s[kb][e] = -INFINITY;
+            }
+        }
+        maximum();
+#pragma unroll
+        for (int ks = 0; ks < NKB; ++ks) probabilities(ks);
+      }
+      // the running maximum rarely moves after the first tiles: skip the rescaling of the
+      // output accumulators when no lane of the wave needs it
+      if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+        l_run *= alpha;
+#pragma unroll
+        for (int i = 0; i < DB; ++i)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) oacc[i][e] *= alpha;
+        m_run = m_new;
+      }
+      // ---- O^T += V^T P^T, the second half of the probabilities between the matrix instructions of the first
+#pragma unroll
+      for (int ks = NKB; ks < 2 * NKB; ++ks) probabilities(ks);
+#pragma unroll
+      for (int ks = 0; ks < 2 * NKB; ++ks)
+#pragma unroll
+        for (int db = 0; db < DB; ++db) oacc[db] = mma32<F16>(tr_frag<D>(vbuf(cur), voff, kb0 * 2 + ks, db), pf[ks], oacc[db]);
+      interleave<2 * NKB * DB, 2, 2 * NKB * DB < 3 ? 2 * NKB * DB : 3, 0, 0, 4>();
+      l_run += psum;
+    };
+    for (int kt = 0; kt < nkv; kt += 2) {
+      tile(std::integral_constant<int, 0>{}, kt);
+      if (kt + 1 < nkv) tile(std::integral_constant<int, 1>{}, kt + 1);
     }
-    if constexpr (SW == 1) GPTS_PRIO(0);
-    // ---- causal mask (only tiles that reach past the first query of the wave) --------
-    if (kw0 + NKB * 32 - 1 > q0 + rw * 32) {
+  } else {
+    dma_tile<D, NW>(base + P, ld, 0, S, lds, wave, lane);
+    dma_tile<D, NW>(base + 2 * P, ld, 0, S, lds + TILE, wave, lane);
+
+    for (int kt = 0; kt < nkv; ++kt) {
+      asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      const int k0 = kt * BKV;
+      const char* tK = lds + (kt & 1) * 2 * TILE;
+      const char* tV = tK + TILE;
+      if (kt + 1 < nkv) {
+        char* nK = lds + ((kt + 1) & 1) * 2 * TILE;
+        dma_tile<D, NW>(base + P, ld, k0 + BKV, S, nK, wave, lane);
+        dma_tile<D, NW>(base + 2 * P, ld, k0 + BKV, S, nK + TILE, wave, lane);
+      }
+      if (k0 + BKV > S) {   // (uniform) keys past the last one: p = 0 has to meet v = 0
+        zero_rows<D, NW>(lds + (kt & 1) * 2 * TILE + TILE, S - k0, wave, lane);
+        __syncthreads();
+      }
+      const int kw0 = k0 + kb0 * 32;
+      if (kw0 > qmax_wave) continue;  // every key of this tile is masked for this wave
+
+      // ---- S^T = K Q^T for the wave's 32-key blocks ----------------------------------
+      f32x16 sacc[NKB];
+      if constexpr (SW == 1) GPTS_PRIO(1);
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sacc[kb][e] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS; ++kk) {
+          const bf16x8 kf = natural_frag<D>(tK, koff, kb0 + kb, kk);
+          sacc[kb] = mma32<F16>(kf, qf[kk], sacc[kb]);
+        }
+      }
+      if constexpr (SW == 1) GPTS_PRIO(0);
+      // ---- causal mask (only tiles that reach past the first query of the wave) --------
+      if (kw0 + NKB * 32 - 1 > q0 + rw * 32) {
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int key = kw0 + kb * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
+            if (key > qrow) sacc[kb][e] = -INFINITY;
+          }
+      }
+      // ---- online softmax ------------------------------------------------------------------
+      float mx = sacc[0][0];
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[kb][e]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m_run, mx);
+      const float mc = m_new * c;
+      float psum = 0.f;
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int key = kw0 + kb * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
-          if (key > qrow) sacc[kb][e] = -INFINITY;
+          const float p = __builtin_amdgcn_exp2f(fmaf(sacc[kb][e], c, -mc));
+          sacc[kb][e] = p;
+          psum += p;
         }
-    }
-    // ---- online softmax ------------------------------------------------------------------
-    float mx = sacc[0][0];
+      // the running maximum rarely moves after the first tiles: skip the rescaling of the
+      // output accumulators when no lane of the wave needs it
+      if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+        l_run *= alpha;
 #pragma unroll
-    for (int kb = 0; kb < NKB; ++kb)
+        for (int i = 0; i < DB; ++i)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[kb][e]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m_run, mx);
-    const float mc = m_new * c;
-    float psum = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(sacc[kb][e], c, -mc));
-        sacc[kb][e] = p;
-        psum += p;
+          for (int e = 0; e < 16; ++e) oacc[i][e] *= alpha;
+        m_run = m_new;
       }
-    // the running maximum rarely moves after the first tiles: skip the rescaling of the
-    // output accumulators when no lane of the wave needs it
-    if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
-      l_run *= alpha;
+      l_run += psum;
+      // ---- O^T += V^T P^T ------------------------------------------------------------------------
+      if constexpr (SW == 1) GPTS_PRIO(1);
 #pragma unroll
-      for (int i = 0; i < DB; ++i)
+      for (int ks = 0; ks < 2 * NKB; ++ks) {     // 16 keys per step
+        const bf16x8 pf = pack8<F16>(sacc[ks >> 1], (ks & 1) * 8);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) oacc[i][e] *= alpha;
-      m_run = m_new;
-    }
-    l_run += psum;
-    // ---- O^T += V^T P^T ------------------------------------------------------------------------
-    if constexpr (SW == 1) GPTS_PRIO(1);
-#pragma unroll
-    for (int ks = 0; ks < 2 * NKB; ++ks) {     // 16 keys per step
-      const bf16x8 pf = pack8<F16>(sacc[ks >> 1], (ks & 1) * 8);
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        const bf16x8 vf = tr_frag<D>(tV, voff, kb0 * 2 + ks, db);
-        oacc[db] = mma32<F16>(vf, pf, oacc[db]);
+        for (int db = 0; db < DB; ++db) {
+          const bf16x8 vf = tr_frag<D>(tV, voff, kb0 * 2 + ks, db);
+          oacc[db] = mma32<F16>(vf, pf, oacc[db]);
+        }
       }
+      if constexpr (SW == 1) GPTS_PRIO(0);
     }
-    if constexpr (SW == 1) GPTS_PRIO(0);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
@@ -869,6 +998,10 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 //             S=4096  n1280  71.0 | 67.4    n1536  76.0 | 78.2
 //      D=32   S=256   n 768   5.8 |  6.0    n 896   5.9 |  6.3      S=1024  n1152  16.0 | 15.6    n1280  15.6 | 16.7
 //             S=4096  n1280  49.1 | 48.2    n1536  53.7 | 55.5
+//   forward, 128 rows and four waves | 256 rows and eight, which copy each tile for twice the rows, D=128: whole pairs of rounds
+//      of the compute units or just under 1x4096x32 172 | 167, 1x8191x16 300 | 281, 4x2048x16 86.9 | 84.2, 1x3000x40 116 | 112,
+//      8x1024x16 56.8 | 55.7, but 16x512x16 40.3 | 43.0 and 32x256x16 33.1 | 36.1; between 1x6000x16 168 | 176, 4x1024x40
+//      67.4 | 72.9, 1x4096x24 118 | 126, 2x1984x16 53.7 | 58.8.
 //   backward, 128 rows and one wave per 32, one launch | 64 rows and two waves, one launch:
 //      D=128  S=128   n 128  13.9 | 12.9    n 192  14.7 | 16.4      S=256   n 256  21.4 | 19.9    n 320  24.0 | 24.6
 //             S=512   n 448  36.9 | 36.8    n 512  38.0 | 39.2      S=1024  n 576  63.3 | 61.6    n 640  64.5 | 67.7
@@ -901,6 +1034,11 @@ bool split_fwd(int B, int S, int a, int d) {
   static constexpr Limit k32[] = {{64, 1280}, {128, 768}, {192, 1536}, {400, 768}, {699, 912}, {4095, 1152}, {kAnyRows, 1280}};
   return d == 128 ? within(k128, B, S, a) : d == 64 ? within(k64, B, S, a) : within(k32, B, S, a);
 }
+// workgroups of 256 rows in whole pairs of rounds, a heavy one and a light one, or just under
+bool pairs_of_rounds(int B, int S, int a) {
+  const long wg = row_blocks(B, S, a, 256), pairs = (wg + 511) / 512;
+  return 7 * (pairs * 512 - wg) <= 512;
+}
 enum BwdForm { BWD_SPLIT64, BWD_BOTH128, BWD_EACH128, BWD_EACH256 };
 BwdForm bwd_form(int B, int S, int a, int d) {
   static constexpr Limit k128[] = {{64, 0},     {128, 128},  {192, 256},  {320, 288},       {512, 448},
@@ -911,15 +1049,23 @@ BwdForm bwd_form(int B, int S, int a, int d) {
                                   {800, 768}, {1500, 1024}, {3500, 1152}, {kAnyRows, 1536}};
   if (d == 128 ? within(k128, B, S, a) : d == 64 ? within(k64, B, S, a) : within(k32, B, S, a)) return BWD_SPLIT64;
   if (row_blocks(B, S, a, 64) <= 1700) return BWD_BOTH128;
-  const long wg = row_blocks(B, S, a, 256), rounds2 = (wg + 511) / 512;   // pairs of rounds: a heavy workgroup and a light one
-  return d == 128 && 7 * (rounds2 * 512 - wg) <= 512 && (S >= 3500 || rounds2 == 1) ? BWD_EACH256 : BWD_EACH128;
+  return d == 128 && pairs_of_rounds(B, S, a) && (S >= 3500 || row_blocks(B, S, a, 256) <= 512) ? BWD_EACH256 : BWD_EACH128;
 }
 
 template <int D, bool F16>
 void launch_fwd(const bf16* qkv, bf16* out, float* lse, int B, int S, int a, int n, size_t stride, hipStream_t st) {
   auto grid = [&](int rows) { return dim3(a, B * n, (S + rows - 1) / rows); };
-  if (split_fwd(B, S, a, D)) hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 2, 2>), grid(64), dim3(256), 0, st, qkv, out, lse, S, a, B, stride);
-  else hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 4, 1>), grid(128), dim3(256), 0, st, qkv, out, lse, S, a, B, stride);
+  if (split_fwd(B, S, a, D)) {
+    hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 2, 2>), grid(64), dim3(256), 0, st, qkv, out, lse, S, a, B, stride);
+    return;
+  }
+  if constexpr (D == 128) {
+    if (S >= 1000 && pairs_of_rounds(B, S, a)) {
+      hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 8, 1>), grid(256), dim3(512), 0, st, qkv, out, lse, S, a, B, stride);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 4, 1>), grid(128), dim3(256), 0, st, qkv, out, lse, S, a, B, stride);
 }
 
 template <int D, bool F16> void launch_bwd(const bf16* out, BwdArgs p, int n, hipStream_t st) {

@@ -1000,6 +1000,33 @@ def test_op_attention_bf16_forms_with_one_wave_agree_bit_for_bit(S, few, many, d
         assert torch.equal(x[:few], y), name
 
 
+@pytest.mark.parametrize("S,few,many", [(1000, 100, 128), (1030, 64, 90), (1279, 60, 102), (1281, 60, 80)])
+def test_op_attention_bf16_forward_in_eight_waves(S, few, many):
+    """Many long sequences of head dimension 128 go in workgroups of eight waves, fewer in four: the same bits.  Keys 4 .. 7 of
+    every eight have logits eight times as large, so that the maximum is in the other half of the wave from half of the
+    keys; against 64 bits: out rounds to bf16 the sum of probabilities rounded to bf16."""
+    print(f"[case] attention forward eight waves S={S} sequences={few},{many}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(S)
+    qkv = torch.empty(many, S, 3 * 128, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    big = torch.arange(S, device="cuda") % 8 >= 4
+    qkv[:, big, 128:256] *= 8
+    got = []
+    for n in (many, few):
+        out = torch.full((n, S, 128), 7.0, dtype=torch.bfloat16, device="cuda")
+        lse = torch.full((n, 1, S), 7.0, device="cuda")
+        scratch = torch.empty(256, dtype=torch.uint8, device="cuda")
+        B.gpt_stage_op_attention_fwd(B.GPTS_BF16, n, S, 1, 128, qkv[:n].contiguous(), out, lse, scratch)
+        got.append((out, lse))
+    assert torch.equal(got[0][0][:few], got[1][0]) and torch.equal(got[0][1][:few], got[1][1])
+    q, k, v = (t.double() for t in qkv[many - 1].split(128, dim=1))
+    s = (q @ k.t() / 128 ** 0.5).masked_fill(torch.ones(S, S, dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+    p = torch.softmax(s, dim=-1)
+    bound = 2.0 ** -8 * (p @ v.abs()) + 2.0 ** -8 * (p @ v).abs() + 1e-6
+    assert ((got[0][0][many - 1].double() - p @ v).abs() <= bound).all()
+    assert (got[0][1][many - 1, 0].double() - torch.logsumexp(s, dim=-1)).abs().max().item() <= 1e-4
+
+
 @pytest.mark.parametrize("S,a,d", [(70, 2, 128), (97, 1, 64), (65, 3, 32), (70, 500, 64)])
 def test_op_attention_bf16_rows_past_the_end_count_as_zeros(S, a, d):
     """The last tile's rows past the sequence's end hold a copy of its last row: with an infinite value there
