@@ -195,6 +195,18 @@ template <int D> __device__ __forceinline__ bf16x8 natural_frag(const char* tile
   return *reinterpret_cast<const bf16x8*>(tile + kk / KP * kPanelBytes<D> + rb * 32 * (kPanel<D> * 2) + (off ^ (kk % KP << 5)));
 }
 
+// element e of 16 bf16 values: an operation on the packed pair, where a conversion would first take it apart
+__device__ __forceinline__ float element_of(const bf16x8 (&v)[2], int e) {
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  const unsigned w = __builtin_bit_cast(u32x4, v[e >> 3])[(e & 7) >> 1];
+  return __builtin_bit_cast(float, e & 1 ? w & 0xffff0000u : w << 16);
+}
+
+template <int... I, class F> __device__ __forceinline__ void static_for_seq(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F> __device__ __forceinline__ void static_for(F&& f) { static_for_seq(std::make_integer_sequence<int, N>{}, f); }
+
 // the larger of a lane's value and that of lane ^ 32
 __device__ __forceinline__ float max_of_halves(float v) {
   const unsigned x = __builtin_bit_cast(unsigned, v);
@@ -682,6 +694,8 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
         }
         pf[0] = pack8(sacc, 0);
         pf[1] = pack8(sacc, 8);
+        settle(pf[0]);
+        settle(pf[1]);
       }
       {
         // dP begins at -delta (not at D = 32, whose two steps leave the read of -delta nothing to hide behind)
@@ -699,15 +713,43 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
         for (int kk = 0; kk < KSTEPS; ++kk)
           dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(natural_frag<D>(tO, aoff, qb, kk), vfr[kk], dpacc, 0, 0, 0);
         GPTS_PRIO(0);
+        if constexpr (FROM_DELTA) {
+          // dV's run of matrix instructions with dS between them, then dK's, instead of dS in front of both.  With dS from the
+          // packed P, which leaves 16 conversions and 8 registers out, us for both sides, before | after: 1x8191x16x128
+          // 857 | 828, 1x4096x32x128 453 | 443, 1x4096x24x128 365 | 355, 1x2048x40x128 170.5 | 166.8, 1x2048x16x128 90.9 | 85.2,
+          // 2x4096x32x64 550 | 542, 4x1024x16x64 49.9 | 48.4; without the packed P 2x4096x32x64 562, 1x2048x16x128 98.  (The
+          // exponentials between dP's too: spills, 898 at 1x8191x16x128; the query side in such runs: 415 | 421 of its own.)
+          constexpr int N = 2 * DB, AHEAD = 2;
+          bf16x8 fr[2 * N];
+          auto load = [&](auto i_c) {
+            constexpr int i = decltype(i_c)::value, x = i % N;
+            fr[i] = tr_frag<D>(i < N ? tO : tQ, toff, qb * 2 + x / DB, x % DB);
+          };
+          static_for<AHEAD>(load);
+          __builtin_amdgcn_sched_barrier(0);
+          static_for<2 * N>([&](auto i_c) {
+            constexpr int i = decltype(i_c)::value, x = i % N;
+            // the elements of dS after instruction x: none after the first, beside which dP is completed
+            constexpr int first = x < 2 ? 0 : (x - 1) * 16 / (N - 1), last = x * 16 / (N - 1);
+            if constexpr (i + AHEAD < 2 * N) load(std::integral_constant<int, i + AHEAD>{});
+            if constexpr (i < N) {
+              dv[x % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], pf[x / DB], dv[x % DB], 0, 0, 0);
+#pragma unroll
+              for (int e = first; e < last; ++e) dpacc[e] = element_of(pf, e) * dpacc[e];
+              if constexpr (first < 8 && last >= 8) dsf[0] = pack8(dpacc, 0);
+              if constexpr (last == 16) dsf[1] = pack8(dpacc, 8);
+            } else {
+              dk[x % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], dsf[x / DB], dk[x % DB], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          });
+          continue;
+        }
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          f32x4 Dn = {0.f, 0.f, 0.f, 0.f};
-          if constexpr (!FROM_DELTA) Dn = *reinterpret_cast<const f32x4*>(Ds + g * 8);
+          const f32x4 Dn = *reinterpret_cast<const f32x4*>(Ds + g * 8);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float dp = FROM_DELTA ? dpacc[g * 4 + e] : dpacc[g * 4 + e] + Dn[e];
-            dpacc[g * 4 + e] = (float)pf[g >> 1][(g & 1) * 4 + e] * dp;
-          }
+          for (int e = 0; e < 4; ++e) dpacc[g * 4 + e] = element_of(pf, g * 4 + e) * (dpacc[g * 4 + e] + Dn[e]);
         }
         dsf[0] = pack8(dpacc, 0);
         dsf[1] = pack8(dpacc, 8);
