@@ -1000,13 +1000,15 @@ __device__ __forceinline__ void dq_block(const BwdArgs& args, int qt, char* lds)
 }
 
 // Key side and query side a launch each, 32 RW rows per workgroup, the query side first (it forms delta): the form for
-// many workgroups.
-template <int D, bool F16S, int RW> __global__ __launch_bounds__(64 * RW) void attn_bwd_dkv_mfma_kernel(const BwdArgs p) {
+// many workgroups.  Held to 256 registers (they need 254 and 253 at head dimension 128, nothing spilt), two workgroups of four
+// waves share a unit; left to itself the compiler took 278 and 304, and accumulators apart from the others.  Both sides,
+// us: 2x4096x24x128 1005 | 687, 4x2048x24x128 562 | 389, 16x512x24x128 239 | 181, 2x4096x32x64 543 | 496, 1x8191x32x32 730 | 595.
+template <int D, bool F16S, int RW> __global__ __launch_bounds__(64 * RW, 2) void attn_bwd_dkv_mfma_kernel(const BwdArgs p) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kBwdTiles<F16S> * BKV * D * 2];
   __shared__ __attribute__((aligned(256))) float stat[2][2][BKV];  // [stage][lse | delta][row]
   dkv_block<D, F16S, RW, 1, true>(p, blockIdx.z, lds, stat);
 }
-template <int D, bool F16S, int RW> __global__ __launch_bounds__(64 * RW) void attn_bwd_dq_mfma_kernel(const BwdArgs p) {
+template <int D, bool F16S, int RW> __global__ __launch_bounds__(64 * RW, 2) void attn_bwd_dq_mfma_kernel(const BwdArgs p) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kBwdTiles<F16S> * BKV * D * 2];
   dq_block<D, F16S, RW, 1>(p, gridDim.z - 1 - blockIdx.z, lds);
 }
@@ -1055,11 +1057,11 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 //             S=512   n 768  21.2 | 19.8    n 896  22.0 | 22.2      S=1024  n1024  34.6 | 33.2    n1152  35.7 | 37.0
 //             S=4096  n1536   148 |  143    n1792   166 |  166
 //   backward, 128 rows, time of a launch each over that of one launch, D=128 | 64, S 1024 ... 16384: n 1536 0.95 ... 1.04 |
-//      0.94 ... 1.06, n 2560 0.96 ... 1.07 | 0.96 ... 1.01, n 5120 0.90 ... 0.97 | 0.85 ... 0.99 (the one launch needs
-//      delta from a pass of its own, and its two kinds of workgroup share no tiles).
+//      0.94 ... 1.06, beyond less (the one launch needs delta from a pass of its own, and its two kinds of workgroup share no
+//      tiles).
 //   backward, a launch each, time of 256 rows over 128: D=128, S >= 3500, whole pairs of rounds of the compute units or
-//      just under: n 1792 0.96 ... 0.99, n 2048 0.92 ... 0.96, n 4096 0.96 ... 1.01; between: n 2304 1.01 ... 1.03, n 2560
-//      1.03 ... 1.06; S=2048 n 2048 0.95, n 4096 1.03; D=64 and 32 1.0 ... 1.3 everywhere.
+//      just under: n 2048 0.93, n 4096 0.96; between: n 3072 1.00; S=2048 n 2048 0.97, n 3072 1.01; S=1024 n 3072 1.04; S=512
+//      1.09; D=64 and 32 1.0 ... 1.3 everywhere.
 // (192 rows are three blocks of 64 or two of 128, whose second one is half empty: a limit of their own at D=32.)
 long row_blocks(int B, int S, int a, int rows) { return (long)a * B * ((S + rows - 1) / rows); }
 struct Limit { int rows, most; };   // sequences of up to `rows`: at most so many blocks of 64 rows
