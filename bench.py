@@ -36,8 +36,8 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 # commands and the per-kernel figures).  Only reported while the sources of the kernel and of the
 # choice of its tiles are the ones the counters were taken on.
 GEMM_SOURCES = ("agpr_ops.hpp", "gemm_tiles.hpp", "gemm_mfma.hip")
-GEMM_TRAFFIC = {"workload": "decoupled_bf16", "weight_phase": True, "bytes_per_launch": 970.6 * 2**20,
-                "source_sha256_16": "c85973da4f2e5473"}
+GEMM_TRAFFIC = {"workload": "decoupled_bf16", "weight_phase": True, "bytes_per_launch": 966.8 * 2**20,
+                "source_sha256_16": "ecb8a41049140eff"}
 PEAK_FP32_TFLOPS = 157.3    # MI355X fp32 vector
 DEFAULT_WORKLOAD = "decoupled_bf16"
 
