@@ -140,7 +140,7 @@ template <int D, int NW> __device__ __forceinline__ void zero_rows(char* tile, i
     if (i / CPR % BKV >= first) *reinterpret_cast<f32x4*>(tile + i * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
-// -delta[b][n][s], delta = sum_d dO * O (the key side's dP begins at it): one row of a head per D/8 lanes.
+// delta[b][n][s] = sum_d dO * O: one row of a head per D/8 lanes.
 template <int D, bool O16>
 __global__ __launch_bounds__(256) void attn_delta_kernel(const bf16* __restrict__ out0, const bf16* __restrict__ dout0,
                                                          float* __restrict__ delta0, int S, int a, int total, size_t stride) {
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const bf16* __restrict_
   for (int x = TPR / 2; x > 0; x >>= 1) acc += __shfl_xor(acc, x, 64);
   if (cc == 0 && i < total) {
     const int n = i % a, bs = i / a, b = bs / S, row = bs % S;
-    delta[((size_t)b * a + n) * S + row] = -acc;
+    delta[((size_t)b * a + n) * S + row] = acc;
   }
 }
 
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(64 * RW * SW, 2) void attn_fwd_mfma_kernel(const bf
 struct BwdArgs {
   const bf16 *qkv, *qk16, *dout, *out;   // out: where the query side forms delta, else null
   const float* lse;
-  float* delta;          // -delta, [b][n][s]; where the query side forms it, -lse log2(e) behind
+  float* delta;
   bf16* dqkv;
   int S, a, B;           // B sequences per micro-batch
   size_t act, grad;      // bytes between the micro-batches' dqkv (grad) and everything else (act)
@@ -557,7 +557,7 @@ __device__ __forceinline__ BwdArgs at_microbatch(BwdArgs p, int mb) {
 // query rows at and after them in tiles of 64: Q and dO, lse and delta, all by DMA.  Per wave and 32-query block:
 //   S[q][k]  = Q K^T       (A = Q fragment from LDS, B = K fragment in registers)
 //   dP[q][k] = dO V^T      (A = dO fragment from LDS, B = V fragment in registers)
-//   P = exp(S/sqrt(D) - lse_q),  dS = P (dP - delta_q), dP's accumulator beginning at -delta_q
+//   P = exp(S/sqrt(D) - lse_q),  dS = P (dP - delta_q)
 //   dV^T[d][k] += dO^T P   (A = transposing fragment of dO, B = P from the accumulator)
 //   dK^T[d][k] += Q^T dS   (A = transposing fragment of Q,  B = dS)
 // so a lane owns one key column and nothing moves between lanes.
@@ -568,17 +568,18 @@ __device__ __forceinline__ BwdArgs at_microbatch(BwdArgs p, int mb) {
 // RW x SW waves: RW blocks of 32 keys; with SW = 2 a second wave per block takes the other 32 queries
 // of every tile and the two sums are added through LDS at the end.
 template <bool F16S> constexpr int kBwdTiles = F16S ? 3 : 2;   // LDS tiles of a stage: [Q | dO | fp16 Q] or [K | V | fp16 K]
-// SCALED: the query side ran before and has left -lse log2(e), else that is formed here (the same bits).  That is 1 % of both
-// sides at 1x8191x16x128, dP beginning at -delta 1 % (943 -> 925 us together) and 1.5 % at 4x1024x16x64 (55.9 -> 55.0).  Left
-// to attn_delta_kernel, whose lanes have one head each, its scattered second array costs more than it gives (16x333x12x32
-// 21.7 -> 22.4 us).
-template <int D, bool F16S, int RW, int SW, bool SCALED>
+// The exponent is S/sqrt(D) - lse, rounded once, times log2(e), and delta is subtracted from the whole dP.  log2(e) taken into
+// both terms beforehand, or dP begun at -delta, would be an operation an element less (1 % of both sides each at
+// 1x8191x16x128), but round at the terms' size and not at the difference's: P's relative error at logits of 100, D = 64, 1.4e-7 ->
+// 1.5e-6, at 32 and 128 9e-7 -> 2e-6.
+template <int D, bool F16S, int RW, int SW>
 __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* lds, float (*stat)[2][BKV]) {
   const int mb = microbatch(args.B, args.act);
   const BwdArgs p = at_microbatch(args, mb);
   const bf16* const __restrict__ qkv = p.qkv;
   const bf16* const __restrict__ qk16 = p.qk16;
   const bf16* const __restrict__ dout = p.dout;
+  const float* const __restrict__ lse = p.lse;
   const float* const __restrict__ delta = p.delta;
   bf16* const __restrict__ dqkv = p.dqkv;
   const int S = p.S, a = p.a;
@@ -593,7 +594,7 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
   const bf16* base16 = qk16 + (size_t)b * S * ld + (size_t)n * D;
   const bf16* dobase = dout + (size_t)b * S * P + (size_t)n * D;
   const int ntile = (S + BKV - 1) / BKV;
-  const float* lse_h = (SCALED ? delta + (size_t)p.B * a * S : p.lse) + ((size_t)b * a + n) * S;
+  const float* lse_h = lse + ((size_t)b * a + n) * S;
   const float* delta_h = delta + ((size_t)b * a + n) * S;
   const int rw = wave % RW, half = wave / RW;
   const int k0 = blk * (32 * RW);
@@ -601,7 +602,7 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
   const int ql = lane & 31, h = lane >> 5;
   const int key = kw0 + ql;
   const int kclamp = key < S ? key : S - 1;
-  const float c = 1.4426950408889634f / sqrtf((float)D);  // log2(e)/sqrt(D)
+  const float rsd = 1.f / sqrtf((float)D);
 
   bf16x8 kfr[KSTEPS], vfr[KSTEPS];
 #pragma unroll
@@ -683,7 +684,7 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
           const f32x4 L = *reinterpret_cast<const f32x4*>(Ls + g * 8);
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            sacc[g * 4 + e] = __builtin_amdgcn_exp2f(fmaf(sacc[g * 4 + e], c, SCALED ? L[e] : L[e] * -1.4426950408889634f));
+            sacc[g * 4 + e] = __builtin_amdgcn_exp2f(fmaf(sacc[g * 4 + e], rsd, -L[e]) * 1.4426950408889634f);
         }
         if (masked) {
 #pragma unroll
@@ -698,44 +699,49 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
         settle(pf[1]);
       }
       {
-        // dP begins at -delta (not at D = 32, whose two steps leave the read of -delta nothing to hide behind)
-        constexpr bool FROM_DELTA = D >= 64;
         f32x16 dpacc;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          f32x4 Dn = {0.f, 0.f, 0.f, 0.f};
-          if constexpr (FROM_DELTA) Dn = *reinterpret_cast<const f32x4*>(Ds + g * 8);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dpacc[g * 4 + e] = Dn[e];
-        }
+        for (int e = 0; e < 16; ++e) dpacc[e] = 0.f;
         GPTS_PRIO(1);
 #pragma unroll
         for (int kk = 0; kk < KSTEPS; ++kk)
           dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(natural_frag<D>(tO, aoff, qb, kk), vfr[kk], dpacc, 0, 0, 0);
         GPTS_PRIO(0);
-        if constexpr (FROM_DELTA) {
+        if constexpr (D >= 64) {
           // dV's run of matrix instructions with dS between them, then dK's, instead of dS in front of both.  With dS from the
-          // packed P, which leaves 16 conversions and 8 registers out, us for both sides, before | after: 1x8191x16x128
-          // 857 | 828, 1x4096x32x128 453 | 443, 1x4096x24x128 365 | 355, 1x2048x40x128 170.5 | 166.8, 1x2048x16x128 90.9 | 85.2,
-          // 2x4096x32x64 550 | 542, 4x1024x16x64 49.9 | 48.4; without the packed P 2x4096x32x64 562, 1x2048x16x128 98.  (The
-          // exponentials between dP's too: spills, 898 at 1x8191x16x128; the query side in such runs: 415 | 421 of its own.)
+          // packed P, which leaves 16 conversions and 8 registers out, us for both sides, in front unpacked | in front from the
+          // packed P | this: 1x8191x16x128 869 | 856 | 842, 1x2048x16x128 88.9 | 88.3 | 84.4, 4x1000x16x128 83.5 | 82.5 | 81.0,
+          // 2x4096x32x64 517 | 506 | 497, 4x1024x16x64 50.3 | 48.4 | 46.9; no gain where a head has few blocks, 8x333x24x128 58.4 |
+          // 59.5 | 58.7.  (The exponentials between dP's too: spills, 898 against 828 with dP begun at -delta at 1x8191x16x128; the
+          // query side in such runs: 415 | 421 of its own.)
           constexpr int N = 2 * DB, AHEAD = 2;
           bf16x8 fr[2 * N];
+          f32x4 Dl[4];
           auto load = [&](auto i_c) {
             constexpr int i = decltype(i_c)::value, x = i % N;
             fr[i] = tr_frag<D>(i < N ? tO : tQ, toff, qb * 2 + x / DB, x % DB);
           };
+          // delta, four at a time: all in front at D = 64 (4x1024x16x64 47.6 -> 46.9), at 128, where registers are few, ahead of
+          // their elements by an instruction or two
+          auto load_delta = [&](int g) { Dl[g] = *reinterpret_cast<const f32x4*>(Ds + g * 8); };
           static_for<AHEAD>(load);
+#pragma unroll
+          for (int g = 0; g < (D == 64 ? 4 : 1); ++g) load_delta(g);
           __builtin_amdgcn_sched_barrier(0);
           static_for<2 * N>([&](auto i_c) {
             constexpr int i = decltype(i_c)::value, x = i % N;
             // the elements of dS after instruction x: none after the first, beside which dP is completed
             constexpr int first = x < 2 ? 0 : (x - 1) * 16 / (N - 1), last = x * 16 / (N - 1);
             if constexpr (i + AHEAD < 2 * N) load(std::integral_constant<int, i + AHEAD>{});
+            if constexpr (D != 64) {
+#pragma unroll
+              for (int g = 1; g < 4; ++g)
+                if (i == 4 * g * (N - 1) / 16) load_delta(g);
+            }
             if constexpr (i < N) {
               dv[x % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i], pf[x / DB], dv[x % DB], 0, 0, 0);
 #pragma unroll
-              for (int e = first; e < last; ++e) dpacc[e] = element_of(pf, e) * dpacc[e];
+              for (int e = first; e < last; ++e) dpacc[e] = element_of(pf, e) * (dpacc[e] - Dl[e >> 2][e & 3]);
               if constexpr (first < 8 && last >= 8) dsf[0] = pack8(dpacc, 0);
               if constexpr (last == 16) dsf[1] = pack8(dpacc, 8);
             } else {
@@ -747,9 +753,9 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
         }
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const f32x4 Dn = *reinterpret_cast<const f32x4*>(Ds + g * 8);
+          const f32x4 Dl = *reinterpret_cast<const f32x4*>(Ds + g * 8);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) dpacc[g * 4 + e] = element_of(pf, g * 4 + e) * (dpacc[g * 4 + e] + Dn[e]);
+          for (int e = 0; e < 4; ++e) dpacc[g * 4 + e] = element_of(pf, g * 4 + e) * (dpacc[g * 4 + e] - Dl[e]);
         }
         dsf[0] = pack8(dpacc, 0);
         dsf[1] = pack8(dpacc, 8);
@@ -819,7 +825,7 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
 // grid (heads, batch, query blocks), heaviest first.
 // RW x SW waves as above, SW = 2 splitting the keys of a tile.
 // out (may be null): the forward output (fp16 with F16S); delta_q = sum_d dO * O is then formed here, where dO is in
-// registers anyway, and written for the key side, which runs after, with lse_q.  Null: they are there already.
+// registers anyway, and written for the key side, which runs after.  Null: delta is there already.
 template <int D, bool F16S, int RW, int SW>
 __device__ __forceinline__ void dq_block(const BwdArgs& args, int qt, char* lds) {
   const int mb = microbatch(args.B, args.act);
@@ -871,13 +877,9 @@ __device__ __forceinline__ void dq_block(const BwdArgs& args, int qt, char* lds)
 #pragma unroll
       for (int kk = 0; kk < x; ++kk) part[kk] += part[kk + x];
     Dl = part[0] + __shfl_xor(part[0], 32, 64);
-    if (kb0 == 0 && h == 0 && qrow < S) {
-      const size_t j = ((size_t)b * a + n) * S + qrow;
-      delta[j] = -Dl;
-      delta[(size_t)p.B * a * S + j] = -L2;
-    }
+    if (kb0 == 0 && h == 0 && qrow < S) delta[((size_t)b * a + n) * S + qrow] = Dl;
   } else {
-    Dl = -delta[((size_t)b * a + n) * S + qclamp];
+    Dl = delta[((size_t)b * a + n) * S + qclamp];
   }
 #pragma unroll
   for (int kk = 0; kk < KSTEPS; ++kk) {
@@ -1006,7 +1008,7 @@ __device__ __forceinline__ void dq_block(const BwdArgs& args, int qt, char* lds)
 template <int D, bool F16S, int RW> __global__ __launch_bounds__(64 * RW, 2) void attn_bwd_dkv_mfma_kernel(const BwdArgs p) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kBwdTiles<F16S> * BKV * D * 2];
   __shared__ __attribute__((aligned(256))) float stat[2][2][BKV];  // [stage][lse | delta][row]
-  dkv_block<D, F16S, RW, 1, true>(p, blockIdx.z, lds, stat);
+  dkv_block<D, F16S, RW, 1>(p, blockIdx.z, lds, stat);
 }
 template <int D, bool F16S, int RW> __global__ __launch_bounds__(64 * RW, 2) void attn_bwd_dq_mfma_kernel(const BwdArgs p) {
   __shared__ __attribute__((aligned(1024))) char lds[2 * kBwdTiles<F16S> * BKV * D * 2];
@@ -1022,7 +1024,7 @@ __global__ __launch_bounds__(64 * RW * SW, F16S && D == 128 && RW * SW == 4 ? 1 
   __shared__ __attribute__((aligned(256))) float stat[2][2][BKV];
   const int i = blockIdx.z >> 1;
   if ((blockIdx.z & 1) == 0)
-    dkv_block<D, F16S, RW, SW, false>(p, i, lds, stat);
+    dkv_block<D, F16S, RW, SW>(p, i, lds, stat);
   else
     dq_block<D, F16S, RW, SW>(p, (int)(gridDim.z >> 1) - 1 - i, lds);
 }
@@ -1156,7 +1158,7 @@ static bool microbatches_fit(int B, int n) { return n == 1 || (n > 1 && (long)B 
 
 size_t attention_mfma_scratch_bytes(int B, int S, int a, int d, int phase) {
   // forward uses none; the least amount keeps a null scratch refused, as where it does
-  return phase == 0 ? 256 : align256(2 * (size_t)B * a * S * sizeof(float));   // delta, lse
+  return phase == 0 ? 256 : align256((size_t)B * a * S * sizeof(float));   // delta
 }
 
 hipError_t attention_fwd_mfma(int B, int S, int a, int d, const void* qkv, void* out, float* lse,

@@ -162,7 +162,7 @@ hipError_t attention_fwd_f32(int B, int S, int a, int d, const void* qkv, void* 
 hipError_t attention_bwd_f32(int B, int S, int a, int d, const void* qkv, const void* out, const float* lse,
                              const void* dout, void* dqkv, hipStream_t st);
 
-// bf16 MFMA attention (head_dim 32, 64 or 128).  scratch (backward: delta and lse of every query): device memory of
+// bf16 MFMA attention (head_dim 32, 64 or 128).  scratch (backward: delta): device memory of
 // attention_mfma_scratch_bytes(B, S, a, d, 1) bytes; phase 0: what the forward entry points ask for, see there.
 bool attention_mfma_supported(int B, int S, int a, int d);   // head_dim 32/64/128 and index ranges
 size_t attention_mfma_scratch_bytes(int B, int S, int a, int d, int phase);

@@ -814,7 +814,7 @@ int stage_window(const gpt_stage_params* p, int W, size_t act_stride, size_t gra
   const Dims D(c);
   const int widest = D.H > D.P ? D.H : D.P;
   bool ok = attention_mfma_supported(D.B, D.S, D.a, D.d) && D.F >= widest && fc1_sum_rows(D, c.dtype) > 0 &&
-            attention_mfma_scratch_bytes(D.B, D.S, D.a, D.d, 1) <= align_up((size_t)D.T * D.H * kResBytes, 256);
+            (size_t)D.T * D.a * 4 <= (size_t)D.T * D.H * kResBytes;
   LinDims L[4];
   linears(D, L);
   for (const LinDims& lin : L)

@@ -1000,6 +1000,53 @@ def test_op_attention_bf16_forms_with_one_wave_agree_bit_for_bit(S, few, many, d
         assert torch.equal(x[:few], y), name
 
 
+_KEY_SIDE_FORMS = pytest.mark.parametrize("S,a", [(32, 2), (70, 2), (128, 300), (130, 1200)])   # 64 rows, 128, 128 in a launch for each side
+
+
+def _attention_bwd_op(qkv, out, lse, dout):
+    _, S, _, a, d = qkv.shape
+    scratch = torch.empty(max(B.gpt_stage_op_attention_scratch_bytes(B.GPTS_BF16, 1, S, a, d, 1), 256), dtype=torch.uint8, device="cuda")
+    dqkv = torch.full_like(qkv, 7.0)
+    B.gpt_stage_op_attention_bwd(B.GPTS_BF16, 1, S, a, d, qkv, out, lse, dout, dqkv, scratch)
+    return dqkv[0].float()
+
+
+@_KEY_SIDE_FORMS
+def test_op_attention_bf16_key_side_exponent_rounds_at_the_size_of_the_difference(S, a):
+    """Logits of 2^20 for the last query and an lse 3/8 above them, both whole eighths: P = exp(-3/8) but for the roundings of the
+    difference, of log2(e) and of the power, under 2^-20 together, so dV is 32 times bf16(P) (175.95/256, far from a tie).
+    The other queries' P is 0 (lse 2^20 above their logits)."""
+    print(f"[case] attention key side exponent S={S} a={a}", flush=True)
+    qkv = torch.zeros(1, S, 3, a, 64, dtype=torch.bfloat16, device="cuda")
+    out, dout = torch.zeros(2, 1, S, a, 64, dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((1, a, S), 2.0 ** 20, device="cuda")
+    qkv[:, -1, 0, :, 0] = 2.0 ** 12
+    qkv[:, :, 1, :, 0] = 2.0 ** 11
+    dout[:, -1] = 32.0
+    lse[:, :, -1] += 0.375
+    dv = _attention_bwd_op(qkv, out, lse, dout)[:, 2]
+    assert torch.equal(dv, torch.full_like(dv, 32.0 * 176 / 256))
+
+
+@_KEY_SIDE_FORMS
+def test_op_attention_bf16_key_side_takes_delta_from_the_whole_dp(S, a):
+    """delta = -(2^24 + 2^16), halfway between two bf16 values, and dP = 4, one from every 16 columns: dP - delta is
+    2^24 + 2^16 + 4 exactly and rounds up; a sum that began at -delta would stay halfway.  The last query's P is 1 (logits and lse
+    0), the others' 0, and dK = dS q / sqrt(64)."""
+    print(f"[case] attention key side delta S={S} a={a}", flush=True)
+    qkv = torch.zeros(1, S, 3, a, 64, dtype=torch.bfloat16, device="cuda")
+    out, dout = torch.zeros(2, 1, S, a, 64, dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((1, a, S), 2.0 ** 20, device="cuda")
+    lse[:, :, -1] = 0.0
+    qkv[:, -1, 0, :, 1] = 1.0                   # (K is 0: the logits stay 0)
+    qkv[:, :, 2, :, ::16] = 2.0 ** -12
+    dout[:, -1, :, ::16] = 2.0 ** 12
+    out[:, -1, :, 0] = -(2.0 ** 12)
+    out[:, -1, :, 16] = -(2.0 ** 4)
+    dk = _attention_bwd_op(qkv, out, lse, dout)[:, 1, :, 1]
+    assert torch.equal(dk, torch.full_like(dk, (2.0 ** 24 + 2.0 ** 17) / 8))
+
+
 @pytest.mark.parametrize("S,few,many", [(1000, 100, 128), (1030, 64, 90), (1279, 60, 102), (1281, 60, 80)])
 def test_op_attention_bf16_forward_in_eight_waves(S, few, many):
     """Many long sequences of head dimension 128 go in workgroups of eight waves, fewer in four: the same bits.  Keys 4 .. 7 of
