@@ -464,14 +464,20 @@ def test_dpp_weight_phase_per_chunk_and_window():
     (128, 2, 64, 256, 64, 1, 1, 4, 4, True), (192, 4, 32, 320, 192, 3, 2, 7, 3, False), (320, 2, 128, 448, 320, 1, 1, 5, 5, False),
     (1024, 16, 64, 4096, 512, 1, 1, 8, 8, False), (2048, 4, 128, 2112, 64, 2, 2, 3, 2, True),
     (512, 8, 64, 512, 1216, 1, 1, 8, 8, True), (768, 12, 64, 3072, 576, 1, 1, 8, 8, False),
-    (1024, 16, 64, 4096, 960, 1, 1, 8, 8, True), (1280, 20, 64, 5120, 1088, 1, 1, 8, 8, False)])
+    (1024, 16, 64, 4096, 960, 1, 1, 8, 8, True), (1280, 20, 64, 5120, 1088, 1, 1, 8, 8, False),
+    (256, 4, 64, 512, 384, 1, 1, 8, 8, True), (256, 4, 64, 512, 384, 1, 2, 8, 8, False),
+    (64, 64, 32, 2048, 1728, 1, 1, 4, 4, True), (64, 64, 128, 8192, 1792, 1, 1, 4, 4, False)])
 def test_dpp_passes_over_a_window_keep_every_bit(hidden, heads, d, ffn, seq, batch, layers, M, W, spaced):
     """A chunk's micro-batches of a window run as one pass per operator; under a tracer they run one by one.  The
     same bits in every output, with the callers' buffers equally spaced or not, dx in place of dy, gradients that
-    are not zero to begin with, boundary buffers just enough for the plan, and the last window shorter.  The last
-    four have products of at most 256 tiles a micro-batch and more in a pass, most with ragged rows: 512 k in 128x128 and
+    are not zero to begin with, boundary buffers just enough for the plan, and the last window shorter.  The sixth to
+    ninth have products of at most 256 tiles a micro-batch and more in a pass, most with ragged rows: 512 k in 128x128 and
     128x64 with two stages; 768 k in 128x128, and GeLU' in 128x64 with four stages alone and two in a pass; 256x192, 256x256,
-    and GeLU' in 128x128 with four and two stages; 192x192, 256x160, 256x128, and 128x128 with two stages (3840 k) and four (5120)."""
+    and GeLU' in 128x128 with four and two stages; 192x192, 256x160, 256x128, and 128x128 with two stages (3840 k) and four (5120).
+    All but the tenth and eleventh have room for the partial sums of the qkv and fc2 bias gradients and of the first LayerNorm
+    beside each other; these two reduce the first before the others take their place (fc2's in the top layer only).  The last two
+    have as many heads as columns, the most that X1 leaves room for delta of, and an attention backward with a launch
+    for each side: 128 rows, and 256."""
     import torch
     C = 3
     shape = synth.StageShape(name="dpp_pass", n_layers=layers, hidden=hidden, n_heads=heads, head_dim=d, ffn=ffn, seq=seq,

@@ -1074,6 +1074,24 @@ def test_op_attention_bf16_forward_in_eight_waves(S, few, many):
     assert (got[0][1][many - 1, 0].double() - torch.logsumexp(s, dim=-1)).abs().max().item() <= 1e-4
 
 
+def test_fp16_stage_with_the_attention_forward_in_eight_waves():
+    """fp16 forward activations, 24 sequences of 1040 tokens in 4 heads of 128: 480 workgroups of 256 rows, the last with 16,
+    take eight waves; 20 sequences take four (400 workgroups are not nearly a pair of rounds).  The same bits, and the last
+    two sequences as the oracle has them."""
+    shape = W[1].with_(name="fp16_eight_waves", n_layers=1, hidden=128, n_heads=4, head_dim=128, ffn=128, seq=1040, batch=24,
+                       bias_std=0.02, ln_jitter=0.1, fwd_fp16=True)
+    print(f"[case] stage {shape}", flush=True)
+    params, xs, dys = _inputs(shape)
+    got = []
+    for n in (24, 20):
+        y, dx, _ = gpu_run(shape.with_(batch=n), params, [xs[0][:n]], [dys[0][:n]])
+        got.append((y[0], dx[0]))
+    assert np.array_equal(got[0][0][:20], got[1][0])
+    ref_y, ref_dx, _ = oracle_run(shape, params, [xs[0][22:]], [dys[0][22:]])
+    for g, r in zip(got[0], (ref_y[0], ref_dx[0])):
+        assert max_norm_err(g[22:], r) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("S,a,d", [(70, 2, 128), (97, 1, 64), (65, 3, 32), (70, 500, 64)])
 def test_op_attention_bf16_rows_past_the_end_count_as_zeros(S, a, d):
     """The last tile's rows past the sequence's end hold a copy of its last row: with an infinite value there
