@@ -721,19 +721,20 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
             constexpr int i = decltype(i_c)::value, x = i % N;
             fr[i] = tr_frag<D>(i < N ? tO : tQ, toff, qb * 2 + x / DB, x % DB);
           };
-          // delta, four at a time: all in front at D = 64 (4x1024x16x64 47.6 -> 46.9), at 128, where registers are few, ahead of
-          // their elements by an instruction or two
+          // delta, four at a time, an instruction or two ahead of their elements; all in front where that has registers and other
+          // workgroups hide it (D = 64 in one wave per 32 rows, 4x1024x16x64 47.6 -> 46.9; in two waves 4x8076x3x64 427 -> 470)
+          constexpr bool IN_FRONT = D == 64 && SW == 1;
           auto load_delta = [&](int g) { Dl[g] = *reinterpret_cast<const f32x4*>(Ds + g * 8); };
           static_for<AHEAD>(load);
 #pragma unroll
-          for (int g = 0; g < (D == 64 ? 4 : 1); ++g) load_delta(g);
+          for (int g = 0; g < (IN_FRONT ? 4 : 1); ++g) load_delta(g);
           __builtin_amdgcn_sched_barrier(0);
           static_for<2 * N>([&](auto i_c) {
             constexpr int i = decltype(i_c)::value, x = i % N;
             // the elements of dS after instruction x: none after the first, beside which dP is completed
             constexpr int first = x < 2 ? 0 : (x - 1) * 16 / (N - 1), last = x * 16 / (N - 1);
             if constexpr (i + AHEAD < 2 * N) load(std::integral_constant<int, i + AHEAD>{});
-            if constexpr (D != 64) {
+            if constexpr (!IN_FRONT) {
 #pragma unroll
               for (int g = 1; g < 4; ++g)
                 if (i == 4 * g * (N - 1) / 16) load_delta(g);
@@ -778,7 +779,9 @@ __device__ __forceinline__ void dkv_block(const BwdArgs& args, int blk, char* ld
   bf16* drow = dqkv + ((size_t)b * S + key) * ld + (size_t)n * D;
   if constexpr (SW == 2) {
     // the first wave of a key block finishes dK, the second dV: each hands the other its share, 32 columns at a time
-    f32x4* ex = reinterpret_cast<f32x4*>(lds) + rw * (2 * 4 * kWave) + lane;
+    int at;   // the lane, found again: kept through the loop it was a register too many at D = 128
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(at));
+    f32x4* ex = reinterpret_cast<f32x4*>(lds) + rw * (2 * 4 * kWave) + at;
     auto finish = [&](f32x16(&keep)[DB], f32x16(&give)[DB], int mine, float sc, size_t off) {
 #pragma unroll
       for (int i = 0; i < DB; ++i) {
