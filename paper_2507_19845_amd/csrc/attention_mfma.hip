@@ -1047,10 +1047,12 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 //             S=4096  n1280  71.0 | 67.4    n1536  76.0 | 78.2
 //      D=32   S=256   n 768   5.8 |  6.0    n 896   5.9 |  6.3      S=1024  n1152  16.0 | 15.6    n1280  15.6 | 16.7
 //             S=4096  n1280  49.1 | 48.2    n1536  53.7 | 55.5
-//   forward, 128 rows and four waves | 256 rows and eight, which copy each tile for twice the rows, D=128: whole pairs of rounds
-//      of the compute units or just under 1x4096x32 172 | 167, 1x8191x16 300 | 281, 4x2048x16 86.9 | 84.2, 1x3000x40 116 | 112,
-//      8x1024x16 56.8 | 55.7, but 16x512x16 40.3 | 43.0 and 32x256x16 33.1 | 36.1; between 1x6000x16 168 | 176, 4x1024x40
-//      67.4 | 72.9, 1x4096x24 118 | 126, 2x1984x16 53.7 | 58.8.
+//   forward, time of 256 rows and eight waves, which copy each tile for twice the rows, over that of 128 rows and four waves,
+//      D=128, bf16 and fp16 alike: whole pairs of rounds of the compute units or just under, the last workgroup of a sequence
+//      more than half full, one pair: S 1000 ... 1500 0.94 ... 1.06, beyond 0.92 ... 1.00 (4x2048x16 0.98, 1x4096x32 0.97, 1x8191x16
+//      0.94); more pairs: S 1000 ... 1700 0.93 ... 1.08 and 16x1024x16 1.19, ... 2200 0.93 ... 1.04, beyond 0.95 ... 1.01 (2x4096x32
+//      0.98); the last at most half full: S 1000 ... 2000 1.03 ... 1.14, ... 5000 1.00 ... 1.10, beyond 5900 0.97 ... 0.99.  Not just
+//      under pairs: 1x6000x16 1.05, 4x1024x40 1.08, 1x4096x24 1.07, 2x1984x16 1.09.
 //   backward, 128 rows and one wave per 32, one launch | 64 rows and two waves, one launch:
 //      D=128  S=128   n 128  13.9 | 12.9    n 192  14.7 | 16.4      S=256   n 256  21.4 | 19.9    n 320  24.0 | 24.6
 //             S=512   n 448  36.9 | 36.8    n 512  38.0 | 39.2      S=1024  n 576  63.3 | 61.6    n 640  64.5 | 67.7
@@ -1088,6 +1090,12 @@ bool pairs_of_rounds(int B, int S, int a) {
   const long wg = row_blocks(B, S, a, 256), pairs = (wg + 511) / 512;
   return 7 * (pairs * 512 - wg) <= 512;
 }
+// such workgroups for the forward: the last one of a sequence more than half full, unless it is one of many
+bool eight_waves_fwd(int B, int S, int a) {
+  if (!pairs_of_rounds(B, S, a)) return false;
+  if ((S - 1) % 256 < 128) return S >= 5500;
+  return S >= (row_blocks(B, S, a, 256) <= 512 ? 1500 : 2200);
+}
 enum BwdForm { BWD_SPLIT64, BWD_BOTH128, BWD_EACH128, BWD_EACH256 };
 BwdForm bwd_form(int B, int S, int a, int d) {
   static constexpr Limit k128[] = {{64, 0},     {128, 128},  {192, 256},  {320, 288},       {512, 448},
@@ -1109,7 +1117,7 @@ void launch_fwd(const bf16* qkv, bf16* out, float* lse, int B, int S, int a, int
     return;
   }
   if constexpr (D == 128) {
-    if (S >= 1000 && pairs_of_rounds(B, S, a)) {
+    if (eight_waves_fwd(B, S, a)) {
       hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, F16, 8, 1>), grid(256), dim3(512), 0, st, qkv, out, lse, S, a, B, stride);
       return;
     }
