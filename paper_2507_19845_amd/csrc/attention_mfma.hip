@@ -1005,7 +1005,7 @@ __device__ __forceinline__ void dq_block(const BwdArgs& args, int qt, char* lds)
 }
 
 // Key side and query side a launch each, 32 RW rows per workgroup, the query side first (it forms delta): the form for
-// many workgroups.  Held to 256 registers (they need 254 and 253 at head dimension 128, nothing spilt), two workgroups of four
+// many workgroups.  Held to 256 registers (they need 256 and 253 at head dimension 128, nothing spilt), two workgroups of four
 // waves share a unit; left to itself the compiler took 278 and 304, and accumulators apart from the others.  Both sides,
 // us: 2x4096x24x128 1005 | 687, 4x2048x24x128 562 | 389, 16x512x24x128 239 | 181, 2x4096x32x64 543 | 496, 1x8191x32x32 730 | 595.
 template <int D, bool F16S, int RW> __global__ __launch_bounds__(64 * RW, 2) void attn_bwd_dkv_mfma_kernel(const BwdArgs p) {
@@ -1063,9 +1063,10 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 //      D=32   S=128   n 384   9.1 |  8.9    n 448   9.3 |  9.6      S=256   n 512  12.3 | 12.1    n 576  13.6 | 13.6
 //             S=512   n 768  21.2 | 19.8    n 896  22.0 | 22.2      S=1024  n1024  34.6 | 33.2    n1152  35.7 | 37.0
 //             S=4096  n1536   148 |  143    n1792   166 |  166
-//   backward, 128 rows, time of a launch each over that of one launch, D=128 | 64, S 1024 ... 16384: n 1536 0.95 ... 1.04 |
-//      0.94 ... 1.06, beyond less (the one launch needs delta from a pass of its own, and its two kinds of workgroup share no
-//      tiles).
+//   backward, time of a launch each over that of one launch of 128 rows (which needs delta from a pass of its own, and whose two
+//      kinds of workgroup share no tiles), S 192 ... 16384, D=128 | 64 | 32: n 1280 0.97 ... 1.13 | 1.00 ... 1.08 | 1.05 ... 1.26, n 1536
+//      0.98 ... 1.05 | 0.95 ... 1.03 | 1.04 ... 1.11, n 1792 0.97 ... 1.07 | 0.96 ... 1.01 | 1.04 ... 1.10, n 2048 0.91 ... 1.03 |
+//      0.92 ... 0.98 | 0.95 ... 1.05.
 //   backward, a launch each, time of 256 rows over 128: D=128, S >= 3500, whole pairs of rounds of the compute units or
 //      just under: n 2048 0.93, n 4096 0.96; between: n 3072 1.00; S=2048 n 2048 0.97, n 3072 1.01; S=1024 n 3072 1.04; S=512
 //      1.09; D=64 and 32 1.0 ... 1.3 everywhere.

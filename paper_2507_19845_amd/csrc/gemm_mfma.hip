@@ -216,7 +216,10 @@ namespace {
 // from there by the next.  Cached | non-temporal, us a step.  Accumulated: 4096 tokens 1024 wide 2005 | 1986, 2048 tokens
 // 5120 wide 7579 | 7457, 12288 wide in 12 heads 6342 | 6259, backward of 2048 tokens 2048 wide 1245 | 1215; 512 tokens 832
 // wide (24 MB a layer) 123.8 | 125.5, 192 tokens 320 wide 298.7 | 299.9.  u on top: 4096 tokens 1024 wide 1997 | 1973, forward
-// of 3968 tokens 2048 wide 888 | 882, 8 x 4096 tokens 4096 wide 141.9 | 141.2 ms.
+// of 3968 tokens 2048 wide 888 | 882, 8 x 4096 tokens 4096 wide 141.9 | 141.2 ms.  u alone where the launch behind reads it again:
+// recompute == 1, backward of 2048 tokens 2048 wide 1241 | 1241, 4096 tokens 1024 wide 1050 | 1047, 8192 tokens 512 wide 928 |
+// 919, 4096 tokens 4096 wide 4854 | 4874; recompute == 2, the same 1533 | 1521, 1247 | 1219, 1104 | 1085, 5812 | 5804, 2048 tokens
+// 5120 wide 4546 | 4552; fp16, 2048 tokens 2048 wide 962 | 962 (two runs differ by 0.5 %, the 4096-wide by 1.4).
 constexpr size_t kOnceBytes = (size_t)32 << 20;
 MfmaArgs make_args(int M, int N, int K, const void* A, const void* B, void* C, const GemmEpilogue& ep) {
   MfmaArgs a;

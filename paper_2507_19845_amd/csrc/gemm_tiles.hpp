@@ -63,8 +63,9 @@ struct MfmaArgs {
   bf16* gelu_out;
   const bf16* dgelu_u;
   float* colsum;   // GeLU' epilogue only, may be null: column sums of C per group of tile rows
-  // The accumulated matrix, or the pre-activation u that a GeLU epilogue writes and a GeLU' epilogue reads for the last
-  // time, is met again only after more has passed than the caches hold: non-temporal, it pushes no operand out of them.
+  // The accumulated matrix, or the pre-activation u that a GeLU epilogue writes and a GeLU' epilogue reads, goes past the
+  // caches non-temporally and pushes no operand out of them.  It is met again only after more has passed than they hold, but
+  // for u where a backward pass recomputes, which reads it once more right behind; measured with kOnceBytes.
   int once = 0;
   int b_img = 0;   // B is the weight's tiled image (tiles of 256 rows, slices of kImageK): kernels with BK = kImageK only
   // The tokens of several micro-batches, each in its own buffer.
@@ -679,7 +680,8 @@ __global__ __launch_bounds__(256, (gemm_waves<MB, NB, BK, NS>())) void gemm_mi16
   gemm_tile<EPI, FORM, F16, MB, NB, BK, NS>(g.p[k], blockIdx.x - g.first[k], lds);
 }
 
-// The kinds and tiles that have a form for MfmaArgs::once (tiles below 128x128 are for matrices that fit the caches).
+// The kinds and tiles that have a form for MfmaArgs::once.  Tiles below 128x128 have none: they are for smaller matrices, but for
+// the GeLU' product of a pass over a window, which keeps the tile of one micro-batch.
 template <int EPI, int MB, int NB> constexpr bool has_once() {
   return MB * NB >= 16 && (EPI == EPI_ACCUM || EPI == EPI_GELU_TANH || EPI == EPI_GELU_ERF || EPI == EPI_DGELU_TANH || EPI == EPI_DGELU_ERF);
 }

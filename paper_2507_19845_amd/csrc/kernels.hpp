@@ -138,11 +138,12 @@ struct WgradItem {
   const void* in;
   float* dw;
 };
-// sums (n_sums of them, each of one micro-batch): what reduce_partials() would do, in the launch of the last products.
+// sums (n_sums of them, each of one micro-batch): what reduce_partials() would do, in the launch of the products, or in one of
+// its own behind them where they are a launch each.
 constexpr int kMaxWgrads = 4;
 hipError_t gemm_wgrad_group(const WgradItem* items, int n, int K, int segments, size_t seg_stride_dout,
                             size_t seg_stride_in, hipStream_t st, const ReduceSeg* sums = nullptr, int n_sums = 0);
-// the same for fp32 buffers, every shape and buffer gemm_f32_supported()
+// the same for fp32 buffers, every shape and buffer gemm_f32_supported(); the sums in the last launch, whatever their number
 hipError_t gemm_f32_wgrad_group(const WgradItem* items, int n, int K, hipStream_t st, const ReduceSeg* sums = nullptr,
                                 int n_sums = 0);
 bool gemm_wgrad_segments_supported(int M, int N, int K, int segments);

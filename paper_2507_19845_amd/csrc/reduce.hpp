@@ -13,8 +13,9 @@ namespace gpts {
 // the arguments: 0.3 us less to launch.
 // NB: micro-batches there is room for.  Their loads go out together, and each one's row groups are added by 32
 // threads of its own, before the eight sums are added to out in order: the same sums as one micro-batch after the
-// other, which waited for memory and two barriers each time: eight times 64 rows of partial sums 9.9 -> 4.7 us,
-// three launches a layer and window (4 chunks of width 1024, 8 micro-batches of 512 tokens 2328 -> 2265 us).
+// other, which waited for memory and two barriers each time: eight times 64 rows of partial sums 9.9 -> 4.7 us (with three such
+// launches a layer and window, 4 chunks of width 1024, 8 micro-batches of 512 tokens 2328 -> 2265 us; two are left where the late
+// sums have room beside each other).
 template <int NS> struct ReduceArgs {
   ReduceSeg seg[NS];
   int first[NS];   // first workgroup of a segment
