@@ -571,11 +571,13 @@ def test_bias_gradients_beside_the_layernorm(dtype, hidden, ffn, seq, batch, lay
 # ------------------------------------------------------- single operations ----
 @pytest.mark.parametrize("dtype,layers,hidden,heads,ffn,seq,batch", [("fp32", 1, 128, 4, 512, 33, 2), ("fp32", 2, 136, 2, 200, 37, 3),
                                                                     ("bf16", 1, 320, 5, 832, 64, 1), ("bf16", 2, 192, 3, 2112, 96, 2),
-                                                                    ("bf16", 3, 1024, 16, 4096, 320, 1), ("bf16", 2, 64, 1, 128, 64, 1)])
+                                                                    ("bf16", 3, 1024, 16, 4096, 320, 1), ("bf16", 2, 64, 1, 128, 64, 1),
+                                                                    ("bf16", 1, 4096, 64, 4096, 1024, 16)])
 @pytest.mark.parametrize("in_place", [False, True])
 def test_partial_sums_beside_the_weight_gradients(dtype, layers, hidden, heads, ffn, seq, batch, in_place):
-    """A layer's partial column sums are added up in the launch of its weight gradients, in one of their own under a tracer and
-    where a single layer's dx lies on dy: every output bit for bit the same either way, on widths that the matrix cores take in
+    """A layer's partial column sums are added up in the launch of its weight gradients, in one of their own under a tracer,
+    where a single layer's dx lies on dy and where the gradients are a launch each (the last shape: whole rounds of tiles,
+    16384 tokens): every output bit for bit the same either way, on widths that the matrix cores take in
     different tiles and on some that they do not take."""
     print(f"[case] sums beside wgrads {dtype} L={layers} H={hidden} F={ffn} T={seq * batch} {in_place}", flush=True)
     shape = synth.WORKLOADS[0].with_(name="sums_beside_wgrads", dtype=dtype, n_layers=layers, hidden=hidden, n_heads=heads,
